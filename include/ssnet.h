@@ -153,7 +153,7 @@ int ssnet_conv1x1_mod_prepacked(ssnet_ctx *ctx, const void *d_x_packed, const vo
 
 /* Convolution without a materialised im2col matrix (SSS-Linear step 1, Sec.
  * VI-A, for kh x kw kernels with C a multiple of 64): the input is kept as
- * channel-innermost int8 limb planes, per party [limb 0..7][b][h][w][c] plus a
+ * int8 limb planes, per party [limb 0..7][channel block of 16][b][h][w][16] plus a
  * 256-byte pad (ssnet_conv_planes_bytes(B, C, H, W) bytes per party, n parties
  * back to back, 16-byte aligned; 0 for an unsupported shape), from which the
  * product kernel gathers the 16 channels of one tap of one output pixel as 16
@@ -360,7 +360,7 @@ int ssnet_relu_pool(ssnet_ctx *ctx, const uint64_t *d_x, const uint64_t *d_beta,
  * NonLinear (Sec. VII-A) in one launch: ssnet_degree_reduce_truncate(stream_id)
  * of the product shares d_c [n][B][C][HW], then ssnet_relu with the masks
  * d_beta, d_betainv [n][B][C][HW]; d_out [n][B][C][HW] holds the residues these
- * two calls give, and d_planes, if not NULL, the same values as channel-innermost
+ * two calls give, and d_planes, if not NULL, the same values as
  * limb planes for the next ssnet_conv_mod_planes (C a multiple of 64 then).
  * Messages behind the workspace header: those of the reduction and truncation,
  * then the 2t+1 masked products and the plain value of the ReLU, as planes of

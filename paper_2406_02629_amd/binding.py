@@ -298,7 +298,7 @@ class SSNet:
                                                       _dptr(out)), "ssnet_conv1x1_mod_prepacked")
         return out
 
-    # ---- convolution on channel-innermost limb planes (no im2col matrix) ----
+    # ---- convolution on limb planes (no im2col matrix) ----
     def planes_supported(self, B: int, C: int, H: int, W: int) -> bool:
         return self.lib.ssnet_conv_planes_bytes(B, C, H, W) != 0
 

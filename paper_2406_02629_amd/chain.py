@@ -74,7 +74,7 @@ class Chain:
         that follows adds them up (ssnet_*_product_*); otherwise the product kernel writes them out whole."""
         self.ss, self.layers, self.batch, self.deferred = ss, layers, batch, deferred
         dev = ss.device
-        # k x k layers whose channel count allows it read their input from channel-innermost limb planes
+        # k x k layers whose channel count allows it read their input from limb planes
         # instead of an im2col matrix; their weights are packed in (tap, channel) order
         self.on_planes = [L.kind == "conv" and L.ksize > 1 and ss.planes_supported(batch, L.cin, L.hin, L.hin)
                           for L in layers]

@@ -55,7 +55,7 @@ __device__ __forceinline__ void store_digits(const u64 (&y)[4], v4i *tile, int r
 // grid (Rb, Kb, n), block 256: thread t -> row t%16, k group t/16.
 // taps > 0: the contraction index of the packed operand runs (tap, channel) while the source runs (channel,
 // tap) with `taps` taps per channel (convolution weights for the kernel that reads its other operand from
-// channel-innermost planes); stride_k is then the stride of the source's own index.
+// limb planes); stride_k is then the stride of the source's own index.
 __global__ __launch_bounds__(256) void pack_matrix_kernel(const u64 *__restrict__ src, v4i *__restrict__ dst,
                                                           int rows, int K, int Kb, size_t party_stride,
                                                           size_t stride_r, size_t stride_k, size_t dst_party_stride,
@@ -169,9 +169,11 @@ __global__ __launch_bounds__(256) void share_pack_kernel(const u64 *__restrict__
     }
 }
 
-// Conv input [B][C][H][W] -> channel-innermost limb planes [party][limb][b][h][w][c] (int8), the form the
-// convolution kernel gathers its second operand from (16 consecutive channels of one tap of one output pixel
-// are 16 consecutive bytes).  GEN: the input is the plaintext tensor and the kernel also is GEN (Eq. 1):
+// Conv input [B][C][H][W] -> limb planes [party][limb][channel block of 16][b][h][w][16 channels] (int8), the form
+// the convolution kernel gathers its second operand from: 16 consecutive channels of one tap of one output pixel
+// are 16 consecutive bytes, and those of neighbouring pixels follow one another, so that a wave's gather is (all
+// but) contiguous.  (With all channels innermost four neighbouring lanes meet four cache lines, and such loads run
+// at 16 bytes per clock and CU instead of 64, measured on data in L2.)  GEN: the input is the plaintext tensor and the kernel also is GEN (Eq. 1):
 // it writes the n shares and their planes; otherwise the input is the share tensor [n][B][C][H][W].
 // grid (pixel blocks of 16, C / 16), block 256: wave w of block (x, y) takes channels 16 y + 4 w .. +3.
 // Every party's planes end in a pad whose first 16 bytes are zero (the source of taps in the padding).
@@ -203,8 +205,7 @@ __global__ __launch_bounds__(256) void planes_kernel(const u64 *__restrict__ in,
         }
     }
     // The four lanes of a pixel swap their digit words, the limb dwords of the wave's four channels go through
-    // LDS, and the block's 16 channels of one pixel and limb leave as one 16-byte store (a dword per wave would
-    // be a 4-byte store at a stride of C bytes).
+    // LDS, and the block's 16 channels of its 16 pixels leave as 256 bytes in a row.
     __shared__ __align__(16) u32 stage[MAXP][NL][16][4];   // [party][limb][pixel][wave]
     const int w = threadIdx.x >> 6;
 #pragma unroll
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(256) void planes_kernel(const u64 *__restrict__ in,
         }
     }
     __syncthreads();
-    store_staged_planes<MAXP>(stage, planes, party_bytes, plane, blockIdx.x * 16, B * HW, C, blockIdx.y * 16, n);
+    store_staged_planes<MAXP>(stage, planes, party_bytes, plane, blockIdx.x * 16, B * HW, blockIdx.y * 16, n);
 }
 
 // The same with four channels per thread (thread t of block (pixel block, channel block of 64): pixel t%16,
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(256) void planes4_kernel(const u64 *__restrict__ in
 #pragma unroll
     for (int p = 0; p < MAXP; p++) {
         if (p < n) {
-            u32 *dst = reinterpret_cast<u32 *>(planes + p * party_bytes + (size_t)pix * C + c0);
+            u32 *dst = reinterpret_cast<u32 *>(planes + p * party_bytes + ((size_t)(c0 >> 4) * (B * HW) + pix) * 16 + (c0 & 15));
 #pragma unroll
             for (int limb = 0; limb < NL; limb++) dst[limb * (plane / 4)] = limb_dword(y[p], limb);
         }
@@ -301,11 +302,11 @@ struct gemm_args {
     fdiv dG, dKb, dCT, dRT, dRowcost, dTilecost, dWlast, dCdiv;
     size_t a_party_stride, b_party_stride, out_party_stride, stride_row, stride_cb;
     int cdiv;
-    // second operand read straight from channel-innermost limb planes (convolution without a materialised
-    // im2col): planes [party][limb][b][h][w][c] int8, contraction index (tap, channel), C a multiple of 64
+    // second operand read straight from limb planes (convolution without a materialised im2col): planes
+    // [party][limb][channel block of 16][b][h][w][16] int8, contraction index (tap, channel), C a multiple of 64
     const v4i *planes, *zero;          // zero: 16 zero bytes, for taps that fall into the padding
     unsigned plane16, party16;         // strides of a limb plane and of a party, in 16-byte units
-    int cvH, cvW, cvC16, cvKw, cvStride, cvPad, cvHoWo, cvWo, cvKbTap;   // C16 = C/16, KbTap = C/64
+    int cvH, cvW, cvPixels, cvKw, cvStride, cvPad, cvHoWo, cvWo, cvKbTap;   // Pixels = images * H * W, KbTap = C/64
     fdiv dHoWo, dWo, dKbTap, dKw;
 };
 
@@ -450,7 +451,7 @@ __device__ __forceinline__ const v4i *unit_base(const gemm_args &g, const wave_s
     const int hi = (ws.hw >> 16) + r, wi = (int)(short)(ws.hw & 0xffff) + sx;
     const bool ok = ws.bpix >= 0 && (unsigned)hi < (unsigned)g.cvH && (unsigned)wi < (unsigned)g.cvW;
     qs = ok ? g.plane16 : 0;
-    return ok ? ws.p + (size_t)(ws.bpix + hi * g.cvW + wi) * g.cvC16 + c16 : g.zero;
+    return ok ? ws.p + (size_t)c16 * g.cvPixels + (ws.bpix + hi * g.cvW + wi) : g.zero;
 }
 
 // Planes that get zeros from workgroup `slot`, whose range ends at unit u1.  A workgroup that starts a tile
@@ -937,7 +938,7 @@ hipError_t ss_launch_pack_im2col(const u64 *x, void *dst, int n, int B, int C, i
 
 namespace {
 
-struct conv_planes {   // geometry of an operand given as channel-innermost limb planes
+struct conv_planes {   // geometry of an operand given as limb planes
     const void *planes;
     int B, C, H, W, kh, kw, stride, pad, Ho, Wo;
 };
@@ -1003,7 +1004,7 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
         g.plane16 = (unsigned)(plane / 16);
         g.party16 = (unsigned)(ss_planes_bytes(cv->B, cv->C, cv->H, cv->W) / 16);
         g.zero = g.planes + (size_t)NL * g.plane16;   // the pad behind the first party's planes
-        g.cvH = cv->H, g.cvW = cv->W, g.cvC16 = cv->C / 16, g.cvKw = cv->kw, g.cvStride = cv->stride, g.cvPad = cv->pad;
+        g.cvH = cv->H, g.cvW = cv->W, g.cvPixels = cv->B * cv->H * cv->W, g.cvKw = cv->kw, g.cvStride = cv->stride, g.cvPad = cv->pad;
         g.cvHoWo = cv->Ho * cv->Wo, g.cvWo = cv->Wo, g.cvKbTap = cv->C / 64;
         g.dHoWo = fdz((unsigned)g.cvHoWo);
         g.dWo = fdz((unsigned)g.cvWo);

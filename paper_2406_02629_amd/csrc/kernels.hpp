@@ -132,7 +132,7 @@ hipError_t ss_launch_pack_matrix(const u64 *src, void *dst, int n, int rows, int
 // degree-t shares of secret [B][K][HW] -> shares [n][B][K][HW] and their packed operand (rows (b, hw), k)
 hipError_t ss_launch_share_pack(const u64 *secret, u64 *shares, void *dst, int n, int t, int B, int K, int HW,
                                 const ss_keys &keys, hipStream_t stream);
-// Channel-innermost limb planes of a conv input: per party [limb 0..7][b][h][w][c] int8 and a 256-byte pad
+// Limb planes of a conv input: per party [limb 0..7][channel block of 16][b][h][w][16 channels] int8 and a 256-byte pad
 // whose first 16 bytes are zero; C a multiple of 64.
 size_t ss_planes_bytes(int B, int C, int H, int W);   // per party
 // gen: `in` is the plaintext [B][C][HW] and the shares [n][B][C][HW] are written too; else `in` is the shares

@@ -548,7 +548,7 @@ __device__ __forceinline__ void relu_fixed(const u64 (&x)[N], size_t em, size_t 
 
 // Linear - Truncation - NonLinear tail of a convolution layer in one launch (the order of Sec. VII-A):
 // reduction + RERAND + truncation of the product shares c [n][B][C][HW], then ReLU under the mask, the
-// result stored as shares and, if planes != nullptr, as channel-innermost limb planes for the next
+// result stored as shares and, if planes != nullptr, as limb planes for the next
 // convolution.  One element per thread, lanes arranged as in the share + planes kernel (lane l: pixel l%16,
 // channel 4 g + l/16 of the wave's group g).  The messages hold the values of the separate kernels, in the
 // order of this kernel's threads (so that a wave writes 512 consecutive bytes of every message plane): the
@@ -613,7 +613,7 @@ __global__ __launch_bounds__(BLOCK) void layer_tail_kernel(const u64 *c, u64 *__
         }
     }
     __syncthreads();
-    store_staged_planes<N>(stage, planes, party_bytes, count, blockIdx.x * 16, B * HW, C, blockIdx.y * 16, N);
+    store_staged_planes<N>(stage, planes, party_bytes, count, blockIdx.x * 16, B * HW, blockIdx.y * 16, N);
 }
 
 // The outputs of the layer tail without the protocol (all parties on one device): as for
@@ -678,7 +678,7 @@ __global__ __launch_bounds__(BLOCK) void tail_direct_kernel(const u64 *c, const 
         }
     }
     __syncthreads();
-    store_staged_planes<SS_MAXN>(stage, planes, party_bytes, count, blockIdx.x * 16, B * HW, C, blockIdx.y * 16, n);
+    store_staged_planes<SS_MAXN>(stage, planes, party_bytes, count, blockIdx.x * 16, B * HW, blockIdx.y * 16, n);
 }
 
 // Same computation for small tensors, where the serial work of one thread per
