@@ -56,8 +56,13 @@ SS_HD u64 ss_reduce128(u64 hi, u64 lo)
     return ss_reduce((lo & SS_PMASK) + SS_PC * upper);    // < 2^45 + 2^63
 }
 
-// a, b < 2^45: product < 2^90, hi < 2^26
-SS_HD u64 ss_mul(u64 a, u64 b) { return ss_reduce128(ss_mulhi(a, b), a * b); }
+// a < 2^46, b < 2^45: the product cut at bit 45, the upper part weighs 55: < 2^45 + 2^52, same residue
+SS_HD u64 ss_mul_lazy(u64 a, u64 b)
+{
+    const unsigned __int128 t = (unsigned __int128)a * b;
+    return ((u64)t & SS_PMASK) + SS_PC * (u64)(t >> 45);
+}
+SS_HD u64 ss_mul(u64 a, u64 b) { return ss_reduce(ss_mul_lazy(a, b)); }
 
 // 128-bit accumulator for sums of a few products of canonical values
 struct ss_acc {
@@ -109,8 +114,9 @@ SS_HD u64 ss_fold(u64 x) { return (x & SS_P) + (x >> 61); }
 // x < 2p  ->  canonical
 SS_HD u64 ss_canon(u64 x) { return x >= SS_P ? x - SS_P : x; }
 
-// any x < 2^64  ->  canonical
-SS_HD u64 ss_reduce(u64 x) { return ss_canon(ss_fold(x)); }
+// x < 2^64 - 8  ->  canonical, without a comparison: with x = a 2^61 + b the residue is a + b, or a + b - p if that
+// is not below p, which is when a + b + 1 carries into bit 61: (x + q) mod 2^61 with q = a or a + 1
+SS_HD u64 ss_reduce(u64 x) { return (x + ((x + (x >> 61) + 1) >> 61)) & SS_P; }
 
 SS_HD u64 ss_add(u64 a, u64 b) { return ss_canon(a + b); }          // a, b canonical
 SS_HD u64 ss_sub(u64 a, u64 b) { return ss_canon(a + SS_P - b); }   // a, b canonical
@@ -124,8 +130,13 @@ SS_HD u64 ss_reduce128(u64 hi, u64 lo)
     return ss_reduce(r);
 }
 
-// a, b < 2^61: product < 2^122, hi < 2^58
-SS_HD u64 ss_mul(u64 a, u64 b) { return ss_reduce128(ss_mulhi(a, b), a * b); }
+// a < 2^62, b < 2^61: the product cut at bit 61 is two words below 2^61 and 2^62; sum < 2^63, same residue
+SS_HD u64 ss_mul_lazy(u64 a, u64 b)
+{
+    const unsigned __int128 t = (unsigned __int128)a * b;
+    return ((u64)t & SS_P) + (u64)(t >> 61);
+}
+SS_HD u64 ss_mul(u64 a, u64 b) { return ss_reduce(ss_mul_lazy(a, b)); }
 
 // 128-bit accumulator for sums of a few products of canonical values
 struct ss_acc {
@@ -208,6 +219,17 @@ SS_HD u64 ss_draw_field(u64 key, u64 e) { return ss_field_of(ss_draw(key, e)); }
 SS_HD u64 ss_counter(u64 e) { return (e + 1) * SS_GAMMA; }
 SS_HD u64 ss_draw_at(u64 key, u64 counter) { return ss_mix64(key + counter); }
 SS_HD u64 ss_draw_field_at(u64 key, u64 counter) { return ss_field_of(ss_draw_at(key, counter)); }
+
+// the field element of a draw up to a multiple of p: p itself may come out as p (2^61 - 1), or anything below
+// 2^45 + 2^22 (2^45 - 55); for values that are reduced after they were used anyway
+SS_HD u64 ss_draw_lazy_at(u64 key, u64 counter)
+{
+#if defined(SS_FIELD_P45)
+    return ss_fold(ss_draw_at(key, counter) >> 3);
+#else
+    return ss_draw_at(key, counter) >> 3;
+#endif
+}
 
 // polynomial a0 + c[0] x + ... + c[d-1] x^d at the small point x (1..8), by
 // Horner.  MAXD bounds d at compile time so that c[] stays in registers.

@@ -31,6 +31,7 @@ struct ss_dr_params {             // RED + RERAND constants
     int ibinv[2 * SS_MAXT + 1][SS_MAXK];         // D * (first k columns of B^-1), Eq. 3
     int irmat[2 * SS_MAXT + 1][SS_MAXN];         // D * R, R = B^-1 P B, [reducing party][receiving party]
     u64 dinv;                                    // D^-1
+    int ilambda0[2 * SS_MAXT + 1];               // ibinv[i][0] / D: Lagrange multipliers of IDs 1..2t+1, integers
     int ilambda[SS_MAXK];                        // Lagrange multipliers of IDs 1..k: (-1)^(q-1) C(k, q)
 };
 

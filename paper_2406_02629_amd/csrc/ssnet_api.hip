@@ -37,6 +37,7 @@ struct ssnet_ctx {
     int ibinv[2 * SS_MAXT + 1][SS_MAXK];
     int irmat[2 * SS_MAXT + 1][SS_MAXN];
     int ilambda_k[SS_MAXK];
+    int ilambda_r[2 * SS_MAXT + 1];       // Lagrange multipliers of IDs 1..2t+1 (integers: (-1)^(i-1) C(2t+1, i))
     u64 dinv;
     // optional per-kernel-class timing with HIP events on the context's stream
     bool prof;
@@ -370,6 +371,10 @@ int ssnet_create(ssnet_ctx **out, int n, int t, uint64_t p, int f, uint64_t seed
     bool ok = h_lagrange_int(ids, t + 1, c->ilambda_k, &one) && one == 1 &&
               h_reduction_tables_int(2 * t + 1, t + 1, n, c->ibinv, c->irmat, &c->dinv);
     for (int q = 0; ok && q <= t; q++) ok = h_from_signed(c->ilambda_k[q]) == c->lambda_k[q];
+    int all[2 * SS_MAXT + 1];
+    for (int i = 0; i < 2 * t + 1; i++) all[i] = i + 1;
+    ok = ok && h_lagrange_int(all, 2 * t + 1, c->ilambda_r, &one) && one == 1;
+    for (int i = 0; ok && i < 2 * t + 1; i++) ok = h_from_signed(c->ilambda_r[i]) == c->binv[i][0];
     for (int i = 0; ok && i < 2 * t + 1; i++)
         for (int j = 0; ok && j <= t; j++) ok = ss_mul(h_from_signed(c->ibinv[i][j]), c->dinv) == c->binv[i][j];
     if (!ok) {
@@ -778,6 +783,7 @@ static ss_dr_params make_dr_params(const ssnet_ctx *ctx, uint64_t stream_id)
         for (int m = 0; m < n; m++) dp.irmat[i][m] = ctx->irmat[i][m];
     }
     dp.dinv = ctx->dinv;
+    for (int i = 0; i < nr; i++) dp.ilambda0[i] = ctx->ilambda_r[i];
     for (int q = 0; q < k; q++) dp.ilambda[q] = ctx->ilambda_k[q];
     return dp;
 }
@@ -968,9 +974,9 @@ static bool make_nl_params(const ssnet_ctx *ctx, uint64_t stream_id, ss_nl_param
         np->bgen_key[j - 1] = ss_key(ctx->seed, SSNET_DOM_BETA_GEN, stream_id, 0, (u64)j);
         np->bigen_key[j - 1] = ss_key(ctx->seed, SSNET_DOM_BETAINV_GEN, stream_id, 0, (u64)j);
     }
-    int ids[2 * SS_MAXT + 1];
-    for (int i = 0; i < 2 * ctx->t + 1; i++) ids[i] = i + 1;
-    return h_lagrange_int(ids, 2 * ctx->t + 1, np->ilambda, &np->dinv);
+    for (int i = 0; i < 2 * ctx->t + 1; i++) np->ilambda[i] = ctx->ilambda_r[i];
+    np->dinv = 1;
+    return true;
 }
 
 }  // namespace

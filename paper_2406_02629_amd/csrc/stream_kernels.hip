@@ -363,15 +363,18 @@ __global__ __launch_bounds__(BLOCK) void degree_reduce_kernel(const u64 *c, u64 
 }
 
 // ---- the same steps with n and t fixed at compile time ((k,n) = (2,3), (3,5)) ----
-// Same messages, same outputs, fewer instructions:
-//  * a party evaluates its polynomial at the consecutive points 1, 2, ... by
-//    forward differences (one or two additions per point) instead of Horner
-//    with a modular multiplication per coefficient;
-//  * sums of value * small signed constant keep the value in two pieces of 31
-//    and 30 bits and accumulate in signed 64-bit words (one multiply-add per
-//    piece), with no case split on the sign of the constant;
-//  * sums stay unreduced ("lazy", any 64-bit word of the right residue) until
-//    a value is stored or multiplied.
+// Same messages, same outputs.  At the sizes of a network's layers this code is bound by its instructions (all of them
+// issue at the same rate on this machine, 64-bit multiply-adds included), so it carries the polynomials behind the
+// messages along and works on coefficients where the protocol works on values:
+//  * a party evaluates its polynomial at the consecutive points 1, 2, ... by forward differences (one or two additions
+//    per point instead of Horner with a modular multiplication per coefficient);
+//  * what the parties 1..k reconstruct from the sub-shares of step 2 (step 3 of RED) is the combination of the k
+//    polynomials with the Lagrange multipliers, so the coefficients are combined, not their values at every ID; the
+//    sharings of zero and of the mask are added coefficient by coefficient too, and the sum is evaluated once;
+//  * REC of a sharing whose polynomial is at hand is its constant term, whichever IDs are asked for;
+//  * sums of value * small signed constant keep the value in two pieces of 31 and 30 bits and accumulate in signed
+//    64-bit words (one multiply-add per piece), with no case split on the sign of the constant;
+//  * sums stay unreduced (any word of the right residue within the bounds noted) until a value is stored.
 
 // sum of v * c over at most 8 terms, v canonical given as v = w0 + w1 2^31 (w0 < 2^31), |c| < 2^26
 struct ss_sacc2 {
@@ -382,38 +385,36 @@ struct ss_sacc2 {
         lo += (long long)(int)w0 * c;   // |sum| < 8 * 2^31 * 2^26 = 2^60
         hi += (long long)(int)w1 * c;
     }
-    __device__ __forceinline__ u64 value() const
+    // the sum, below 2^61 + 2^3 (2^45 + 2^25)
+    __device__ __forceinline__ u64 lazy() const
     {
 #if defined(SS_FIELD_P45)
         // here |hi| < 2^43 (w1 < 2^14).  Offsets that are multiples of p make both words positive;
         // h 2^31 with h = a 2^14 + b: a 2^45 + b 2^31 = 55 a + b 2^31
         const u64 l = (u64)(lo + (long long)(SS_P << 16)), h = (u64)(hi + (long long)SS_P);   // < 2^62, < 2^46
-        return ss_reduce(l + SS_PC * (h >> 14) + ((h & 0x3FFFull) << 31));
+        return ss_fold(l + SS_PC * (h >> 14) + ((h & 0x3FFFull) << 31));
 #else
         const u64 l = (u64)(lo + (long long)SS_P), h = (u64)(hi + (long long)SS_P);   // in (2^60, 2^62)
         // h 2^31 with 2^61 = 1: low 30 bits of h shifted, the rest wraps to weight 1
-        return ss_reduce(l + ((h & 0x3FFFFFFFull) << 31) + (h >> 30));
+        return ss_fold(l + ((h & 0x3FFFFFFFull) << 31) + (h >> 30));
 #endif
     }
+    __device__ __forceinline__ u64 value() const { return ss_canon(lazy()); }
 };
 #define SS_SPLIT31(v, w0, w1) const u32 w0 = (u32)(v)&0x7FFFFFFFu, w1 = (u32)((v) >> 31)
 
 // all steps for element e; the messages go to the workspace, the new shares (reduced and re-randomised, with
-// TRUNC also truncated) come back in o[]
+// TRUNC also truncated) come back in o[], their secret (what any k of them reconstruct to) in `secret`
 // (em, mcount: position and plane size of this element in the message buffers, which need not be e, count)
 template <int N, int T, bool TRUNC>
 __device__ __forceinline__ void reduce_truncate_fixed(size_t e, size_t count, size_t em, size_t mcount, const u64 *c,
                                                       u64 *__restrict__ msg1, u64 *__restrict__ msg2,
                                                       u64 *__restrict__ umsg, u64 *__restrict__ wsh,
                                                       const ss_dr_params &dp, const ss_tr_params &tp,
-                                                      const ss_part_src &ps, u64 (&o)[N])
+                                                      const ss_part_src &ps, u64 (&o)[N], u64 &secret)
 {
     constexpr int K = T + 1, NR = 2 * T + 1;
     const u64 counter = ss_counter(e);
-    auto draw = [&](const u64 *keys, u64 (&r)[T]) {
-#pragma unroll
-        for (int j = 0; j < T; j++) r[j] = ss_draw_field_at(keys[j], counter);
-    };
 
     // all incoming shares are requested at once
     u64 cin[NR];
@@ -427,7 +428,7 @@ __device__ __forceinline__ void reduce_truncate_fixed(size_t e, size_t count, si
         for (int i = 0; i < NR; i++) cin[i] = ss_add(cin[i], more[i]);
     }
 
-    // step 1, and of step 2 the sums coef[q][j] = sum_i msg1[i][q] * D binv[i][j]
+    // step 1, and of step 2 the sums coef[q][j] = sum_i msg1[i][q] * D binv[i][j] (j = 0: without D, see ilambda0)
     ss_sacc2 coef[K][K];
 #pragma unroll
     for (int q = 0; q < K; q++)
@@ -435,67 +436,63 @@ __device__ __forceinline__ void reduce_truncate_fixed(size_t e, size_t count, si
         for (int j = 0; j < K; j++) coef[q][j].clear();
 #pragma unroll
     for (int i = 0; i < NR; i++) {
-        const u64 ci = cin[i];
         u64 r[T];
-        draw(dp.reshare_key[i], r);
-        eval_points<T, K>(ci, r, [&](int q, u64 v) {
+#pragma unroll
+        for (int j = 0; j < T; j++) r[j] = ss_draw_lazy_at(dp.reshare_key[i][j], counter);
+        eval_points<T, K>(cin[i], r, [&](int q, u64 v) {
             msg1[((size_t)i * K + q) * mcount + em] = v;
             SS_SPLIT31(v, w0, w1);
+            coef[q][0].mac(w0, w1, dp.ilambda0[i]);
 #pragma unroll
-            for (int j = 0; j < K; j++) coef[q][j].mac(w0, w1, dp.ibinv[i][j]);
+            for (int j = 1; j < K; j++) coef[q][j].mac(w0, w1, dp.ibinv[i][j]);
         });
     }
 
-    // rest of step 2 (party q evaluates its polynomial at every party ID), and of step 3 the sums
-    // red[m] = sum_q lambda_q msg2[q][m]
-    ss_sacc2 red[N];
-#pragma unroll
-    for (int m = 0; m < N; m++) red[m].clear();
+    // rest of step 2: party q evaluates its polynomial at every party ID
+    u64 poly[K][K];   // [coefficient][q], < 2^61 + 2^3
 #pragma unroll
     for (int q = 0; q < K; q++) {
-        const u64 a0 = ss_mul(coef[q][0].value(), dp.dinv);
+        poly[0][q] = coef[q][0].lazy();
         u64 cf[T];
 #pragma unroll
-        for (int j = 1; j < K; j++) cf[j - 1] = ss_mul(coef[q][j].value(), dp.dinv);
-        eval_points<T, N>(a0, cf, [&](int m, u64 v) {
-            msg2[((size_t)q * N + m) * mcount + em] = v;
-            SS_SPLIT31(v, w0, w1);
-            red[m].mac(w0, w1, dp.ilambda[q]);
-        });
+        for (int j = 1; j < K; j++) cf[j - 1] = poly[j][q] = ss_fold(ss_mul_lazy(coef[q][j].lazy(), dp.dinv));
+        eval_points<T, N>(poly[0][q], cf, [&](int m, u64 v) { msg2[((size_t)q * N + m) * mcount + em] = v; });
     }
-
-    // rest of step 3 and RERAND
-    u64 z[T], y[N];
-    draw(dp.zero_key, z);
-    eval_points<T, N>(0, z, [&](int m, u64 v) { y[m] = ss_add(red[m].value(), v); });
-    if (!TRUNC) {
+    // step 3: sum_q lambda_q poly[.][q], lambda = (2, -1) or (3, -3, 1), then RERAND and the mask of truncation step 1
+    u64 u[K];
+    u64 ev = 0;
+    if (TRUNC) ev = mask_e(tp.e_key, e, tp.f);
 #pragma unroll
-        for (int m = 0; m < N; m++) o[m] = y[m];
+    for (int j = 0; j < K; j++) {
+        const u64 d = ss_fold(poly[j][0] + 2 * SS_P - poly[j][1]);   // < 2^61 + 2^3
+        u64 v = T == 1 ? d + poly[j][0] : 2 * d + d + poly[j][T];    // < 4 (2^61 + 2^3)
+        if (j > 0) {
+            v += ss_draw_lazy_at(dp.zero_key[j - 1], counter);
+            if (TRUNC) v += ss_draw_lazy_at(tp.alpha_key[j - 1], counter);
+        } else if (TRUNC) {
+            v += ev << tp.f;
+        }
+        u[j] = ss_fold(v);
+    }
+    const u64(&uc)[T] = *reinterpret_cast<const u64(*)[T]>(&u[1]);
+    if (!TRUNC) {
+        eval_points<T, N>(u[0], uc, [&](int m, u64 v) { o[m] = v; });
+        secret = ss_canon(u[0]);
         return;
     }
-
-    // truncation step 1 (parties 1..k mask their share) and the elite party's REC of x + alpha
-    const u64 ev = mask_e(tp.e_key, e, tp.f);
-    u64 ca[T], cw[T], cat[T];
-    draw(tp.alpha_key, ca);
-    ss_sacc2 acc;
-    acc.clear();
-    eval_points<T, K>(ev << tp.f, ca, [&](int q, u64 v) {
-        const u64 um = ss_add(y[q], v);
-        umsg[(size_t)q * mcount + em] = um;
-        SS_SPLIT31(um, w0, w1);
-        acc.mac(w0, w1, tp.ilambda[q]);
-    });
+    // the masked shares of parties 1..k; the elite party's REC of x + alpha is the constant term
+    eval_points<T, K>(u[0], uc, [&](int q, u64 v) { umsg[(size_t)q * mcount + em] = v; });
     // step 2: shift and re-share; step 3: unmask
-    const u64 w = shift_signed(acc.value(), tp.f);
-    draw(tp.gen_key, cw);
-    draw(tp.alphat_key, cat);
-    u64 ws[N];
-    eval_points<T, N>(w, cw, [&](int m, u64 v) {
-        wsh[(size_t)m * mcount + em] = v;
-        ws[m] = v;
-    });
-    eval_points<T, N>(SS_P - ev, cat, [&](int m, u64 v) { o[m] = ss_add(ws[m], v); });
+    const u64 w = shift_signed(ss_canon(u[0]), tp.f);
+    u64 cw[T], co[T];
+#pragma unroll
+    for (int j = 0; j < T; j++) {
+        cw[j] = ss_draw_lazy_at(tp.gen_key[j], counter);
+        co[j] = ss_fold(cw[j] + ss_draw_lazy_at(tp.alphat_key[j], counter));
+    }
+    eval_points<T, N>(w, cw, [&](int m, u64 v) { wsh[(size_t)m * mcount + em] = v; });
+    secret = ss_canon(w + SS_P - ev);
+    eval_points<T, N>(secret, co, [&](int m, u64 v) { o[m] = v; });
 }
 
 template <int N, int T, bool TRUNC>
@@ -503,24 +500,15 @@ __global__ __launch_bounds__(BLOCK) void degree_reduce_fixed_kernel(const u64 *c
                                                                     u64 *__restrict__ msg2, u64 *__restrict__ umsg,
                                                                     u64 *__restrict__ wsh, u64 *out,
                                                                     u64 *__restrict__ rec, size_t count,
-                                                                    ss_dr_params dp, ss_tr_params tp, ss_recf_params rf,
-                                                                    ss_part_src ps)
+                                                                    ss_dr_params dp, ss_tr_params tp, ss_part_src ps)
 {
     const size_t e = (size_t)blockIdx.x * BLOCK + threadIdx.x;
     if (e >= count) return;
-    u64 o[N];
-    reduce_truncate_fixed<N, T, TRUNC>(e, count, e, count, c, msg1, msg2, umsg, wsh, dp, tp, ps, o);
-    ss_sacc2 racc;   // if asked for, REC of the result
-    racc.clear();
+    u64 o[N], secret;
+    reduce_truncate_fixed<N, T, TRUNC>(e, count, e, count, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
 #pragma unroll
-    for (int m = 0; m < N; m++) {
-        out[(size_t)m * count + e] = o[m];
-        if (TRUNC && rec) {
-            SS_SPLIT31(o[m], w0, w1);
-            racc.mac(w0, w1, rf.coef[m]);
-        }
-    }
-    if (TRUNC && rec) rec[e] = rf.dinv == 1 ? racc.value() : ss_mul(racc.value(), rf.dinv);
+    for (int m = 0; m < N; m++) out[(size_t)m * count + e] = o[m];
+    if (TRUNC && rec) rec[e] = secret;   // if asked for, REC of the result
 }
 
 // ReLU under the multiplicative mask for one element (the three steps of relu_kernel below), n and t
@@ -589,7 +577,8 @@ __global__ __launch_bounds__(BLOCK) void layer_tail_kernel(const u64 *c, u64 *__
         for (int i = 0; i < 2 * T + 1; i++) mb[i] = sh_b[(size_t)i * count + e];
 #pragma unroll
         for (int m = 0; m < N; m++) mbi[m] = sh_bi[(size_t)m * count + e];
-        reduce_truncate_fixed<N, T, true>(e, count, em, mcount, c, msg1, msg2, umsg, wsh, dp, tp, ps, o);
+        u64 secret;
+        reduce_truncate_fixed<N, T, true>(e, count, em, mcount, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
         relu_fixed<N, T>(o, em, mcount, mb, mbi, rmsg, yplain, np, r);
 #pragma unroll
         for (int p = 0; p < N; p++) {
@@ -1109,10 +1098,10 @@ hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out,
                            c, msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, norec, ps);
     else if (dp.n == 5 && dp.t == 2)
         hipLaunchKernelGGL((degree_reduce_fixed_kernel<5, 2, false>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c,
-                           msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, norec, ps);
+                           msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, ps);
     else if (dp.n == 3 && dp.t == 1)
         hipLaunchKernelGGL((degree_reduce_fixed_kernel<3, 1, false>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c,
-                           msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, norec, ps);
+                           msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, ps);
     else   // one element per thread: the k*k + n wide accumulators of two elements would not fit the register file
         hipLaunchKernelGGL((degree_reduce_kernel<1, false>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1,
                            msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, norec, ps);
@@ -1132,10 +1121,10 @@ hipError_t ss_launch_degree_reduce_truncate(const u64 *c, u64 *msg1, u64 *msg2, 
                            c, msg1, msg2, u, wsh, out, rec, count, dp, tp, rf, ps);
     else if (dp.n == 5 && dp.t == 2)
         hipLaunchKernelGGL((degree_reduce_fixed_kernel<5, 2, true>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c,
-                           msg1, msg2, u, wsh, out, rec, count, dp, tp, rf, ps);
+                           msg1, msg2, u, wsh, out, rec, count, dp, tp, ps);
     else if (dp.n == 3 && dp.t == 1)
         hipLaunchKernelGGL((degree_reduce_fixed_kernel<3, 1, true>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c,
-                           msg1, msg2, u, wsh, out, rec, count, dp, tp, rf, ps);
+                           msg1, msg2, u, wsh, out, rec, count, dp, tp, ps);
     else
         hipLaunchKernelGGL((degree_reduce_kernel<1, true>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1,
                            msg2, u, wsh, out, rec, count, dp, tp, rf, ps);
