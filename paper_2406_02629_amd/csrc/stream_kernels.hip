@@ -22,6 +22,8 @@ struct pack_t<1> {
     __device__ __forceinline__ void load(const u64 *p) { v[0] = *p; }
     __device__ __forceinline__ void store(u64 *p) const { *p = v[0]; }
     __device__ __forceinline__ void store_streaming(u64 *p) const { __builtin_nontemporal_store(v[0], p); }
+    template <bool STREAM>
+    __device__ __forceinline__ void send(u64 *p) const { STREAM ? store_streaming(p) : store(p); }
 };
 template <>
 struct pack_t<2> {
@@ -46,7 +48,19 @@ struct pack_t<2> {
         v2u q = {v[0], v[1]};
         __builtin_nontemporal_store(q, reinterpret_cast<v2u *>(p));
     }
+    template <bool STREAM>
+    __device__ __forceinline__ void send(u64 *p) const { STREAM ? store_streaming(p) : store(p); }
 };
+
+// A message that nothing in the launch reads again.  STREAM: past the caches, see streams_messages.
+template <bool STREAM>
+__device__ __forceinline__ void send(u64 *p, u64 v)
+{
+    if constexpr (STREAM)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
 
 // share i of element e of the incoming product, which may be given as a sum of planes (the partial-sum form
 // of the product kernels): canonical sum of the planes' values
@@ -406,7 +420,7 @@ struct ss_sacc2 {
 // all steps for element e; the messages go to the workspace, the new shares (reduced and re-randomised, with
 // TRUNC also truncated) come back in o[], their secret (what any k of them reconstruct to) in `secret`
 // (em, mcount: position and plane size of this element in the message buffers, which need not be e, count)
-template <int N, int T, bool TRUNC>
+template <int N, int T, bool TRUNC, bool STREAM>
 __device__ __forceinline__ void reduce_truncate_fixed(size_t e, size_t count, size_t em, size_t mcount, const u64 *c,
                                                       u64 *__restrict__ msg1, u64 *__restrict__ msg2,
                                                       u64 *__restrict__ umsg, u64 *__restrict__ wsh,
@@ -440,7 +454,7 @@ __device__ __forceinline__ void reduce_truncate_fixed(size_t e, size_t count, si
 #pragma unroll
         for (int j = 0; j < T; j++) r[j] = ss_draw_lazy_at(dp.reshare_key[i][j], counter);
         eval_points<T, K>(cin[i], r, [&](int q, u64 v) {
-            msg1[((size_t)i * K + q) * mcount + em] = v;
+            send<STREAM>(msg1 + ((size_t)i * K + q) * mcount + em, v);
             SS_SPLIT31(v, w0, w1);
             coef[q][0].mac(w0, w1, dp.ilambda0[i]);
 #pragma unroll
@@ -456,7 +470,7 @@ __device__ __forceinline__ void reduce_truncate_fixed(size_t e, size_t count, si
         u64 cf[T];
 #pragma unroll
         for (int j = 1; j < K; j++) cf[j - 1] = poly[j][q] = ss_fold(ss_mul_lazy(coef[q][j].lazy(), dp.dinv));
-        eval_points<T, N>(poly[0][q], cf, [&](int m, u64 v) { msg2[((size_t)q * N + m) * mcount + em] = v; });
+        eval_points<T, N>(poly[0][q], cf, [&](int m, u64 v) { send<STREAM>(msg2 + ((size_t)q * N + m) * mcount + em, v); });
     }
     // step 3: sum_q lambda_q poly[.][q], lambda = (2, -1) or (3, -3, 1), then RERAND and the mask of truncation step 1
     u64 u[K];
@@ -481,7 +495,7 @@ __device__ __forceinline__ void reduce_truncate_fixed(size_t e, size_t count, si
         return;
     }
     // the masked shares of parties 1..k; the elite party's REC of x + alpha is the constant term
-    eval_points<T, K>(u[0], uc, [&](int q, u64 v) { umsg[(size_t)q * mcount + em] = v; });
+    eval_points<T, K>(u[0], uc, [&](int q, u64 v) { send<STREAM>(umsg + (size_t)q * mcount + em, v); });
     // step 2: shift and re-share; step 3: unmask
     const u64 w = shift_signed(ss_canon(u[0]), tp.f);
     u64 cw[T], co[T];
@@ -490,12 +504,12 @@ __device__ __forceinline__ void reduce_truncate_fixed(size_t e, size_t count, si
         cw[j] = ss_draw_lazy_at(tp.gen_key[j], counter);
         co[j] = ss_fold(cw[j] + ss_draw_lazy_at(tp.alphat_key[j], counter));
     }
-    eval_points<T, N>(w, cw, [&](int m, u64 v) { wsh[(size_t)m * mcount + em] = v; });
+    eval_points<T, N>(w, cw, [&](int m, u64 v) { send<STREAM>(wsh + (size_t)m * mcount + em, v); });
     secret = ss_canon(w + SS_P - ev);
     eval_points<T, N>(secret, co, [&](int m, u64 v) { o[m] = v; });
 }
 
-template <int N, int T, bool TRUNC>
+template <int N, int T, bool TRUNC, bool STREAM>
 __global__ __launch_bounds__(BLOCK) void degree_reduce_fixed_kernel(const u64 *c, u64 *__restrict__ msg1,
                                                                     u64 *__restrict__ msg2, u64 *__restrict__ umsg,
                                                                     u64 *__restrict__ wsh, u64 *out,
@@ -505,7 +519,7 @@ __global__ __launch_bounds__(BLOCK) void degree_reduce_fixed_kernel(const u64 *c
     const size_t e = (size_t)blockIdx.x * BLOCK + threadIdx.x;
     if (e >= count) return;
     u64 o[N], secret;
-    reduce_truncate_fixed<N, T, TRUNC>(e, count, e, count, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
+    reduce_truncate_fixed<N, T, TRUNC, STREAM>(e, count, e, count, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
 #pragma unroll
     for (int m = 0; m < N; m++) out[(size_t)m * count + e] = o[m];
     if (TRUNC && rec) rec[e] = secret;   // if asked for, REC of the result
@@ -513,7 +527,7 @@ __global__ __launch_bounds__(BLOCK) void degree_reduce_fixed_kernel(const u64 *c
 
 // ReLU under the multiplicative mask for one element (the three steps of relu_kernel below), n and t
 // fixed: x[] the n shares, r[] the n output shares
-template <int N, int T>
+template <int N, int T, bool STREAM>
 __device__ __forceinline__ void relu_fixed(const u64 (&x)[N], size_t em, size_t mcount, const u64 (&b)[2 * T + 1],
                                            const u64 (&bi)[N], u64 *__restrict__ msg, u64 *__restrict__ yplain,
                                            const ss_nl_params &np, u64 (&r)[N])
@@ -524,12 +538,12 @@ __device__ __forceinline__ void relu_fixed(const u64 (&x)[N], size_t em, size_t 
 #pragma unroll
     for (int i = 0; i < NR; i++) {
         const u64 m = ss_mul(x[i], b[i]);
-        msg[(size_t)i * mcount + em] = m;
+        send<STREAM>(msg + (size_t)i * mcount + em, m);
         acc.mac(m, np.ilambda[i]);
     }
     const u64 v = np.dinv == 1 ? acc.value() : ss_mul(acc.value(), np.dinv);
     const u64 y = v <= (SS_P - 1) / 2 ? v : 0;
-    yplain[em] = y;
+    send<STREAM>(yplain + em, y);
 #pragma unroll
     for (int m = 0; m < N; m++) r[m] = ss_mul(y, bi[m]);
 }
@@ -542,7 +556,7 @@ __device__ __forceinline__ void relu_fixed(const u64 (&x)[N], size_t em, size_t 
 // order of this kernel's threads (so that a wave writes 512 consecutive bytes of every message plane): the
 // element of thread t of block (x, y) is at position (y gridDim.x + x) 256 + t of a plane of gridDim.x
 // gridDim.y 256 positions.
-template <int N, int T>
+template <int N, int T, bool STREAM>
 __global__ __launch_bounds__(BLOCK) void layer_tail_kernel(const u64 *c, u64 *__restrict__ msg1, u64 *__restrict__ msg2,
                                                            u64 *__restrict__ umsg, u64 *__restrict__ wsh,
                                                            u64 *__restrict__ rmsg, u64 *__restrict__ yplain,
@@ -578,8 +592,8 @@ __global__ __launch_bounds__(BLOCK) void layer_tail_kernel(const u64 *c, u64 *__
 #pragma unroll
         for (int m = 0; m < N; m++) mbi[m] = sh_bi[(size_t)m * count + e];
         u64 secret;
-        reduce_truncate_fixed<N, T, true>(e, count, em, mcount, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
-        relu_fixed<N, T>(o, em, mcount, mb, mbi, rmsg, yplain, np, r);
+        reduce_truncate_fixed<N, T, true, STREAM>(e, count, em, mcount, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
+        relu_fixed<N, T, STREAM>(o, em, mcount, mb, mbi, rmsg, yplain, np, r);
 #pragma unroll
         for (int p = 0; p < N; p++) {
             out[(size_t)p * count + e] = r[p];
@@ -909,7 +923,7 @@ __global__ __launch_bounds__(BLOCK) void nonlinear_masks_kernel(u64 *__restrict_
 //      signed value, in the clear                                   -> yplain
 //   3. every party: out_i = y * betainv_i                            -> out[i]
 // MASKOFF = false stops after step 2 (the pooled form continues from yplain in another kernel).
-template <int VEC, bool MASKOFF = true>
+template <int VEC, bool MASKOFF, bool STREAM>
 __global__ __launch_bounds__(BLOCK) void relu_kernel(const u64 *x, const u64 *__restrict__ sh_b,
                                                      const u64 *__restrict__ sh_bi, u64 *__restrict__ msg,
                                                      u64 *__restrict__ yplain, u64 *out, size_t count,
@@ -942,7 +956,7 @@ __global__ __launch_bounds__(BLOCK) void relu_kernel(const u64 *x, const u64 *__
                 m.v[u] = ss_mul(xi[i].v[u], bi[i].v[u]);
                 acc[u].mac(m.v[u], np.ilambda[i]);
             }
-            m.store(msg + (size_t)i * count + e0);
+            m.template send<STREAM>(msg + (size_t)i * count + e0);
         }
     }
     pack_t<VEC> y;
@@ -951,7 +965,10 @@ __global__ __launch_bounds__(BLOCK) void relu_kernel(const u64 *x, const u64 *__
         const u64 v = np.dinv == 1 ? acc[u].value() : ss_mul(acc[u].value(), np.dinv);
         y.v[u] = v <= (SS_P - 1) / 2 ? v : 0;   // negative values are the upper half of the field
     }
-    y.store(yplain + e0);
+    if constexpr (MASKOFF)
+        y.template send<STREAM>(yplain + e0);
+    else
+        y.store(yplain + e0);   // read by the pooling launch
 #pragma unroll
     for (int m = 0; m < SS_MAXN; m++) {
         if (MASKOFF && m < np.n) {
@@ -1024,6 +1041,12 @@ constexpr size_t LANES_MAX_COUNT = 160 * 1024;   // measured cross-over on MI355
 // the same cross-over against the kernels with n and t fixed at compile time
 constexpr size_t LANES_MAX_COUNT_FIXED = 8 * 1024;
 
+// Messages are written once and not read by the library again.  Left to the caches they cost nothing while a call's
+// traffic fits the 256 MB of the last level (the next call overwrites them there); beyond, writing them past the
+// caches is faster.  44 planes written per 5 read, no arithmetic, MI355X: 24.4 / 26.7 us (cached / streamed) at 157 MB,
+// 56.2 / 53.1 us at 315 MB, 324 / 273 us at 1.65 GB.
+inline bool streams_messages(size_t words) { return words * sizeof(u64) > ((size_t)256 << 20); }
+
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 inline unsigned blocks_for(size_t count, int vec)
@@ -1087,6 +1110,16 @@ hipError_t ss_launch_sum_planes(u64 *dst, const u64 *c, size_t total, const ss_p
     return hipGetLastError();
 }
 
+// words per element: the shares read and written, the messages of reduction and (TR) truncation
+#define SS_REDUCE_FIXED(NC, TC, TR, U, W, REC, TP)                                                                        \
+    do {                                                                                                                  \
+        constexpr size_t words = 2 * NC + (2 * TC + 1) * (TC + 1) + (TC + 1) * NC + (TR ? TC + 1 + NC : 0);               \
+        hipLaunchKernelGGL((streams_messages(words * count) ? degree_reduce_fixed_kernel<NC, TC, TR, true>                \
+                                                            : degree_reduce_fixed_kernel<NC, TC, TR, false>),             \
+                           dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, (u64 *)(U), (u64 *)(W), out, \
+                           (u64 *)(REC), count, dp, TP, ps);                                                              \
+    } while (0)
+
 hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out, size_t count,
                                    const ss_dr_params &dp, const ss_part_src &ps, hipStream_t stream)
 {
@@ -1097,11 +1130,9 @@ hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out,
         hipLaunchKernelGGL(degree_reduce_lanes_kernel<false>, dim3((unsigned)((count + 31) / 32)), dim3(BLOCK), 0, stream,
                            c, msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, norec, ps);
     else if (dp.n == 5 && dp.t == 2)
-        hipLaunchKernelGGL((degree_reduce_fixed_kernel<5, 2, false>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c,
-                           msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, ps);
+        SS_REDUCE_FIXED(5, 2, false, nullptr, nullptr, nullptr, none);
     else if (dp.n == 3 && dp.t == 1)
-        hipLaunchKernelGGL((degree_reduce_fixed_kernel<3, 1, false>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c,
-                           msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, ps);
+        SS_REDUCE_FIXED(3, 1, false, nullptr, nullptr, nullptr, none);
     else   // one element per thread: the k*k + n wide accumulators of two elements would not fit the register file
         hipLaunchKernelGGL((degree_reduce_kernel<1, false>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1,
                            msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, norec, ps);
@@ -1120,11 +1151,9 @@ hipError_t ss_launch_degree_reduce_truncate(const u64 *c, u64 *msg1, u64 *msg2, 
         hipLaunchKernelGGL(degree_reduce_lanes_kernel<true>, dim3((unsigned)((count + 31) / 32)), dim3(BLOCK), 0, stream,
                            c, msg1, msg2, u, wsh, out, rec, count, dp, tp, rf, ps);
     else if (dp.n == 5 && dp.t == 2)
-        hipLaunchKernelGGL((degree_reduce_fixed_kernel<5, 2, true>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c,
-                           msg1, msg2, u, wsh, out, rec, count, dp, tp, ps);
+        SS_REDUCE_FIXED(5, 2, true, u, wsh, rec, tp);
     else if (dp.n == 3 && dp.t == 1)
-        hipLaunchKernelGGL((degree_reduce_fixed_kernel<3, 1, true>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c,
-                           msg1, msg2, u, wsh, out, rec, count, dp, tp, ps);
+        SS_REDUCE_FIXED(3, 1, true, u, wsh, rec, tp);
     else
         hipLaunchKernelGGL((degree_reduce_kernel<1, true>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1,
                            msg2, u, wsh, out, rec, count, dp, tp, rf, ps);
@@ -1153,8 +1182,16 @@ hipError_t ss_launch_relu(const u64 *x, const u64 *sh_b, const u64 *sh_bi, u64 *
 {
     const bool v2 = (count % 2 == 0) && aligned16(x) && aligned16(sh_b) && aligned16(sh_bi) && aligned16(msg) &&
                     aligned16(yplain) && aligned16(out) && count >= VEC2_MIN_COUNT;
-    auto grid = [&](int vec) { return dim3(blocks_for(count, vec)); };
-    SS_DISPATCH_VEC(v2, relu_kernel, grid, x, sh_b, sh_bi, msg, yplain, out, count, np);
+    const size_t nr = 2 * np.t + 1, n = np.n;
+    const bool streams = streams_messages((2 * n + nr + n + nr + 1) * count);
+#define SS_RELU(VEC)                                                                                                       \
+    hipLaunchKernelGGL((streams ? relu_kernel<VEC, true, true> : relu_kernel<VEC, true, false>), dim3(blocks_for(count, VEC)), \
+                       dim3(BLOCK), 0, stream, x, sh_b, sh_bi, msg, yplain, out, count, np)
+    if (v2)
+        SS_RELU(2);
+    else
+        SS_RELU(1);
+#undef SS_RELU
     return hipGetLastError();
 }
 
@@ -1172,8 +1209,9 @@ hipError_t ss_launch_relu_pool(const u64 *x, const u64 *sh_b, const u64 *sh_bi, 
                                hipStream_t stream)
 {
     const size_t cin = planes * g.H * g.W, cout = planes * g.Ho * g.Wo;
-    hipLaunchKernelGGL((relu_kernel<1, false>), dim3(blocks_for(cin, 1)), dim3(BLOCK), 0, stream, x, sh_b,
-                       (const u64 *)nullptr, msg, rplain, (u64 *)nullptr, cin, np);
+    const bool streams = streams_messages((size_t)(3 * (2 * np.t + 1) + 1) * cin);
+    hipLaunchKernelGGL((streams ? relu_kernel<1, false, true> : relu_kernel<1, false, false>), dim3(blocks_for(cin, 1)),
+                       dim3(BLOCK), 0, stream, x, sh_b, (const u64 *)nullptr, msg, rplain, (u64 *)nullptr, cin, np);
     hipLaunchKernelGGL(pool_maskoff_kernel, dim3(blocks_for(cout, 1)), dim3(BLOCK), 0, stream, rplain, sh_bi, yplain, out,
                        cout, g, np.n);
     return hipGetLastError();
@@ -1209,14 +1247,20 @@ hipError_t ss_launch_layer_tail(const u64 *c, u64 *msg1, u64 *msg2, u64 *umsg, u
     if (tp.kdiv != 1) return hipErrorInvalidValue;   // no rounding division in this kernel
     const dim3 grid((B * HW + 15) / 16, (C + 15) / 16), block(BLOCK);
     const size_t party_bytes = ss_planes_bytes(B, C, HW, 1);
+    const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
+    // shares in and out, mask shares, messages
+    const bool streams = streams_messages((2 * n + nr + n + nr * k + k * n + k + n + nr + 1) * (size_t)B * C * HW);
+#define SS_TAIL(NC, TC)                                                                                                \
+    hipLaunchKernelGGL((streams ? layer_tail_kernel<NC, TC, true> : layer_tail_kernel<NC, TC, false>), grid, block, 0, \
+                       stream, c, msg1, msg2, umsg, wsh, rmsg, yplain, sh_b, sh_bi, out, (signed char *)planes, B, C, HW, \
+                       party_bytes, dp, tp, np, ps)
     if (dp.n == 5 && dp.t == 2)
-        hipLaunchKernelGGL((layer_tail_kernel<5, 2>), grid, block, 0, stream, c, msg1, msg2, umsg, wsh, rmsg, yplain, sh_b,
-                           sh_bi, out, (signed char *)planes, B, C, HW, party_bytes, dp, tp, np, ps);
+        SS_TAIL(5, 2);
     else if (dp.n == 3 && dp.t == 1)
-        hipLaunchKernelGGL((layer_tail_kernel<3, 1>), grid, block, 0, stream, c, msg1, msg2, umsg, wsh, rmsg, yplain, sh_b,
-                           sh_bi, out, (signed char *)planes, B, C, HW, party_bytes, dp, tp, np, ps);
+        SS_TAIL(3, 1);
     else
         return hipErrorInvalidValue;   // the caller runs the separate kernels for other schemes
+#undef SS_TAIL
     return hipGetLastError();
 }
 
