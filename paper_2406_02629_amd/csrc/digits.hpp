@@ -18,20 +18,50 @@ __device__ __forceinline__ u32 limb_dword(const u64 (&y)[4], int limb)
     return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, sel), __builtin_amdgcn_perm(b, a, sel), 0x05040100u);
 }
 
-// Limb dwords of a block of 16 pixels x 16 channels, staged in LDS as [party][limb][pixel][group of four
-// channels], to limb planes (per party [limb][channel block of 16][pixel][16 channels], int8): thread t of the 256
-// takes limb t/16 % SS_NLIMB of pixel t%16 for the parties t/(16 SS_NLIMB), that + 2, ... and writes the 16 channels
-// c0..c0+15 as one 16-byte store; 16 threads make 256 bytes in a row.
+// Limb dwords of the digit words that the lanes of a 256-thread block hold one per party: lane l of wave w has row (pixel)
+// l%16 and contraction index (channel) 4 w + l/16 of the block -> stage[party][limb][row][w].  The four lanes of a row
+// swap their digit words, after which each of them owns all four and writes two of the limb dwords.
+template <int MAXP>
+__device__ __forceinline__ void stage_limbs(const u64 (&dig)[MAXP], u32 (&stage)[MAXP][SS_NLIMB][16][4], int n)
+{
+    const int lane = threadIdx.x & 63, r16 = lane & 15, j = lane >> 4, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int p = 0; p < MAXP; p++) {
+        if (p < n) {
+            u64 y[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) y[q] = __shfl(dig[p], r16 + 16 * q);
+            if (2 * j < SS_NLIMB) {
+                stage[p][2 * j][r16][w] = limb_dword(y, 2 * j);
+                stage[p][2 * j + 1][r16][w] = limb_dword(y, 2 * j + 1);
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// ... and out of LDS: thread t of the 256 takes limb t/16 % SS_NLIMB of row t%16 for the parties t/(16 SS_NLIMB), that
+// + 2, ... and writes its 16 bytes to where(party, limb, row) (nullptr: not at all); the 16 rows of a (party, limb) lie
+// one after the other, so that 16 threads make 256 bytes in a row (a dword per wave would be a store of 4 of every 16
+// bytes).
+template <int MAXP, typename F>
+__device__ __forceinline__ void store_staged(const u32 (&stage)[MAXP][SS_NLIMB][16][4], int n, F &&where)
+{
+    constexpr int PSTEP = 256 / (16 * SS_NLIMB);   // parties in flight: 2
+    const int t = threadIdx.x, row = t & 15, limb = (t >> 4) % SS_NLIMB, p0 = t / (16 * SS_NLIMB);
+    if (p0 >= PSTEP) return;
+    for (int p = p0; p < n; p += PSTEP)
+        if (signed char *dst = where(p, limb, row)) *reinterpret_cast<int4 *>(dst) = *reinterpret_cast<const int4 *>(&stage[p][limb][row][0]);
+}
+
+// to limb planes (per party [limb][channel block of 16][pixel][16 channels], int8): the channels c0..c0+15 of the pixels
+// pix0..pix0+15
 template <int MAXP>
 __device__ __forceinline__ void store_staged_planes(const u32 (&stage)[MAXP][SS_NLIMB][16][4],
                                                     signed char *__restrict__ planes, size_t party_bytes, size_t plane,
                                                     int pix0, int npix, int c0, int n)
 {
-    constexpr int PSTEP = 256 / (16 * SS_NLIMB);   // parties in flight: 2
-    const int t = threadIdx.x, px = t & 15, limb = (t >> 4) % SS_NLIMB, p0 = t / (16 * SS_NLIMB);
-    if (pix0 + px >= npix || p0 >= PSTEP) return;
-    for (int p = p0; p < n; p += PSTEP) {
-        const int4 val = *reinterpret_cast<const int4 *>(&stage[p][limb][px][0]);
-        *reinterpret_cast<int4 *>(planes + p * party_bytes + (size_t)limb * plane + ((size_t)(c0 >> 4) * npix + pix0 + px) * 16) = val;
-    }
+    store_staged<MAXP>(stage, n, [&](int p, int limb, int px) {
+        return pix0 + px < npix ? planes + p * party_bytes + limb * plane + ((size_t)(c0 >> 4) * npix + pix0 + px) * 16 : nullptr;
+    });
 }

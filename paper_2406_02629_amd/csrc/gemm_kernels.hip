@@ -99,9 +99,8 @@ __global__ __launch_bounds__(256) void pack_im2col_kernel(const u64 *__restrict_
 }
 
 // The two kernels below take one element per thread: lane l of a wave holds row (or pixel) l%16 and the
-// contraction index (or channel) 4 g + l/16 of the wave's group g of four.  The four lanes of a row swap
-// their digit words (ds_bpermute), after which each of them owns all four and writes two of the eight limb
-// dwords.  The layers of a batch-1 network are small: one element per thread is what fills the chip.
+// contraction index (or channel) 4 g + l/16 of the wave's group g of four, and the limb dwords of the block leave
+// through LDS (stage_limbs).  The layers of a batch-1 network are small: one element per thread is what fills the chip.
 
 // shares of element e of the plaintext tensor, as GEN (Eq. 1) draws them (element index = position in the
 // tensor, so the values are those of the plain share kernel): stored, and returned as digit words
@@ -153,20 +152,10 @@ __global__ __launch_bounds__(256) void share_pack_kernel(const u64 *__restrict__
         const int b = row / HW, hw = row - b * HW;
         gen_digits<N, T>(secret, shares, (size_t)B * K * HW, ((size_t)b * K + k) * HW + hw, n, t, keys, dig);
     }
-    u32 *base = reinterpret_cast<u32 *>(dst + ((size_t)rb * Kb + kb) * TILE) + (r16 + 16 * (kq >> 2)) * 4 + (kq & 3);
-#pragma unroll
-    for (int p = 0; p < MAXP; p++) {
-        if (p < n) {
-            u64 y[4];
-#pragma unroll
-            for (int q = 0; q < 4; q++) y[q] = __shfl(dig[p], r16 + 16 * q);
-            u32 *bp = base + (size_t)p * dst_party_stride * 4;
-            if (2 * j < NL) {   // lane group j writes limbs 2j and 2j+1
-                bp[(2 * j) * 256] = limb_dword(y, 2 * j);
-                bp[(2 * j + 1) * 256] = limb_dword(y, 2 * j + 1);
-            }
-        }
-    }
+    __shared__ __align__(16) u32 stage[MAXP][NL][16][4];   // [party][limb][row][wave]
+    stage_limbs<MAXP>(dig, stage, n);
+    signed char *tile = reinterpret_cast<signed char *>(dst + ((size_t)rb * Kb + kb) * TILE + 16 * (kq >> 2));   // kq / 4 is the same for all waves
+    store_staged<MAXP>(stage, n, [&](int p, int limb, int r) { return tile + (p * dst_party_stride + limb * 64 + r) * 16; });
 }
 
 // Conv input [B][C][H][W] -> limb planes [party][limb][channel block of 16][b][h][w][16 channels] (int8), the form
@@ -204,23 +193,8 @@ __global__ __launch_bounds__(256) void planes_kernel(const u64 *__restrict__ in,
                 if (p < n) dig[p] = balanced_digits(in[(size_t)p * plane + e]);
         }
     }
-    // The four lanes of a pixel swap their digit words, the limb dwords of the wave's four channels go through
-    // LDS, and the block's 16 channels of its 16 pixels leave as 256 bytes in a row.
     __shared__ __align__(16) u32 stage[MAXP][NL][16][4];   // [party][limb][pixel][wave]
-    const int w = threadIdx.x >> 6;
-#pragma unroll
-    for (int p = 0; p < MAXP; p++) {
-        if (p < n) {
-            u64 y[4];
-#pragma unroll
-            for (int q = 0; q < 4; q++) y[q] = __shfl(dig[p], r16 + 16 * q);
-            if (2 * j < NL) {
-                stage[p][2 * j][r16][w] = limb_dword(y, 2 * j);
-                stage[p][2 * j + 1][r16][w] = limb_dword(y, 2 * j + 1);
-            }
-        }
-    }
-    __syncthreads();
+    stage_limbs<MAXP>(dig, stage, n);
     store_staged_planes<MAXP>(stage, planes, party_bytes, plane, blockIdx.x * 16, B * HW, blockIdx.y * 16, n);
 }
 

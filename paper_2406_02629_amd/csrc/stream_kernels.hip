@@ -533,15 +533,16 @@ __device__ __forceinline__ void relu_fixed(const u64 (&x)[N], size_t em, size_t 
                                            const ss_nl_params &np, u64 (&r)[N])
 {
     constexpr int NR = 2 * T + 1;
-    ss_sacc acc;
+    ss_sacc2 acc;
     acc.clear();
 #pragma unroll
     for (int i = 0; i < NR; i++) {
         const u64 m = ss_mul(x[i], b[i]);
         send<STREAM>(msg + (size_t)i * mcount + em, m);
-        acc.mac(m, np.ilambda[i]);
+        SS_SPLIT31(m, w0, w1);
+        acc.mac(w0, w1, np.ilambda[i]);
     }
-    const u64 v = np.dinv == 1 ? acc.value() : ss_mul(acc.value(), np.dinv);
+    const u64 v = acc.value();   // the multipliers of IDs 1..2t+1 are integers
     const u64 y = v <= (SS_P - 1) / 2 ? v : 0;
     send<STREAM>(yplain + em, y);
 #pragma unroll
@@ -601,21 +602,8 @@ __global__ __launch_bounds__(BLOCK) void layer_tail_kernel(const u64 *c, u64 *__
         }
     }
     if (!planes) return;   // uniform
-    // the four lanes of a pixel swap their digit words; the limb dwords go through LDS and leave as 16-byte
-    // stores of the block's 16 channels (see store_staged_planes)
     __shared__ __align__(16) u32 stage[N][SS_NLIMB][16][4];   // [party][limb][pixel][wave]
-    const int w = threadIdx.x >> 6;
-#pragma unroll
-    for (int p = 0; p < N; p++) {
-        u64 y[4];
-#pragma unroll
-        for (int q = 0; q < 4; q++) y[q] = __shfl(dig[p], r16 + 16 * q);
-        if (2 * j < SS_NLIMB) {
-            stage[p][2 * j][r16][w] = limb_dword(y, 2 * j);
-            stage[p][2 * j + 1][r16][w] = limb_dword(y, 2 * j + 1);
-        }
-    }
-    __syncthreads();
+    stage_limbs<N>(dig, stage, N);
     store_staged_planes<N>(stage, planes, party_bytes, count, blockIdx.x * 16, B * HW, blockIdx.y * 16, N);
 }
 
@@ -667,20 +655,7 @@ __global__ __launch_bounds__(BLOCK) void tail_direct_kernel(const u64 *c, const 
     }
     if (!planes) return;   // uniform
     __shared__ __align__(16) u32 stage[SS_MAXN][SS_NLIMB][16][4];   // [party][limb][pixel][wave]
-    const int w = threadIdx.x >> 6;
-#pragma unroll
-    for (int p = 0; p < SS_MAXN; p++) {
-        if (p < n) {
-            u64 y4[4];
-#pragma unroll
-            for (int q = 0; q < 4; q++) y4[q] = __shfl(dig[p], r16 + 16 * q);
-            if (2 * j < SS_NLIMB) {
-                stage[p][2 * j][r16][w] = limb_dword(y4, 2 * j);
-                stage[p][2 * j + 1][r16][w] = limb_dword(y4, 2 * j + 1);
-            }
-        }
-    }
-    __syncthreads();
+    stage_limbs<SS_MAXN>(dig, stage, n);
     store_staged_planes<SS_MAXN>(stage, planes, party_bytes, count, blockIdx.x * 16, B * HW, blockIdx.y * 16, n);
 }
 
