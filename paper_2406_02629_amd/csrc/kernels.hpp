@@ -45,11 +45,6 @@ struct ss_tr_params {             // truncation constants
     int ilambda[SS_MAXK];
 };
 
-struct ss_recf_params {           // REC fused behind another step: multiplier of every party's share
-    int coef[SS_MAXN];            // ilambda of the party, 0 for a party that does not take part
-    u64 dinv;
-};
-
 struct ss_nl_params {             // SSS-NonLinear
     int n, t, bbits;              // beta uniform in [1, 2^bbits]
     u64 beta_key;
@@ -85,15 +80,15 @@ hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out,
 hipError_t ss_launch_sum_planes(u64 *dst, const u64 *c, size_t total, const ss_part_src &ps, hipStream_t stream);
 hipError_t ss_launch_truncate(const u64 *x, u64 *u, u64 *wsh, u64 *out, size_t count, const ss_tr_params &tp,
                               hipStream_t stream);
-// rec != nullptr: also REC of the truncated shares with the multipliers rf (one more output, same launch)
+// rec != nullptr: also REC of the truncated shares (one more output, same launch)
 hipError_t ss_launch_degree_reduce_truncate(const u64 *c, u64 *msg1, u64 *msg2, u64 *u, u64 *wsh, u64 *out,
                                             u64 *rec, size_t count, const ss_dr_params &dp, const ss_tr_params &tp,
-                                            const ss_recf_params &rf, const ss_part_src &ps, hipStream_t stream);
+                                            const ss_part_src &ps, hipStream_t stream);
 
 // outputs of reduction + truncation taken directly from the secret (no messages); open_all carries the
 // multipliers of REC from the IDs 1..2t+1
 hipError_t ss_launch_reduce_truncate_direct(const u64 *c, u64 *out, u64 *rec, size_t count, const ss_nl_params &open_all,
-                                            const ss_tr_params &tp, const ss_recf_params &rf, hipStream_t stream);
+                                            const ss_tr_params &tp, const ss_part_src &ps, hipStream_t stream);
 // SSS-NonLinear (Sec. VI-C): the trusted source's masks, then ReLU under the mask
 hipError_t ss_launch_nonlinear_masks(u64 *sh_b, u64 *sh_bi, size_t count, const ss_nl_params &np, hipStream_t stream);
 hipError_t ss_launch_relu(const u64 *x, const u64 *sh_b, const u64 *sh_bi, u64 *msg, u64 *yplain, u64 *out,

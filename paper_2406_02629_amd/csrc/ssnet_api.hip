@@ -907,24 +907,26 @@ int ssnet_truncate_div(ssnet_ctx *ctx, const uint64_t *d_x, size_t count, int kd
 
 namespace {
 
+// IDs to reconstruct a degree-t sharing from: distinct, in 1..n, at least t+1 of them.  (The kernels that open a sharing
+// they have just made know its secret; which of the admissible IDs are named does not matter to them.)
+static int check_ids(const ssnet_ctx *ctx, const int *party_ids, int m)
+{
+    if (!party_ids || m < 1 || m > ctx->n) return SSNET_EINVAL;
+    for (int i = 0; i < m; i++) {
+        if (party_ids[i] < 1 || party_ids[i] > ctx->n) return SSNET_EID;
+        for (int j = 0; j < i; j++)
+            if (party_ids[j] == party_ids[i]) return SSNET_EID;
+    }
+    return m < ctx->t + 1 ? SSNET_ESHARES : SSNET_OK;
+}
+
 // shared by the two fused entry points; d_rec == nullptr: no reconstruction
 static int degree_reduce_truncate(ssnet_ctx *ctx, const uint64_t *d_c, size_t count, uint64_t stream_id, uint64_t *d_out,
                            const int *party_ids, int m, uint64_t *d_rec, int kdiv = 1)
 {
     if (!ctx || !d_out || count == 0 || count > MAX_COUNT || !kdiv_fits(ctx, kdiv)) return SSNET_EINVAL;
-    ss_recf_params rf = {};
-    if (d_rec) {
-        if (!party_ids || m < 1 || m > ctx->n) return SSNET_EINVAL;
-        for (int i = 0; i < m; i++) {
-            if (party_ids[i] < 1 || party_ids[i] > ctx->n) return SSNET_EID;
-            for (int j = 0; j < i; j++)
-                if (party_ids[j] == party_ids[i]) return SSNET_EID;
-        }
-        if (m < ctx->t + 1) return SSNET_ESHARES;
-        int il[SS_MAXN];
-        if (!h_lagrange_int(party_ids, m, il, &rf.dinv)) return SSNET_EINVAL;
-        for (int i = 0; i < m; i++) rf.coef[party_ids[i] - 1] = il[i];
-    }
+    if (d_rec)
+        if (int rc = check_ids(ctx, party_ids, m)) return rc;
     const int k = ctx->t + 1, nr = 2 * ctx->t + 1, n = ctx->n;
     const size_t need = ((size_t)nr * k + (size_t)k * n + k + n) * count * 8;
     const u64 *c;
@@ -936,7 +938,7 @@ static int degree_reduce_truncate(ssnet_ctx *ctx, const uint64_t *d_c, size_t co
     set_kdiv(ctx, tp, kdiv);
     timed tm(ctx, SSNET_PROF_DEGREE_REDUCE);
     hipError_t e = ss_launch_degree_reduce_truncate(c, msg1, msg2, u, wsh, d_out, d_rec, count,
-                                                    make_dr_params(ctx, stream_id), tp, rf, ps, ctx->stream);
+                                                    make_dr_params(ctx, stream_id), tp, ps, ctx->stream);
     return e == hipSuccess ? SSNET_OK : fail_hip(ctx, e);
 }
 
@@ -985,33 +987,17 @@ int ssnet_reduce_truncate_direct(ssnet_ctx *ctx, const uint64_t *d_c, size_t cou
                                  uint64_t *d_out, const int *party_ids, int m, uint64_t *d_secret)
 {
     if (!ctx || !d_out || count == 0 || count > MAX_COUNT) return SSNET_EINVAL;
-    ss_recf_params rf = {};
-    if (d_secret) {
-        if (!party_ids || m < 1 || m > ctx->n) return SSNET_EINVAL;
-        for (int i = 0; i < m; i++) {
-            if (party_ids[i] < 1 || party_ids[i] > ctx->n) return SSNET_EID;
-            for (int j = 0; j < i; j++)
-                if (party_ids[j] == party_ids[i]) return SSNET_EID;
-        }
-        if (m < ctx->t + 1) return SSNET_ESHARES;
-        int il[SS_MAXN];
-        if (!h_lagrange_int(party_ids, m, il, &rf.dinv)) return SSNET_EINVAL;
-        for (int i = 0; i < m; i++) rf.coef[party_ids[i] - 1] = il[i];
-    }
+    if (d_secret)
+        if (int rc = check_ids(ctx, party_ids, m)) return rc;
     ss_nl_params open_all;
     if (!make_nl_params(ctx, 0, &open_all)) return SSNET_EINVAL;
     const u64 *c = d_c;
-    if (!d_c) {   // the pending product: this kernel reads one plane, so the planes are summed first
-        ss_part_src ps;
+    ss_part_src ps = {1, 0};
+    if (!d_c)
         if (int rc = incoming_product(ctx, nullptr, count, 0, &c, &ps)) return rc;
-        timed tm(ctx, SSNET_PROF_DEGREE_REDUCE);
-        hipError_t e = ss_launch_sum_planes(ctx->pending.base, ctx->pending.base, (size_t)ctx->n * count, ps, ctx->stream);
-        if (e != hipSuccess) return fail_hip(ctx, e);
-        ctx->pending.planes = 1;
-    }
     timed tm(ctx, SSNET_PROF_DEGREE_REDUCE);
-    hipError_t e = ss_launch_reduce_truncate_direct(c, d_out, d_secret, count, open_all, make_tr_params(ctx, stream_id),
-                                                    rf, ctx->stream);
+    hipError_t e = ss_launch_reduce_truncate_direct(c, d_out, d_secret, count, open_all, make_tr_params(ctx, stream_id), ps,
+                                                    ctx->stream);
     return e == hipSuccess ? SSNET_OK : fail_hip(ctx, e);
 }
 
@@ -1066,11 +1052,9 @@ int ssnet_reduce_truncate_relu(ssnet_ctx *ctx, const uint64_t *d_c, int B, int C
         e = ss_launch_layer_tail(c, msg1, msg2, u, wsh, rmsg, yplain, d_beta, d_betainv, d_out, d_planes, B, C, HW, dp, tp, np,
                                  ps, ctx->stream);
     } else {   // other schemes: the same steps, messages and results in three launches
-        const ss_recf_params norec = {};
         {
             timed tm(ctx, SSNET_PROF_DEGREE_REDUCE);
-            e = ss_launch_degree_reduce_truncate(c, msg1, msg2, u, wsh, d_out, nullptr, count, dp, tp, norec, ps,
-                                                 ctx->stream);
+            e = ss_launch_degree_reduce_truncate(c, msg1, msg2, u, wsh, d_out, nullptr, count, dp, tp, ps, ctx->stream);
         }
         if (e == hipSuccess) {
             timed tm(ctx, SSNET_PROF_NONLINEAR);

@@ -175,220 +175,34 @@ __device__ __forceinline__ u64 shift_round_div(u64 v, int f, int kdiv)
     return a >= 0 ? (u64)a / d : SS_P - ((u64)(-a) + d - 1) / d;
 }
 
-// The three steps of masked truncation for the elements a thread owns, with
-// the same send-to-workspace / receive-from-registers convention as above:
-//   1. parties q = 1..k add their share of alpha = e * 2^f          -> umsg[q]
-//      (alpha = e * 2^f * kdiv with the rounding division)
-//   2. the elite party reconstructs x + alpha, divides by 2^f with floor on
-//      the signed value (then by kdiv with rounding) and shares the quotient -> wsh[m]
-//   3. every party m adds its share of alpha~ = -e                   -> out[m]
-// x[q] holds the shares of parties q+1 = 1..k.  With rec != nullptr the new
-// shares are also reconstructed (REC, Eq. 2) with the multipliers rf   -> rec
-template <int VEC>
-__device__ __forceinline__ void truncate_steps(const pack_t<VEC> *x, u64 *__restrict__ umsg, u64 *__restrict__ wsh,
-                                               u64 *out, size_t count, size_t e0, const ss_tr_params &tp,
-                                               u64 *__restrict__ rec, const ss_recf_params &rf)
-{
-    const int k = tp.t + 1;
-    u64 ev[VEC], ca[VEC][SS_MAXT];
-    ss_sacc acc[VEC];
-#pragma unroll
-    for (int u = 0; u < VEC; u++) {
-        ev[u] = tp.kdiv > 1 ? mask_e_below(tp.e_key, e0 + u, tp.e_range) : mask_e(tp.e_key, e0 + u, tp.f);
-        draw_coeffs<SS_MAXT>(ca[u], tp.alpha_key, tp.t, e0 + u);
-        acc[u].clear();
-    }
-#pragma unroll
-    for (int q = 0; q < SS_MAXK; q++) {
-        if (q < k) {
-            pack_t<VEC> s;
-#pragma unroll
-            for (int u = 0; u < VEC; u++) {
-                const u64 alpha = tp.kdiv > 1 ? (ev[u] * (u64)tp.kdiv) << tp.f : ev[u] << tp.f;   // <= 2^32
-                s.v[u] = ss_add(x[q].v[u], ss_poly_eval<SS_MAXT>(alpha, ca[u], tp.t, q + 1));
-                acc[u].mac(s.v[u], tp.ilambda[q]);
-            }
-            s.store(umsg + (size_t)q * count + e0);
-        }
-    }
-    u64 w[VEC], at[VEC], cw[VEC][SS_MAXT], cat[VEC][SS_MAXT];
-#pragma unroll
-    for (int u = 0; u < VEC; u++) {
-        w[u] = tp.kdiv > 1 ? shift_round_div(acc[u].value(), tp.f, tp.kdiv) : shift_signed(acc[u].value(), tp.f);
-        at[u] = SS_P - ev[u];
-        draw_coeffs<SS_MAXT>(cw[u], tp.gen_key, tp.t, e0 + u);
-        draw_coeffs<SS_MAXT>(cat[u], tp.alphat_key, tp.t, e0 + u);
-    }
-    ss_sacc racc[VEC];
-#pragma unroll
-    for (int u = 0; u < VEC; u++) racc[u].clear();
-#pragma unroll
-    for (int m = 0; m < SS_MAXN; m++) {
-        if (m < tp.n) {
-            pack_t<VEC> ws, s;
-#pragma unroll
-            for (int u = 0; u < VEC; u++) {
-                ws.v[u] = ss_poly_eval<SS_MAXT>(w[u], cw[u], tp.t, m + 1);
-                s.v[u] = ss_add(ws.v[u], ss_poly_eval<SS_MAXT>(at[u], cat[u], tp.t, m + 1));
-                if (rec && rf.coef[m] != 0) racc[u].mac(s.v[u], rf.coef[m]);
-            }
-            ws.store(wsh + (size_t)m * count + e0);
-            s.store(out + (size_t)m * count + e0);
-        }
-    }
-    if (rec) {
-        pack_t<VEC> r;
-#pragma unroll
-        for (int u = 0; u < VEC; u++) r.v[u] = rf.dinv == 1 ? racc[u].value() : ss_mul(racc[u].value(), rf.dinv);
-        r.store(rec + e0);
-    }
-}
-
-template <int VEC>
-__global__ __launch_bounds__(BLOCK) void truncate_kernel(const u64 *x, u64 *__restrict__ umsg,
-                                                         u64 *__restrict__ wsh, u64 *out, size_t count,
-                                                         ss_tr_params tp)
-{
-    const size_t e0 = ((size_t)blockIdx.x * BLOCK + threadIdx.x) * VEC;
-    if (e0 >= count) return;
-    pack_t<VEC> xs[SS_MAXK];
-#pragma unroll
-    for (int q = 0; q < SS_MAXK; q++)
-        if (q <= tp.t) xs[q].load(x + (size_t)q * count + e0);
-    const ss_recf_params none = {};
-    truncate_steps<VEC>(xs, umsg, wsh, out, count, e0, tp, nullptr, none);
-}
-
-// ------------------------------------------------------------------ RED + RERAND
-// The three protocol steps for the elements a thread owns.  All parties are
-// simulated by that one thread, so a message is written to the workspace (the
-// "send") and consumed from registers (the "receive"); arithmetic and message
-// contents are exactly those of the per-party steps:
-//   1. party i = 1..2t+1: sub-shares of c_i for parties q = 1..k     -> msg1[i][q]
-//   2. party q: received row vector times R, applied in factored form
-//      R = B^-1[:, :k] * V (V[j][m] = m^j): first the k low coefficients of the
-//      polynomial through the received values, then its value at every party
-//      ID -- same residues as the (2t+1) x n product                 -> msg2[q][m]
-//   3. party m: REC of the k received values, plus its share of zero  -> out[m]
-//
-// With TRUNC the reduced, re-randomised shares do not go to `out` but straight
-// into the three truncation steps (truncate_kernel below), whose messages go to
-// umsg / wsh: SSS-Linear followed by SSS-Truncation in one launch.
-template <int VEC, bool TRUNC>
-__global__ __launch_bounds__(BLOCK) void degree_reduce_kernel(const u64 *c, u64 *__restrict__ msg1,
-                                                              u64 *__restrict__ msg2, u64 *__restrict__ umsg,
-                                                              u64 *__restrict__ wsh, u64 *out, u64 *__restrict__ rec,
-                                                              size_t count, ss_dr_params dp, ss_tr_params tp,
-                                                              ss_recf_params rf, ss_part_src ps)
-{
-    const size_t e0 = ((size_t)blockIdx.x * BLOCK + threadIdx.x) * VEC;
-    if (e0 >= count) return;
-    const int k = dp.t + 1, nr = 2 * dp.t + 1;
-
-    // step 1 fused with the accumulation of step 2: coef[q][j] = sum_i msg1[i][q] * binv[i][j]
-    ss_sacc coef[VEC][SS_MAXK][SS_MAXK];
-#pragma unroll
-    for (int u = 0; u < VEC; u++)
-#pragma unroll
-        for (int q = 0; q < SS_MAXK; q++)
-#pragma unroll
-            for (int j = 0; j < SS_MAXK; j++) coef[u][q][j].clear();
-#pragma unroll
-    for (int i = 0; i < 2 * SS_MAXT + 1; i++) {
-        if (i < nr) {
-            pack_t<VEC> ci;
-            ci.load(c + (size_t)i * count + e0);
-            for (int s = 1; s < ps.planes; s++) {
-                pack_t<VEC> more;
-                more.load(c + (size_t)s * ps.stride + (size_t)i * count + e0);
-#pragma unroll
-                for (int u = 0; u < VEC; u++) ci.v[u] = ss_add(ci.v[u], more.v[u]);
-            }
-            u64 r[VEC][SS_MAXT];
-#pragma unroll
-            for (int u = 0; u < VEC; u++) draw_coeffs<SS_MAXT>(r[u], dp.reshare_key[i], dp.t, e0 + u);
-#pragma unroll
-            for (int q = 0; q < SS_MAXK; q++) {
-                if (q < k) {
-                    pack_t<VEC> s;
-#pragma unroll
-                    for (int u = 0; u < VEC; u++) {
-                        s.v[u] = ss_poly_eval<SS_MAXT>(ci.v[u], r[u], dp.t, q + 1);
-#pragma unroll
-                        for (int j = 0; j < SS_MAXK; j++)
-                            if (j < k) coef[u][q][j].mac(s.v[u], dp.ibinv[i][j]);
-                    }
-                    s.store(msg1 + ((size_t)i * k + q) * count + e0);
-                }
-            }
-        }
-    }
-
-    // rest of step 2, fused with the accumulation of step 3: red[m] = sum_q lambda_q msg2[q][m]
-    ss_sacc red[VEC][SS_MAXN];
-#pragma unroll
-    for (int u = 0; u < VEC; u++)
-#pragma unroll
-        for (int m = 0; m < SS_MAXN; m++) red[u][m].clear();
-#pragma unroll
-    for (int q = 0; q < SS_MAXK; q++) {
-        if (q < k) {
-            u64 a0[VEC], cf[VEC][SS_MAXT];
-#pragma unroll
-            for (int u = 0; u < VEC; u++) {
-                a0[u] = ss_mul(coef[u][q][0].value(), dp.dinv);
-#pragma unroll
-                for (int j = 1; j < SS_MAXK; j++) cf[u][j - 1] = (j < k) ? ss_mul(coef[u][q][j].value(), dp.dinv) : 0;
-            }
-#pragma unroll
-            for (int m = 0; m < SS_MAXN; m++) {
-                if (m < dp.n) {
-                    pack_t<VEC> s;
-#pragma unroll
-                    for (int u = 0; u < VEC; u++) {
-                        s.v[u] = ss_poly_eval<SS_MAXT>(a0[u], cf[u], dp.t, m + 1);
-                        red[u][m].mac(s.v[u], dp.ilambda[q]);
-                    }
-                    s.store(msg2 + ((size_t)q * dp.n + m) * count + e0);
-                }
-            }
-        }
-    }
-
-    // rest of step 3 and RERAND
-    u64 z[VEC][SS_MAXT];
-#pragma unroll
-    for (int u = 0; u < VEC; u++) draw_coeffs<SS_MAXT>(z[u], dp.zero_key, dp.t, e0 + u);
-    pack_t<VEC> y[TRUNC ? SS_MAXK : 1];   // with TRUNC: the new shares of parties 1..k
-#pragma unroll
-    for (int m = 0; m < SS_MAXN; m++) {
-        if (m < dp.n) {
-            pack_t<VEC> s;
-#pragma unroll
-            for (int u = 0; u < VEC; u++)
-                s.v[u] = ss_add(red[u][m].value(), ss_poly_eval<SS_MAXT>(0, z[u], dp.t, m + 1));
-            if (!TRUNC)
-                s.store(out + (size_t)m * count + e0);
-            else if (m < SS_MAXK)
-                y[m] = s;
-        }
-    }
-    if (TRUNC) truncate_steps<VEC>(y, umsg, wsh, out, count, e0, tp, rec, rf);
-}
-
-// ---- the same steps with n and t fixed at compile time ((k,n) = (2,3), (3,5)) ----
-// Same messages, same outputs.  At the sizes of a network's layers this code is bound by its instructions (all of them
-// issue at the same rate on this machine, 64-bit multiply-adds included), so it carries the polynomials behind the
-// messages along and works on coefficients where the protocol works on values:
-//  * a party evaluates its polynomial at the consecutive points 1, 2, ... by forward differences (one or two additions
-//    per point instead of Horner with a modular multiplication per coefficient);
-//  * what the parties 1..k reconstruct from the sub-shares of step 2 (step 3 of RED) is the combination of the k
-//    polynomials with the Lagrange multipliers, so the coefficients are combined, not their values at every ID; the
-//    sharings of zero and of the mask are added coefficient by coefficient too, and the sum is evaluated once;
+// ------------------------------------------------------------------ RED + RERAND, truncation
+// The protocol steps for the element a thread owns.  All parties are simulated by that one thread, so a message is
+// written to the workspace (the "send") and what follows from it is computed in registers (the "receive"); messages and
+// results are exactly those of the per-party steps:
+//   RED   1. party i = 1..2t+1: sub-shares of c_i for parties q = 1..k                   -> msg1[i][q]
+//         2. party q: received row vector times R, in factored form R = B^-1[:, :k] * V (V[j][m] = m^j): first the
+//            k low coefficients of the polynomial through the received values, then its value at every party ID
+//            -- same residues as the (2t+1) x n product                                  -> msg2[q][m]
+//         3. party m: REC of the k received values, plus its share of zero (RERAND)
+//   trunc 1. parties q = 1..k add their share of alpha = e * 2^f (e * 2^f * kdiv with the rounding division) -> umsg[q]
+//         2. the elite party reconstructs x + alpha, divides by 2^f with floor on the signed value (then by kdiv with
+//            rounding) and shares the quotient                                           -> wsh[m]
+//         3. every party m adds its share of alpha~ = -e
+// At the sizes of a network's layers this code is bound by its instructions (all of them issue at the same rate on
+// this machine, 64-bit multiply-adds included), so it carries the polynomials behind the messages along and works on
+// coefficients where the protocol works on values:
+//  * a party evaluates its polynomial at the consecutive points 1, 2, ... by forward differences (eval_points);
+//  * what the parties reconstruct in step 3 of RED is the combination of the k polynomials of step 2 with the Lagrange
+//    multipliers, so the coefficients are combined, not their values at every ID; the sharings of zero and of the mask
+//    are added coefficient by coefficient too, and the sum is evaluated once;
 //  * REC of a sharing whose polynomial is at hand is its constant term, whichever IDs are asked for;
 //  * sums of value * small signed constant keep the value in two pieces of 31 and 30 bits and accumulate in signed
 //    64-bit words (one multiply-add per piece), with no case split on the sign of the constant;
 //  * sums stay unreduced (any word of the right residue within the bounds noted) until a value is stored.
+// n = 5, t = 2, reduce + truncate + open on MI355X: 24.0 -> 15.4 us at 200 K elements, where writing the same words
+// without any arithmetic takes 13.9 us.
+// n = 7, t = 3: 50.4 -> 27.1 us; n = 4, t = 1: 18.9 -> 10.1 us (against values at every ID and loops over n and t).
+// N: parties fixed at compile time, or 0 for the run-time value n; T: degree.
 
 // sum of v * c over at most 8 terms, v canonical given as v = w0 + w1 2^31 (w0 < 2^31), |c| < 2^26
 struct ss_sacc2 {
@@ -417,17 +231,48 @@ struct ss_sacc2 {
 };
 #define SS_SPLIT31(v, w0, w1) const u32 w0 = (u32)(v)&0x7FFFFFFFu, w1 = (u32)((v) >> 31)
 
-// all steps for element e; the messages go to the workspace, the new shares (reduced and re-randomised, with
-// TRUNC also truncated) come back in o[], their secret (what any k of them reconstruct to) in `secret`
+
+template <int N>
+constexpr int MAXP = N ? N : SS_MAXN;
+
+template <int T>
+__device__ __forceinline__ u64 mask_of(const ss_tr_params &tp, size_t e, u64 &alpha)
+{
+    const u64 ev = tp.kdiv > 1 ? mask_e_below(tp.e_key, e, tp.e_range) : mask_e(tp.e_key, e, tp.f);
+    alpha = tp.kdiv > 1 ? (ev * (u64)tp.kdiv) << tp.f : ev << tp.f;   // <= 2^32
+    return ev;
+}
+
+// truncation steps 2 and 3 from the opened x + alpha (canonical): the new shares in o[], their secret in `secret`; the
+// messages of step 2 go to wsh unless it is nullptr
+template <int N, int T, bool STREAM>
+__device__ __forceinline__ void shift_and_unmask(u64 opened, u64 ev, u64 counter, size_t em, size_t mcount,
+                                                 u64 *__restrict__ wsh, const ss_tr_params &tp, int n, u64 (&o)[MAXP<N>],
+                                                 u64 &secret)
+{
+    const u64 w = tp.kdiv > 1 ? shift_round_div(opened, tp.f, tp.kdiv) : shift_signed(opened, tp.f);
+    u64 cw[T], co[T];
+#pragma unroll
+    for (int j = 0; j < T; j++) {
+        cw[j] = ss_draw_lazy_at(tp.gen_key[j], counter);
+        co[j] = ss_fold(cw[j] + ss_draw_lazy_at(tp.alphat_key[j], counter));
+    }
+    if (wsh) eval_points<T, MAXP<N>>(w, cw, [&](int m, u64 v) { send<STREAM>(wsh + (size_t)m * mcount + em, v); }, n);
+    secret = ss_canon(w + SS_P - ev);
+    eval_points<T, MAXP<N>>(secret, co, [&](int m, u64 v) { o[m] = v; }, n);
+}
+
+// RED + RERAND and, with TRUNC, truncation of element e: the new shares come back in o[], their secret (what any k of
+// them reconstruct to) in `secret`
 // (em, mcount: position and plane size of this element in the message buffers, which need not be e, count)
 template <int N, int T, bool TRUNC, bool STREAM>
-__device__ __forceinline__ void reduce_truncate_fixed(size_t e, size_t count, size_t em, size_t mcount, const u64 *c,
-                                                      u64 *__restrict__ msg1, u64 *__restrict__ msg2,
-                                                      u64 *__restrict__ umsg, u64 *__restrict__ wsh,
-                                                      const ss_dr_params &dp, const ss_tr_params &tp,
-                                                      const ss_part_src &ps, u64 (&o)[N], u64 &secret)
+__device__ __forceinline__ void reduce_truncate(size_t e, size_t count, size_t em, size_t mcount, const u64 *c,
+                                                u64 *__restrict__ msg1, u64 *__restrict__ msg2, u64 *__restrict__ umsg,
+                                                u64 *__restrict__ wsh, const ss_dr_params &dp, const ss_tr_params &tp,
+                                                const ss_part_src &ps, u64 (&o)[MAXP<N>], u64 &secret)
 {
     constexpr int K = T + 1, NR = 2 * T + 1;
+    const int n = N ? N : dp.n;
     const u64 counter = ss_counter(e);
 
     // all incoming shares are requested at once
@@ -466,63 +311,145 @@ __device__ __forceinline__ void reduce_truncate_fixed(size_t e, size_t count, si
     u64 poly[K][K];   // [coefficient][q], < 2^61 + 2^3
 #pragma unroll
     for (int q = 0; q < K; q++) {
-        poly[0][q] = coef[q][0].lazy();
         u64 cf[T];
+        poly[0][q] = coef[q][0].lazy();
 #pragma unroll
         for (int j = 1; j < K; j++) cf[j - 1] = poly[j][q] = ss_fold(ss_mul_lazy(coef[q][j].lazy(), dp.dinv));
-        eval_points<T, N>(poly[0][q], cf, [&](int m, u64 v) { send<STREAM>(msg2 + ((size_t)q * N + m) * mcount + em, v); });
+        eval_points<T, MAXP<N>>(poly[0][q], cf,
+                                [&](int m, u64 v) { send<STREAM>(msg2 + ((size_t)q * n + m) * mcount + em, v); }, n);
     }
-    // step 3: sum_q lambda_q poly[.][q], lambda = (2, -1) or (3, -3, 1), then RERAND and the mask of truncation step 1
-    u64 u[K];
-    u64 ev = 0;
-    if (TRUNC) ev = mask_e(tp.e_key, e, tp.f);
+    // step 3: sum_q lambda_q poly[.][q], lambda = (2, -1), (3, -3, 1) or (4, -6, 4, -1), then RERAND and the mask of
+    // truncation step 1
+    u64 u[K], ev = 0, alpha = 0;
+    if (TRUNC) ev = mask_of<T>(tp, e, alpha);
 #pragma unroll
     for (int j = 0; j < K; j++) {
-        const u64 d = ss_fold(poly[j][0] + 2 * SS_P - poly[j][1]);   // < 2^61 + 2^3
-        u64 v = T == 1 ? d + poly[j][0] : 2 * d + d + poly[j][T];    // < 4 (2^61 + 2^3)
+        auto minus = [](u64 a, u64 b) { return ss_fold(a + 2 * SS_P - b); };   // a, b and the result < 2^61 + 2^3
+        const u64 d = minus(poly[j][0], poly[j][1]);
+        u64 v;   // < 5 (2^61 + 2^3)
+        if constexpr (T == 1)
+            v = d + poly[j][0];
+        else if constexpr (T == 2)
+            v = 2 * d + d + poly[j][2];
+        else
+            v = poly[j][0] + 3 * minus(d, minus(poly[j][1], poly[j][2])) + minus(poly[j][2], poly[j][3]);
         if (j > 0) {
             v += ss_draw_lazy_at(dp.zero_key[j - 1], counter);
             if (TRUNC) v += ss_draw_lazy_at(tp.alpha_key[j - 1], counter);
         } else if (TRUNC) {
-            v += ev << tp.f;
+            v += alpha;
         }
         u[j] = ss_fold(v);
     }
-    const u64(&uc)[T] = *reinterpret_cast<const u64(*)[T]>(&u[1]);
-    if (!TRUNC) {
-        eval_points<T, N>(u[0], uc, [&](int m, u64 v) { o[m] = v; });
-        secret = ss_canon(u[0]);
-        return;
-    }
-    // the masked shares of parties 1..k; the elite party's REC of x + alpha is the constant term
-    eval_points<T, K>(u[0], uc, [&](int q, u64 v) { send<STREAM>(umsg + (size_t)q * mcount + em, v); });
-    // step 2: shift and re-share; step 3: unmask
-    const u64 w = shift_signed(ss_canon(u[0]), tp.f);
-    u64 cw[T], co[T];
+    u64 uc[T];
 #pragma unroll
-    for (int j = 0; j < T; j++) {
-        cw[j] = ss_draw_lazy_at(tp.gen_key[j], counter);
-        co[j] = ss_fold(cw[j] + ss_draw_lazy_at(tp.alphat_key[j], counter));
+    for (int j = 0; j < T; j++) uc[j] = u[j + 1];
+    if constexpr (!TRUNC) {
+        eval_points<T, MAXP<N>>(u[0], uc, [&](int m, u64 v) { o[m] = v; }, n);
+        secret = ss_canon(u[0]);
+    } else {
+        // the masked shares of parties 1..k; the elite party's REC of x + alpha is the constant term
+        eval_points<T, K>(u[0], uc, [&](int q, u64 v) { send<STREAM>(umsg + (size_t)q * mcount + em, v); });
+        shift_and_unmask<N, T, STREAM>(ss_canon(u[0]), ev, counter, em, mcount, wsh, tp, n, o, secret);
     }
-    eval_points<T, N>(w, cw, [&](int m, u64 v) { send<STREAM>(wsh + (size_t)m * mcount + em, v); });
-    secret = ss_canon(w + SS_P - ev);
-    eval_points<T, N>(secret, co, [&](int m, u64 v) { o[m] = v; });
 }
 
+// (t = 3: without the second bound the compiler takes 157 registers, three waves per SIMD, to no gain)
 template <int N, int T, bool TRUNC, bool STREAM>
-__global__ __launch_bounds__(BLOCK) void degree_reduce_fixed_kernel(const u64 *c, u64 *__restrict__ msg1,
-                                                                    u64 *__restrict__ msg2, u64 *__restrict__ umsg,
-                                                                    u64 *__restrict__ wsh, u64 *out,
-                                                                    u64 *__restrict__ rec, size_t count,
-                                                                    ss_dr_params dp, ss_tr_params tp, ss_part_src ps)
+__global__ __launch_bounds__(BLOCK, T == 3 ? 4 : 1) void degree_reduce_kernel(const u64 *c, u64 *__restrict__ msg1, u64 *__restrict__ msg2,
+                                                              u64 *__restrict__ umsg, u64 *__restrict__ wsh, u64 *out,
+                                                              u64 *__restrict__ rec, size_t count, ss_dr_params dp,
+                                                              ss_tr_params tp, ss_part_src ps)
 {
     const size_t e = (size_t)blockIdx.x * BLOCK + threadIdx.x;
     if (e >= count) return;
-    u64 o[N], secret;
-    reduce_truncate_fixed<N, T, TRUNC, STREAM>(e, count, e, count, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
+    u64 o[MAXP<N>], secret;
+    reduce_truncate<N, T, TRUNC, STREAM>(e, count, e, count, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
 #pragma unroll
-    for (int m = 0; m < N; m++) out[(size_t)m * count + e] = o[m];
+    for (int m = 0; m < MAXP<N>; m++)
+        if (N != 0 || m < dp.n) out[(size_t)m * count + e] = o[m];
     if (TRUNC && rec) rec[e] = secret;   // if asked for, REC of the result
+}
+
+// RED + RERAND of small tensors with t = 3, where the serial work of one thread per element leaves most of the chip idle: a
+// workgroup takes 32 elements and eight party lanes per element.  Lane p = 0..6 first plays reducing party p+1 (step 1)
+// while lane 7 draws the sharing of zero; then, after these went through LDS, lane p plays receiving party p+1: it forms
+// the four values that parties 1..4 would send it (step 2, with the full matrix R instead of its factors, so that the
+// lanes do not wait on each other) and reconstructs from them (step 3).  Same messages and results.
+// 4 K elements, n = 8: 7.0 us against 8.2 us of the kernel above.
+__global__ __launch_bounds__(BLOCK) void degree_reduce_lanes_kernel(const u64 *c, u64 *__restrict__ msg1,
+                                                                    u64 *__restrict__ msg2, u64 *out, size_t count,
+                                                                    ss_dr_params dp, ss_part_src ps)
+{
+    constexpr int T = 3, K = T + 1, NR = 2 * T + 1;
+    __shared__ u64 sub[NR][K][32];
+    __shared__ u64 zero[T][32];
+    const int el = threadIdx.x & 31, p = threadIdx.x >> 5;
+    const size_t e = (size_t)blockIdx.x * 32 + el;
+    const bool live = e < count;
+    if (live && p < NR) {
+        const u64 ci = load_product(c, (size_t)p * count + e, ps);
+        u64 r[T];
+        draw_coeffs<T>(r, dp.reshare_key[p], T, e);
+        eval_points<T, K>(ci, r, [&](int q, u64 v) {
+            sub[p][q][el] = v;
+            msg1[((size_t)p * K + q) * count + e] = v;
+        });
+    } else if (live) {
+        u64 z[T];
+        draw_coeffs<T>(z, dp.zero_key, T, e);
+#pragma unroll
+        for (int j = 0; j < T; j++) zero[j][el] = z[j];
+    }
+    __syncthreads();
+    if (!live || p >= dp.n) return;
+    ss_sacc red;
+    red.clear();
+#pragma unroll
+    for (int q = 0; q < K; q++) {
+        ss_sacc acc;
+        acc.clear();
+#pragma unroll
+        for (int i = 0; i < NR; i++) acc.mac(sub[i][q][el], dp.irmat[i][p]);
+        const u64 v = ss_mul(acc.value(), dp.dinv);
+        msg2[((size_t)q * dp.n + p) * count + e] = v;
+        red.mac(v, dp.ilambda[q]);
+    }
+    u64 z[T];
+#pragma unroll
+    for (int j = 0; j < T; j++) z[j] = zero[j][el];
+    out[(size_t)p * count + e] = ss_add(red.value(), ss_poly_eval<T>(0, z, T, p + 1));
+}
+
+// truncation of given shares (parties 1..k are read)
+template <int N, int T, bool STREAM>
+__global__ __launch_bounds__(BLOCK) void truncate_kernel(const u64 *x, u64 *__restrict__ umsg, u64 *__restrict__ wsh,
+                                                         u64 *out, size_t count, ss_tr_params tp)
+{
+    const size_t e = (size_t)blockIdx.x * BLOCK + threadIdx.x;
+    if (e >= count) return;
+    constexpr int K = T + 1;
+    const u64 counter = ss_counter(e);
+    u64 xs[K];
+#pragma unroll
+    for (int q = 0; q < K; q++) xs[q] = x[(size_t)q * count + e];
+    u64 alpha, ca[T];
+    const u64 ev = mask_of<T>(tp, e, alpha);
+#pragma unroll
+    for (int j = 0; j < T; j++) ca[j] = ss_draw_lazy_at(tp.alpha_key[j], counter);
+    ss_sacc2 acc;
+    acc.clear();
+    eval_points<T, K>(alpha, ca, [&](int q, u64 v) {
+        const u64 um = ss_add(xs[q], v);
+        send<STREAM>(umsg + (size_t)q * count + e, um);
+        SS_SPLIT31(um, w0, w1);
+        acc.mac(w0, w1, tp.ilambda[q]);
+    });
+    u64 o[MAXP<N>], secret;
+    shift_and_unmask<N, T, STREAM>(acc.value(), ev, counter, e, count, wsh, tp, N ? N : tp.n, o, secret);
+#pragma unroll
+    for (int m = 0; m < MAXP<N>; m++)
+        if (N != 0 || m < tp.n) out[(size_t)m * count + e] = o[m];
 }
 
 // ReLU under the multiplicative mask for one element (the three steps of relu_kernel below), n and t
@@ -593,7 +520,7 @@ __global__ __launch_bounds__(BLOCK) void layer_tail_kernel(const u64 *c, u64 *__
 #pragma unroll
         for (int m = 0; m < N; m++) mbi[m] = sh_bi[(size_t)m * count + e];
         u64 secret;
-        reduce_truncate_fixed<N, T, true, STREAM>(e, count, em, mcount, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
+        reduce_truncate<N, T, true, STREAM>(e, count, em, mcount, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
         relu_fixed<N, T, STREAM>(o, em, mcount, mb, mbi, rmsg, yplain, np, r);
 #pragma unroll
         for (int p = 0; p < N; p++) {
@@ -659,128 +586,6 @@ __global__ __launch_bounds__(BLOCK) void tail_direct_kernel(const u64 *c, const 
     store_staged_planes<SS_MAXN>(stage, planes, party_bytes, count, blockIdx.x * 16, B * HW, blockIdx.y * 16, n);
 }
 
-// Same computation for small tensors, where the serial work of one thread per
-// element leaves most of the chip idle: a workgroup takes 32 elements and eight
-// party lanes per element.  Lane p first plays reducing party p+1 (step 1),
-// while the lanes that do not reduce (2t+1 <= 7, so lane 7 at least) draw the
-// coefficients every party needs later; then, after these went through LDS, lane
-// p plays receiving party p+1: it forms the k values that parties 1..k would
-// send it (step 2, with the full matrix R instead of its factors, so that the
-// lanes do not wait on each other) and reconstructs from them (step 3, RERAND).
-// With TRUNC the lanes go on with the truncation steps (mask, reconstruct and
-// shift at the elite party, unmask), exchanging the k masked shares through LDS.
-// Messages and outputs are the same residues as in the kernels above.
-template <bool TRUNC>
-__global__ __launch_bounds__(BLOCK) void degree_reduce_lanes_kernel(const u64 *c, u64 *__restrict__ msg1,
-                                                                    u64 *__restrict__ msg2, u64 *__restrict__ umsg,
-                                                                    u64 *__restrict__ wsh, u64 *out,
-                                                                    u64 *__restrict__ rec, size_t count,
-                                                                    ss_dr_params dp, ss_tr_params tp, ss_recf_params rf,
-                                                                    ss_part_src ps)
-{
-    __shared__ u64 sub[2 * SS_MAXT + 1][SS_MAXK][32];
-    // drawn once per element by the spare lanes: 0 zero sharing, 1 alpha, 2 elite re-sharing, 3 alpha~
-    __shared__ u64 coef[4][SS_MAXT][32];
-    __shared__ u64 mask[32];             // e of the truncation mask
-    __shared__ u64 masked[SS_MAXK][32];  // x_q + alpha_q
-    __shared__ u64 fin[SS_MAXN][32];     // truncated shares, for the fused REC
-    const int el = threadIdx.x & 31, p = threadIdx.x >> 5;
-    const size_t e = (size_t)blockIdx.x * 32 + el;
-    const bool live = e < count;
-    const int k = dp.t + 1, nr = 2 * dp.t + 1;
-    if (live && p < nr) {
-        const u64 ci = load_product(c, (size_t)p * count + e, ps);
-        u64 r[SS_MAXT];
-        draw_coeffs<SS_MAXT>(r, dp.reshare_key[p], dp.t, e);
-#pragma unroll
-        for (int q = 0; q < SS_MAXK; q++) {
-            if (q < k) {
-                const u64 v = ss_poly_eval<SS_MAXT>(ci, r, dp.t, q + 1);
-                sub[p][q][el] = v;
-                msg1[((size_t)p * k + q) * count + e] = v;
-            }
-        }
-    } else if (live) {   // spare lanes nr..7 share the drawing jobs round-robin
-        const int spare = 8 - nr, me = p - nr;
-#pragma unroll
-        for (int job = 0; job < (TRUNC ? 4 : 1); job++) {
-            if (job % spare == me) {
-                const u64 *keys = job == 0 ? dp.zero_key : job == 1 ? tp.alpha_key : job == 2 ? tp.gen_key : tp.alphat_key;
-                u64 z[SS_MAXT];
-                draw_coeffs<SS_MAXT>(z, keys, dp.t, e);
-#pragma unroll
-                for (int j = 0; j < SS_MAXT; j++) coef[job][j][el] = z[j];
-                if (job == 1) mask[el] = mask_e(tp.e_key, e, tp.f);
-            }
-        }
-    }
-    __syncthreads();
-    const bool party = live && p < dp.n;
-    u64 y = 0;   // this party's reduced, re-randomised share
-    if (party) {
-        ss_sacc red;
-        red.clear();
-#pragma unroll
-        for (int q = 0; q < SS_MAXK; q++) {
-            if (q < k) {
-                ss_sacc acc;
-                acc.clear();
-#pragma unroll
-                for (int i = 0; i < 2 * SS_MAXT + 1; i++)
-                    if (i < nr) acc.mac(sub[i][q][el], dp.irmat[i][p]);
-                const u64 v = ss_mul(acc.value(), dp.dinv);
-                msg2[((size_t)q * dp.n + p) * count + e] = v;
-                red.mac(v, dp.ilambda[q]);
-            }
-        }
-        u64 z[SS_MAXT];
-#pragma unroll
-        for (int j = 0; j < SS_MAXT; j++) z[j] = coef[0][j][el];
-        y = ss_add(red.value(), ss_poly_eval<SS_MAXT>(0, z, dp.t, p + 1));
-        if (!TRUNC) out[(size_t)p * count + e] = y;
-    }
-    if (!TRUNC) return;
-
-    if (party && p < k) {   // truncation step 1 on parties 1..k
-        u64 ca[SS_MAXT];
-#pragma unroll
-        for (int j = 0; j < SS_MAXT; j++) ca[j] = coef[1][j][el];
-        const u64 um = ss_add(y, ss_poly_eval<SS_MAXT>(mask[el] << tp.f, ca, tp.t, p + 1));
-        masked[p][el] = um;
-        umsg[(size_t)p * count + e] = um;
-    }
-    __syncthreads();
-    if (party) {   // step 2 (the elite party's result, recomputed by every lane) and step 3
-        ss_sacc acc;
-        acc.clear();
-#pragma unroll
-        for (int q = 0; q < SS_MAXK; q++)
-            if (q < k) acc.mac(masked[q][el], tp.ilambda[q]);
-        const u64 w = shift_signed(acc.value(), tp.f);
-        u64 cw[SS_MAXT], cat[SS_MAXT];
-#pragma unroll
-        for (int j = 0; j < SS_MAXT; j++) {
-            cw[j] = coef[2][j][el];
-            cat[j] = coef[3][j][el];
-        }
-        const u64 ws = ss_poly_eval<SS_MAXT>(w, cw, tp.t, p + 1);
-        wsh[(size_t)p * count + e] = ws;
-        const u64 o = ss_add(ws, ss_poly_eval<SS_MAXT>(SS_P - mask[el], cat, tp.t, p + 1));
-        out[(size_t)p * count + e] = o;
-        fin[p][el] = o;
-    }
-    if (!rec) return;   // uniform over the grid
-    __syncthreads();
-    if (live && p == 0) {
-        ss_sacc acc;
-        acc.clear();
-#pragma unroll
-        for (int m = 0; m < SS_MAXN; m++)
-            if (m < dp.n && rf.coef[m] != 0) acc.mac(fin[m][el], rf.coef[m]);
-        rec[e] = rf.dinv == 1 ? acc.value() : ss_mul(acc.value(), rf.dinv);
-    }
-}
-
 // ------------------------------------------------------------------ reduction + truncation, all parties at once
 // The outputs of RED + RERAND + truncation do not depend on the reshare or zero
 // randomness: the elite party of the truncation reconstructs x + alpha, where x
@@ -790,58 +595,29 @@ __global__ __launch_bounds__(BLOCK) void degree_reduce_lanes_kernel(const u64 *c
 // it as in truncation steps 2 and 3.  Same residues in `out` (and `rec`) as the
 // protocol kernels; no message is formed, so this is not what the parties of the
 // protocol compute, only what they end up with.
-template <int VEC>
+template <int N, int T>
 __global__ __launch_bounds__(BLOCK) void reduce_truncate_direct_kernel(const u64 *c, u64 *out, u64 *__restrict__ rec,
                                                                        size_t count, ss_nl_params open_all,
-                                                                       ss_tr_params tp, ss_recf_params rf)
+                                                                       ss_tr_params tp, ss_part_src ps)
 {
-    const size_t e0 = ((size_t)blockIdx.x * BLOCK + threadIdx.x) * VEC;
-    if (e0 >= count) return;
-    const int nr = 2 * tp.t + 1;
-    ss_sacc acc[VEC], racc[VEC];
+    const size_t e = (size_t)blockIdx.x * BLOCK + threadIdx.x;
+    if (e >= count) return;
+    ss_sacc2 acc;
+    acc.clear();
 #pragma unroll
-    for (int u = 0; u < VEC; u++) {
-        acc[u].clear();
-        racc[u].clear();
+    for (int i = 0; i < 2 * T + 1; i++) {
+        const u64 ci = load_product(c, (size_t)i * count + e, ps);
+        SS_SPLIT31(ci, w0, w1);
+        acc.mac(w0, w1, open_all.ilambda[i]);
     }
+    u64 alpha, o[MAXP<N>], secret;
+    const u64 ev = mask_of<T>(tp, e, alpha);
+    shift_and_unmask<N, T, false>(ss_canon(ss_fold(acc.lazy() + alpha)), ev, ss_counter(e), e, count, nullptr, tp,
+                                  N ? N : tp.n, o, secret);
 #pragma unroll
-    for (int i = 0; i < 2 * SS_MAXT + 1; i++) {
-        if (i < nr) {
-            pack_t<VEC> ci;
-            ci.load(c + (size_t)i * count + e0);
-#pragma unroll
-            for (int u = 0; u < VEC; u++) acc[u].mac(ci.v[u], open_all.ilambda[i]);
-        }
-    }
-    u64 w[VEC], at[VEC], cw[VEC][SS_MAXT], cat[VEC][SS_MAXT];
-#pragma unroll
-    for (int u = 0; u < VEC; u++) {
-        const u64 x = open_all.dinv == 1 ? acc[u].value() : ss_mul(acc[u].value(), open_all.dinv);
-        const u64 ev = mask_e(tp.e_key, e0 + u, tp.f);
-        w[u] = shift_signed(ss_add(x, ev << tp.f), tp.f);
-        at[u] = SS_P - ev;
-        draw_coeffs<SS_MAXT>(cw[u], tp.gen_key, tp.t, e0 + u);
-        draw_coeffs<SS_MAXT>(cat[u], tp.alphat_key, tp.t, e0 + u);
-    }
-#pragma unroll
-    for (int m = 0; m < SS_MAXN; m++) {
-        if (m < tp.n) {
-            pack_t<VEC> s;
-#pragma unroll
-            for (int u = 0; u < VEC; u++) {
-                s.v[u] = ss_add(ss_poly_eval<SS_MAXT>(w[u], cw[u], tp.t, m + 1),
-                                ss_poly_eval<SS_MAXT>(at[u], cat[u], tp.t, m + 1));
-                if (rec && rf.coef[m] != 0) racc[u].mac(s.v[u], rf.coef[m]);
-            }
-            s.store(out + (size_t)m * count + e0);
-        }
-    }
-    if (rec) {
-        pack_t<VEC> r;
-#pragma unroll
-        for (int u = 0; u < VEC; u++) r.v[u] = rf.dinv == 1 ? racc[u].value() : ss_mul(racc[u].value(), rf.dinv);
-        r.store(rec + e0);
-    }
+    for (int m = 0; m < MAXP<N>; m++)
+        if (N != 0 || m < tp.n) out[(size_t)m * count + e] = o[m];
+    if (rec) rec[e] = secret;
 }
 
 // ------------------------------------------------------------------ SSS-NonLinear (Sec. VI-C)
@@ -1011,10 +787,10 @@ __global__ __launch_bounds__(BLOCK) void pool_maskoff_kernel(const u64 *__restri
 
 // below this many elements one element per thread gives more waves to hide latency
 constexpr size_t VEC2_MIN_COUNT = (size_t)1 << 20;
-// below this many elements degree reduction spreads an element over party lanes
-constexpr size_t LANES_MAX_COUNT = 160 * 1024;   // measured cross-over on MI355X (n = 5, t = 2)
-// the same cross-over against the kernels with n and t fixed at compile time
-constexpr size_t LANES_MAX_COUNT_FIXED = 8 * 1024;
+// Below this many elements RED + RERAND alone with t = 3 spreads an element over party lanes: the one-thread kernel takes
+// 1.2 times as long at 1 K elements and as long at 16 K.  For t = 1 and 2, and with the truncation in the same launch, it
+// is the faster one at every size (n = 5, 64 elements: 4.2 against 6.5 us).
+constexpr size_t LANES_MAX_COUNT = 16 * 1024;
 
 // Messages are written once and not read by the library again.  Left to the caches they cost nothing while a call's
 // traffic fits the 256 MB of the last level (the next call overwrites them there); beyond, writing them past the
@@ -1085,63 +861,61 @@ hipError_t ss_launch_sum_planes(u64 *dst, const u64 *c, size_t total, const ss_p
     return hipGetLastError();
 }
 
-// words per element: the shares read and written, the messages of reduction and (TR) truncation
-#define SS_REDUCE_FIXED(NC, TC, TR, U, W, REC, TP)                                                                        \
-    do {                                                                                                                  \
-        constexpr size_t words = 2 * NC + (2 * TC + 1) * (TC + 1) + (TC + 1) * NC + (TR ? TC + 1 + NC : 0);               \
-        hipLaunchKernelGGL((streams_messages(words * count) ? degree_reduce_fixed_kernel<NC, TC, TR, true>                \
-                                                            : degree_reduce_fixed_kernel<NC, TC, TR, false>),             \
-                           dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, (u64 *)(U), (u64 *)(W), out, \
-                           (u64 *)(REC), count, dp, TP, ps);                                                              \
+// (3,1) and (5,2), and the two counts of t = 3, have their party count fixed at compile time; the other counts of t = 1 and
+// 2 take theirs at run time.  SS_SCHEME(n, t, LAUNCH) runs LAUNCH(N, T).
+#define SS_SCHEME(n_, t_, LAUNCH)               \
+    do {                                        \
+        if ((n_) == 5 && (t_) == 2) LAUNCH(5, 2); \
+        else if ((n_) == 3 && (t_) == 1) LAUNCH(3, 1); \
+        else if ((t_) == 1) LAUNCH(0, 1);       \
+        else if ((t_) == 2) LAUNCH(0, 2);       \
+        else if ((n_) == 7) LAUNCH(7, 3);       \
+        else LAUNCH(8, 3);                      \
     } while (0)
 
 hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out, size_t count,
                                    const ss_dr_params &dp, const ss_part_src &ps, hipStream_t stream)
 {
     const ss_tr_params none = {};
-    const ss_recf_params norec = {};
-    const bool fixed = (dp.n == 5 && dp.t == 2) || (dp.n == 3 && dp.t == 1);
-    if (count < (fixed ? LANES_MAX_COUNT_FIXED : LANES_MAX_COUNT))
-        hipLaunchKernelGGL(degree_reduce_lanes_kernel<false>, dim3((unsigned)((count + 31) / 32)), dim3(BLOCK), 0, stream,
-                           c, msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, norec, ps);
-    else if (dp.n == 5 && dp.t == 2)
-        SS_REDUCE_FIXED(5, 2, false, nullptr, nullptr, nullptr, none);
-    else if (dp.n == 3 && dp.t == 1)
-        SS_REDUCE_FIXED(3, 1, false, nullptr, nullptr, nullptr, none);
-    else   // one element per thread: the k*k + n wide accumulators of two elements would not fit the register file
-        hipLaunchKernelGGL((degree_reduce_kernel<1, false>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1,
-                           msg2, (u64 *)nullptr, (u64 *)nullptr, out, (u64 *)nullptr, count, dp, none, norec, ps);
+    if (dp.t == 3 && count < LANES_MAX_COUNT) {
+        hipLaunchKernelGGL(degree_reduce_lanes_kernel, dim3((unsigned)((count + 31) / 32)), dim3(BLOCK), 0, stream, c, msg1,
+                           msg2, out, count, dp, ps);
+        return hipGetLastError();
+    }
+    const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
+    const bool streams = streams_messages((nr + n + nr * k + k * n) * count);
+#define SS_LAUNCH(NC, TC)                                                                                               \
+    hipLaunchKernelGGL((streams ? degree_reduce_kernel<NC, TC, false, true> : degree_reduce_kernel<NC, TC, false, false>), \
+                       dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, \
+                       out, (u64 *)nullptr, count, dp, none, ps)
+    SS_SCHEME(dp.n, dp.t, SS_LAUNCH);
+#undef SS_LAUNCH
     return hipGetLastError();
 }
 
 hipError_t ss_launch_degree_reduce_truncate(const u64 *c, u64 *msg1, u64 *msg2, u64 *u, u64 *wsh, u64 *out,
                                             u64 *rec, size_t count, const ss_dr_params &dp, const ss_tr_params &tp,
-                                            const ss_recf_params &rf, const ss_part_src &ps, hipStream_t stream)
+                                            const ss_part_src &ps, hipStream_t stream)
 {
-    const bool fixed = (dp.n == 5 && dp.t == 2) || (dp.n == 3 && dp.t == 1);
-    if (tp.kdiv > 1)   // the rounding division exists in the general kernel only
-        hipLaunchKernelGGL((degree_reduce_kernel<1, true>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1,
-                           msg2, u, wsh, out, rec, count, dp, tp, rf, ps);
-    else if (count < (fixed ? LANES_MAX_COUNT_FIXED : LANES_MAX_COUNT))
-        hipLaunchKernelGGL(degree_reduce_lanes_kernel<true>, dim3((unsigned)((count + 31) / 32)), dim3(BLOCK), 0, stream,
-                           c, msg1, msg2, u, wsh, out, rec, count, dp, tp, rf, ps);
-    else if (dp.n == 5 && dp.t == 2)
-        SS_REDUCE_FIXED(5, 2, true, u, wsh, rec, tp);
-    else if (dp.n == 3 && dp.t == 1)
-        SS_REDUCE_FIXED(3, 1, true, u, wsh, rec, tp);
-    else
-        hipLaunchKernelGGL((degree_reduce_kernel<1, true>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1,
-                           msg2, u, wsh, out, rec, count, dp, tp, rf, ps);
+    const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
+    const bool streams = streams_messages((nr + n + nr * k + k * n + k + n) * count);
+#define SS_LAUNCH(NC, TC)                                                                                               \
+    hipLaunchKernelGGL((streams ? degree_reduce_kernel<NC, TC, true, true> : degree_reduce_kernel<NC, TC, true, false>), \
+                       dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, u, wsh, out, rec, count, dp, tp, ps)
+    SS_SCHEME(dp.n, dp.t, SS_LAUNCH);
+#undef SS_LAUNCH
     return hipGetLastError();
 }
 
 hipError_t ss_launch_truncate(const u64 *x, u64 *u, u64 *wsh, u64 *out, size_t count, const ss_tr_params &tp,
                               hipStream_t stream)
 {
-    const bool v2 = (count % 2 == 0) && aligned16(x) && aligned16(u) && aligned16(wsh) && aligned16(out) &&
-                    count >= VEC2_MIN_COUNT;
-    auto grid = [&](int vec) { return dim3(blocks_for(count, vec)); };
-    SS_DISPATCH_VEC(v2, truncate_kernel, grid, x, u, wsh, out, count, tp);
+    const bool streams = streams_messages((size_t)(2 * (tp.t + 1) + 2 * tp.n) * count);
+#define SS_LAUNCH(NC, TC)                                                                                           \
+    hipLaunchKernelGGL((streams ? truncate_kernel<NC, TC, true> : truncate_kernel<NC, TC, false>), dim3(blocks_for(count, 1)), \
+                       dim3(BLOCK), 0, stream, x, u, wsh, out, count, tp)
+    SS_SCHEME(tp.n, tp.t, SS_LAUNCH);
+#undef SS_LAUNCH
     return hipGetLastError();
 }
 
@@ -1193,13 +967,13 @@ hipError_t ss_launch_relu_pool(const u64 *x, const u64 *sh_b, const u64 *sh_bi, 
 }
 
 hipError_t ss_launch_reduce_truncate_direct(const u64 *c, u64 *out, u64 *rec, size_t count, const ss_nl_params &open_all,
-                                            const ss_tr_params &tp, const ss_recf_params &rf, hipStream_t stream)
+                                            const ss_tr_params &tp, const ss_part_src &ps, hipStream_t stream)
 {
-    if (tp.kdiv != 1) return hipErrorInvalidValue;   // no rounding division in this kernel
-    const bool v2 = (count % 2 == 0) && aligned16(c) && aligned16(out) && (!rec || aligned16(rec)) &&
-                    count >= VEC2_MIN_COUNT;
-    auto grid = [&](int vec) { return dim3(blocks_for(count, vec)); };
-    SS_DISPATCH_VEC(v2, reduce_truncate_direct_kernel, grid, c, out, rec, count, open_all, tp, rf);
+#define SS_LAUNCH(NC, TC)                                                                                       \
+    hipLaunchKernelGGL((reduce_truncate_direct_kernel<NC, TC>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, out, \
+                       rec, count, open_all, tp, ps)
+    SS_SCHEME(tp.n, tp.t, SS_LAUNCH);
+#undef SS_LAUNCH
     return hipGetLastError();
 }
 

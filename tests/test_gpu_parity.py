@@ -597,3 +597,29 @@ def test_relu_pool_stem_size():
                else torch.nn.functional.avg_pool2d(q, kern, stride, pad) * (kern[0] * kern[1]))
         opened = orc.lift(to_np(s.reconstruct(got, [1, 3, 5])), P61)
         assert np.array_equal(opened.reshape(-1), ref.round().to(torch.int64).numpy().reshape(-1))
+
+
+@pytest.mark.parametrize("n,t,counts", [(4, 1, (257, 420001)), (8, 1, (1, 4099)), (6, 2, (1, 257, 420001)), (8, 2, (255,)),
+                                        (7, 3, (16383, 16384, 420001)), (8, 3, (1, 16383, 16385, 300001))])
+def test_reduction_kernels_of_every_degree(n, t, counts):
+    """Every degree, with the party count fixed at compile time or not; on both sides of the line where t = 3 spreads an
+    element over lanes, and where a call's traffic exceeds the last cache level (messages stored past the caches):
+    all messages and results, and the rounding division."""
+    s = SSNet(n, t, f=13, seed=19)
+    k, nr = t + 1, 2 * t + 1
+    for count in counts:
+        say("reduction kernels", n, t, count)
+        xs = np.random.default_rng(count).integers(-(1 << 55), 1 << 55, count, dtype=np.int64)
+        c = orc.share(np.where(xs < 0, xs + P61, xs).astype(np.uint64), n, 2 * t, P61, 5, 0)
+        want_r, m1, m2, _ = orc.degree_reduce(c, n, t, P61, 19, 9, full=True)
+        want, u, wsh = orc.truncate(want_r, n, t, 13, P61, 19, 9, full=True)
+        red, trunc = np.concatenate([m1.ravel(), m2.ravel()]), np.concatenate([u.ravel(), wsh.ravel()])
+        d = to_dev(c)
+        assert np.array_equal(to_np(s.degree_reduce(d, stream_id=9)), want_r)
+        assert np.array_equal(to_np(s.messages()[: red.size]), red)
+        assert np.array_equal(to_np(s.truncate(to_dev(want_r), stream_id=9)), want)
+        assert np.array_equal(to_np(s.messages()[: trunc.size]), trunc)
+        assert np.array_equal(to_np(s.degree_reduce_truncate(d, stream_id=9)), want)
+        assert np.array_equal(to_np(s.messages()[: red.size + trunc.size]), np.concatenate([red, trunc]))
+        assert np.array_equal(to_np(s.degree_reduce_truncate_div(d, 49, stream_id=9)),
+                              orc.truncate_div(want_r, n, t, 13, 49, P61, 19, 9))
