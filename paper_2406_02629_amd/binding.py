@@ -122,6 +122,12 @@ def _check_i64(t: torch.Tensor, name: str) -> torch.Tensor:
     return t
 
 
+def _per_party(t: torch.Tensor) -> int:
+    """elements of one party's share in [n][...]; t[0].numel() without making the view (1.3 us of a call's 6 to 10)"""
+    total = t.numel()
+    return total // t.size(0) if total else t[0].numel()
+
+
 class SSNet:
     """One (k = t+1, n) scheme over F_p, p = 2^61-1 (or P45, served by the second library), fixed-point
     fraction bits f."""
@@ -139,6 +145,10 @@ class SSNet:
             self._ctx = None
             raise SSNetError(rc, "ssnet_create")
         self._ws: Optional[torch.Tensor] = None
+        # sizes that the library has given for a shape, and the largest element count whose messages are known to fit
+        # the workspace _fits_ws: asking again costs a foreign call (0.5 to 1.1 us), which small layers feel
+        self._sizes: dict = {}
+        self._fits_ws, self._fits_count = None, 0
 
     def close(self):
         if getattr(self, "_ctx", None):
@@ -151,6 +161,17 @@ class SSNet:
         except Exception:
             pass
 
+    def _size(self, fn, *shape) -> int:
+        """what the size function `fn` of the library says for `shape` (ctx first where it takes one)"""
+        key = (fn, shape)
+        size = self._sizes.get(key)
+        if size is None:
+            if len(self._sizes) >= 4096:
+                self._sizes.clear()
+            call = getattr(self.lib, fn)
+            size = self._sizes[key] = call(self._ctx, *shape) if call.argtypes[0] is _ptr else call(*shape)
+        return size
+
     def _ok(self, rc: int, where: str):
         if rc:
             raise SSNetError(rc, where, self.lib.ssnet_last_hip_error(self._ctx))
@@ -162,6 +183,12 @@ class SSNet:
             self._ws = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
             self._ok(self.lib.ssnet_set_workspace(self._ctx, _dptr(self._ws), self._ws.numel()), "ssnet_set_workspace")
 
+    def _reserve_stream(self, count: int):
+        """room for the messages of an element-wise call over `count` elements per party"""
+        if count > self._fits_count or self._fits_ws is not self._ws or self._ws is None:
+            self.reserve(self.workspace_bytes_stream(count))
+            self._fits_ws, self._fits_count = self._ws, count
+
     def messages(self) -> torch.Tensor:
         """int64 view of the workspace behind its header: where the inter-party
         messages of the last degree_reduce / truncate call were written."""
@@ -171,10 +198,10 @@ class SSNet:
         return self.lib.ssnet_workspace_bytes_stream(self._ctx, count)
 
     def workspace_bytes_linear(self, M: int, K: int, N: int) -> int:
-        return self.lib.ssnet_workspace_bytes_linear(self._ctx, M, K, N)
+        return self._size("ssnet_workspace_bytes_linear", M, K, N)
 
     def workspace_bytes_conv(self, B, Ci, H, W, Co, kh, kw, stride, pad) -> int:
-        return self.lib.ssnet_workspace_bytes_conv(self._ctx, B, Ci, H, W, Co, kh, kw, stride, pad)
+        return self._size("ssnet_workspace_bytes_conv", B, Ci, H, W, Co, kh, kw, stride, pad)
 
     # ---- GEN / REC ----
     def share(self, secret: torch.Tensor, stream_id: int, degree: Optional[int] = None,
@@ -191,7 +218,7 @@ class SSNet:
                     out: Optional[torch.Tensor] = None) -> torch.Tensor:
         _check_i64(shares, "shares")
         degree = self.t if degree is None else degree
-        count = shares[0].numel()
+        count = _per_party(shares)
         if out is None:
             out = torch.empty(tuple(shares.shape[1:]), dtype=torch.int64, device=shares.device)
         arr = (_int * len(ids))(*ids)
@@ -271,7 +298,7 @@ class SSNet:
             raise SSNetError(EINVAL, "share_packed: secret must be [M][K] or [B][C][H][W]")
         if out is None:
             out = torch.empty((self.n,) + tuple(secret.shape), dtype=torch.int64, device=secret.device)
-        nbytes = self.n * self.lib.ssnet_packed_weight_bytes(B * HW, K)
+        nbytes = self.n * self._size("ssnet_packed_weight_bytes", B * HW, K)
         if packed is None:
             packed = torch.empty(nbytes, dtype=torch.uint8, device=secret.device)
         elif packed.numel() * packed.element_size() < nbytes:
@@ -303,7 +330,7 @@ class SSNet:
         return self.lib.ssnet_conv_planes_bytes(B, C, H, W) != 0
 
     def _planes_buffer(self, B, C, H, W, planes, device):
-        nbytes = self.n * self.lib.ssnet_conv_planes_bytes(B, C, H, W)
+        nbytes = self.n * self._size("ssnet_conv_planes_bytes", B, C, H, W)
         if nbytes == 0:
             raise SSNetError(EINVAL, "ssnet_conv_planes_bytes")
         if planes is None:
@@ -358,24 +385,25 @@ class SSNet:
         """room for the pending product plus the messages of whichever call consumes it"""
         if product_bytes == 0:
             raise SSNetError(EINVAL, "ssnet_product_bytes")
-        msgs = max(self.workspace_bytes_stream(B * C * HW), self.lib.ssnet_workspace_bytes_layer_tail(self._ctx, B, C, HW))
+        msgs = max(self._size("ssnet_workspace_bytes_stream", B * C * HW),
+                   self._size("ssnet_workspace_bytes_layer_tail", B, C, HW))
         self.reserve(msgs + product_bytes)
 
     def linear_product_prepacked(self, x_packed: torch.Tensor, w_packed: torch.Tensor, M: int, K: int, N: int):
-        self._reserve_product(self.lib.ssnet_product_bytes_linear(self._ctx, M, K, N), M, N, 1)
+        self._reserve_product(self._size("ssnet_product_bytes_linear", M, K, N), M, N, 1)
         self._ok(self.lib.ssnet_linear_product_prepacked(self._ctx, _dptr(x_packed), _dptr(w_packed), M, K, N),
                  "ssnet_linear_product_prepacked")
 
     def conv1x1_product_prepacked(self, x_packed: torch.Tensor, w_packed: torch.Tensor, B: int, C: int, H: int, W: int,
                                   Co: int):
-        self._reserve_product(self.lib.ssnet_product_bytes_conv(self._ctx, B, C, H, W, Co, 1, 1, 1, 0), B, Co, H * W)
+        self._reserve_product(self._size("ssnet_product_bytes_conv", B, C, H, W, Co, 1, 1, 1, 0), B, Co, H * W)
         self._ok(self.lib.ssnet_conv1x1_product_prepacked(self._ctx, _dptr(x_packed), _dptr(w_packed), B, C, H * W, Co),
                  "ssnet_conv1x1_product_prepacked")
 
     def conv_product_planes(self, planes: torch.Tensor, w_packed: torch.Tensor, B: int, C: int, H: int, W: int, Co: int,
                             kh: int, kw: int, stride: int, pad: int):
         Ho, Wo = (H + 2 * pad - kh) // stride + 1, (W + 2 * pad - kw) // stride + 1
-        self._reserve_product(self.lib.ssnet_product_bytes_conv(self._ctx, B, C, H, W, Co, kh, kw, stride, pad), B, Co,
+        self._reserve_product(self._size("ssnet_product_bytes_conv", B, C, H, W, Co, kh, kw, stride, pad), B, Co,
                               Ho * Wo)
         self._ok(self.lib.ssnet_conv_product_planes(self._ctx, _dptr(planes), _dptr(w_packed), B, C, H, W, Co, kh, kw,
                                                     stride, pad), "ssnet_conv_product_planes")
@@ -408,8 +436,8 @@ class SSNet:
 
     def degree_reduce(self, c: Optional[torch.Tensor], stream_id: int, out: Optional[torch.Tensor] = None) -> torch.Tensor:
         cp, c = self._incoming(c, out)
-        count = c[0].numel()
-        self.reserve(self.workspace_bytes_stream(count))
+        count = _per_party(c)
+        self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(c)
         self._ok(self.lib.ssnet_degree_reduce(self._ctx, cp, count, stream_id, _dptr(out)),
@@ -427,8 +455,8 @@ class SSNet:
 
     def truncate(self, x: torch.Tensor, stream_id: int, out: Optional[torch.Tensor] = None) -> torch.Tensor:
         _check_i64(x, "x")
-        count = x[0].numel()
-        self.reserve(self.workspace_bytes_stream(count))
+        count = _per_party(x)
+        self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(x)
         self._ok(self.lib.ssnet_truncate(self._ctx, _dptr(x), count, stream_id, _dptr(out)), "ssnet_truncate")
@@ -437,8 +465,8 @@ class SSNet:
     def degree_reduce_truncate(self, c: Optional[torch.Tensor], stream_id: int,
                                out: Optional[torch.Tensor] = None) -> torch.Tensor:
         cp, c = self._incoming(c, out)
-        count = c[0].numel()
-        self.reserve(self.workspace_bytes_stream(count))
+        count = _per_party(c)
+        self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(c)
         self._ok(self.lib.ssnet_degree_reduce_truncate(self._ctx, cp, count, stream_id, _dptr(out)),
@@ -447,8 +475,8 @@ class SSNet:
 
     def truncate_div(self, x: torch.Tensor, kdiv: int, stream_id: int, out: Optional[torch.Tensor] = None) -> torch.Tensor:
         _check_i64(x, "x")
-        count = x[0].numel()
-        self.reserve(self.workspace_bytes_stream(count))
+        count = _per_party(x)
+        self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(x)
         self._ok(self.lib.ssnet_truncate_div(self._ctx, _dptr(x), count, kdiv, stream_id, _dptr(out)), "ssnet_truncate_div")
@@ -457,8 +485,8 @@ class SSNet:
     def degree_reduce_truncate_div(self, c: Optional[torch.Tensor], kdiv: int, stream_id: int,
                                    out: Optional[torch.Tensor] = None) -> torch.Tensor:
         cp, c = self._incoming(c, out)
-        count = c[0].numel()
-        self.reserve(self.workspace_bytes_stream(count))
+        count = _per_party(c)
+        self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(c)
         self._ok(self.lib.ssnet_degree_reduce_truncate_div(self._ctx, cp, count, kdiv, stream_id, _dptr(out)),
@@ -470,8 +498,8 @@ class SSNet:
                                            secret: Optional[torch.Tensor] = None):
         """-> (truncated shares [n][...], their reconstruction from the parties `ids`)"""
         cp, c = self._incoming(c, out)
-        count = c[0].numel()
-        self.reserve(self.workspace_bytes_stream(count))
+        count = _per_party(c)
+        self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(c)
         if secret is None:
@@ -489,7 +517,7 @@ class SSNet:
                                out: Optional[torch.Tensor] = None, secret: Optional[torch.Tensor] = None):
         """-> (truncated shares, their reconstruction or None): the outputs of the protocol calls, no messages"""
         cp, c = self._incoming(c, out)
-        count = c[0].numel()
+        count = _per_party(c)
         if out is None:
             out = torch.empty_like(c)
         if ids is not None and secret is None:
@@ -506,12 +534,11 @@ class SSNet:
                              want_planes: bool = False):
         """c [n][B][C][H][W] (or [n][B][C]) product shares -> (shares of ReLU(trunc(.)), limb planes or None)"""
         cp, c = self._incoming(c, out)
-        n, B, C = c.shape[0], c.shape[1], c.shape[2]
-        HW = c[0, 0, 0].numel()
-        count = c[0].numel()
+        B, C = c.size(1), c.size(2)
+        HW = _per_party(c) // (B * C) if c.numel() else c[0, 0, 0].numel()
         if beta.numel() != c.numel() or betainv.numel() != c.numel():
             raise SSNetError(EINVAL, "reduce_truncate_relu: mask shares must have the shape of c")
-        self.reserve(self.lib.ssnet_workspace_bytes_layer_tail(self._ctx, B, C, HW))
+        self.reserve(self._size("ssnet_workspace_bytes_layer_tail", B, C, HW))
         if out is None:
             out = torch.empty_like(c)
         if want_planes and planes is None:
@@ -526,8 +553,8 @@ class SSNet:
                                     want_planes: bool = False):
         """the outputs of reduce_truncate_relu (shares, limb planes) in one pass without messages"""
         cp, c = self._incoming(c, out)
-        B, C = c.shape[1], c.shape[2]
-        HW = c[0, 0, 0].numel()
+        B, C = c.size(1), c.size(2)
+        HW = _per_party(c) // (B * C) if c.numel() else c[0, 0, 0].numel()
         if beta.numel() != c.numel() or betainv.numel() != c.numel():
             raise SSNetError(EINVAL, "reduce_truncate_relu_direct: mask shares must have the shape of c")
         if out is None:
@@ -554,10 +581,10 @@ class SSNet:
         _check_i64(x, "x")
         _check_i64(beta, "beta")
         _check_i64(betainv, "betainv")
-        count = x[0].numel()
+        count = _per_party(x)
         if beta.numel() != x.numel() or betainv.numel() != x.numel():
             raise SSNetError(EINVAL, "relu: mask shares must have the shape of x")
-        self.reserve(self.workspace_bytes_stream(count))
+        self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(x)
         self._ok(self.lib.ssnet_relu(self._ctx, _dptr(x), _dptr(beta), _dptr(betainv), count, _dptr(out)), "ssnet_relu")
@@ -571,7 +598,7 @@ class SSNet:
     def pool_masks(self, planes: int, H: int, W: int, kernel, stride, pad, stream_id: int, device=None):
         """-> (shares of beta [n, planes, H, W], shares of beta^-1 [n, planes, Ho, Wo]); offline preprocessing"""
         (kh, kw), (sh, sw), (ph, pw) = kernel, stride, pad
-        Ho, Wo = self.pool_out_size(H, kh, sh, ph), self.pool_out_size(W, kw, sw, pw)
+        Ho, Wo = self._size("ssnet_pool_out_size", H, kh, sh, ph), self._size("ssnet_pool_out_size", W, kw, sw, pw)
         if Ho < 1 or Wo < 1:
             raise SSNetError(EINVAL, "pool_masks: the pooling kernel does not fit the image")
         device = device or self.device or "cuda"
@@ -589,11 +616,11 @@ class SSNet:
         _check_i64(betainv, "betainv")
         (kh, kw), (sh, sw), (ph, pw) = kernel, stride, pad
         H, W = x.shape[-2], x.shape[-1]
-        planes = x[0].numel() // (H * W)
-        Ho, Wo = self.pool_out_size(H, kh, sh, ph), self.pool_out_size(W, kw, sw, pw)
+        planes = _per_party(x) // (H * W)
+        Ho, Wo = self._size("ssnet_pool_out_size", H, kh, sh, ph), self._size("ssnet_pool_out_size", W, kw, sw, pw)
         if Ho < 1 or Wo < 1 or beta.numel() != x.numel() or betainv.numel() != self.n * planes * Ho * Wo:
             raise SSNetError(EINVAL, "relu_pool: mask shares do not fit x and the pooling kernel")
-        self.reserve(self.workspace_bytes_stream(max(planes * H * W, planes * Ho * Wo)))
+        self._reserve_stream(max(planes * H * W, planes * Ho * Wo))
         if out is None:
             out = torch.empty(tuple(x.shape[:-2]) + (Ho, Wo), dtype=torch.int64, device=x.device)
         elif out.numel() != self.n * planes * Ho * Wo:

@@ -174,20 +174,19 @@ class Chain:
                 ss.conv_mod_packed(xs, self.packed[l], L.cout, L.ksize, L.ksize, L.stride, L.pad, out=y)
             else:
                 ss.linear_mod_packed(xs, self.packed[l], L.cout, out=y)
-        yv = y.view(ss.n, -1)
-        c = None if pending else yv    # None: the pending product
+        c = None if pending else y     # None: the pending product
         if "D" in stages:   # the outputs of reduction, truncation and opening without the protocol's messages
-            ss.reduce_truncate_direct(c, stream_id=l, ids=self.ids, out=yv, secret=self.rec[l])
+            ss.reduce_truncate_direct(c, stream_id=l, ids=self.ids, out=y, secret=self.rec[l])
             return self.rec[l]
         if "d" in stages and "t" in stages and "r" in stages:   # one launch for the three steps
-            ss.degree_reduce_truncate_reconstruct(c, stream_id=l, ids=self.ids, out=yv, secret=self.rec[l])
+            ss.degree_reduce_truncate_reconstruct(c, stream_id=l, ids=self.ids, out=y, secret=self.rec[l])
             return self.rec[l]
         if "d" in stages and "t" in stages:
-            ss.degree_reduce_truncate(c, stream_id=l, out=yv)
+            ss.degree_reduce_truncate(c, stream_id=l, out=y)
         elif "d" in stages:
-            ss.degree_reduce(c, stream_id=l, out=yv)
+            ss.degree_reduce(c, stream_id=l, out=y)
         elif "t" in stages:
-            ss.truncate(yv, stream_id=l, out=yv)
+            ss.truncate(y, stream_id=l, out=y)
         if "r" in stages:
             ss.reconstruct(y, self.ids, out=self.rec[l])
         return self.rec[l]
@@ -225,9 +224,10 @@ class Chain:
         ss = self.ss
         dev = ss.device or "cuda"
         self.pool_on_shares = pool_on_shares
+        self.pool_specs = [pool_spec(L) for L in self.layers]
         self.masks, self.pooled = [], []
         for l, L in enumerate(self.layers):
-            spec = pool_spec(L) if pool_on_shares else None
+            spec = self.pool_specs[l] if pool_on_shares else None
             if L.post == "relu":
                 self.masks.append(ss.nonlinear_masks(self._out_shape(L), stream_id=self.MASK_STREAM_BASE + l, device=dev))
             elif spec is not None:
@@ -274,27 +274,26 @@ class Chain:
             ss.conv_mod_packed(x_shares, self.packed[l], L.cout, L.ksize, L.ksize, L.stride, L.pad, out=y)
         else:
             ss.linear_mod_packed(x_shares, self.packed[l], L.cout, out=y)
-        yv = y.view(ss.n, -1)
-        c = None if pending else yv
+        c = None if pending else y
         if L.post == "relu":
             # reduce + truncate + ReLU in one launch, which also leaves the next layer's limb planes
             b, bi = self.masks[l]
             nxt = l + 1 < len(self.layers) and self.sec_planes[l + 1]
             if direct:   # the same shares and planes in one pass without the protocol's messages
-                ss.reduce_truncate_relu_direct(None if pending else y, b, bi, out=y, planes=self.x_planes if nxt else None)
+                ss.reduce_truncate_relu_direct(c, b, bi, out=y, planes=self.x_planes if nxt else None)
             else:
-                ss.reduce_truncate_relu(None if pending else y, l, b, bi, out=y, planes=self.x_planes if nxt else None)
+                ss.reduce_truncate_relu(c, l, b, bi, out=y, planes=self.x_planes if nxt else None)
             return y, None
         if self.pooled[l] is not None:
             # reduce + truncate (with the division of an average), then ReLU and pooling under the mask
-            kern, stride, pad, mode, kdiv = pool_spec(L)
+            kern, stride, pad, mode, kdiv = self.pool_specs[l]
             b, bi = self.masks[l]
             if kdiv > 1:
-                ss.degree_reduce_truncate_div(c, kdiv, stream_id=l, out=yv)
+                ss.degree_reduce_truncate_div(c, kdiv, stream_id=l, out=y)
             else:
-                ss.degree_reduce_truncate(c, stream_id=l, out=yv)
+                ss.degree_reduce_truncate(c, stream_id=l, out=y)
             return ss.relu_pool(y, b, bi, kern, stride, pad, mode, out=self.pooled[l]), None
-        ss.degree_reduce_truncate_reconstruct(c, stream_id=l, ids=self.ids, out=yv, secret=self.rec[l])
+        ss.degree_reduce_truncate_reconstruct(c, stream_id=l, ids=self.ids, out=y, secret=self.rec[l])
         return None, self.rec[l]
 
     def _planes_ready(self, l: int, x_shares) -> bool:
