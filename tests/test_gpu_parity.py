@@ -623,3 +623,33 @@ def test_reduction_kernels_of_every_degree(n, t, counts):
         assert np.array_equal(to_np(s.messages()[: red.size + trunc.size]), np.concatenate([red, trunc]))
         assert np.array_equal(to_np(s.degree_reduce_truncate_div(d, 49, stream_id=9)),
                               orc.truncate_div(want_r, n, t, 13, 49, P61, 19, 9))
+
+
+@pytest.mark.parametrize("n,t,geoms", [
+    (3, 1, [(1, 515, 512, (3, 3), (2, 2), (1, 1)),      # few wide planes: two launches
+            (2, 50, 40, (7, 7), (7, 7), (0, 0))]),      # runs of one output row, rows left over
+    (5, 2, [(2, 11, 3000, (3, 3), (1, 1), (1, 1)),      # a kernel's rows exceed LDS: two launches
+            (2, 30, 20, (7, 5), (1, 2), (3, 2)),        # first rows of a run lie in the padding
+            (3, 40, 17, (2, 2), (5, 3), (0, 0))]),      # gaps between kernels
+    (7, 3, [(125, 112, 112, (3, 3), (2, 2), (1, 1)),    # messages stored past the caches
+            (37, 5, 5, (2, 2), (1, 1), (0, 0))])])      # last run holds fewer planes
+def test_relu_pool_runs(n, t, geoms):
+    """How the one-launch form cuts the planes into runs: results and every message (each element opened by one owner)."""
+    s = SSNet(n, t, seed=23)
+    nr = 2 * t + 1
+    for planes, H, W, kern, stride, pad in geoms:
+        say("relu_pool runs", n, t, planes, H, W, kern, stride, pad)
+        geo = (H, W) + kern + stride + pad
+        sb, sbi = s.pool_masks(planes, H, W, kern, stride, pad, stream_id=4)
+        osb, osbi = to_np(sb).reshape(n, -1), to_np(sbi).reshape(n, -1)
+        cin, cout = planes * H * W, osbi.shape[1]
+        xs = np.random.default_rng(planes).integers(-(1 << 25), 1 << 25, cin, dtype=np.int64)
+        x = orc.share(np.where(xs < 0, xs + P61, xs).astype(np.uint64), n, t, P61, 23, 13)
+        for mode in (SSNet.POOL_MAX, SSNet.POOL_SUM):
+            want, msg, y = orc.relu_pool(x, osb, osbi, planes, *geo, mode, n, t, P61, full=True)
+            s._ws[65536:].zero_() if s._ws is not None else None      # so that a message left out shows
+            got = s.relu_pool(to_dev(x).view(n, planes, H, W), sb, sbi, kern, stride, pad, mode)
+            ws = to_np(s.messages()[: (nr + 1) * cin + cout])
+            assert np.array_equal(ws[: nr * cin].reshape(nr, cin), msg)
+            assert np.array_equal(ws[(nr + 1) * cin:], y)
+            assert np.array_equal(to_np(got).reshape(n, -1), want)
