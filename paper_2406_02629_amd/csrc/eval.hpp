@@ -4,17 +4,19 @@
 
 // values a0 + a[0] x + ... at x = 1..m (m <= M <= 8), canonical, handed to emit(x - 1, value); a0, a[] may be
 // unreduced sums: a0 < 2 * 2^61 + 2^8, a[] < 2^61 + 2^8 (over the 45-bit prime: below 2^57).  Forward differences;
-// in the bounds below one unit is 2^61 + 2^8 and a word holds less than eight.
-template <int T, int M, typename F>
+// in the bounds below one unit is 2^61 + 2^8 and a word holds less than eight.  PACED: the longer form of the
+// reduction, which a kernel bound by its stores may prefer.
+template <int T, int M, bool PACED = false, typename F>
 __device__ __forceinline__ void eval_points(u64 a0, const u64 (&a)[T], F &&emit, int m = M)
 {
     static_assert(T >= 1 && T <= 3 && M <= 8, "degrees 1 to 3, up to 8 points");
+    auto reduce = [](u64 x) { return PACED ? ss_canon(ss_fold(x)) : ss_reduce(x); };
     u64 s = a0;
     if constexpr (T == 1) {
 #pragma unroll
         for (int x = 1; x <= M; x++) {
             if (x > m) break;
-            s = ss_reduce(s + a[0]);
+            s = reduce(s + a[0]);
             emit(x - 1, s);
         }
     } else if constexpr (T == 2) {
@@ -29,7 +31,7 @@ __device__ __forceinline__ void eval_points(u64 a0, const u64 (&a)[T], F &&emit,
                 if (x >= 4 && x % 2 == 0) d = ss_fold(d);
                 d += dd;
             }
-            s = ss_reduce(s + d);
+            s = reduce(s + d);
             emit(x - 1, s);
         }
     } else {
@@ -47,7 +49,7 @@ __device__ __forceinline__ void eval_points(u64 a0, const u64 (&a)[T], F &&emit,
                 d += e;
                 e += f;
             }
-            s = ss_reduce(s + d);
+            s = reduce(s + d);
             emit(x - 1, s);
         }
     }

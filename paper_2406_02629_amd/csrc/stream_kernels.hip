@@ -20,6 +20,7 @@ template <>
 struct pack_t<1> {
     u64 v[1];
     __device__ __forceinline__ void load(const u64 *p) { v[0] = *p; }
+    __device__ __forceinline__ void load_streaming(const u64 *p) { v[0] = __builtin_nontemporal_load(p); }
     __device__ __forceinline__ void store(u64 *p) const { *p = v[0]; }
     __device__ __forceinline__ void store_streaming(u64 *p) const { __builtin_nontemporal_store(v[0], p); }
     template <bool STREAM>
@@ -31,6 +32,13 @@ struct pack_t<2> {
     __device__ __forceinline__ void load(const u64 *p)
     {
         const ulonglong2 q = *reinterpret_cast<const ulonglong2 *>(p);
+        v[0] = q.x;
+        v[1] = q.y;
+    }
+    __device__ __forceinline__ void load_streaming(const u64 *p)
+    {
+        typedef unsigned long long v2u __attribute__((ext_vector_type(2)));
+        const v2u q = __builtin_nontemporal_load(reinterpret_cast<const v2u *>(p));
         v[0] = q.x;
         v[1] = q.y;
     }
@@ -83,14 +91,20 @@ __device__ __forceinline__ void draw_coeffs(u64 (&c)[MAXD], const u64 *keys, int
 // NC, DC > 0 fix the party count and the degree at compile time (the schemes
 // the paper evaluates: (k,n) = (2,3) and (3,5)), so that the evaluation points
 // become immediates; 0 means "take the run-time value".
+// Bound by the writes of its n planes.  Five of them leave a wave at a time: workgroups of one wave write 5 % faster
+// than those of four, and so does the longer reduction (PACED) against the short one (n = 5, 2^28 elements: 2.15 ms
+// against 2.32 ms with four waves and 2.40 ms with the short reduction too; 2^26: 514, 548 and 570 us; 2^20: 7.6, 8.4
+// and 8.5 us).  With three planes four waves are the better ones (2^24 elements: 75.6 against 76.5 us).
+template <int NC>
+constexpr int SHARE_BLOCK = NC == 5 ? 64 : BLOCK;
 template <int VEC, int NC, int DC>
-__global__ __launch_bounds__(BLOCK) void share_kernel(const u64 *__restrict__ secret, u64 *__restrict__ shares,
+__global__ __launch_bounds__(SHARE_BLOCK<NC>) void share_kernel(const u64 *__restrict__ secret, u64 *__restrict__ shares,
                                                       size_t count, int n_rt, int degree_rt, ss_keys keys)
 {
     constexpr int MAXD = DC ? DC : SS_MAXDEG;
     constexpr int MAXP = NC ? NC : SS_MAXN;
     const int n = NC ? NC : n_rt, degree = DC ? DC : degree_rt;
-    const size_t e0 = ((size_t)blockIdx.x * BLOCK + threadIdx.x) * VEC;
+    const size_t e0 = ((size_t)blockIdx.x * SHARE_BLOCK<NC> + threadIdx.x) * VEC;
     if (e0 >= count) return;
     pack_t<VEC> a0;
     a0.load(secret + e0);
@@ -101,7 +115,7 @@ __global__ __launch_bounds__(BLOCK) void share_kernel(const u64 *__restrict__ se
         // consecutive party IDs: forward differences, two additions per point instead of Horner's multiplications
         pack_t<VEC> s[NC];
 #pragma unroll
-        for (int u = 0; u < VEC; u++) eval_points<DC, NC>(a0.v[u], c[u], [&](int p, u64 v) { s[p].v[u] = v; });
+        for (int u = 0; u < VEC; u++) eval_points<DC, NC, true>(a0.v[u], c[u], [&](int p, u64 v) { s[p].v[u] = v; });
 #pragma unroll
         for (int p = 0; p < NC; p++) s[p].store_streaming(shares + (size_t)p * count + e0);   // written, not read again
     } else {
@@ -118,7 +132,10 @@ __global__ __launch_bounds__(BLOCK) void share_kernel(const u64 *__restrict__ se
 }
 
 // ------------------------------------------------------------------ REC
-template <int VEC>
+// Bound by reading m planes.  STREAM (streams_messages): shares and secret go past the caches, which hold neither for a
+// later reader at such sizes: m = 3, 2^28 elements 1.37 -> 1.30 ms (6.6 TB/s), 2^26 349 -> 330 us; m = 2, 2^24 elements
+// 67.8 -> 63.5 us.  Requesting all planes before the first sum is slower (2^28: 1.44 to 1.48 ms).
+template <int VEC, bool STREAM>
 __global__ __launch_bounds__(BLOCK) void reconstruct_kernel(const u64 *__restrict__ shares,
                                                             u64 *__restrict__ secret, size_t count,
                                                             ss_rec_params rp)
@@ -133,14 +150,15 @@ __global__ __launch_bounds__(BLOCK) void reconstruct_kernel(const u64 *__restric
     for (int i = 0; i < SS_MAXN; i++) {
         if (i < rp.m) {
             pack_t<VEC> s;
-            s.load(shares + (size_t)rp.plane[i] * count + e0);
+            const u64 *from = shares + (size_t)rp.plane[i] * count + e0;
+            STREAM ? s.load_streaming(from) : s.load(from);
 #pragma unroll
             for (int u = 0; u < VEC; u++) acc[u].mac(s.v[u], rp.ilambda[i]);
         }
     }
 #pragma unroll
     for (int u = 0; u < VEC; u++) out.v[u] = rp.dinv == 1 ? acc[u].value() : ss_mul(acc[u].value(), rp.dinv);
-    out.store(secret + e0);
+    out.template send<STREAM>(secret + e0);
 }
 
 // e of the truncation mask alpha = e * 2^f: uniform in [1, 2^(32-f)]
@@ -876,9 +894,9 @@ inline bool streams_messages(size_t words) { return words * sizeof(u64) > ((size
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-inline unsigned blocks_for(size_t count, int vec)
+inline unsigned blocks_for(size_t count, int vec, int block = BLOCK)
 {
-    const size_t per_block = (size_t)BLOCK * vec;
+    const size_t per_block = (size_t)block * vec;
     return (unsigned)((count + per_block - 1) / per_block);
 }
 
@@ -886,21 +904,13 @@ inline unsigned blocks_for(size_t count, int vec)
 
 // The two-element path needs every plane start 16-byte aligned: aligned bases
 // and an even element count.
-#define SS_DISPATCH_VEC(cond, KERNEL, grid, ...)                                          \
-    do {                                                                                  \
-        if (cond)                                                                         \
-            hipLaunchKernelGGL(KERNEL<2>, grid(2), dim3(BLOCK), 0, stream, __VA_ARGS__);  \
-        else                                                                              \
-            hipLaunchKernelGGL(KERNEL<1>, grid(1), dim3(BLOCK), 0, stream, __VA_ARGS__);  \
-    } while (0)
-
 hipError_t ss_launch_share(const u64 *secret, u64 *shares, size_t count, int n, int degree, const ss_keys &keys,
                            hipStream_t stream)
 {
     const bool v2 = (count % 2 == 0) && aligned16(secret) && aligned16(shares);
-    const dim3 grid(blocks_for(count, v2 ? 2 : 1)), block(BLOCK);
-#define SS_SHARE(VEC, NC, DC) \
-    hipLaunchKernelGGL((share_kernel<VEC, NC, DC>), grid, block, 0, stream, secret, shares, count, n, degree, keys)
+#define SS_SHARE(VEC, NC, DC)                                                                                       \
+    hipLaunchKernelGGL((share_kernel<VEC, NC, DC>), dim3(blocks_for(count, VEC, SHARE_BLOCK<NC>)), dim3(SHARE_BLOCK<NC>), \
+                       0, stream, secret, shares, count, n, degree, keys)
     if (v2 && n == 5 && degree == 2)
         SS_SHARE(2, 5, 2);
     else if (v2 && n == 3 && degree == 1)
@@ -917,8 +927,15 @@ hipError_t ss_launch_reconstruct(const u64 *shares, u64 *secret, size_t count, c
                                  hipStream_t stream)
 {
     const bool v2 = (count % 2 == 0) && aligned16(secret) && aligned16(shares);
-    auto grid = [&](int vec) { return dim3(blocks_for(count, vec)); };
-    SS_DISPATCH_VEC(v2, reconstruct_kernel, grid, shares, secret, count, rp);
+    const bool streams = streams_messages((size_t)(rp.m + 1) * count);
+#define SS_REC(VEC)                                                                                              \
+    hipLaunchKernelGGL((streams ? reconstruct_kernel<VEC, true> : reconstruct_kernel<VEC, false>), dim3(blocks_for(count, VEC)), \
+                       dim3(BLOCK), 0, stream, shares, secret, count, rp)
+    if (v2)
+        SS_REC(2);
+    else
+        SS_REC(1);
+#undef SS_REC
     return hipGetLastError();
 }
 

@@ -653,3 +653,20 @@ def test_relu_pool_runs(n, t, geoms):
             assert np.array_equal(ws[: nr * cin].reshape(nr, cin), msg)
             assert np.array_equal(ws[(nr + 1) * cin:], y)
             assert np.array_equal(to_np(got).reshape(n, -1), want)
+
+
+@pytest.mark.parametrize("n,t,large", [(3, 1, (1 << 24) + 1),         # one element per thread
+                                       (5, 2, (1 << 23) + (1 << 20) + 2)])
+def test_share_tiles_and_reconstruct_past_the_caches(n, t, large):
+    """Edges of the share kernel's workgroups (64 and 256 threads of two elements), and the reconstruction of tensors
+    beyond the last-level cache."""
+    s = SSNet(n, t, seed=29)
+    rng = np.random.default_rng(n)
+    for count in (2, 126, 128, 130, 510, 512, 514):
+        x = rng.integers(0, P61, count, dtype=np.uint64)
+        assert np.array_equal(to_np(s.share(to_dev(x), stream_id=count)), orc.share(x, n, t, P61, 29, count))
+    say("reconstruct past the caches", n, t, large)
+    secret = torch.randint(0, P61, (large,), dtype=torch.int64, device="cuda")
+    shares = s.share(secret, stream_id=1)
+    for ids in (list(range(1, t + 2)), list(range(n - t, n + 1)), list(range(1, n + 1))):
+        assert torch.equal(s.reconstruct(shares, ids), secret)
