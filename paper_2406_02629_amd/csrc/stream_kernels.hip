@@ -7,6 +7,7 @@
 #include "kernels.hpp"
 #include "eval.hpp"
 #include "digits.hpp"
+#include "pool_plan.hpp"
 
 namespace SS_NS {
 
@@ -780,9 +781,9 @@ __global__ __launch_bounds__(BLOCK) void pool_masks_kernel(u64 *__restrict__ sh,
 // ReLU and pooling in one launch: a workgroup opens a run of input elements (steps 1 and 2 of relu_kernel), keeps the
 // rectified values in LDS, pools them there and takes the mask off.  Bound by memory: 2 (2t+1) words read and 2t+2 written
 // per input element, and the pooled values never make the way through memory between two launches.  A run is `P` whole
-// planes or, for larger ones, the input rows of `R` output rows of one plane (`strips` runs per plane): both are contiguous.
-// Rows that the next run's kernels share with this one's are opened by both and their messages are written by the later
-// run, so a run owns the rows from its first kernel's to the next run's first.
+// planes or, for larger ones, the input rows of `R` output rows of one plane (`strips` runs per plane, ss_pool_cut): both
+// are contiguous.  Rows that the next run's kernels share with this one's are opened by both and their messages are written
+// by the later run, so a run owns the rows from its first kernel's to the next run's first.
 // n = 5, 3 x 3 / 2 on 192 planes of 112 x 112: 59.0 us, in two launches 64.1; 7 x 7 on 2048 planes
 // of 7 x 7: 9.8 and 21.8 us.
 template <int T, bool STREAM>
@@ -797,10 +798,7 @@ __global__ __launch_bounds__(512) void relu_pool_kernel(const u64 *__restrict__ 
     const size_t cin = (size_t)planes * g.H * g.W, cout = (size_t)planes * g.Ho * g.Wo;
     const int plane = strips == 1 ? blockIdx.x * P : blockIdx.x / strips, s = strips == 1 ? 0 : blockIdx.x - plane * strips;
     const int many = min(P, planes - plane);
-    const int oh0 = s * R, oh1 = min(g.Ho, oh0 + R);
-    const int row0 = s == 0 ? 0 : max(0, oh0 * g.sh - g.ph);                             // first row of the run
-    const int own1 = s == strips - 1 ? g.H : max(0, oh1 * g.sh - g.ph);                  // first row of the next run
-    const int need1 = min(g.H, (oh1 - 1) * g.sh - g.ph + g.kh);                          // past the last row pooled here
+    const auto [oh0, oh1, row0, own1, need1] = ss_pool_cut(s, strips, R, g.H, g.kh, g.sh, g.ph, g.Ho);
     const bool whole = strips == 1;
     const int open = whole ? many * g.H * g.W : (max(own1, need1) - row0) * g.W, own = whole ? open : (own1 - row0) * g.W,
               keep = whole ? open : (need1 - row0) * g.W;
@@ -849,9 +847,9 @@ __global__ __launch_bounds__(512) void relu_pool_kernel(const u64 *__restrict__ 
     }
 }
 
-// The same from the rectified values in memory, where a kernel's rows do not fit into LDS: one thread per
-// pooled element: the maximum or the sum of the opened, rectified products r = max(x*beta, 0) over the
-// kernel's elements inside the plane (padding adds nothing to a sum and cannot win a maximum of
+// The same from the rectified values in memory, where a kernel's rows do not fit into LDS or the output lies in the
+// mask (ss_plan_pool).  One thread per pooled element: the maximum or the sum of the opened, rectified products
+// r = max(x*beta, 0) over the kernel's elements inside the plane (padding adds nothing to a sum and cannot win a maximum of
 // non-negative values), then y * betainv_m for every party.
 __global__ __launch_bounds__(BLOCK) void pool_maskoff_kernel(const u64 *__restrict__ rplain,
                                                              const u64 *__restrict__ sh_bi, u64 *__restrict__ yplain,
@@ -881,10 +879,6 @@ constexpr size_t VEC2_MIN_COUNT = (size_t)1 << 20;
 // 1.2 times as long at 1 K elements and as long at 16 K.  For t = 1 and 2, and with the truncation in the same launch, it
 // is the faster one at every size (n = 5, 64 elements: 4.2 against 6.5 us).
 constexpr size_t LANES_MAX_COUNT = 16 * 1024;
-
-// Most LDS that a run of relu_pool_kernel may take (what a launch gets without asking for more): kernels of up to 8192
-// elements in all their full rows.
-constexpr size_t POOL_LDS_BYTES = 64 * 1024;
 
 // Messages are written once and not read by the library again.  Left to the caches they cost nothing while a call's
 // traffic fits the 256 MB of the last level (the next call overwrites them there); beyond, writing them past the
@@ -1052,31 +1046,14 @@ hipError_t ss_launch_relu_pool(const u64 *x, const u64 *sh_b, const u64 *sh_bi, 
 {
     const size_t cin = planes * g.H * g.W, cout = planes * g.Ho * g.Wo;
     const bool streams = streams_messages((size_t)(3 * (2 * np.t + 1) + 1) * cin);
-    // A run is about as many elements as the workgroup has threads: longer ones are slower (2 x 2 on 1024 planes of 64 x 64,
-    // n = 5: 115 us with runs of 256, 147 us with 1024; 118 us in two launches).  Kernels that overlap make it longer, until
-    // at most one row in eight is opened twice, as far as there are enough output rows for four workgroups per CU.
-    const size_t target = 256, enough = 1024, plane = (size_t)g.H * g.W;
-    int P = 1, R = g.Ho, strips = 1;
-    if (plane <= target) {
-        P = (int)(target / plane);
-    } else {
-        const size_t rows = target / g.W;   // input rows of a run
-        R = rows > (size_t)g.kh ? (int)((rows - g.kh) / g.sh + 1) : 1;
-        if (g.kh > g.sh) R = max(R, (int)min((size_t)((8 * (g.kh - g.sh) + g.sh - 1) / g.sh), planes * g.Ho / enough));
-        R = min(R, g.Ho);
-        strips = (g.Ho + R - 1) / R;
-        if (strips == 1) R = g.Ho;
-    }
-    const size_t run = strips == 1 ? P * plane : (size_t)((R - 1) * g.sh + g.kh) * g.W, lds = run * sizeof(u64);
-    const size_t blocks = strips == 1 ? (planes + P - 1) / P : planes * strips;
-    const int threads = run > 256 && run <= 512 ? 512 : 256;   // one pass over the run if it takes twice the threads
-    // few wide planes under overlapping kernels would open half their rows twice (4 planes of 400 x 400, 3 x 3 / 2: 23.8
-    // against 21.5 us in two launches); below 256 K elements the launch saved is worth more (16 of 112 x 112: 9.6, 10.6 us)
-    const bool twice = strips > 1 && 3 * (g.kh - g.sh) > R * g.sh && cin >= ((size_t)1 << 18);
-    if (lds <= POOL_LDS_BYTES && !twice && planes < ((size_t)1 << 31) && blocks < ((size_t)1 << 31)) {
+    // the shares of parties 1..2t+1 are what a call reads of the mask
+    const bool out_in_mask = out < sh_b + (2 * np.t + 1) * cin && sh_b < out + (size_t)np.n * cout;
+    const ss_pool_plan p = ss_plan_pool(planes, g.H, g.W, g.kh, g.sh, g.Ho, out_in_mask);
+    if (p.one_launch) {
 #define SS_POOL(T)                                                                                                    \
-    hipLaunchKernelGGL((streams ? relu_pool_kernel<T, true> : relu_pool_kernel<T, false>), dim3((unsigned)blocks), dim3(threads), \
-                       lds, stream, x, sh_b, sh_bi, msg, rplain, yplain, out, (int)planes, P, R, strips, g, np)
+    hipLaunchKernelGGL((streams ? relu_pool_kernel<T, true> : relu_pool_kernel<T, false>), dim3((unsigned)p.blocks), \
+                       dim3(p.threads), p.lds, stream, x, sh_b, sh_bi, msg, rplain, yplain, out, (int)planes, p.P, p.R, \
+                       p.strips, g, np)
         if (np.t == 1)
             SS_POOL(1);
         else if (np.t == 2)

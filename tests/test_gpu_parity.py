@@ -655,6 +655,33 @@ def test_relu_pool_runs(n, t, geoms):
             assert np.array_equal(to_np(got).reshape(n, -1), want)
 
 
+@pytest.mark.parametrize("n,t", [(3, 1), (5, 2), (7, 3)])
+def test_relu_pool_output_in_the_masks(n, t):
+    """d_out in the memory of d_beta (at its start, across its parties, in shares that the call does not read), and
+    d_out = d_betainv: results and messages as with memory of its own."""
+    s = SSNet(n, t, seed=41)
+    nr = 2 * t + 1
+    for planes, H, W, kern, stride, pad in [(40, 56, 56, (3, 3), (2, 2), (1, 1)), (300, 14, 14, (2, 2), (2, 2), (0, 0)),
+                                            (9, 90, 33, (3, 2), (1, 2), (2, 0))]:
+        geo = (H, W) + kern + stride + pad
+        sb, sbi = s.pool_masks(planes, H, W, kern, stride, pad, stream_id=6)
+        osb, osbi = to_np(sb).reshape(n, -1), to_np(sbi).reshape(n, -1)
+        cin, cout = planes * H * W, osbi.shape[1]
+        xs = np.random.default_rng(planes).integers(-(1 << 25), 1 << 25, cin, dtype=np.int64)
+        x = orc.share(np.where(xs < 0, xs + P61, xs).astype(np.uint64), n, t, P61, 41, 13)
+        want, msg, y = orc.relu_pool(x, osb, osbi, planes, *geo, SSNet.POOL_MAX, n, t, P61, full=True)
+        room = n * cin - n * cout
+        for off in [o for o in (0, room // 2, room) if room >= 0] + ["betainv"]:
+            say("relu_pool into the masks", n, t, planes, H, W, kern, off)
+            beta, betainv = sb.clone(), sbi.clone()
+            out = betainv if off == "betainv" else beta.view(-1)[off: off + n * cout].view(betainv.shape)
+            s.relu_pool(to_dev(x).view(n, planes, H, W), beta, betainv, kern, stride, pad, SSNet.POOL_MAX, out=out)
+            ws = to_np(s.messages()[: (nr + 1) * cin + cout])
+            assert np.array_equal(ws[: nr * cin].reshape(nr, cin), msg)
+            assert np.array_equal(ws[(nr + 1) * cin:], y)
+            assert np.array_equal(to_np(out).reshape(n, -1), want)
+
+
 @pytest.mark.parametrize("n,t,large", [(3, 1, (1 << 24) + 1),         # one element per thread
                                        (5, 2, (1 << 23) + (1 << 20) + 2)])
 def test_share_tiles_and_reconstruct_past_the_caches(n, t, large):
