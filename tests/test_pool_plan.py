@@ -80,3 +80,13 @@ def test_output_in_the_mask_goes_to_the_two_launches(lib):
     """In one launch, workgroups would write the output where others still read d_beta."""
     for planes, H, W, kh, sh, ph, Ho in geometries(5000):
         assert not lib.plan(planes, H, W, kh, sh, Ho, True).one_launch
+
+
+def test_launches_hold_less_than_2_to_the_32_threads(lib):
+    """Runs of less than their workgroup's threads: the two launches take one thread per element and still fit."""
+    for planes, H, W, kh, sh, ph in [((1 << 24) - 1, 1, 129, 1, 1, 0), (1 << 24, 1, 129, 1, 1, 0), (1 << 24, 11, 20, 2, 2, 0),
+                                     (1 << 22, 4, 257, 1, 1, 0), (1 << 21, 4, 257, 1, 1, 0), (1 << 23, 2, 180, 1, 1, 0)]:
+        assert planes * H * W < 1 << 32
+        p = lib.plan(planes, H, W, kh, sh, (H + 2 * ph - kh) // sh + 1, False)
+        assert p.one_launch == (p.blocks * p.threads < 1 << 32), (planes, H, W)
+    assert not lib.plan(1 << 24, 1, 129, 1, 1, 1, False).one_launch
