@@ -85,7 +85,7 @@ def test_output_in_the_mask_goes_to_the_two_launches(lib):
 def test_launches_hold_less_than_2_to_the_32_threads(lib):
     """Runs of less than their workgroup's threads: the two launches take one thread per element and still fit."""
     for planes, H, W, kh, sh, ph in [((1 << 24) - 1, 1, 129, 1, 1, 0), (1 << 24, 1, 129, 1, 1, 0), (1 << 24, 11, 20, 2, 2, 0),
-                                     (1 << 22, 4, 257, 1, 1, 0), (1 << 21, 4, 257, 1, 1, 0), (1 << 23, 2, 180, 1, 1, 0)]:
+                                     (1 << 21, 4, 300, 1, 1, 0), ((1 << 21) - 1, 4, 300, 1, 1, 0), (1 << 23, 2, 180, 1, 1, 0)]:
         assert planes * H * W < 1 << 32
         p = lib.plan(planes, H, W, kh, sh, (H + 2 * ph - kh) // sh + 1, False)
         assert p.one_launch == (p.blocks * p.threads < 1 << 32), (planes, H, W)
