@@ -440,12 +440,12 @@ __global__ __launch_bounds__(BLOCK) void degree_reduce_lanes_kernel(const u64 *c
     out[(size_t)p * count + e] = ss_add(red.value(), ss_poly_eval<T>(0, z, T, p + 1));
 }
 
-// truncation of given shares (parties 1..k are read)
+// truncation of given shares (parties 1..k are read) from element `first` on
 template <int N, int T, bool STREAM>
 __global__ __launch_bounds__(BLOCK) void truncate_kernel(const u64 *x, u64 *__restrict__ umsg, u64 *__restrict__ wsh,
-                                                         u64 *out, size_t count, ss_tr_params tp)
+                                                         u64 *out, size_t count, size_t first, ss_tr_params tp)
 {
-    const size_t e = (size_t)blockIdx.x * BLOCK + threadIdx.x;
+    const size_t e = first + (size_t)blockIdx.x * BLOCK + threadIdx.x;
     if (e >= count) return;
     constexpr int K = T + 1;
     const u64 counter = ss_counter(e);
@@ -616,10 +616,11 @@ __global__ __launch_bounds__(BLOCK) void tail_direct_kernel(const u64 *c, const 
 // protocol compute, only what they end up with.
 template <int N, int T>
 __global__ __launch_bounds__(BLOCK) void reduce_truncate_direct_kernel(const u64 *c, u64 *out, u64 *__restrict__ rec,
-                                                                       size_t count, ss_nl_params open_all,
-                                                                       ss_tr_params tp, ss_part_src ps)
+                                                                       size_t count, size_t first,
+                                                                       ss_nl_params open_all, ss_tr_params tp,
+                                                                       ss_part_src ps)
 {
-    const size_t e = (size_t)blockIdx.x * BLOCK + threadIdx.x;
+    const size_t e = first + (size_t)blockIdx.x * BLOCK + threadIdx.x;   // from element `first` on
     if (e >= count) return;
     ss_sacc2 acc;
     acc.clear();
@@ -894,6 +895,15 @@ inline unsigned blocks_for(size_t count, int vec, int block = BLOCK)
     return (unsigned)((count + per_block - 1) / per_block);
 }
 
+// A launch holds less than 2^32 threads: tensors of more elements that take one thread each go in several launches.
+constexpr size_t LAUNCH_ELEMENTS = (size_t)1 << 31;
+template <typename F>
+inline void for_each_launch(size_t count, F &&launch)
+{
+    for (size_t first = 0; first < count; first += LAUNCH_ELEMENTS)
+        launch(first, dim3(blocks_for(count - first < LAUNCH_ELEMENTS ? count - first : LAUNCH_ELEMENTS, 1)));
+}
+
 }  // namespace
 
 // The two-element path needs every plane start 16-byte aligned: aligned bases
@@ -999,9 +1009,9 @@ hipError_t ss_launch_truncate(const u64 *x, u64 *u, u64 *wsh, u64 *out, size_t c
 {
     const bool streams = streams_messages((size_t)(2 * (tp.t + 1) + 2 * tp.n) * count);
 #define SS_LAUNCH(NC, TC)                                                                                           \
-    hipLaunchKernelGGL((streams ? truncate_kernel<NC, TC, true> : truncate_kernel<NC, TC, false>), dim3(blocks_for(count, 1)), \
-                       dim3(BLOCK), 0, stream, x, u, wsh, out, count, tp)
-    SS_SCHEME(tp.n, tp.t, SS_LAUNCH);
+    hipLaunchKernelGGL((streams ? truncate_kernel<NC, TC, true> : truncate_kernel<NC, TC, false>), grid, dim3(BLOCK), 0, \
+                       stream, x, u, wsh, out, count, first, tp)
+    for_each_launch(count, [&](size_t first, dim3 grid) { SS_SCHEME(tp.n, tp.t, SS_LAUNCH); });
 #undef SS_LAUNCH
     return hipGetLastError();
 }
@@ -1074,9 +1084,9 @@ hipError_t ss_launch_reduce_truncate_direct(const u64 *c, u64 *out, u64 *rec, si
                                             const ss_tr_params &tp, const ss_part_src &ps, hipStream_t stream)
 {
 #define SS_LAUNCH(NC, TC)                                                                                       \
-    hipLaunchKernelGGL((reduce_truncate_direct_kernel<NC, TC>), dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, out, \
-                       rec, count, open_all, tp, ps)
-    SS_SCHEME(tp.n, tp.t, SS_LAUNCH);
+    hipLaunchKernelGGL((reduce_truncate_direct_kernel<NC, TC>), grid, dim3(BLOCK), 0, stream, c, out, rec, count, first, \
+                       open_all, tp, ps)
+    for_each_launch(count, [&](size_t first, dim3 grid) { SS_SCHEME(tp.n, tp.t, SS_LAUNCH); });
 #undef SS_LAUNCH
     return hipGetLastError();
 }

@@ -697,3 +697,29 @@ def test_share_tiles_and_reconstruct_past_the_caches(n, t, large):
     shares = s.share(secret, stream_id=1)
     for ids in (list(range(1, t + 2)), list(range(n - t, n + 1)), list(range(1, n + 1))):
         assert torch.equal(s.reconstruct(shares, ids), secret)
+
+
+def test_reduce_truncate_direct_beyond_one_launch():
+    """2^32 + 2 elements: more than the threads of one launch.  Every share of element e is (e mod m) 2^f, a sharing of
+    that value, so the truncation gives e mod m; shares in place, the elements around the launches' edges word by word."""
+    n, t, f, seed, sid, m = 3, 1, 13, 31, 5, 1000003
+    count = (1 << 32) + 2
+    if torch.cuda.mem_get_info()[0] < 200 << 30:
+        pytest.skip("needs 172 GB of free device memory")
+    say("reduce_truncate_direct", n, t, count)
+    s = SSNet(n, t, f=f, seed=seed)
+    c = torch.empty((n, count), dtype=torch.int64, device="cuda")
+    step = 1 << 28
+    value = lambda e0: torch.arange(e0, min(count, e0 + step), device="cuda") % m
+    for e0 in range(0, count, step):
+        c[:, e0:e0 + step] = value(e0) << f
+    out, rec = s.reduce_truncate_direct(c, stream_id=sid, ids=[1, 2], out=c)
+    again = s.reconstruct(out, [2, 3])
+    for e0 in range(0, count, step):
+        assert torch.equal(rec[e0:e0 + step], value(e0)) and torch.equal(again[e0:e0 + step], value(e0)), e0
+    keys = [binding.rng_key(seed, dom, sid, 0, 1) for dom in (binding.DOM_TRUNC_GEN, binding.DOM_MASK_ALPHAT)]
+    for e in (0, (1 << 31) - 1, 1 << 31, (1 << 32) - 1, 1 << 32, count - 1):
+        slope = sum(binding.rng_field(k, e) for k in keys)
+        assert out[:, e].tolist() == [(e % m + (p + 1) * slope) % P61 for p in range(n)], e
+    del c, out, rec, again
+    torch.cuda.empty_cache()
