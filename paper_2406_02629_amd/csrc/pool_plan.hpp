@@ -59,7 +59,8 @@ inline ss_pool_plan ss_plan_pool(size_t planes, int H, int W, int kh, int sh, in
     // few wide planes under overlapping kernels would open half their rows twice (4 planes of 400 x 400, 3 x 3 / 2: 23.8
     // against 21.5 us in two launches); below 256 K elements the launch saved is worth more (16 of 112 x 112: 9.6, 10.6 us)
     const bool twice = p.strips > 1 && 3 * (kh - sh) > p.R * sh && cin >= ((size_t)1 << 18);
-    // a launch holds less than 2^32 threads, which runs shorter than their workgroup reach before cin does
+    // a launch holds less than 2^32 threads (a larger grid runs in part only), which runs shorter than their workgroup
+    // reach before cin does
     p.one_launch = p.lds <= SS_POOL_LDS_BYTES && !twice && !out_in_mask && planes < ((size_t)1 << 31) &&
                    p.blocks * p.threads < ((size_t)1 << 32);
     return p;

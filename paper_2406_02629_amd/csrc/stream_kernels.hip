@@ -895,8 +895,10 @@ inline unsigned blocks_for(size_t count, int vec, int block = BLOCK)
     return (unsigned)((count + per_block - 1) / per_block);
 }
 
-// A launch holds less than 2^32 threads: tensors of more elements that take one thread each go in several launches.
-constexpr size_t LAUNCH_ELEMENTS = (size_t)1 << 31;
+// A launch holds less than 2^32 threads in each direction.  The runtime takes a larger grid without an error and runs a
+// part of it, so that no launcher may reach it: a tensor goes in several launches or is refused.
+inline bool fits_launch(size_t blocks, int block = BLOCK) { return blocks * block < ((size_t)1 << 32); }
+constexpr size_t LAUNCH_ELEMENTS = (size_t)1 << 31;   // of a tensor that goes in several launches, one thread each
 template <typename F>
 inline void for_each_launch(size_t count, F &&launch)
 {
@@ -912,6 +914,7 @@ hipError_t ss_launch_share(const u64 *secret, u64 *shares, size_t count, int n, 
                            hipStream_t stream)
 {
     const bool v2 = (count % 2 == 0) && aligned16(secret) && aligned16(shares);
+    if (!fits_launch(blocks_for(count, v2 ? 2 : 1))) return hipErrorInvalidConfiguration;
 #define SS_SHARE(VEC, NC, DC)                                                                                       \
     hipLaunchKernelGGL((share_kernel<VEC, NC, DC>), dim3(blocks_for(count, VEC, SHARE_BLOCK<NC>)), dim3(SHARE_BLOCK<NC>), \
                        0, stream, secret, shares, count, n, degree, keys)
@@ -931,6 +934,7 @@ hipError_t ss_launch_reconstruct(const u64 *shares, u64 *secret, size_t count, c
                                  hipStream_t stream)
 {
     const bool v2 = (count % 2 == 0) && aligned16(secret) && aligned16(shares);
+    if (!fits_launch(blocks_for(count, v2 ? 2 : 1))) return hipErrorInvalidConfiguration;
     const bool streams = streams_messages((size_t)(rp.m + 1) * count);
 #define SS_REC(VEC)                                                                                              \
     hipLaunchKernelGGL((streams ? reconstruct_kernel<VEC, true> : reconstruct_kernel<VEC, false>), dim3(blocks_for(count, VEC)), \
@@ -954,7 +958,9 @@ __global__ __launch_bounds__(BLOCK) void sum_planes_kernel(u64 *dst, const u64 *
 hipError_t ss_launch_sum_planes(u64 *dst, const u64 *c, size_t total, const ss_part_src &ps, hipStream_t stream)
 {
     if (ps.planes > 1 || dst != c)
-        hipLaunchKernelGGL(sum_planes_kernel, dim3(blocks_for(total, 1)), dim3(BLOCK), 0, stream, dst, c, total, ps);
+        for_each_launch(total, [&](size_t first, dim3 grid) {
+            hipLaunchKernelGGL(sum_planes_kernel, grid, dim3(BLOCK), 0, stream, dst + first, c + first, total - first, ps);
+        });
     return hipGetLastError();
 }
 
@@ -974,6 +980,7 @@ hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out,
                                    const ss_dr_params &dp, const ss_part_src &ps, hipStream_t stream)
 {
     const ss_tr_params none = {};
+    if (!fits_launch(blocks_for(count, 1))) return hipErrorInvalidConfiguration;
     if (dp.t == 3 && count < LANES_MAX_COUNT) {
         hipLaunchKernelGGL(degree_reduce_lanes_kernel, dim3((unsigned)((count + 31) / 32)), dim3(BLOCK), 0, stream, c, msg1,
                            msg2, out, count, dp, ps);
@@ -994,6 +1001,7 @@ hipError_t ss_launch_degree_reduce_truncate(const u64 *c, u64 *msg1, u64 *msg2, 
                                             u64 *rec, size_t count, const ss_dr_params &dp, const ss_tr_params &tp,
                                             const ss_part_src &ps, hipStream_t stream)
 {
+    if (!fits_launch(blocks_for(count, 1))) return hipErrorInvalidConfiguration;
     const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
     const bool streams = streams_messages((nr + n + nr * k + k * n + k + n) * count);
 #define SS_LAUNCH(NC, TC)                                                                                               \
@@ -1018,6 +1026,7 @@ hipError_t ss_launch_truncate(const u64 *x, u64 *u, u64 *wsh, u64 *out, size_t c
 
 hipError_t ss_launch_nonlinear_masks(u64 *sh_b, u64 *sh_bi, size_t count, const ss_nl_params &np, hipStream_t stream)
 {
+    if (!fits_launch(blocks_for(count, 1))) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(nonlinear_masks_kernel, dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, sh_b, sh_bi, count,
                        np);
     return hipGetLastError();
@@ -1028,6 +1037,7 @@ hipError_t ss_launch_relu(const u64 *x, const u64 *sh_b, const u64 *sh_bi, u64 *
 {
     const bool v2 = (count % 2 == 0) && aligned16(x) && aligned16(sh_b) && aligned16(sh_bi) && aligned16(msg) &&
                     aligned16(yplain) && aligned16(out) && count >= VEC2_MIN_COUNT;
+    if (!fits_launch(blocks_for(count, v2 ? 2 : 1))) return hipErrorInvalidConfiguration;
     const size_t nr = 2 * np.t + 1, n = np.n;
     const bool streams = streams_messages((2 * n + nr + n + nr + 1) * count);
 #define SS_RELU(VEC)                                                                                                       \
@@ -1045,6 +1055,7 @@ hipError_t ss_launch_pool_masks(u64 *sh_b, u64 *sh_bi, size_t planes, const ss_p
                                 hipStream_t stream)
 {
     const size_t cin = planes * g.H * g.W, cout = planes * g.Ho * g.Wo;
+    if (!fits_launch(blocks_for(cin, 1)) || !fits_launch(blocks_for(cout, 1))) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(pool_masks_kernel<false>, dim3(blocks_for(cin, 1)), dim3(BLOCK), 0, stream, sh_b, cin, g, np);
     hipLaunchKernelGGL(pool_masks_kernel<true>, dim3(blocks_for(cout, 1)), dim3(BLOCK), 0, stream, sh_bi, cout, g, np);
     return hipGetLastError();
@@ -1073,6 +1084,7 @@ hipError_t ss_launch_relu_pool(const u64 *x, const u64 *sh_b, const u64 *sh_bi, 
 #undef SS_POOL
         return hipGetLastError();
     }
+    if (!fits_launch(blocks_for(cin, 1)) || !fits_launch(blocks_for(cout, 1))) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((streams ? relu_kernel<1, false, true> : relu_kernel<1, false, false>), dim3(blocks_for(cin, 1)),
                        dim3(BLOCK), 0, stream, x, sh_b, (const u64 *)nullptr, msg, rplain, (u64 *)nullptr, cin, np);
     hipLaunchKernelGGL(pool_maskoff_kernel, dim3(blocks_for(cout, 1)), dim3(BLOCK), 0, stream, rplain, sh_bi, yplain, out,
@@ -1097,6 +1109,7 @@ hipError_t ss_launch_tail_direct(const u64 *c, const u64 *sh_b, const u64 *sh_bi
 {
     if (tp.kdiv != 1) return hipErrorInvalidValue;   // no rounding division in this kernel
     const dim3 grid((B * HW + 15) / 16, (C + 15) / 16), block(BLOCK);
+    if (!fits_launch(grid.x)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(tail_direct_kernel, grid, block, 0, stream, c, sh_b, sh_bi, out, (signed char *)planes, B, C, HW,
                        ss_planes_bytes(B, C, HW, 1), open_all, tp, ps);
     return hipGetLastError();
@@ -1109,6 +1122,7 @@ hipError_t ss_launch_layer_tail(const u64 *c, u64 *msg1, u64 *msg2, u64 *umsg, u
 {
     if (tp.kdiv != 1) return hipErrorInvalidValue;   // no rounding division in this kernel
     const dim3 grid((B * HW + 15) / 16, (C + 15) / 16), block(BLOCK);
+    if (!fits_launch(grid.x)) return hipErrorInvalidConfiguration;
     const size_t party_bytes = ss_planes_bytes(B, C, HW, 1);
     const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
     // shares in and out, mask shares, messages

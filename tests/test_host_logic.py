@@ -210,6 +210,26 @@ def test_pooling_entry_points_check_their_arguments():
     assert lib.ssnet_truncate_div(wide, 16, 8, 256, 0, 16) == binding.EWORKSPACE
 
 
+def test_grids_of_2_to_the_32_threads_are_refused():
+    """The runtime takes such a grid without an error and runs a part of it: the launchers refuse, before any launch."""
+    lib = binding.load_library()
+    s = SSNet(3, 1, device=None)
+    ctx, odd, huge = s._ctx, (1 << 32) + 1, 1 << 60
+    invalid_configuration = 9
+    assert lib.ssnet_set_workspace(ctx, 1 << 20, huge) == 0
+    ids = (C.c_int * 2)(1, 2)
+    pool = (1 << 22, 32, 32, 2, 2, 2, 2, 0, 0)
+    for name, args in [("share", (16, odd, 1, 0, 1 << 30)), ("share", (16, 1 << 33, 1, 0, 1 << 30)),
+                       ("reconstruct", (16, odd, ids, 2, 1, 1 << 30)), ("degree_reduce", (16, 1 << 32, 0, 16)),
+                       ("degree_reduce_truncate", (16, 1 << 32, 0, 16)), ("nonlinear_masks", (1 << 32, 0, 16, 16)),
+                       ("relu", (16, 16, 16, odd, 16)), ("pool_masks", pool + (0, 16, 16)),
+                       ("relu_pool", (1 << 20, 1 << 20, 1 << 20) + pool + (0, 1 << 50)),
+                       ("reduce_truncate_relu", (16, 1, 1, 1 << 28, 0, 16, 16, 16, None)),
+                       ("reduce_truncate_relu_direct", (16, 1, 1, 1 << 28, 16, 16, 16, None))]:
+        assert getattr(lib, "ssnet_" + name)(ctx, *args) == binding.EHIP, name
+        assert lib.ssnet_last_hip_error(ctx) == invalid_configuration, name
+
+
 # ----------------------------------------------------------------- the second library, over p = 2^45 - 55
 P45 = (1 << 45) - 55
 
