@@ -146,9 +146,9 @@ class SSNet:
             raise SSNetError(rc, "ssnet_create")
         self._ws: Optional[torch.Tensor] = None
         # sizes that the library has given for a shape, and the largest element count whose messages are known to fit
-        # the workspace _fits_ws: asking again costs a foreign call (0.5 to 1.1 us), which small layers feel
+        # the present workspace: asking again costs a foreign call (0.5 to 1.1 us), which small layers feel
         self._sizes: dict = {}
-        self._fits_ws, self._fits_count = None, 0
+        self._fits_count = 0
 
     def close(self):
         if getattr(self, "_ctx", None):
@@ -180,14 +180,15 @@ class SSNet:
     def reserve(self, nbytes: int):
         """Make the workspace at least nbytes large (allocates through torch)."""
         if self._ws is None or self._ws.numel() < nbytes:
-            self._ws = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
+            self._ws = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)   # the old one is given back
+            self._fits_count = 0
             self._ok(self.lib.ssnet_set_workspace(self._ctx, _dptr(self._ws), self._ws.numel()), "ssnet_set_workspace")
 
     def _reserve_stream(self, count: int):
         """room for the messages of an element-wise call over `count` elements per party"""
-        if count > self._fits_count or self._fits_ws is not self._ws or self._ws is None:
+        if count > self._fits_count or self._ws is None:
             self.reserve(self.workspace_bytes_stream(count))
-            self._fits_ws, self._fits_count = self._ws, count
+            self._fits_count = count
 
     def messages(self) -> torch.Tensor:
         """int64 view of the workspace behind its header: where the inter-party

@@ -230,6 +230,21 @@ def test_grids_of_2_to_the_32_threads_are_refused():
         assert lib.ssnet_last_hip_error(ctx) == invalid_configuration, name
 
 
+def test_a_replaced_workspace_is_given_back():
+    """Growing the workspace from any call frees the one before it, and element counts that fitted that one are asked
+    for again."""
+    import weakref
+    s = SSNet(3, 1, device=None)
+    s._reserve_stream(1000)
+    old, held = s._ws.numel(), weakref.ref(s._ws)
+    s._reserve_stream(10)
+    assert s._ws is held() and old >= s.workspace_bytes_stream(1000)
+    s.reserve(10 * old)
+    assert held() is None and s._ws.numel() >= 10 * old
+    s._reserve_stream(10000)
+    assert s._ws.numel() >= s.workspace_bytes_stream(10000)
+
+
 # ----------------------------------------------------------------- the second library, over p = 2^45 - 55
 P45 = (1 << 45) - 55
 
