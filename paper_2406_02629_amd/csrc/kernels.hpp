@@ -50,7 +50,6 @@ struct ss_nl_params {             // SSS-NonLinear
     u64 beta_key;
     u64 bgen_key[SS_MAXT], bigen_key[SS_MAXT];   // coefficients of [[beta]], [[beta^-1]]
     int ilambda[2 * SS_MAXT + 1]; // REC from the IDs 1..2t+1 (integers: (-1)^(i-1) C(2t+1, i))
-    u64 dinv;
 };
 
 // Pooling kernel kh x kw moved by (sh, sw) over planes of H x W padded by ph / pw zeros (Sec. VI-C).

@@ -965,20 +965,19 @@ int ssnet_degree_reduce_truncate_reconstruct(ssnet_ctx *ctx, const uint64_t *d_c
 
 namespace {
 
-static bool make_nl_params(const ssnet_ctx *ctx, uint64_t stream_id, ss_nl_params *np)
+static ss_nl_params make_nl_params(const ssnet_ctx *ctx, uint64_t stream_id)
 {
-    *np = {};
-    np->n = ctx->n;
-    np->t = ctx->t;
-    np->bbits = SSNET_BETA_BITS;
-    np->beta_key = ss_key(ctx->seed, SSNET_DOM_MASK_BETA, stream_id, 0, 0);
+    ss_nl_params np = {};
+    np.n = ctx->n;
+    np.t = ctx->t;
+    np.bbits = SSNET_BETA_BITS;
+    np.beta_key = ss_key(ctx->seed, SSNET_DOM_MASK_BETA, stream_id, 0, 0);
     for (int j = 1; j <= ctx->t; j++) {
-        np->bgen_key[j - 1] = ss_key(ctx->seed, SSNET_DOM_BETA_GEN, stream_id, 0, (u64)j);
-        np->bigen_key[j - 1] = ss_key(ctx->seed, SSNET_DOM_BETAINV_GEN, stream_id, 0, (u64)j);
+        np.bgen_key[j - 1] = ss_key(ctx->seed, SSNET_DOM_BETA_GEN, stream_id, 0, (u64)j);
+        np.bigen_key[j - 1] = ss_key(ctx->seed, SSNET_DOM_BETAINV_GEN, stream_id, 0, (u64)j);
     }
-    for (int i = 0; i < 2 * ctx->t + 1; i++) np->ilambda[i] = ctx->ilambda_r[i];
-    np->dinv = 1;
-    return true;
+    for (int i = 0; i < 2 * ctx->t + 1; i++) np.ilambda[i] = ctx->ilambda_r[i];
+    return np;
 }
 
 }  // namespace
@@ -989,8 +988,7 @@ int ssnet_reduce_truncate_direct(ssnet_ctx *ctx, const uint64_t *d_c, size_t cou
     if (!ctx || !d_out || count == 0 || count > MAX_COUNT) return SSNET_EINVAL;
     if (d_secret)
         if (int rc = check_ids(ctx, party_ids, m)) return rc;
-    ss_nl_params open_all;
-    if (!make_nl_params(ctx, 0, &open_all)) return SSNET_EINVAL;
+    const ss_nl_params open_all = make_nl_params(ctx, 0);
     const u64 *c = d_c;
     ss_part_src ps = {1, 0};
     if (!d_c)
@@ -1042,8 +1040,7 @@ int ssnet_reduce_truncate_relu(ssnet_ctx *ctx, const uint64_t *d_c, int B, int C
     u64 *msg1 = (u64 *)ws_scratch(ctx), *msg2 = msg1 + (size_t)nr * k * plane;
     u64 *u = msg2 + (size_t)k * n * plane, *wsh = u + (size_t)k * plane;
     u64 *rmsg = wsh + (size_t)n * plane, *yplain = rmsg + (size_t)nr * plane;
-    ss_nl_params np;
-    if (!make_nl_params(ctx, 0, &np)) return SSNET_EINVAL;
+    const ss_nl_params np = make_nl_params(ctx, 0);
     const ss_dr_params dp = make_dr_params(ctx, stream_id);
     const ss_tr_params tp = make_tr_params(ctx, stream_id);
     hipError_t e;
@@ -1084,8 +1081,7 @@ int ssnet_reduce_truncate_relu_direct(ssnet_ctx *ctx, const uint64_t *d_c, int B
     } else if (int rc = incoming_product(ctx, nullptr, count, 0, &c, &ps)) {
         return rc;
     }
-    ss_nl_params open_all;
-    if (!make_nl_params(ctx, 0, &open_all)) return SSNET_EINVAL;
+    const ss_nl_params open_all = make_nl_params(ctx, 0);
     timed tm(ctx, SSNET_PROF_DEGREE_REDUCE);
     hipError_t e = ss_launch_tail_direct(c, d_beta, d_betainv, d_out, d_planes, B, C, HW, open_all, make_tr_params(ctx, 0),
                                          ps, ctx->stream);
@@ -1095,8 +1091,7 @@ int ssnet_reduce_truncate_relu_direct(ssnet_ctx *ctx, const uint64_t *d_c, int B
 int ssnet_nonlinear_masks(ssnet_ctx *ctx, size_t count, uint64_t stream_id, uint64_t *d_beta, uint64_t *d_betainv)
 {
     if (!ctx || !d_beta || !d_betainv || count == 0 || count > MAX_COUNT) return SSNET_EINVAL;
-    ss_nl_params np;
-    if (!make_nl_params(ctx, stream_id, &np)) return SSNET_EINVAL;
+    const ss_nl_params np = make_nl_params(ctx, stream_id);
     timed tm(ctx, SSNET_PROF_NONLINEAR);
     hipError_t e = ss_launch_nonlinear_masks(d_beta, d_betainv, count, np, ctx->stream);
     return e == hipSuccess ? SSNET_OK : fail_hip(ctx, e);
@@ -1108,8 +1103,7 @@ int ssnet_relu(ssnet_ctx *ctx, const uint64_t *d_x, const uint64_t *d_beta, cons
     if (!ctx || !d_x || !d_beta || !d_betainv || !d_out || count == 0 || count > MAX_COUNT) return SSNET_EINVAL;
     const int nr = 2 * ctx->t + 1;
     if (!ws_fits(ctx, (size_t)(nr + 1) * count * 8)) return SSNET_EWORKSPACE;
-    ss_nl_params np;
-    if (!make_nl_params(ctx, 0, &np)) return SSNET_EINVAL;
+    const ss_nl_params np = make_nl_params(ctx, 0);
     u64 *msg = (u64 *)ws_scratch(ctx), *yplain = msg + (size_t)nr * count;
     timed tm(ctx, SSNET_PROF_NONLINEAR);
     hipError_t e = ss_launch_relu(d_x, d_beta, d_betainv, msg, yplain, d_out, count, np, ctx->stream);
@@ -1147,8 +1141,7 @@ int ssnet_pool_masks(ssnet_ctx *ctx, size_t planes, int H, int W, int kh, int kw
     ss_pool_geom g;
     if (!ctx || !d_beta || !d_betainv || !make_pool_geom(planes, H, W, kh, kw, sh, sw, ph, pw, 0, &g))
         return SSNET_EINVAL;
-    ss_nl_params np;
-    if (!make_nl_params(ctx, stream_id, &np)) return SSNET_EINVAL;
+    const ss_nl_params np = make_nl_params(ctx, stream_id);
     timed tm(ctx, SSNET_PROF_NONLINEAR);
     hipError_t e = ss_launch_pool_masks(d_beta, d_betainv, planes, g, np, ctx->stream);
     return e == hipSuccess ? SSNET_OK : fail_hip(ctx, e);
@@ -1170,8 +1163,7 @@ int ssnet_relu_pool(ssnet_ctx *ctx, const uint64_t *d_x, const uint64_t *d_beta,
         if (x0 < o1 && o0 < x1) return SSNET_EINVAL;
     }
     if (!ws_fits(ctx, ((size_t)(nr + 1) * cin + cout) * 8)) return SSNET_EWORKSPACE;
-    ss_nl_params np;
-    if (!make_nl_params(ctx, 0, &np)) return SSNET_EINVAL;
+    const ss_nl_params np = make_nl_params(ctx, 0);
     u64 *msg = (u64 *)ws_scratch(ctx), *rplain = msg + (size_t)nr * cin, *yplain = rplain + cin;
     timed tm(ctx, SSNET_PROF_NONLINEAR);
     hipError_t e = ss_launch_relu_pool(d_x, d_beta, d_betainv, msg, rplain, yplain, d_out, planes, g, np, ctx->stream);

@@ -587,8 +587,8 @@ __global__ __launch_bounds__(BLOCK) void tail_direct_kernel(const u64 *c, const 
 #pragma unroll
         for (int q = 0; q < SS_MAXK; q++)
             if (q < k) bacc.mac(sh_b[(size_t)q * count + e], tp.ilambda[q]);
-        const u64 x = open_all.dinv == 1 ? acc.value() : ss_mul(acc.value(), open_all.dinv);
-        const u64 v = ss_mul(shift_signed(x, tp.f), bacc.value());   // the multipliers of IDs 1..k are integers
+        // the multipliers of IDs 1..2t+1 and of IDs 1..k are integers
+        const u64 v = ss_mul(shift_signed(acc.value(), tp.f), bacc.value());
         const u64 y = v <= (SS_P - 1) / 2 ? v : 0;
 #pragma unroll
         for (int m = 0; m < SS_MAXN; m++) {
@@ -733,7 +733,7 @@ __global__ __launch_bounds__(BLOCK) void relu_kernel(const u64 *x, const u64 *__
     pack_t<VEC> y;
 #pragma unroll
     for (int u = 0; u < VEC; u++) {
-        const u64 v = np.dinv == 1 ? acc[u].value() : ss_mul(acc[u].value(), np.dinv);
+        const u64 v = acc[u].value();   // the multipliers of IDs 1..2t+1 are integers
         y.v[u] = v <= (SS_P - 1) / 2 ? v : 0;   // negative values are the upper half of the field
     }
     if constexpr (MASKOFF)
