@@ -136,7 +136,7 @@ def conv_layer_roofline(reps):
     x = torch.from_numpy(uniform_below(n * B * C * H * H, P61, 3).view("int64")).cuda().view(n, B, C, H, H)
     w = torch.from_numpy(uniform_below(n * Co * C * k * k, P61, 4).view("int64")).cuda().view(n, Co, C, k, k)
     macs = n * B * H * H * C * k * k * Co
-    # (i) input gathered from channel-innermost limb planes (the path the stack uses for k x k layers)
+    # (i) input gathered from limb planes (the path the stack uses for k x k layers)
     wt = ss.pack_weights_conv_taps(w)
     planes = ss.split_planes(x)
     y = ss.conv_mod_planes(planes, wt, B, C, H, H, Co, k, k, 1, 1)

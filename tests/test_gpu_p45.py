@@ -115,7 +115,7 @@ def test_p45_linear_and_conv(n, t):
 
 @pytest.mark.parametrize("n,t", [(3, 1), (5, 2), (7, 3)])
 def test_p45_limb_tiles_and_planes_paths(n, t):
-    """GEN fused with the limb split (tiles for dense / 1x1 layers, channel-innermost planes for k x k
+    """GEN fused with the limb split (tiles for dense / 1x1 layers, limb planes for k x k
     convolutions) and the convolution that gathers from the planes"""
     s = SSNet(n, t, seed=17, p=P45)
     for (B, C, H, W, Co) in [(1, 3, 5, 7, 2), (2, 70, 9, 9, 33), (1, 128, 14, 14, 64)]:

@@ -76,7 +76,7 @@ def test_degree_reduce_parity_with_messages(n, t):
 
 @pytest.mark.parametrize("n,t", [(3, 1), (5, 2)])
 def test_large_tensors_take_the_one_thread_per_element_kernels(n, t):
-    # degree reduction switches kernels at 160 K elements, truncation vector width at 2^20
+    # a million elements and a ragged end
     s = SSNet(n, t, seed=31)
     count = (1 << 20) + 6
     c = field_uniform((n, count), seed=11)
@@ -355,7 +355,7 @@ def test_relu_parity_with_masks_and_messages(n, t):
 
 @pytest.mark.parametrize("n,t", [(3, 1), (5, 2), (7, 3)])
 def test_conv_on_limb_planes(n, t):
-    """Convolution that gathers its input from channel-innermost limb planes (no im2col matrix):
+    """Convolution that gathers its input from limb planes (no im2col matrix):
     the same residues as the oracle's convolution, for planes made from shares and for planes
     made together with the shares; strides, paddings, ragged pixel counts, several images."""
     s = SSNet(n, t, seed=17)
@@ -395,8 +395,8 @@ def test_layer_tail_in_one_launch(n, t):
     oracle's separate steps.  (7,3) takes the library's three-launch route behind the same entry point."""
     s = SSNet(n, t, f=13, seed=63)
     k, nr = t + 1, 2 * t + 1
-    # the last case is past half a million elements, where the planes are written by a launch of their own
-    for (B, C, H, W) in [(1, 64, 3, 5), (2, 128, 7, 7), (1, 20, 4, 4), (1, 64, 40, 40), (1, 64, 96, 96)]:
+    # the last two cases move more than the last cache level holds, for (5,2) and for (3,1): messages stored past it
+    for (B, C, H, W) in [(1, 64, 3, 5), (2, 128, 7, 7), (1, 20, 4, 4), (1, 64, 40, 40), (1, 64, 96, 96), (1, 64, 125, 128)]:
         say("layer tail", n, t, B, C, H, W)
         count = B * C * H * W
         rng = np.random.default_rng(count)
@@ -602,9 +602,8 @@ def test_relu_pool_stem_size():
 @pytest.mark.parametrize("n,t,counts", [(4, 1, (257, 420001)), (8, 1, (1, 4099)), (6, 2, (1, 257, 420001)), (8, 2, (255,)),
                                         (7, 3, (16383, 16384, 420001)), (8, 3, (1, 16383, 16385, 300001))])
 def test_reduction_kernels_of_every_degree(n, t, counts):
-    """Every degree, with the party count fixed at compile time or not; on both sides of the line where t = 3 spreads an
-    element over lanes, and where a call's traffic exceeds the last cache level (messages stored past the caches):
-    all messages and results, and the rounding division."""
+    """Every degree, with the party count fixed at compile time or not, on both sides of the line where t = 3 spreads an
+    element over lanes: all messages and results, and the rounding division."""
     s = SSNet(n, t, f=13, seed=19)
     k, nr = t + 1, 2 * t + 1
     for count in counts:
@@ -651,6 +650,8 @@ def test_relu_pool_runs(n, t, geoms):
             got = s.relu_pool(to_dev(x).view(n, planes, H, W), sb, sbi, kern, stride, pad, mode)
             ws = to_np(s.messages()[: (nr + 1) * cin + cout])
             assert np.array_equal(ws[: nr * cin].reshape(nr, cin), msg)
+            opened = orc.reconstruct(msg, list(range(1, nr + 1)), P61)        # rectified plain values before pooling
+            assert np.array_equal(ws[nr * cin: (nr + 1) * cin], np.where(opened <= P61 // 2, opened, 0))
             assert np.array_equal(ws[(nr + 1) * cin:], y)
             assert np.array_equal(to_np(got).reshape(n, -1), want)
 
@@ -697,6 +698,79 @@ def test_share_tiles_and_reconstruct_past_the_caches(n, t, large):
     shares = s.share(secret, stream_id=1)
     for ids in (list(range(1, t + 2)), list(range(n - t, n + 1)), list(range(1, n + 1))):
         assert torch.equal(s.reconstruct(shares, ids), secret)
+
+
+LAST_LEVEL_WORDS = (256 << 20) // 8      # a call that moves more stores its messages past the caches
+
+
+@pytest.mark.parametrize("n,t", [(3, 1), (5, 2), (4, 1), (6, 2), (7, 3), (8, 3)])
+def test_messages_stored_past_the_caches(n, t):
+    """The variants that store messages past the caches, at the first counts that take them: words of each call = shares
+    read and written and messages, per element.  All results and messages."""
+    s = SSNet(n, t, f=13, seed=19)
+    k, nr = t + 1, 2 * t + 1
+    red_words, trunc_words = nr * k + k * n, k + n
+
+    def operands(words):
+        count = LAST_LEVEL_WORDS // words + 1
+        xs = np.random.default_rng(count).integers(-(1 << 55), 1 << 55, count, dtype=np.int64)
+        return count, np.where(xs < 0, xs + P61, xs).astype(np.uint64)
+
+    def sent(words, count):
+        return to_np(s.messages()[: words * count])
+
+    count, x = operands(nr + n + red_words)
+    say("past the caches: reduce", n, t, count)
+    c = orc.share(x, n, 2 * t, P61, 5, 0)
+    want, m1, m2, _ = orc.degree_reduce(c, n, t, P61, 19, 9, full=True)
+    assert np.array_equal(to_np(s.degree_reduce(to_dev(c), stream_id=9)), want)
+    assert np.array_equal(sent(red_words, count), np.concatenate([m1.ravel(), m2.ravel()]))
+    count, x = operands(nr + n + red_words + trunc_words)
+    say("past the caches: reduce + truncate", n, t, count)
+    c = orc.share(x, n, 2 * t, P61, 5, 0)
+    red, m1, m2, _ = orc.degree_reduce(c, n, t, P61, 19, 9, full=True)
+    want, u, wsh = orc.truncate(red, n, t, 13, P61, 19, 9, full=True)
+    assert np.array_equal(to_np(s.degree_reduce_truncate(to_dev(c), stream_id=9)), want)
+    assert np.array_equal(sent(red_words + trunc_words, count), np.concatenate([a.ravel() for a in (m1, m2, u, wsh)]))
+    count, x = operands(2 * k + 2 * n)
+    say("past the caches: truncate", n, t, count)
+    sh = orc.share(x, n, t, P61, 5, 0)
+    want, u, wsh = orc.truncate(sh, n, t, 13, P61, 19, 9, full=True)
+    assert np.array_equal(to_np(s.truncate(to_dev(sh), stream_id=9)), want)
+    assert np.array_equal(sent(trunc_words, count), np.concatenate([u.ravel(), wsh.ravel()]))
+    for odd in (0, 1):      # two elements per thread, and one
+        count, _ = operands(3 * n + 2 * nr + 1)
+        count += (count + odd) % 2
+        say("past the caches: relu", n, t, count)
+        xs = np.random.default_rng(count).integers(-(1 << 31), 1 << 31, count, dtype=np.int64)
+        sh = orc.share(np.where(xs < 0, xs + P61, xs).astype(np.uint64), n, t, P61, 5, 0)
+        sb, sbi = s.nonlinear_masks((count,), stream_id=4)
+        want, msg, y = orc.relu(sh, to_np(sb), to_np(sbi), n, t, P61, full=True)
+        assert np.array_equal(to_np(s.relu(to_dev(sh), sb, sbi)), want)
+        assert np.array_equal(sent(nr + 1, count), np.concatenate([msg.ravel(), y]))
+
+
+@pytest.mark.parametrize("n,t,side", [(3, 1, 1840), (5, 2, 1452), (8, 3, 1236)])
+def test_relu_pool_messages_stored_past_the_caches(n, t, side):
+    """Both forms of ReLU with pooling just past the line: one wide plane (two launches), and small ones (one launch)."""
+    s = SSNet(n, t, seed=23)
+    nr = 2 * t + 1
+    for planes, H, W, kern, stride, pad in [(1, side, side, (3, 3), (2, 2), (1, 1)), (side * side // 196 + 1, 14, 14, (2, 2), (2, 2), (0, 0))]:
+        cin = planes * H * W
+        assert (3 * nr + 1) * cin > LAST_LEVEL_WORDS
+        say("past the caches: relu_pool", n, t, planes, H, W)
+        sb, sbi = s.pool_masks(planes, H, W, kern, stride, pad, stream_id=4)
+        osb, osbi = to_np(sb).reshape(n, -1), to_np(sbi).reshape(n, -1)
+        xs = np.random.default_rng(planes).integers(-(1 << 25), 1 << 25, cin, dtype=np.int64)
+        x = orc.share(np.where(xs < 0, xs + P61, xs).astype(np.uint64), n, t, P61, 23, 13)
+        want, msg, y = orc.relu_pool(x, osb, osbi, planes, H, W, *kern, *stride, *pad, SSNet.POOL_MAX, n, t, P61, full=True)
+        got = s.relu_pool(to_dev(x).view(n, planes, H, W), sb, sbi, kern, stride, pad, SSNet.POOL_MAX)
+        ws = to_np(s.messages()[: (nr + 1) * cin + y.size])
+        opened = orc.reconstruct(msg, list(range(1, nr + 1)), P61)
+        assert np.array_equal(ws[: nr * cin].reshape(nr, cin), msg)
+        assert np.array_equal(ws[nr * cin: (nr + 1) * cin], np.where(opened <= P61 // 2, opened, 0))
+        assert np.array_equal(ws[(nr + 1) * cin:], y)
+        assert np.array_equal(to_np(got).reshape(n, -1), want)
 
 
 def test_reduce_truncate_direct_beyond_one_launch():
