@@ -373,7 +373,8 @@ int ssnet_relu_pool(ssnet_ctx *ctx, const uint64_t *d_x, const uint64_t *d_beta,
  * sits at ((c/16) * ceil(B*HW/16) + pix/16) * 256 + (c%16/4) * 64 + (c%4) * 16 +
  * pix%16, and P counts the padded blocks; for other schemes P = B*C*HW in
  * element order.  ssnet_workspace_bytes_layer_tail gives the bytes needed.
- * d_out may alias d_c. */
+ * d_out may alias d_c.  d_planes may lie in the memory of d_c (if d_out does
+ * not), d_beta or d_betainv, which are used up by the call. */
 size_t ssnet_layer_tail_message_plane(const ssnet_ctx *ctx, int B, int C, int HW);
 size_t ssnet_workspace_bytes_layer_tail(const ssnet_ctx *ctx, int B, int C, int HW);
 int ssnet_reduce_truncate_relu(ssnet_ctx *ctx, const uint64_t *d_c, int B, int C, int HW, uint64_t stream_id,
@@ -389,7 +390,8 @@ int ssnet_reduce_truncate_relu(ssnet_ctx *ctx, const uint64_t *d_c, int B, int C
  * result is max(., 0) times its share of beta^-1.  One pass, no message, no
  * workspace (beyond a pending product, d_c = NULL).  A simulation shortcut,
  * reported beside the protocol path, never in its place.  Any scheme; shapes,
- * masks and planes as for ssnet_reduce_truncate_relu.  d_out may alias d_c. */
+ * masks and planes as for ssnet_reduce_truncate_relu.  d_out may alias d_c;
+ * d_planes has memory of its own. */
 int ssnet_reduce_truncate_relu_direct(ssnet_ctx *ctx, const uint64_t *d_c, int B, int C, int HW, const uint64_t *d_beta,
                                       const uint64_t *d_betainv, uint64_t *d_out, void *d_planes);
 

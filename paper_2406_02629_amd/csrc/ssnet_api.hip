@@ -1009,6 +1009,12 @@ static size_t tail_plane(const ssnet_ctx *ctx, int B, int C, int HW)
     return fused ? (size_t)((B * HW + 15) / 16) * ((C + 15) / 16) * 256 : (size_t)B * C * HW;
 }
 
+static bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
+    return a0 < b0 + b_bytes && b0 < a0 + a_bytes;
+}
+
 }  // namespace
 
 size_t ssnet_layer_tail_message_plane(const ssnet_ctx *ctx, int B, int C, int HW)
@@ -1044,11 +1050,18 @@ int ssnet_reduce_truncate_relu(ssnet_ctx *ctx, const uint64_t *d_c, int B, int C
     const ss_dr_params dp = make_dr_params(ctx, stream_id);
     const ss_tr_params tp = make_tr_params(ctx, stream_id);
     hipError_t e;
+    // Planes in memory of the product or of the masks: the tail's workgroups would write them while others still read
+    // those, so the planes are made from d_out by a launch of their own.
+    const size_t planes_bytes = d_planes ? n * ss_planes_bytes(B, C, HW, 1) : 0;
+    bool planes_apart = overlap(d_planes, planes_bytes, c, nr * count * 8) ||
+                        overlap(d_planes, planes_bytes, d_beta, nr * count * 8) ||
+                        overlap(d_planes, planes_bytes, d_betainv, n * count * 8);
     if ((n == 5 && ctx->t == 2) || (n == 3 && ctx->t == 1)) {
         timed tm(ctx, SSNET_PROF_DEGREE_REDUCE);
-        e = ss_launch_layer_tail(c, msg1, msg2, u, wsh, rmsg, yplain, d_beta, d_betainv, d_out, d_planes, B, C, HW, dp, tp, np,
-                                 ps, ctx->stream);
+        e = ss_launch_layer_tail(c, msg1, msg2, u, wsh, rmsg, yplain, d_beta, d_betainv, d_out,
+                                 planes_apart ? nullptr : d_planes, B, C, HW, dp, tp, np, ps, ctx->stream);
     } else {   // other schemes: the same steps, messages and results in three launches
+        planes_apart = d_planes != nullptr;
         {
             timed tm(ctx, SSNET_PROF_DEGREE_REDUCE);
             e = ss_launch_degree_reduce_truncate(c, msg1, msg2, u, wsh, d_out, nullptr, count, dp, tp, ps, ctx->stream);
@@ -1057,11 +1070,11 @@ int ssnet_reduce_truncate_relu(ssnet_ctx *ctx, const uint64_t *d_c, int B, int C
             timed tm(ctx, SSNET_PROF_NONLINEAR);
             e = ss_launch_relu(d_out, d_beta, d_betainv, rmsg, yplain, d_out, count, np, ctx->stream);
         }
-        if (e == hipSuccess && d_planes) {
-            const ss_keys none = {};
-            timed tm(ctx, SSNET_PROF_PACK_X);
-            e = ss_launch_planes(d_out, nullptr, d_planes, n, ctx->t, B, C, HW, false, none, ctx->stream);
-        }
+    }
+    if (e == hipSuccess && planes_apart) {
+        const ss_keys none = {};
+        timed tm(ctx, SSNET_PROF_PACK_X);
+        e = ss_launch_planes(d_out, nullptr, d_planes, n, ctx->t, B, C, HW, false, none, ctx->stream);
     }
     return e == hipSuccess ? SSNET_OK : fail_hip(ctx, e);
 }

@@ -441,6 +441,30 @@ def test_layer_tail_in_one_launch(n, t):
             assert bool(torch.equal(planes2.view(n, per)[:, :data], planes.view(n, per)[:, :data]))
 
 
+@pytest.mark.parametrize("n,t", [(3, 1), (5, 2), (7, 3)])
+def test_layer_tail_planes_in_the_memory_of_its_operands(n, t):
+    """Limb planes in the memory of the product shares, of the masks of beta or of those of its inverse: shares and planes
+    as with memory of their own, below and above half a million elements."""
+    s = SSNet(n, t, seed=63)
+    for (B, C, H, W) in [(1, 64, 3, 5), (2, 128, 7, 7), (1, 64, 96, 96)]:
+        count = B * C * H * W
+        per = 8 * count + 256                       # bytes of one party's planes, the pad included
+        bufs = [torch.empty(n * per // 8, dtype=torch.int64, device="cuda") for _ in range(3)]
+        c, beta, betainv = ops = [b[: n * count].view(n, B, C, H, W) for b in bufs]
+        xs = np.random.default_rng(count).integers(-(1 << 43), 1 << 43, count, dtype=np.int64)
+        product = to_dev(orc.share(np.where(xs < 0, xs + P61, xs).astype(np.uint64), n, 2 * t, P61, 8, 0).reshape(n, B, C, H, W))
+        masks = s.nonlinear_masks((B, C, H, W), stream_id=21)
+        want, want_planes = s.reduce_truncate_relu(product, 5, *masks, want_planes=True)
+        for i, where in enumerate(("product", "beta", "betainv")):
+            say("planes in the", where, n, t, B, C, H, W)
+            for dst, src in zip(ops, (product, *masks)):
+                dst.copy_(src)
+            got, planes = s.reduce_truncate_relu(c, 5, beta, betainv, planes=bufs[i].view(torch.uint8))
+            assert torch.equal(got, want), where
+            data = 8 * count + 16                   # of the pad, the first 16 bytes are written
+            assert torch.equal(planes.view(n, per)[:, :data], want_planes.view(n, per)[:, :data]), where
+
+
 def test_config1_tiny_secure_gemm_end_to_end():
     """n=3, t=1, f=13, X 64x256 ~ N(0,1), W 256x128 ~ N(0,1): share, multiply,
     reduce, truncate, reconstruct, decode."""
