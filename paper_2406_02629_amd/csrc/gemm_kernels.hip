@@ -162,7 +162,8 @@ __global__ __launch_bounds__(256) void share_pack_kernel(const u64 *__restrict__
 // the convolution kernel gathers its second operand from: 16 consecutive channels of one tap of one output pixel
 // are 16 consecutive bytes, and those of neighbouring pixels follow one another, so that a wave's gather is (all
 // but) contiguous.  (With all channels innermost four neighbouring lanes meet four cache lines, and such loads run
-// at 16 bytes per clock and CU instead of 64, measured on data in L2.)  GEN: the input is the plaintext tensor and the kernel also is GEN (Eq. 1):
+// at 16 bytes per clock and CU instead of 64, measured on data in L2; cache accesses of a launch over 8 images of
+// 64 x 56 x 56, n = 3: 22.2 million with all channels innermost, 15.0 as it is, 13.2 from packed tiles.)  GEN: the input is the plaintext tensor and the kernel also is GEN (Eq. 1):
 // it writes the n shares and their planes; otherwise the input is the share tensor [n][B][C][H][W].
 // grid (pixel blocks of 16, C / 16), block 256: wave w of block (x, y) takes channels 16 y + 4 w .. +3.
 // Every party's planes end in a pad whose first 16 bytes are zero (the source of taps in the padding).

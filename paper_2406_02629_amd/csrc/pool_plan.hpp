@@ -35,7 +35,8 @@ inline ss_pool_plan ss_plan_pool(size_t planes, int H, int W, int kh, int sh, in
 {
     // A run is about as many elements as the workgroup has threads: longer ones are slower (2 x 2 on 1024 planes of 64 x 64,
     // n = 5: 115 us with runs of 256, 147 us with 1024; 118 us in two launches).  Kernels that overlap make it longer, until
-    // at most one row in eight is opened twice, as far as there are enough output rows for four workgroups per CU.
+    // at most one row in eight is opened twice, as far as there are enough output rows for four workgroups per CU.  (These
+    // lines and the next ones stand on the shapes named, all n = 5, the same call repeated.)
     const size_t target = 256, enough = 1024, plane = (size_t)H * W, cin = planes * plane;
     ss_pool_plan p = {true, 1, Ho, 1, 256, 0, 0};
     if (plane <= target) {

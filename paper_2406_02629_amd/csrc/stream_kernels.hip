@@ -95,7 +95,9 @@ __device__ __forceinline__ void draw_coeffs(u64 (&c)[MAXD], const u64 *keys, int
 // Bound by the writes of its n planes.  Five of them leave a wave at a time: workgroups of one wave write 5 % faster
 // than those of four, and so does the longer reduction (PACED) against the short one (n = 5, 2^28 elements: 2.15 ms
 // against 2.32 ms with four waves and 2.40 ms with the short reduction too; 2^26: 514, 548 and 570 us; 2^20: 7.6, 8.4
-// and 8.5 us).  With three planes four waves are the better ones (2^24 elements: 75.6 against 76.5 us).
+// and 8.5 us).  With three planes four waves are the better ones (2^24 elements: 75.6 against 76.5 us), and the form of
+// the reduction makes no difference beyond that of two runs (long and short, 2^20: 6.3 and 6.2, 2^24: 75.5 and 75.4, 2^26:
+// 362 and 366, 2^28: 1444 and 1453 us).
 template <int NC>
 constexpr int SHARE_BLOCK = NC == 5 ? 64 : BLOCK;
 template <int VEC, int NC, int DC>
@@ -785,8 +787,8 @@ __global__ __launch_bounds__(BLOCK) void pool_masks_kernel(u64 *__restrict__ sh,
 // planes or, for larger ones, the input rows of `R` output rows of one plane (`strips` runs per plane, ss_pool_cut): both
 // are contiguous.  Rows that the next run's kernels share with this one's are opened by both and their messages are written
 // by the later run, so a run owns the rows from its first kernel's to the next run's first.
-// n = 5, 3 x 3 / 2 on 192 planes of 112 x 112: 59.0 us, in two launches 64.1; 7 x 7 on 2048 planes
-// of 7 x 7: 9.8 and 21.8 us.
+// n = 5, on inputs that change from call to call: 3 x 3 / 2 on 192 planes of 112 x 112 74.9 us, in two launches 75.8 (the
+// same call repeated: 59.8 and 60.7 us); on 64 of them 28.2 and 30.0 us; 7 x 7 on 2048 planes of 7 x 7 11.0 and 22.7 us.
 template <int T, bool STREAM>
 __global__ __launch_bounds__(512) void relu_pool_kernel(const u64 *__restrict__ x, const u64 *__restrict__ sh_b,
                                                           const u64 *__restrict__ sh_bi, u64 *__restrict__ msg,
@@ -883,8 +885,8 @@ constexpr size_t LANES_MAX_COUNT = 16 * 1024;
 
 // Messages are written once and not read by the library again.  Left to the caches they cost nothing while a call's
 // traffic fits the 256 MB of the last level (the next call overwrites them there); beyond, writing them past the
-// caches is faster.  44 planes written per 5 read, no arithmetic, MI355X: 24.4 / 26.7 us (cached / streamed) at 157 MB,
-// 56.2 / 53.1 us at 315 MB, 324 / 273 us at 1.65 GB.
+// caches is faster.  44 planes written per 5 read, no arithmetic, the same call repeated, MI355X: 24.4 / 26.7 us (cached /
+// streamed) at 157 MB, 56.2 / 53.1 us at 315 MB, 324 / 273 us at 1.65 GB.
 inline bool streams_messages(size_t words) { return words * sizeof(u64) > ((size_t)256 << 20); }
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
