@@ -30,6 +30,10 @@
  *     synchronise.  Inputs and outputs must not alias unless stated.
  *   - Inputs must be canonical (< p); outputs always are.
  *   - Return value: SSNET_OK (0) or a negative SSNET_E* code; nothing throws.
+ *   - A launch holds less than 2^32 threads of one or two elements each.  Longer
+ *     tensors are taken by ssnet_truncate(_div), ssnet_reduce_truncate_direct and
+ *     the product calls; the other element-wise calls return SSNET_EHIP for them
+ *     before any launch.
  *   - Randomness: every random polynomial coefficient is a pure function of
  *     (seed, domain, stream_id, party, coefficient index, element index) by the
  *     counter-based generator documented with ssnet_rng_key / ssnet_rng_draw,
