@@ -254,25 +254,17 @@ __global__ __launch_bounds__(256) void planes4_kernel(const u64 *__restrict__ in
     }
 }
 
-// x / d for x < 2^31 by a multiplication: (x * m) >> s with s = 31 + ceil(log2 d), m = ceil(2^s / d) < 2^32.
-// The index arithmetic of the product kernels runs on these (a 64-bit division is some two hundred
-// instructions on this machine, and a launch of a small layer lasts only a few thousand).
-struct fdiv {
-    u32 m, s;
-};
-
-__host__ __device__ __forceinline__ u32 fd_div(u32 x, fdiv d) { return (u32)(((u64)x * d.m) >> d.s); }
-
 struct gemm_args {
     const v4i *A, *B;          // packed operands, all parties
-    u64 *out;                  // `slots` planes of the output's layout, part_stride elements apart
+    u64 *out, *parts;          // the first plane of the product; the others (tiles computed in parts), part_stride elements apart
     size_t part_stride;
     int rows, cols, Rb, Cb, Kb, RT, CT;
-    unsigned units;            // tiles * Kb, or 0: one whole tile per workgroup
+    unsigned units;            // tiles * Kb, or 0: whole tiles only
+    unsigned whole;            // tiles 0 .. whole - 1 are dealt whole, each workgroup's before its range of units
+    unsigned cost0;            // cost position of the first tile dealt by units (number `whole`)
     unsigned wlast;            // cost of one unit of the last column tile (SS_UNIT_COST for the others)
     unsigned tcost, tlast;     // cost of a whole tile, fold included: all column tiles but the last; the last
-    unsigned cost;             // of all tiles (< 2^31)
-    unsigned share, rest;      // cost / G and cost % G for the G workgroups of the launch
+    unsigned share, rest;      // (cost of all tiles - cost0) / G and % G for the G workgroups of the launch
     int slots;                 // planes: the most workgroups that can share a tile (>= 1)
     fdiv dG, dKb, dCT, dRT, dRowcost, dTilecost, dWlast, dCdiv;
     size_t a_party_stride, b_party_stride, out_party_stride, stride_row, stride_cb;
@@ -350,14 +342,17 @@ __device__ __forceinline__ u64 fold_diagonals(const v4i (&acc)[15], int r)
 // much as a unit (SS_FOLD_COST; a workgroup whose range holds the ends of two tiles really is busy that much
 // longer than one whose range lies inside one tile).  On the cost axis a tile is its units followed by its
 // fold; with cp(u) the position of unit u, workgroup s of G owns the units with bound(s) <= cp(u) <
-// bound(s + 1), bound(s) = floor(s cost / G).  cost / G >= SS_UNIT_COST + SS_FOLD_COST, the largest step
-// between two unit starts, so no range is empty.
+// bound(s + 1), bound(s) = cost0 + floor(s (cost - cost0) / G).  (cost - cost0) / G >= SS_UNIT_COST + SS_FOLD_COST, the
+// largest step between two unit starts, so no range is empty.
+//
+// Where there are tiles for several rounds of the chip, the workgroups first take equal runs of whole tiles and only the
+// last 256 to 511 tiles are dealt by cost: the others need no second plane.
 constexpr unsigned SS_UNIT_COST = 18;
 constexpr unsigned SS_FOLD_COST = 16;
 
 __device__ __forceinline__ unsigned range_bound(const gemm_args &g, unsigned s)
 {
-    return s * g.share + fd_div(s * g.rest, g.dG);   // s <= G <= 256, rest < G
+    return g.cost0 + s * g.share + fd_div(s * g.rest, g.dG);   // s <= G <= 256, rest < G
 }
 
 // first unit whose cost position is >= x (x <= cost); positions inside a tile's fold belong to the next tile
@@ -429,6 +424,11 @@ __device__ __forceinline__ const v4i *unit_base(const gemm_args &g, const wave_s
     return ok ? ws.p + (size_t)c16 * g.cvPixels + (ws.bpix + hi * g.cvW + wi) : g.zero;
 }
 
+__device__ __forceinline__ u64 *plane_at(const gemm_args &g, unsigned plane)
+{
+    return plane ? g.parts + (size_t)(plane - 1) * g.part_stride : g.out;
+}
+
 // Planes that get zeros from workgroup `slot`, whose range ends at unit u1.  A workgroup that starts a tile
 // sees to the planes that no part of the tile goes to.  For a tile it computes whole that is all planes but
 // its own; the only tile it can start and not finish is the one its range ends in, which has one more part
@@ -475,19 +475,26 @@ __global__ __launch_bounds__(512) void gemm_limb_kernel(gemm_args g)
     // round-robin to the 8 XCDs), so that neighbours in the list share an L2
     const unsigned slot = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
     const unsigned myplane = g.slots > 1 ? slot % (unsigned)g.slots : 0;
-    unsigned u0, u1;
+    // its whole tiles w0 .. w1 - 1 and its range of units u0 .. u1 - 1; u counts the units of the one, then of the other
+    unsigned w0 = 0, w1 = 0, u0 = 0, u1 = 0;
+    if (g.whole) {
+        w0 = g.whole == G ? slot : (unsigned)((unsigned long long)slot * g.whole / SS_GEMM_CUS);
+        w1 = g.whole == G ? slot + 1 : (unsigned)((unsigned long long)(slot + 1) * g.whole / SS_GEMM_CUS);
+    }
     if (g.units) {
         u0 = unit_at(g, range_bound(g, slot));
         u1 = unit_at(g, range_bound(g, slot + 1));
-    } else {   // one whole tile per workgroup; unit numbers are relative to it
-        u0 = 0;
-        u1 = (unsigned)g.Kb;
     }
-    if (u0 >= u1) return;
+    bool range_ahead = g.whole && u0 < u1;
+    unsigned u = g.whole ? 0 : u0, uend = g.whole ? (w1 - w0) * (unsigned)g.Kb : u1;
+    if (u >= uend) return;
+    unsigned ucopy = uend + (range_ahead ? 1 : 0);   // units below have a copy to send for the next one
+    const unsigned range_tile = fd_div(u0, g.dKb);
+    const int range_kb = (int)(u0 - range_tile * (unsigned)g.Kb);
     v4i *mine = lds + wave * TILE;   // wave-uniform LDS destination of this wave's block
 
-    unsigned tile = g.units ? fd_div(u0, g.dKb) : slot;
-    int kb = (int)(u0 - (g.units ? tile * (unsigned)g.Kb : 0));
+    unsigned tile = g.whole ? w0 : range_tile;
+    int kb = g.whole ? 0 : range_kb;
     wave_src src = tile_source<IMPLICIT>(g, tile, wave, lane);
     {
         unsigned qs;
@@ -499,8 +506,7 @@ __global__ __launch_bounds__(512) void gemm_limb_kernel(gemm_args g)
     // (worked out while the first unit is on its way)
     const int zero_cut = g.slots > 1 ? zero_planes_of_cut_tile(g, u1, slot, G) : 0;
 
-    unsigned u = u0;
-    while (u < u1) {
+    while (u < uend) {
         int ct, rt, party;
         tile_coords(g, tile, ct, rt, party);
         // column blocks of this wave that lie inside the matrix (0 if its row block lies outside): MFMAs of
@@ -514,7 +520,7 @@ __global__ __launch_bounds__(512) void gemm_limb_kernel(gemm_args g)
             for (int s = 0; s < ND; s++) acc[h][s] = (v4i){0, 0, 0, 0};
 
         // units of this tile that belong to this workgroup
-        const int kb_end = min(g.Kb, kb + (int)(u1 - u));
+        const int kb_end = min(g.Kb, kb + (int)(uend - u));
         wave_src next_src = src;
         for (; kb < kb_end; kb++, u++) {
             __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the unit is in LDS
@@ -532,14 +538,15 @@ __global__ __launch_bounds__(512) void gemm_limb_kernel(gemm_args g)
                 }
             }
             // where the next unit's block comes from (nothing is loaded yet)
-            const bool more = u + 1 < u1;
+            const bool more = u + 1 < ucopy;
             const v4i *cp = nullptr;
             unsigned cqs = 64;
             if (more) {
                 int nkb = kb + 1;
                 if (nkb == g.Kb) {
-                    nkb = 0;
-                    next_src = tile_source<IMPLICIT>(g, tile + 1, wave, lane);
+                    const bool jump = u + 1 == uend;   // to the range: it follows on a whole tile
+                    nkb = jump ? range_kb : 0;
+                    next_src = tile_source<IMPLICIT>(g, jump ? range_tile : tile + 1, wave, lane);
                 }
                 cp = unit_base<IMPLICIT>(g, next_src, nkb, wave, lane, cqs);
             }
@@ -610,8 +617,11 @@ __global__ __launch_bounds__(512) void gemm_limb_kernel(gemm_args g)
                 if (h < nblk && col < g.cols && lrow + r < g.rows) mask |= 1u << (4 * h + r);
             }
         }
-        const int nzero = (g.slots > 1 && kb_first == 0) ? (kb_end == g.Kb ? g.slots - 1 : zero_cut) : 0;
-        u64 *o = g.out + (size_t)myplane * g.part_stride;
+        // a tile dealt whole lies in the first plane alone
+        const bool in_range = tile >= g.whole;
+        const unsigned pl = in_range ? myplane : 0;
+        const int nzero = (g.slots > 1 && in_range && kb_first == 0) ? (kb_end == g.Kb ? g.slots - 1 : zero_cut) : 0;
+        u64 *o = plane_at(g, pl);
 #pragma unroll
         for (int h = 0; h < 2; h++)
 #pragma unroll
@@ -620,7 +630,7 @@ __global__ __launch_bounds__(512) void gemm_limb_kernel(gemm_args g)
         for (int z = 0; z < nzero; z++) {
             unsigned zpl = myplane + (unsigned)(g.slots - nzero + z);
             if (zpl >= (unsigned)g.slots) zpl -= (unsigned)g.slots;
-            u64 *zo = g.out + (size_t)zpl * g.part_stride;
+            u64 *zo = plane_at(g, zpl);
 #pragma unroll
             for (int h = 0; h < 2; h++)
 #pragma unroll
@@ -631,6 +641,10 @@ __global__ __launch_bounds__(512) void gemm_limb_kernel(gemm_args g)
             kb = 0;
             tile++;
             src = next_src;
+            if (u == uend && range_ahead) {
+                range_ahead = false;
+                u = u0, uend = ucopy = u1, tile = range_tile, kb = range_kb;
+            }
         }
     }
 }
@@ -730,7 +744,7 @@ __global__ __launch_bounds__(512) void gemm_skinny_kernel(gemm_args g)
         const u32 cq = fd_div((u32)col, g.dCdiv);
         const size_t opos = (size_t)party * g.out_party_stride + (size_t)cq * g.stride_cb + ((u32)col - cq * (u32)g.cdiv);
         const unsigned plane = g.slots > 1 ? slot % (unsigned)g.slots : 0;
-        u64 *outp = g.out + (size_t)plane * g.part_stride;
+        u64 *outp = plane_at(g, plane);
 #pragma unroll
         for (int r = 0; r < 4; r++)
             if (inside && lrow + r < g.rows && col < g.cols)
@@ -739,7 +753,7 @@ __global__ __launch_bounds__(512) void gemm_skinny_kernel(gemm_args g)
         for (int z = 0; z < nzero; z++) {
             unsigned zpl = plane + (unsigned)(g.slots - nzero + z);
             if (zpl >= (unsigned)g.slots) zpl -= (unsigned)g.slots;
-            u64 *zp = g.out + (size_t)zpl * g.part_stride;
+            u64 *zp = plane_at(g, zpl);
 #pragma unroll
             for (int r = 0; r < 4; r++)
                 if (inside && lrow + r < g.rows && col < g.cols) zp[opos + (size_t)(lrow + r) * g.stride_row] = 0;
@@ -753,21 +767,12 @@ __global__ __launch_bounds__(512) void gemm_skinny_kernel(gemm_args g)
     }
 }
 
-fdiv make_fdiv(u32 d)
-{
-    int l = 0;
-    while ((1ull << l) < d) l++;
-    fdiv f;
-    f.s = 31 + (u32)l;
-    f.m = (u32)(((1ull << f.s) + d - 1) / d);   // d > 2^(l-1), so m < 2^32
-    return f;
-}
-
 struct gemm_plan {
     bool skinny;               // first operand of at most 16 rows: tiles of 16 x 128 (gemm_skinny_kernel)
-    long tiles, units;         // units == 0: one whole tile per workgroup
-    int Kb, G, slots;
-    unsigned wlast, tcost, tlast, cost;
+    long tiles, units;         // units == 0: whole tiles only (one per workgroup for the 16-row kernel)
+    int Kb, G, slots, RT, CT;
+    unsigned whole;            // tiles dealt whole, ahead of the ranges
+    unsigned wlast, tcost, tlast, cost, cost0;
 };
 
 // Relative duration of a unit in which `vb` of the four column blocks exist: a fixed part (copy, barrier,
@@ -779,53 +784,110 @@ unsigned unit_cost(int vb)
     return w[vb];
 }
 
+// A further plane of the output is written here and read by whoever takes the product: bytes that take as long as a cost
+// of one (0.15 us at 5 TB/s, what many streams at a time reach).
+constexpr unsigned long long SS_BYTES_PER_COST = 750 * 1000;
+
 // How the units are dealt: one workgroup per CU unless there is too little work for that; slots = the most
 // workgroups that can share one tile.
+// Whole tiles first and the price of the planes, against every tile dealt by cost with two planes, MI355X: layers of eight
+// images of ResNet-50 (n = 5) 16.12 -> 15.30 ms with their tails, 64 channels of 56 x 56 (3 x 3, n = 3, eight images) as a
+// tensor 238 -> 227 us; whole tiles as workgroups of their own instead of runs of one workgroup per CU: 16 rounds of two
+// units 125 us, in runs 107.
 gemm_plan plan_gemm(int n, int rows, int cols, int K, bool allow_skinny)
 {
-    gemm_plan p;
+    typedef unsigned long long ull;
+    gemm_plan p = {};
     p.skinny = allow_skinny && rows <= 16;
     p.Kb = (K + 63) / 64;
-    p.tiles = p.skinny ? (long)n * ((cols + SKINNY_COLS - 1) / SKINNY_COLS)
-                       : (long)n * ((rows + 63) / 64) * ((cols + 63) / 64);
+    p.CT = p.skinny ? (cols + SKINNY_COLS - 1) / SKINNY_COLS : (cols + 63) / 64;
+    p.RT = p.skinny ? 1 : (rows + 63) / 64;
+    p.tiles = (long)n * p.RT * p.CT;
     p.units = p.tiles * p.Kb;
-    const int CT = p.skinny ? (cols + SKINNY_COLS - 1) / SKINNY_COLS : (cols + 63) / 64;
-    const int vb_last = p.skinny ? 4 : (cols + 15) / 16 - 4 * (CT - 1);
+    const int vb_last = p.skinny ? 4 : (cols + 15) / 16 - 4 * (p.CT - 1);
     p.wlast = unit_cost(vb_last);   // (every unit of the 16-row kernel copies the same nine blocks: one cost for all)
     p.tcost = (unsigned)p.Kb * SS_UNIT_COST + SS_FOLD_COST;
     p.tlast = (unsigned)p.Kb * p.wlast + (vb_last == 1 ? SS_FOLD_COST / 2 : SS_FOLD_COST);   // one block per wave to fold
-    const unsigned long long cost = (unsigned long long)(p.tiles / CT) * ((unsigned long long)(CT - 1) * p.tcost + p.tlast);
-    // Whole tiles or tiles in parts?  Dealt by cost, a workgroup is busy for cost / G plus the fold of the
-    // tile its range ends in; with one whole tile per workgroup the launch lasts as many tiles as the fullest
-    // CU gets.  With a single k block tiles are never cut, so there is nothing to choose; launches too large
-    // for the 32-bit range arithmetic have tiles enough for every CU many times over.
+    const ull rowcost = (ull)(p.CT - 1) * p.tcost + p.tlast, cost = (ull)(p.tiles / p.CT) * rowcost;
+    // With one whole tile per workgroup the launch lasts as many tiles as the fullest CU gets.  Dealt by cost, a workgroup
+    // is busy for its share plus the fold of the tile its range ends in, and the tiles that are dealt so have `slots`
+    // planes.  With a single k block tiles are never cut, so there is nothing to choose; launches too large for the
+    // 32-bit range arithmetic (and that of the consumers, ss_part_src) have tiles enough for every CU many times over.
     const unsigned step = SS_UNIT_COST + SS_FOLD_COST;   // largest distance between two unit starts
-    bool whole = cost >= (1ull << 31) || p.units >= (1L << 31);
-    if (!whole && p.Kb > 1) {
-        const unsigned long long rounds = ((unsigned long long)p.tiles + SS_GEMM_CUS - 1) / SS_GEMM_CUS;
-        const unsigned long long g = cost / step < SS_GEMM_CUS ? (cost / step ? cost / step : 1) : SS_GEMM_CUS;
-        whole = rounds * p.tcost <= cost / g + SS_FOLD_COST;
+    bool all_whole = cost >= (1ull << 31) || p.units >= (1L << 31) || (ull)rows * cols >= (1ull << 31);
+    if (!all_whole) {
+        p.cost = (unsigned)cost;
+        // every range must hold at least one unit start
+        const unsigned most = p.cost / step;
+        p.G = (int)(most < SS_GEMM_CUS ? (most ? most : 1) : SS_GEMM_CUS);
+        // Tiles for two rounds and more: all but the last 256 to 511 of them whole, which leaves the ranges longer than a
+        // tile and so two planes, as without.  (A workgroup whose whole tiles are ragged ones idles a little: rows of
+        // tiles are long where there are that many.)
+        if (!p.skinny && p.Kb > 1 && p.tiles >= 2 * SS_GEMM_CUS) {
+            p.whole = (unsigned)(p.tiles / SS_GEMM_CUS - 1) * SS_GEMM_CUS;
+            p.cost0 = (unsigned)(p.whole / p.CT * rowcost + p.whole % p.CT * p.tcost);
+        }
+        // a tile of cost <= tcost meets at most this many ranges of length >= share; ranges are cut between
+        // units, so a tile of Kb units has at most Kb parts
+        const unsigned share = (p.cost - p.cost0) / p.G;
+        p.slots = (int)((p.tcost + share - 1) / share) + 1;
+        if (p.slots > p.Kb) p.slots = p.Kb;
+        if (p.Kb > 1) {
+            const ull plane_bytes = 16ull * n * rows * cols / p.tiles * (p.tiles - p.whole) * (p.slots - 1);
+            const ull rounds = ((ull)p.tiles + SS_GEMM_CUS - 1) / SS_GEMM_CUS;
+            all_whole = rounds * p.tcost <= (ull)(p.whole / SS_GEMM_CUS) * p.tcost + share + SS_FOLD_COST + plane_bytes / SS_BYTES_PER_COST;
+        }
     }
-    if (whole) {
-        p.G = (int)(p.tiles < (1L << 30) ? p.tiles : 0);   // 0: not launchable, rejected by the caller
+    if (all_whole) {
+        const bool launchable = p.tiles < (1L << 30);   // else G = 0, rejected by the caller
+        p.G = (int)(!launchable ? 0 : p.skinny || p.tiles < SS_GEMM_CUS ? p.tiles : SS_GEMM_CUS);
         p.slots = 1;
         p.units = 0;
-        p.cost = 0;
-        return p;
+        p.whole = launchable ? (unsigned)p.tiles : 0;
+        p.cost = p.cost0 = 0;
     }
-    p.cost = (unsigned)cost;
-    // every range must hold at least one unit start
-    const unsigned most = p.cost / step;
-    p.G = (int)(most < SS_GEMM_CUS ? (most ? most : 1) : SS_GEMM_CUS);
-    // a tile of cost <= tcost meets at most this many ranges of length >= cost / G; ranges are cut between
-    // units, so a tile of Kb units has at most Kb parts
-    const unsigned share = p.cost / p.G;
-    p.slots = (int)((p.tcost + share - 1) / share) + 1;
-    if (p.slots > p.Kb) p.slots = p.Kb;
     return p;
 }
 
+// The planes of tiles computed in parts, added up into the first one, for callers that want the product as a tensor: one
+// thread per element, 256 of a tile (4 runs of 64 columns or 2 of 128) per workgroup.
+__global__ __launch_bounds__(256) void add_parts_kernel(gemm_args g, unsigned first_tile, int log_rows, int log_cols)
+{
+    int ct, rt, party;
+    tile_coords(g, first_tile + blockIdx.x, ct, rt, party);
+    const int i = blockIdx.y * 256 + threadIdx.x, row = (rt << log_rows) + (i >> log_cols), col = (ct << log_cols) + (i & ((1 << log_cols) - 1));
+    if (row >= g.rows || col >= g.cols) return;
+    const u32 cq = fd_div((u32)col, g.dCdiv);
+    const size_t off = (size_t)party * g.out_party_stride + (size_t)cq * g.stride_cb + ((u32)col - cq * (u32)g.cdiv) +
+                       (size_t)row * g.stride_row;
+    const u64 *part = g.parts + off;
+    u64 v = g.out[off];
+    int s = 1;
+    for (; s + 3 < g.slots; s += 4, part += 4 * g.part_stride) {   // four requests at a time
+        const u64 x0 = part[0], x1 = part[g.part_stride], x2 = part[2 * g.part_stride], x3 = part[3 * g.part_stride];
+        v = ss_add(ss_add(v, x0), ss_add(ss_add(x1, x2), x3));
+    }
+    for (; s < g.slots; s++, part += g.part_stride) v = ss_add(v, *part);
+    g.out[off] = v;
+}
+
 }  // namespace
+
+ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, bool planes_operand, int hw)
+{
+    const gemm_plan p = plan_gemm(n, rows, cols, K, !planes_operand);
+    ss_part_src ps = {};
+    ps.planes = p.slots;
+    ps.stride = (size_t)n * rows * cols;
+    ps.first_cut = p.whole;
+    ps.party_tiles = (unsigned)p.RT * (unsigned)p.CT;
+    ps.row_tiles = (unsigned)p.CT;
+    ps.hw = (unsigned)hw;
+    ps.rows = (unsigned)rows;
+    ps.dHw = make_fdiv(ps.hw);
+    ps.dRows = make_fdiv(ps.rows);
+    return ps;
+}
 
 int ss_gemm_planes(int n, int rows, int cols, int K, bool planes_operand)
 {
@@ -837,7 +899,7 @@ size_t ss_gemm_scratch_bytes(int n, int rows, int cols, int K)
     // room for either form of the second operand (tiles may take the 16-row kernel, limb planes never do)
     const int a = plan_gemm(n, rows, cols, K, false).slots, b = plan_gemm(n, rows, cols, K, true).slots;
     const int planes = a > b ? a : b;
-    return planes > 1 ? (size_t)planes * n * rows * cols * sizeof(u64) : 0;
+    return (size_t)(planes - 1) * n * rows * cols * sizeof(u64);   // the first plane is the product itself
 }
 
 size_t ss_packed_bytes(int rows, int K)
@@ -918,7 +980,7 @@ struct conv_planes {   // geometry of an operand given as limb planes
     int B, C, H, W, kh, kw, stride, pad, Ho, Wo;
 };
 
-hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_planes *cv, u64 *out, size_t part_stride,
+hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_planes *cv, u64 *out, u64 *parts, bool add_parts,
                        int n, int rows, int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv,
                        size_t stride_cb, hipStream_t stream, hipEvent_t started, hipEvent_t stopped)
 {
@@ -942,21 +1004,23 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
     g.A = (const v4i *)packedA;
     g.B = (const v4i *)packedB;
     g.out = out;
-    g.part_stride = part_stride;
+    g.parts = parts;
+    g.part_stride = (size_t)n * rows * cols;
     g.rows = rows;
     g.cols = cols;
     g.Rb = (rows + 15) / 16;
     g.Cb = (cols + 15) / 16;
     g.Kb = p.Kb;
-    g.RT = p.skinny ? 1 : (rows + 63) / 64;
-    g.CT = p.skinny ? (cols + SKINNY_COLS - 1) / SKINNY_COLS : (cols + 63) / 64;
+    g.RT = p.RT;
+    g.CT = p.CT;
     g.units = (unsigned)p.units;
+    g.whole = p.whole;
+    g.cost0 = p.cost0;
     g.wlast = p.wlast;
     g.tcost = p.tcost;
     g.tlast = p.tlast;
-    g.cost = p.cost;
-    g.share = p.cost / (unsigned)p.G;
-    g.rest = p.cost % (unsigned)p.G;
+    g.share = (p.cost - p.cost0) / (unsigned)p.G;
+    g.rest = (p.cost - p.cost0) % (unsigned)p.G;
     g.slots = p.slots;
     auto fdz = [](unsigned long long d) { return make_fdiv(d >= 1 && d < (1ull << 32) ? (u32)d : 1u); };
     g.dG = fdz((unsigned)p.G);
@@ -1002,6 +1066,11 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
     else
         SS_LAUNCH_PRODUCT(gemm_limb_kernel<false>, LDS_BYTES);
 #undef SS_LAUNCH_PRODUCT
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !add_parts || p.slots == 1) return e;
+    const unsigned first = p.whole;
+    hipLaunchKernelGGL(add_parts_kernel, dim3((unsigned)p.tiles - first, p.skinny ? 8 : 16), dim3(256), 0, stream, g, first,
+                       p.skinny ? 4 : 6, p.skinny ? 7 : 6);
     return hipGetLastError();
 }
 
@@ -1012,22 +1081,22 @@ size_t ss_planes_bytes(int B, int C, int H, int W)
     return (size_t)NL * B * H * W * C + 256;   // the limb planes and a pad that starts with 16 zero bytes
 }
 
-hipError_t ss_launch_gemm(const void *packedA, const void *packedB, u64 *out, size_t part_stride, int n, int rows,
+hipError_t ss_launch_gemm(const void *packedA, const void *packedB, u64 *out, u64 *parts, bool add_parts, int n, int rows,
                           int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv, size_t stride_cb,
                           hipStream_t stream, hipEvent_t started, hipEvent_t stopped)
 {
-    return launch_gemm(packedA, packedB, nullptr, out, part_stride, n, rows, cols, K, out_party_stride, stride_row, cdiv,
+    return launch_gemm(packedA, packedB, nullptr, out, parts, add_parts, n, rows, cols, K, out_party_stride, stride_row, cdiv,
                        stride_cb, stream, started, stopped);
 }
 
-hipError_t ss_launch_gemm_conv(const void *packedW, const void *planes, u64 *out, size_t part_stride, int n, int B, int C,
-                               int H, int W, int Co, int kh, int kw, int stride, int pad, int Ho, int Wo,
+hipError_t ss_launch_gemm_conv(const void *packedW, const void *planes, u64 *out, u64 *parts, bool add_parts, int n, int B,
+                               int C, int H, int W, int Co, int kh, int kw, int stride, int pad, int Ho, int Wo,
                                hipStream_t stream, hipEvent_t started, hipEvent_t stopped)
 {
     const conv_planes cv = {planes, B, C, H, W, kh, kw, stride, pad, Ho, Wo};
     const size_t HW = (size_t)Ho * Wo;
     // rows = output channel, cols = (b, ho, wo): y[b][co][hw]
-    return launch_gemm(packedW, nullptr, &cv, out, part_stride, n, Co, (int)(B * HW), C * kh * kw, (size_t)B * Co * HW, HW,
+    return launch_gemm(packedW, nullptr, &cv, out, parts, add_parts, n, Co, (int)(B * HW), C * kh * kw, (size_t)B * Co * HW, HW,
                        (int)HW, (size_t)Co * HW, stream, started, stopped);
 }
 

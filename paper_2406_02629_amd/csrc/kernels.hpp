@@ -60,12 +60,35 @@ struct ss_pool_geom {
     int mode;                     // 0: maximum, 1: sum
 };
 
+// x / d for x < 2^31 by a multiplication: (x * m) >> s with s = 31 + ceil(log2 d), m = ceil(2^s / d) < 2^32.
+// The index arithmetic of the product kernels runs on these (a 64-bit division is some two hundred
+// instructions on this machine, and a launch of a small layer lasts only a few thousand).
+struct fdiv {
+    u32 m, s;
+};
+
+__host__ __device__ __forceinline__ u32 fd_div(u32 x, fdiv d) { return (u32)(((u64)x * d.m) >> d.s); }
+
+inline fdiv make_fdiv(u32 d)
+{
+    int l = 0;
+    while ((1ull << l) < d) l++;
+    fdiv f;
+    f.s = 31 + (u32)l;
+    f.m = (u32)(((1ull << f.s) + d - 1) / d);   // d > 2^(l-1), so m < 2^32
+    return f;
+}
+
 // The incoming product shares of a reduction given as a sum of planes (the partial-sum form of the product
 // kernels): share i of element e is the sum mod p of c[s * stride + i * count + e] over s < planes.
-// planes <= 1: one plane, the plain tensor.
+// planes <= 1: one plane, the plain tensor.  Tiles of the product below number first_cut (party-major, then row tiles, then
+// column tiles) lie in the first plane alone; first_cut = 0: every tile has all planes.  Element e = (b, row, i), i < hw,
+// is row `row` and column b hw + i of the product, in tiles of 64 x 64.
 struct ss_part_src {
     int planes;
     size_t stride;
+    unsigned first_cut, party_tiles, row_tiles, hw, rows;
+    fdiv dHw, dRows;
 };
 
 // ---- streaming family (stream_kernels.hip) ----
@@ -75,8 +98,6 @@ hipError_t ss_launch_reconstruct(const u64 *shares, u64 *secret, size_t count, c
                                  hipStream_t stream);
 hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out, size_t count,
                                    const ss_dr_params &dp, const ss_part_src &ps, hipStream_t stream);
-// dst[i] = sum over the planes of c, i < total (dst may be c: for consumers that read one plane)
-hipError_t ss_launch_sum_planes(u64 *dst, const u64 *c, size_t total, const ss_part_src &ps, hipStream_t stream);
 hipError_t ss_launch_truncate(const u64 *x, u64 *u, u64 *wsh, u64 *out, size_t count, const ss_tr_params &tp,
                               hipStream_t stream);
 // rec != nullptr: also REC of the truncated shares (one more output, same launch)
@@ -134,26 +155,28 @@ size_t ss_planes_bytes(int B, int C, int H, int W);   // per party
 hipError_t ss_launch_planes(const u64 *in, u64 *shares, void *planes, int n, int t, int B, int C, int HW, bool gen,
                             const ss_keys &keys, hipStream_t stream);
 // convolution with the input given as planes and the weights packed with contraction index (tap, channel);
-// out and part_stride as for ss_launch_gemm
+// out, parts and add_parts as for ss_launch_gemm
 // (started, stopped: see ss_launch_gemm)
-hipError_t ss_launch_gemm_conv(const void *packedW, const void *planes, u64 *out, size_t part_stride, int n, int B, int C,
-                               int H, int W, int Co, int kh, int kw, int stride, int pad, int Ho, int Wo,
+hipError_t ss_launch_gemm_conv(const void *packedW, const void *planes, u64 *out, u64 *parts, bool add_parts, int n, int B,
+                               int C, int H, int W, int Co, int kh, int kw, int stride, int pad, int Ho, int Wo,
                                hipStream_t stream, hipEvent_t started = nullptr, hipEvent_t stopped = nullptr);
 // rows = (b, ho, wo), k = (c, r, s) of x [n][B][C][H][W]
 hipError_t ss_launch_pack_im2col(const u64 *x, void *dst, int n, int B, int C, int H, int W, int kh, int kw,
                                  int stride, int pad, int Ho, int Wo, hipStream_t stream);
 // product[i][row*stride_row + (col / cdiv)*stride_cb + col % cdiv] = sum_k A_i[row][k] * B_i[col][k] mod p, left as
-// ss_gemm_planes(...) planes of that layout, part_stride elements apart, whose sum mod p is the product: a tile
-// of the output may be computed in parts by several workgroups, each of which stores its part in a plane of
-// its own; every position of every plane is written in every launch, nothing passes between workgroups.
-// With one plane `out` is the product itself.
+// ss_gemm_planes(...) planes of that layout whose sum mod p is the product: a tile of the output may be computed in parts
+// by several workgroups, each of which stores its part in a plane of its own.  The first plane is `out`, the others follow
+// one another at `parts`; every position of every plane is written in every launch but for those of tiles that were not cut
+// (ss_gemm_parts), nothing passes between workgroups.  add_parts: one more launch adds them up, `out` is then the product.
 #define SS_GEMM_CUS 256
 int ss_gemm_planes(int n, int rows, int cols, int K, bool planes_operand);
-// bytes of the planes for either form of the second operand if there are several, else 0
+// the planes and the tiles they hold, for the consumers of a product whose rows run over hw columns at a time
+ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, bool planes_operand, int hw);
+// bytes of all planes but the first for either form of the second operand
 size_t ss_gemm_scratch_bytes(int n, int rows, int cols, int K);
 // started / stopped, if given, take the times at which the product kernel itself starts and ends on the GPU (the
 // dispatch's own time stamps, without the gap between two launches that events recorded around a launch include)
-hipError_t ss_launch_gemm(const void *packedA, const void *packedB, u64 *out, size_t part_stride, int n, int rows,
+hipError_t ss_launch_gemm(const void *packedA, const void *packedB, u64 *out, u64 *parts, bool add_parts, int n, int rows,
                           int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv, size_t stride_cb,
                           hipStream_t stream, hipEvent_t started = nullptr, hipEvent_t stopped = nullptr);
 

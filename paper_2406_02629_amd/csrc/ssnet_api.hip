@@ -28,7 +28,7 @@ struct ssnet_ctx {
         bool on;
         size_t count;                     // per party
         u64 *base;                        // [planes][n][count]
-        int planes;
+        ss_part_src src;                  // which tiles have how many planes
     } pending;
     int last_hip;
     u64 binv[2 * SS_MAXT + 1][SS_MAXK];   // first k columns of the inverse Vandermonde matrix (Eq. 3)
@@ -277,27 +277,23 @@ bool gemm_shape_ok(long rows, long cols, long K)
     return rows >= 1 && cols >= 1 && K >= 1 && K <= SSNET_MAX_K && rows <= 16L * 65535 * 2 && cols <= (1L << 30);
 }
 
-// A product for a caller that wants the tensor itself: the kernel's planes go to the start of the scratch
-// area and one more launch adds them up into d_y; with a single plane the kernel writes d_y directly.
-// launch(out, part_stride) enqueues the product kernel.
+// A product for a caller that wants the tensor itself: the kernel's first plane is d_y, the others, where tiles were
+// computed in parts, go to the start of the scratch area and one more launch adds them up.  launch(parts) enqueues both.
 template <typename F>
-int run_product(ssnet_ctx *ctx, u64 *d_y, int rows, int cols, int K, bool planes_operand, F &&launch)
+int run_product(ssnet_ctx *ctx, F &&launch)
 {
-    const size_t total = (size_t)ctx->n * rows * cols;
-    const int planes = ss_gemm_planes(ctx->n, rows, cols, K, planes_operand);
     timed tm(ctx, SSNET_PROF_GEMM);
     kernel_span ks(ctx);
-    hipError_t e = launch(planes > 1 ? (u64 *)ws_scratch(ctx) : d_y, total, ks.started(), ks.stopped());
+    hipError_t e = launch((u64 *)ws_scratch(ctx), ks.started(), ks.stopped());
     ks.done(e);
-    if (e == hipSuccess && planes > 1) e = ss_launch_sum_planes(d_y, (const u64 *)ws_scratch(ctx), total, {planes, total}, ctx->stream);
     return e == hipSuccess ? SSNET_OK : fail_hip(ctx, e);
 }
 
 int run_gemm(ssnet_ctx *ctx, const void *pa, const void *pb, u64 *out, int rows, int cols, int K,
              size_t out_party_stride, size_t stride_row, int cdiv, size_t stride_cb)
 {
-    return run_product(ctx, out, rows, cols, K, false, [&](u64 *o, size_t part_stride, hipEvent_t ea, hipEvent_t eb) {
-        return ss_launch_gemm(pa, pb, o, part_stride, ctx->n, rows, cols, K, out_party_stride, stride_row, cdiv, stride_cb,
+    return run_product(ctx, [&](u64 *parts, hipEvent_t ea, hipEvent_t eb) {
+        return ss_launch_gemm(pa, pb, out, parts, true, ctx->n, rows, cols, K, out_party_stride, stride_row, cdiv, stride_cb,
                               ctx->stream, ea, eb);
     });
 }
@@ -309,7 +305,7 @@ size_t product_bytes(const ssnet_ctx *ctx, int rows, int cols, int K, bool plane
 
 // Room for a product of `planes` planes at the very end of the workspace; the messages of the call that
 // consumes it grow from the front.  nullptr if the workspace is too small.
-u64 *reserve_pending(ssnet_ctx *ctx, int rows, int cols, int K, bool planes_operand)
+u64 *reserve_pending(ssnet_ctx *ctx, int rows, int cols, int K, bool planes_operand, int hw)
 {
     ctx->pending.on = false;
     const size_t bytes = product_bytes(ctx, rows, cols, K, planes_operand);
@@ -318,7 +314,7 @@ u64 *reserve_pending(ssnet_ctx *ctx, int rows, int cols, int K, bool planes_oper
     if (end - bytes < (uintptr_t)ws_scratch(ctx)) return nullptr;
     ctx->pending.base = (u64 *)(end - bytes);
     ctx->pending.count = (size_t)rows * cols;
-    ctx->pending.planes = ss_gemm_planes(ctx->n, rows, cols, K, planes_operand);
+    ctx->pending.src = ss_gemm_parts(ctx->n, rows, cols, K, planes_operand, hw);
     return ctx->pending.base;
 }
 
@@ -330,13 +326,13 @@ int incoming_product(ssnet_ctx *ctx, const uint64_t *d_c, size_t count, size_t m
         if (!ws_fits(ctx, msg_bytes)) return SSNET_EWORKSPACE;
         // a tensor of the caller's may be the pending product's consumer's output: it stays valid
         *c = d_c;
-        *ps = {1, 0};
+        *ps = {1};
         return SSNET_OK;
     }
     if (!ctx->pending.on || ctx->pending.count != count) return SSNET_EINVAL;
     if ((uintptr_t)ws_scratch(ctx) + msg_bytes > (uintptr_t)ctx->pending.base) return SSNET_EWORKSPACE;
     *c = ctx->pending.base;
-    *ps = {ctx->pending.planes, (size_t)ctx->n * count};
+    *ps = ctx->pending.src;
     return SSNET_OK;
 }
 
@@ -359,7 +355,7 @@ int ssnet_create(ssnet_ctx **out, int n, int t, uint64_t p, int f, uint64_t seed
     c->stream = (hipStream_t)hip_stream;
     c->ws = nullptr;
     c->ws_bytes = 0;
-    c->pending = {false, 0, nullptr, 0};
+    c->pending = {};
     c->last_hip = 0;
     c->prof = false;
     int ids[SS_MAXK];
@@ -638,8 +634,8 @@ int ssnet_conv_mod_planes(ssnet_ctx *ctx, const void *d_planes, const void *d_w_
     const long M = (long)B * Ho * Wo, K = (long)C * kh * kw;
     if (!gemm_shape_ok(Co, M, K)) return SSNET_EINVAL;
     if (!ws_fits(ctx, align256(ss_gemm_scratch_bytes(ctx->n, Co, (int)M, (int)K)))) return SSNET_EWORKSPACE;
-    return run_product(ctx, d_y, Co, (int)M, (int)K, true, [&](u64 *o, size_t part_stride, hipEvent_t ea, hipEvent_t eb) {
-        return ss_launch_gemm_conv(d_w_packed, d_planes, o, part_stride, ctx->n, B, C, H, W, Co, kh, kw, stride, pad, Ho, Wo,
+    return run_product(ctx, [&](u64 *parts, hipEvent_t ea, hipEvent_t eb) {
+        return ss_launch_gemm_conv(d_w_packed, d_planes, d_y, parts, true, ctx->n, B, C, H, W, Co, kh, kw, stride, pad, Ho, Wo,
                                    ctx->stream, ea, eb);
     });
 }
@@ -665,11 +661,11 @@ size_t ssnet_product_bytes_conv(const ssnet_ctx *ctx, int B, int C, int H, int W
 int ssnet_linear_product_prepacked(ssnet_ctx *ctx, const void *d_x_packed, const void *d_w_packed, int M, int K, int N)
 {
     if (!ctx || !d_x_packed || !d_w_packed || !gemm_shape_ok(M, N, K)) return SSNET_EINVAL;
-    u64 *parts = reserve_pending(ctx, M, N, K, false);
-    if (!parts) return SSNET_EWORKSPACE;
+    u64 *c = reserve_pending(ctx, M, N, K, false, N);
+    if (!c) return SSNET_EWORKSPACE;
     timed tm(ctx, SSNET_PROF_GEMM);
     kernel_span ks(ctx);
-    hipError_t e = ss_launch_gemm(d_x_packed, d_w_packed, parts, (size_t)ctx->n * M * N, ctx->n, M, N, K, (size_t)M * N,
+    hipError_t e = ss_launch_gemm(d_x_packed, d_w_packed, c, c + (size_t)ctx->n * M * N, false, ctx->n, M, N, K, (size_t)M * N,
                                   (size_t)N, INT_MAX, 0, ctx->stream, ks.started(), ks.stopped());
     ks.done(e);
     ctx->pending.on = e == hipSuccess;
@@ -683,11 +679,11 @@ int ssnet_conv1x1_product_prepacked(ssnet_ctx *ctx, const void *d_x_packed, cons
         !gemm_shape_ok(Co, (long)B * HW, C))
         return SSNET_EINVAL;
     const int M = B * HW;
-    u64 *parts = reserve_pending(ctx, Co, M, C, false);
-    if (!parts) return SSNET_EWORKSPACE;
+    u64 *c = reserve_pending(ctx, Co, M, C, false, HW);
+    if (!c) return SSNET_EWORKSPACE;
     timed tm(ctx, SSNET_PROF_GEMM);
     kernel_span ks(ctx);
-    hipError_t e = ss_launch_gemm(d_w_packed, d_x_packed, parts, (size_t)ctx->n * Co * M, ctx->n, Co, M, C,
+    hipError_t e = ss_launch_gemm(d_w_packed, d_x_packed, c, c + (size_t)ctx->n * Co * M, false, ctx->n, Co, M, C,
                                   (size_t)B * Co * HW, (size_t)HW, HW, (size_t)Co * HW, ctx->stream, ks.started(),
                                   ks.stopped());
     ks.done(e);
@@ -705,11 +701,11 @@ int ssnet_conv_product_planes(ssnet_ctx *ctx, const void *d_planes, const void *
     if (Ho < 1 || Wo < 1) return SSNET_EINVAL;
     const long M = (long)B * Ho * Wo, K = (long)C * kh * kw;
     if (!gemm_shape_ok(Co, M, K)) return SSNET_EINVAL;
-    u64 *parts = reserve_pending(ctx, Co, (int)M, (int)K, true);
-    if (!parts) return SSNET_EWORKSPACE;
+    u64 *c = reserve_pending(ctx, Co, (int)M, (int)K, true, Ho * Wo);
+    if (!c) return SSNET_EWORKSPACE;
     timed tm(ctx, SSNET_PROF_GEMM);
     kernel_span ks(ctx);
-    hipError_t e = ss_launch_gemm_conv(d_w_packed, d_planes, parts, (size_t)ctx->n * Co * M, ctx->n, B, C, H, W, Co, kh, kw,
+    hipError_t e = ss_launch_gemm_conv(d_w_packed, d_planes, c, c + (size_t)ctx->n * Co * M, false, ctx->n, B, C, H, W, Co, kh, kw,
                                        stride, pad, Ho, Wo, ctx->stream, ks.started(), ks.stopped());
     ks.done(e);
     ctx->pending.on = e == hipSuccess;
@@ -860,7 +856,7 @@ int ssnet_degree_reduce_static(ssnet_ctx *ctx, const uint64_t *d_c, size_t count
     if (e != hipSuccess) return fail_hip(ctx, e);
     // both message arrays are written in full by the launch before anything reads them: nothing to clear
     u64 *msg1 = (u64 *)base, *msg2 = msg1 + (size_t)nr * k * count;
-    e = ss_launch_degree_reduce(d_c, msg1, msg2, d_out, count, make_dr_params(ctx, stream_id), {1, 0}, ctx->stream);
+    e = ss_launch_degree_reduce(d_c, msg1, msg2, d_out, count, make_dr_params(ctx, stream_id), {1}, ctx->stream);
     return e == hipSuccess ? SSNET_OK : fail_hip(ctx, e);
 }
 
@@ -990,7 +986,7 @@ int ssnet_reduce_truncate_direct(ssnet_ctx *ctx, const uint64_t *d_c, size_t cou
         if (int rc = check_ids(ctx, party_ids, m)) return rc;
     const ss_nl_params open_all = make_nl_params(ctx, 0);
     const u64 *c = d_c;
-    ss_part_src ps = {1, 0};
+    ss_part_src ps = {1};
     if (!d_c)
         if (int rc = incoming_product(ctx, nullptr, count, 0, &c, &ps)) return rc;
     timed tm(ctx, SSNET_PROF_DEGREE_REDUCE);
@@ -1090,7 +1086,7 @@ int ssnet_reduce_truncate_relu_direct(ssnet_ctx *ctx, const uint64_t *d_c, int B
     ss_part_src ps;
     if (d_c) {
         c = d_c;
-        ps = {1, 0};
+        ps = {1};
     } else if (int rc = incoming_product(ctx, nullptr, count, 0, &c, &ps)) {
         return rc;
     }

@@ -71,12 +71,63 @@ __device__ __forceinline__ void send(u64 *p, u64 v)
         *p = v;
 }
 
+// First party whose share of element e has more than one plane of the incoming product: the tiles of the last parties are
+// the ones dealt in parts (ss_part_src).
+__device__ __forceinline__ int first_cut_party(const ss_part_src &ps, size_t e)
+{
+    if (ps.first_cut == 0) return 0;   // uniform
+    const u32 q = fd_div((u32)e, ps.dHw), b = fd_div(q, ps.dRows), row = q - b * ps.rows, col = b * ps.hw + ((u32)e - q * ps.hw);
+    const u32 tile = (row >> 6) * ps.row_tiles + (col >> 6);
+    int i = 0;
+    for (u32 t = tile; t < ps.first_cut; t += ps.party_tiles) i++;
+    return i;
+}
+
+// the further planes of the first NR shares of element e, added to v[]: two planes requested at a time
+template <int NR>
+__device__ __forceinline__ void add_planes(u64 (&v)[NR], const u64 *c, size_t count, size_t e, const ss_part_src &ps)
+{
+    c += e;
+    if (ps.first_cut == 0) {   // uniform: every tile has all planes
+        int s = 1;
+        for (; s + 1 < ps.planes; s += 2) {
+            u64 x[NR], y[NR];
+#pragma unroll
+            for (int i = 0; i < NR; i++) {
+                x[i] = c[(size_t)s * ps.stride + (size_t)i * count];
+                y[i] = c[(size_t)(s + 1) * ps.stride + (size_t)i * count];
+            }
+#pragma unroll
+            for (int i = 0; i < NR; i++) v[i] = ss_add(v[i], ss_add(x[i], y[i]));
+        }
+        if (s < ps.planes) {
+            u64 x[NR];
+#pragma unroll
+            for (int i = 0; i < NR; i++) x[i] = c[(size_t)s * ps.stride + (size_t)i * count];
+#pragma unroll
+            for (int i = 0; i < NR; i++) v[i] = ss_add(v[i], x[i]);
+        }
+        return;
+    }
+    const int cut = first_cut_party(ps, e);
+    if (cut >= NR) return;
+    for (int s = 1; s < ps.planes; s++) {
+        u64 x[NR];
+#pragma unroll
+        for (int i = 0; i < NR; i++) x[i] = i >= cut ? c[(size_t)s * ps.stride + (size_t)i * count] : 0;
+#pragma unroll
+        for (int i = 0; i < NR; i++) v[i] = ss_add(v[i], x[i]);
+    }
+}
+
 // share i of element e of the incoming product, which may be given as a sum of planes (the partial-sum form
 // of the product kernels): canonical sum of the planes' values
-__device__ __forceinline__ u64 load_product(const u64 *c, size_t idx, const ss_part_src &ps)
+__device__ __forceinline__ u64 load_product(const u64 *c, int i, size_t count, size_t e, const ss_part_src &ps, int first_cut)
 {
+    const size_t idx = (size_t)i * count + e;
     u64 v = c[idx];
-    for (int s = 1; s < ps.planes; s++) v = ss_add(v, c[idx + (size_t)s * ps.stride]);
+    if (i >= first_cut)
+        for (int s = 1; s < ps.planes; s++) v = ss_add(v, c[idx + (size_t)s * ps.stride]);
     return v;
 }
 
@@ -300,13 +351,7 @@ __device__ __forceinline__ void reduce_truncate(size_t e, size_t count, size_t e
     u64 cin[NR];
 #pragma unroll
     for (int i = 0; i < NR; i++) cin[i] = c[(size_t)i * count + e];
-    for (int s = 1; s < ps.planes; s++) {   // the product as a sum of planes: one more round of loads per plane
-        u64 more[NR];
-#pragma unroll
-        for (int i = 0; i < NR; i++) more[i] = c[(size_t)s * ps.stride + (size_t)i * count + e];
-#pragma unroll
-        for (int i = 0; i < NR; i++) cin[i] = ss_add(cin[i], more[i]);
-    }
+    if (ps.planes > 1) add_planes<NR>(cin, c, count, e, ps);
 
     // step 1, and of step 2 the sums coef[q][j] = sum_i msg1[i][q] * D binv[i][j] (j = 0: without D, see ilambda0)
     ss_sacc2 coef[K][K];
@@ -409,7 +454,7 @@ __global__ __launch_bounds__(BLOCK) void degree_reduce_lanes_kernel(const u64 *c
     const size_t e = (size_t)blockIdx.x * 32 + el;
     const bool live = e < count;
     if (live && p < NR) {
-        const u64 ci = load_product(c, (size_t)p * count + e, ps);
+        const u64 ci = load_product(c, p, count, e, ps, ps.planes > 1 ? first_cut_party(ps, e) : 0);
         u64 r[T];
         draw_coeffs<T>(r, dp.reshare_key[p], T, e);
         eval_points<T, K>(ci, r, [&](int q, u64 v) {
@@ -583,9 +628,10 @@ __global__ __launch_bounds__(BLOCK) void tail_direct_kernel(const u64 *c, const 
         ss_sacc acc, bacc;
         acc.clear();
         bacc.clear();
+        const int cut = ps.planes > 1 ? first_cut_party(ps, e) : 0;
 #pragma unroll
         for (int i = 0; i < 2 * SS_MAXT + 1; i++)
-            if (i < nr) acc.mac(load_product(c, (size_t)i * count + e, ps), open_all.ilambda[i]);
+            if (i < nr) acc.mac(load_product(c, i, count, e, ps, cut), open_all.ilambda[i]);
 #pragma unroll
         for (int q = 0; q < SS_MAXK; q++)
             if (q < k) bacc.mac(sh_b[(size_t)q * count + e], tp.ilambda[q]);
@@ -626,9 +672,10 @@ __global__ __launch_bounds__(BLOCK) void reduce_truncate_direct_kernel(const u64
     if (e >= count) return;
     ss_sacc2 acc;
     acc.clear();
+    const int cut = ps.planes > 1 ? first_cut_party(ps, e) : 0;
 #pragma unroll
     for (int i = 0; i < 2 * T + 1; i++) {
-        const u64 ci = load_product(c, (size_t)i * count + e, ps);
+        const u64 ci = load_product(c, i, count, e, ps, cut);
         SS_SPLIT31(ci, w0, w1);
         acc.mac(w0, w1, open_all.ilambda[i]);
     }
@@ -946,23 +993,6 @@ hipError_t ss_launch_reconstruct(const u64 *shares, u64 *secret, size_t count, c
     else
         SS_REC(1);
 #undef SS_REC
-    return hipGetLastError();
-}
-
-// sum of the product's planes, written to dst (which may be the first plane: each thread reads its element
-// of every plane before it writes)
-__global__ __launch_bounds__(BLOCK) void sum_planes_kernel(u64 *dst, const u64 *c, size_t total, ss_part_src ps)
-{
-    const size_t i = (size_t)blockIdx.x * BLOCK + threadIdx.x;
-    if (i < total) dst[i] = load_product(c, i, ps);
-}
-
-hipError_t ss_launch_sum_planes(u64 *dst, const u64 *c, size_t total, const ss_part_src &ps, hipStream_t stream)
-{
-    if (ps.planes > 1 || dst != c)
-        for_each_launch(total, [&](size_t first, dim3 grid) {
-            hipLaunchKernelGGL(sum_planes_kernel, grid, dim3(BLOCK), 0, stream, dst + first, c + first, total - first, ps);
-        });
     return hipGetLastError();
 }
 

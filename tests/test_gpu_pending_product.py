@@ -183,3 +183,31 @@ def test_pending_product_errors():
     with pytest.raises(SSNetError) as ei:
         s.degree_reduce(None, stream_id=0, out=out)
     assert ei.value.code == binding.EINVAL
+
+
+@pytest.mark.parametrize("n,t,p", [(5, 2, binding.P61), (3, 1, binding.P45)])
+def test_products_with_whole_tiles_ahead_of_the_cut_ones(n, t, p):
+    """Tiles for two rounds of the chip and more: all but the last 256 to 511 lie in the first plane alone.  Ragged rows
+    and columns, columns that run over several images, and the same product as a tensor (the parts added up)."""
+    s = SSNet(n, t, f=12, seed=94, p=p)
+    bits = 11 if p == binding.P45 else 15
+    per = -(-560 // n)                                   # tiles of a party
+    M, K, N = 130, 320, 64 * (-(-per // 3)) - 37         # three row tiles, the last one ragged
+    say("dense product, whole tiles first", n, t, hex(p), M, K, N)
+    x = small_secrets((M, K), 5, bits, p)
+    ws = orc.share(small_secrets((K, N), 6, bits - 2, p), n, t, p, 94, 9)
+    y = orc.linear(orc.share(x, n, t, p, 94, 8), ws, p)
+    _, tiles = s.share_packed(to_dev(x), stream_id=8)
+    wp = s.pack_weights_linear(to_dev(ws))
+    check_consumers(s, p, y, (M, N, 1, 1), lambda: s.linear_product_prepacked(tiles, wp, M, K, N), seed=94)
+    assert np.array_equal(to_np(s.linear_mod_prepacked(tiles, wp, M, K, N)), y)
+    C, Co, H, k = 64, 128, 14, 3
+    B = -(-64 * per // (2 * H * H))
+    say("conv product, whole tiles first", n, t, hex(p), B, C, H, Co)
+    xs = orc.share(small_secrets((B, C, H, H), 1, bits, p), n, t, p, 94, 5)
+    ws = orc.share(small_secrets((Co, C, k, k), 2, bits - 2, p), n, t, p, 94, 6)
+    y = orc.conv(xs, ws, 1, 1, p)
+    planes, wp = s.split_planes(to_dev(xs)), s.pack_weights_conv_taps(to_dev(ws))
+    geom = (B, C, H, H, Co, k, k, 1, 1)
+    check_consumers(s, p, y, (B, Co, H, H), lambda: s.conv_product_planes(planes, wp, *geom), seed=94)
+    assert np.array_equal(to_np(s.conv_mod_planes(planes, wp, *geom)), y)
