@@ -381,22 +381,17 @@ __device__ __forceinline__ void tile_coords(const gemm_args &g, unsigned tile, i
     rt = (int)(rem - (unsigned)party * (unsigned)g.RT);
 }
 
-// this wave's source block of tile `tile`: block `wave` of A for waves 0..3, of
-// B for waves 4..7; blocks past the end are clamped (their products are
+// where column block cb of a party's second operand comes from (blocks past the end are clamped: their products are
 // computed and never stored)
 template <bool IMPLICIT>
-__device__ __forceinline__ wave_src tile_source(const gemm_args &g, unsigned tile, int wave, int lane)
+__device__ __forceinline__ wave_src column_source(const gemm_args &g, int party, int cb, int lane)
 {
-    int ct, rt, party;
-    tile_coords(g, tile, ct, rt, party);
     wave_src ws = {nullptr, 0, 0};
-    if (wave < 4) {
-        ws.p = g.A + (size_t)party * g.a_party_stride + (size_t)min(rt * 4 + wave, g.Rb - 1) * g.Kb * TILE + lane;
-    } else if (!IMPLICIT) {
-        ws.p = g.B + (size_t)party * g.b_party_stride + (size_t)min(ct * 4 + wave - 4, g.Cb - 1) * g.Kb * TILE + lane;
+    if (!IMPLICIT) {
+        ws.p = g.B + (size_t)party * g.b_party_stride + (size_t)min(cb, g.Cb - 1) * g.Kb * TILE + lane;
     } else {
         // lane l of a block holds column 16 cb + l%16 = output pixel (b, ho, wo)
-        const int col = min(ct * 4 + wave - 4, g.Cb - 1) * 16 + (lane & 15);
+        const int col = min(cb, g.Cb - 1) * 16 + (lane & 15);
         const int cc = min(col, g.cols - 1), b = (int)fd_div((u32)cc, g.dHoWo), r = cc - b * g.cvHoWo,
                   ho = (int)fd_div((u32)r, g.dWo), wo = r - ho * g.cvWo;
         ws.p = g.planes + (size_t)party * g.party16;
@@ -406,12 +401,22 @@ __device__ __forceinline__ wave_src tile_source(const gemm_args &g, unsigned til
     return ws;
 }
 
-// base address and limb stride (16-byte units) of the wave's block for k block kb
+// this wave's source block of tile `tile`: block `wave` of A for waves 0..3, of
+// B for waves 4..7
 template <bool IMPLICIT>
-__device__ __forceinline__ const v4i *unit_base(const gemm_args &g, const wave_src &ws, int kb, int wave, int lane,
-                                                unsigned &qs)
+__device__ __forceinline__ wave_src tile_source(const gemm_args &g, unsigned tile, int wave, int lane)
 {
-    if (!IMPLICIT || wave < 4) {
+    int ct, rt, party;
+    tile_coords(g, tile, ct, rt, party);
+    if (wave >= 4) return column_source<IMPLICIT>(g, party, ct * 4 + wave - 4, lane);
+    return {g.A + (size_t)party * g.a_party_stride + (size_t)min(rt * 4 + wave, g.Rb - 1) * g.Kb * TILE + lane, 0, 0};
+}
+
+// base address and limb stride (16-byte units) of a column block for k block kb
+template <bool IMPLICIT>
+__device__ __forceinline__ const v4i *column_base(const gemm_args &g, const wave_src &ws, int kb, int lane, unsigned &qs)
+{
+    if (!IMPLICIT) {
         qs = 64;
         return ws.p + (size_t)kb * TILE;
     }
@@ -422,6 +427,18 @@ __device__ __forceinline__ const v4i *unit_base(const gemm_args &g, const wave_s
     const bool ok = ws.bpix >= 0 && (unsigned)hi < (unsigned)g.cvH && (unsigned)wi < (unsigned)g.cvW;
     qs = ok ? g.plane16 : 0;
     return ok ? ws.p + (size_t)c16 * g.cvPixels + (ws.bpix + hi * g.cvW + wi) : g.zero;
+}
+
+// the same for the block of a wave of the big kernel
+template <bool IMPLICIT>
+__device__ __forceinline__ const v4i *unit_base(const gemm_args &g, const wave_src &ws, int kb, int wave, int lane,
+                                                unsigned &qs)
+{
+    if (!IMPLICIT || wave < 4) {
+        qs = 64;
+        return ws.p + (size_t)kb * TILE;
+    }
+    return column_base<IMPLICIT>(g, ws, kb, lane, qs);
 }
 
 __device__ __forceinline__ u64 *plane_at(const gemm_args &g, unsigned plane)
@@ -439,6 +456,14 @@ __device__ __forceinline__ int zero_planes_of_cut_tile(const gemm_args &g, unsig
     int nc = 1;
     while (slot + nc < G && nc < g.slots && unit_at(g, range_bound(g, slot + nc)) < tile_end) nc++;
     return g.slots - nc;
+}
+
+// Place of a workgroup in the list of ranges or tiles: workgroups are dealt round-robin to the 8 XCDs, and consecutive places
+// go to workgroups of the same XCD, so that neighbours in the list share an L2.
+__device__ __forceinline__ unsigned xcd_slot(unsigned block, unsigned G)
+{
+    const unsigned xcd = block & 7;
+    return xcd * (G >> 3) + min(xcd, G & 7) + (block >> 3);
 }
 
 // Persistent kernel, one workgroup of 8 waves (4 x 2) per CU.  The work is the
@@ -471,9 +496,7 @@ __global__ __launch_bounds__(512) void gemm_limb_kernel(gemm_args g)
     constexpr int STAGE = 8 * TILE;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wr = wave & 3, wc = wave >> 2;
     const unsigned G = gridDim.x;
-    // consecutive ranges go to workgroups of the same XCD (workgroups are dealt
-    // round-robin to the 8 XCDs), so that neighbours in the list share an L2
-    const unsigned slot = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
+    const unsigned slot = xcd_slot(blockIdx.x, G);
     const unsigned myplane = g.slots > 1 ? slot % (unsigned)g.slots : 0;
     // its whole tiles w0 .. w1 - 1 and its range of units u0 .. u1 - 1; u counts the units of the one, then of the other
     unsigned w0 = 0, w1 = 0, u0 = 0, u1 = 0;
@@ -649,8 +672,100 @@ __global__ __launch_bounds__(512) void gemm_limb_kernel(gemm_args g)
     }
 }
 
-// The same contraction for a first operand of at most 16 rows (dense layers at a small batch, convolutions
-// with few output channels).  There the time goes into reading the second operand once, so a launch is as
+// The same contraction for products that are too small, or too narrow, for tiles of 64 x 64 and operands shared through LDS:
+// there a launch lasts as long as its chain of dependent steps, or as it takes to read the one large operand once.  A wave
+// owns a tile of 16 x 16, takes every KS-th of the k blocks and reads both operand blocks straight into registers, the
+// next unit's while the MFMAs of the current one run; the KS waves that share a tile add their residues through LDS.  CW
+// tiles, neighbours in the list, make a workgroup.  Where that leaves CUs idle the k blocks are also divided into `parts` equal
+// runs, each with a plane of its own (every tile has all of them).
+template <bool IMPLICIT, int KS>
+__global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void gemm_ksplit_kernel(gemm_args g, fdiv dParts)
+{
+    constexpr int NW = KS == 8 ? 8 : 4, CW = NW / KS;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), cw = wave % CW, ks = wave / CW;
+    const unsigned slot = xcd_slot(blockIdx.x, gridDim.x);
+    const unsigned group = fd_div(slot, dParts), part = slot - group * (unsigned)g.slots;
+    // tile `block` of the list: party-major, then the longer side of the product, then the shorter one, so that the tiles
+    // that read one block of the longer side are neighbours
+    auto coords = [&](unsigned block, int &cb, int &rb, int &party) {
+        int minor, major;
+        tile_coords(g, block, minor, major, party);
+        cb = g.Rb < g.Cb ? major : minor;
+        rb = g.Rb < g.Cb ? minor : major;
+    };
+    const unsigned block = group * CW + cw;
+    int cb, rb, party;
+    coords(block, cb, rb, party);
+    const bool inside = block < g.units;
+    const int k0 = (int)fd_div(part * (unsigned)g.Kb, dParts) + ks, k1 = (int)fd_div((part + 1) * (unsigned)g.Kb, dParts);
+
+    v4i acc[ND];
+#pragma unroll
+    for (int s = 0; s < ND; s++) acc[s] = (v4i){0, 0, 0, 0};
+    if (inside) {
+        const v4i *const pa = g.A + (size_t)party * g.a_party_stride + (size_t)rb * g.Kb * TILE + lane;
+        const wave_src src = column_source<IMPLICIT>(g, party, cb, lane);
+        auto load = [&](v4i (&a)[NL], v4i (&b)[NL], int kb) {
+            unsigned qs;
+            const v4i *pb = column_base<IMPLICIT>(g, src, kb, lane, qs);
+#pragma unroll
+            for (int q = 0; q < NL; q++) {
+                a[q] = pa[(size_t)kb * TILE + q * 64];
+                b[q] = pb[(size_t)q * qs];
+            }
+        };
+        auto multiply = [&](const v4i (&a)[NL], const v4i (&b)[NL]) {
+#pragma unroll
+            for (int i = 0; i < NL; i++)
+#pragma unroll
+                for (int j = 0; j < NL; j++)
+                    acc[i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b[j], acc[i + j], 0, 0, 0);
+        };
+        v4i a0[NL], b0[NL], a1[NL], b1[NL];
+        if (k0 < k1) load(a0, b0, k0);
+        for (int kb = k0; kb < k1; kb += 2 * KS) {
+            if (kb + KS < k1) load(a1, b1, kb + KS);
+            multiply(a0, b0);
+            if (kb + KS < k1) {
+                if (kb + 2 * KS < k1) load(a0, b0, kb + 2 * KS);
+                multiply(a1, b1);
+            }
+        }
+    }
+
+    // lane holds column lane%16 and rows 4*(lane/16)+r of its tile
+    u64 v[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) v[r] = fold_diagonals(acc, r);
+    auto store = [&](unsigned which, int r, u64 value) {
+        int scb, srb, sparty;
+        coords(which, scb, srb, sparty);
+        const int row = srb * 16 + 4 * (lane >> 4) + r, col = scb * 16 + (lane & 15);
+        if (which >= g.units || row >= g.rows || col >= g.cols) return;
+        const u32 cq = fd_div((u32)col, g.dCdiv);
+        plane_at(g, part)[(size_t)sparty * g.out_party_stride + (size_t)cq * g.stride_cb + ((u32)col - cq * (u32)g.cdiv) +
+                          (size_t)row * g.stride_row] = value;
+    };
+    if constexpr (KS == 1) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) store(block, r, v[r]);
+    } else {
+        __shared__ u64 sums[NW][4][64];
+#pragma unroll
+        for (int r = 0; r < 4; r++) sums[wave][r][lane] = v[r];
+        __syncthreads();
+        // wave w adds the KS residues of the (tile, row) pairs w, w + NW, ... of the CW x 4
+        for (int i = wave; i < 4 * CW; i += NW) {
+            u64 x = sums[i >> 2][i & 3][lane];
+#pragma unroll
+            for (int k = 1; k < KS; k++) x = ss_add(x, sums[k * CW + (i >> 2)][i & 3][lane]);
+            store(group * CW + (i >> 2), i & 3, x);
+        }
+    }
+}
+
+// The same contraction for a first operand of at most 16 rows and a large second one (dense layers at a small batch).
+// There the time goes into reading the second operand once, so a launch is as
 // fast as it keeps bytes in flight: a workgroup's tile is 16 rows x 128 columns, one row block and eight
 // column blocks per unit, twice the column blocks of the square tile in the same LDS, and no MFMA is spent on
 // row blocks that do not exist.  Wave w copies column block w and limb slice w of the row block, and owns
@@ -663,7 +778,7 @@ __global__ __launch_bounds__(512) void gemm_skinny_kernel(gemm_args g)
     constexpr int STAGE = 9 * TILE;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned G = gridDim.x;
-    const unsigned slot = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
+    const unsigned slot = xcd_slot(blockIdx.x, G);
     unsigned u0, u1;
     if (g.units) {
         u0 = unit_at(g, range_bound(g, slot));
@@ -769,7 +884,8 @@ __global__ __launch_bounds__(512) void gemm_skinny_kernel(gemm_args g)
 
 struct gemm_plan {
     bool skinny;               // first operand of at most 16 rows: tiles of 16 x 128 (gemm_skinny_kernel)
-    long tiles, units;         // units == 0: whole tiles only (one per workgroup for the 16-row kernel)
+    int ksplit;                // waves that share a tile of 16 x 16 in gemm_ksplit_kernel; 0: gemm_limb_kernel
+    long tiles, units;         // units == 0: whole tiles only
     int Kb, G, slots, RT, CT;
     unsigned whole;            // tiles dealt whole, ahead of the ranges
     unsigned wlast, tcost, tlast, cost, cost0;
@@ -788,6 +904,54 @@ unsigned unit_cost(int vb)
 // of one (0.15 us at 5 TB/s, what many streams at a time reach).
 constexpr unsigned long long SS_BYTES_PER_COST = 750 * 1000;
 
+// Plan for gemm_ksplit_kernel and what it takes, in units (16 x 16, one k block, four side by side on a CU): a CU's waves get
+// their operand blocks out of the caches at about 30 bytes per clock, so a launch lasts as long as the fullest CU has units.
+gemm_plan plan_ksplit(int n, int rows, int cols, int Kb, double *busy)
+{
+    gemm_plan best = {};
+    const long Rb = (rows + 15) / 16, Cb = (cols + 15) / 16, blocks = n * Rb * Cb;
+    best.Kb = Kb;
+    best.RT = (int)(Rb < Cb ? Cb : Rb);
+    best.CT = (int)(Rb < Cb ? Rb : Cb);
+    best.tiles = best.units = blocks;
+    if (blocks >= (1L << 28)) return best;   // (refused by the caller: busy stays)
+    for (int ks = 1; ks <= 8 && (ks == 1 || ks <= Kb); ks *= 2) {
+        const int cw = ks == 8 ? 1 : 4 / ks, fours = ks == 8 ? 2 : 1;   // tiles, and groups of four waves, of a workgroup
+        const long groups = (blocks + cw - 1) / cw;
+        int parts = 1;
+        // CUs left over: k blocks in parts, as long as every wave keeps two units
+        while (ks == 8 && (parts + 1) * groups <= SS_GEMM_CUS && Kb >= 16 * (parts + 1)) parts++;
+        const long wgs = groups * parts, units = (Kb + ks * parts - 1) / (ks * parts);
+        // workgroups of four that the fullest CU runs; over many rounds they even out
+        const double fullest = wgs <= 2 * SS_GEMM_CUS ? (double)((wgs + SS_GEMM_CUS - 1) / SS_GEMM_CUS * fours)
+                                                      : (double)wgs / SS_GEMM_CUS * fours + 0.3 * fours;
+        // (a lone wave on a SIMD waits for its operands a little; half a unit for a wave's fold and start)
+        const double cost = fullest * ((fullest == 1 ? 1.15 : 1.0) * units + 0.5);
+        if (best.G == 0 || cost < *busy) {
+            *busy = cost;
+            best.ksplit = ks;
+            best.slots = parts;
+            best.G = (int)wgs;
+        }
+    }
+    return best;
+}
+
+// gemm_ksplit_kernel takes 3.4 us and 0.88 us (0.53 us over the 45-bit prime) for each of those; the big kernel 5.3 us and 0.15 us
+// (8.5 and 0.085 us) for a cost of one of its busiest workgroup.  With a single k block the stores decide from some 2560 tiles
+// on.  Measured on both sides of the line, n = 5 / n = 3 / n = 3 over the 45-bit prime, us, big kernel -> this one (rows x columns x
+// contraction): 64 x 128 x 256 9.3 -> 4.7 / 8.8 -> 4.5 / 8.1 -> 4.3; 128 x 784 x 512 19.4 -> 16.7 / 14.2 -> 12.7 / 13.8 -> 9.7;
+// 1024 x 196 x 256 20.6 -> 19.7 / 15.3 -> 13.3 / 13.1 -> 9.3; 256 x 196 x 1024 20.3 -> 21.2 / 14.2 -> 12.7 / 14.6 -> 8.8; 512 x 64 x 4608
+// 41 -> 51 / 26 -> 32 / 20.7 -> 23.1; 256 x 3136 x 64 21.1 -> 25.0 / 16.6 -> 16.1 / 16.4 -> 14.1.  Against the 16-row kernel:
+// 4 x 4096 x 512 16.7 -> 17.2 / 12.2 -> 11.4 / 9.3 -> 9.8; 1 x 1000 x 2048 17.3 -> 21.7 / 13.1 -> 13.2 / 10.0 -> 9.6.
+bool ksplit_is_faster(const gemm_plan &k, bool skinny, double busy, unsigned long long big)
+{
+    if (k.G <= 0 || k.tiles * k.Kb >= (1L << 31)) return false;
+    if (skinny) return k.tiles * k.Kb <= 6144;
+    if (NL == 8) return busy * 5.87 < (double)big + 12.7 && (k.Kb > 1 || k.tiles <= 2560);
+    return busy * 6.2 < (double)big + 62 && (k.Kb > 1 || k.tiles <= 10240);
+}
+
 // How the units are dealt: one workgroup per CU unless there is too little work for that; slots = the most
 // workgroups that can share one tile.
 // Whole tiles first and the price of the planes, against every tile dealt by cost with two planes, MI355X: layers of eight
@@ -798,8 +962,8 @@ gemm_plan plan_gemm(int n, int rows, int cols, int K, bool allow_skinny)
 {
     typedef unsigned long long ull;
     gemm_plan p = {};
-    p.skinny = allow_skinny && rows <= 16;
     p.Kb = (K + 63) / 64;
+    p.skinny = allow_skinny && rows <= 16;
     p.CT = p.skinny ? (cols + SKINNY_COLS - 1) / SKINNY_COLS : (cols + 63) / 64;
     p.RT = p.skinny ? 1 : (rows + 63) / 64;
     p.tiles = (long)n * p.RT * p.CT;
@@ -814,6 +978,7 @@ gemm_plan plan_gemm(int n, int rows, int cols, int K, bool allow_skinny)
     // planes.  With a single k block tiles are never cut, so there is nothing to choose; launches too large for the
     // 32-bit range arithmetic (and that of the consumers, ss_part_src) have tiles enough for every CU many times over.
     const unsigned step = SS_UNIT_COST + SS_FOLD_COST;   // largest distance between two unit starts
+    ull busy = ~0ull;   // cost of the busiest workgroup
     bool all_whole = cost >= (1ull << 31) || p.units >= (1L << 31) || (ull)rows * cols >= (1ull << 31);
     if (!all_whole) {
         p.cost = (unsigned)cost;
@@ -832,11 +997,17 @@ gemm_plan plan_gemm(int n, int rows, int cols, int K, bool allow_skinny)
         const unsigned share = (p.cost - p.cost0) / p.G;
         p.slots = (int)((p.tcost + share - 1) / share) + 1;
         if (p.slots > p.Kb) p.slots = p.Kb;
+        busy = (ull)(p.whole / SS_GEMM_CUS) * p.tcost + share + SS_FOLD_COST;
         if (p.Kb > 1) {
             const ull plane_bytes = 16ull * n * rows * cols / p.tiles * (p.tiles - p.whole) * (p.slots - 1);
             const ull rounds = ((ull)p.tiles + SS_GEMM_CUS - 1) / SS_GEMM_CUS;
-            all_whole = rounds * p.tcost <= (ull)(p.whole / SS_GEMM_CUS) * p.tcost + share + SS_FOLD_COST + plane_bytes / SS_BYTES_PER_COST;
+            all_whole = rounds * p.tcost <= busy + plane_bytes / SS_BYTES_PER_COST;
+            if (all_whole) busy = rounds * p.tcost - SS_FOLD_COST;   // (5.3 us hold a fold)
         }
+        double kbusy = 0;
+        const gemm_plan k = plan_ksplit(n, rows, cols, p.Kb, &kbusy);
+        if (p.CT == 1 && vb_last == 2) busy = busy * 7 / 8;   // (units of two column blocks cost less than dealt with)
+        if (ksplit_is_faster(k, p.skinny, kbusy, busy)) return k;
     }
     if (all_whole) {
         const bool launchable = p.tiles < (1L << 30);   // else G = 0, rejected by the caller
@@ -850,11 +1021,16 @@ gemm_plan plan_gemm(int n, int rows, int cols, int K, bool allow_skinny)
 }
 
 // The planes of tiles computed in parts, added up into the first one, for callers that want the product as a tensor: one
-// thread per element, 256 of a tile (4 runs of 64 columns or 2 of 128) per workgroup.
+// thread per element, 256 of a tile (16 x 16, 64 x 64 or 16 x 128) per workgroup.
 __global__ __launch_bounds__(256) void add_parts_kernel(gemm_args g, unsigned first_tile, int log_rows, int log_cols)
 {
     int ct, rt, party;
     tile_coords(g, first_tile + blockIdx.x, ct, rt, party);
+    if (log_rows == log_cols && log_rows == 4 && g.Rb < g.Cb) {   // (the order of gemm_ksplit_kernel)
+        const int minor = ct;
+        ct = rt;
+        rt = minor;
+    }
     const int i = blockIdx.y * 256 + threadIdx.x, row = (rt << log_rows) + (i >> log_cols), col = (ct << log_cols) + (i & ((1 << log_cols) - 1));
     if (row >= g.rows || col >= g.cols) return;
     const u32 cq = fd_div((u32)col, g.dCdiv);
@@ -879,7 +1055,7 @@ ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, bool planes_operand,
     ss_part_src ps = {};
     ps.planes = p.slots;
     ps.stride = (size_t)n * rows * cols;
-    ps.first_cut = p.whole;
+    ps.first_cut = p.ksplit ? 0 : p.whole;
     ps.party_tiles = (unsigned)p.RT * (unsigned)p.CT;
     ps.row_tiles = (unsigned)p.CT;
     ps.hw = (unsigned)hw;
@@ -897,9 +1073,8 @@ int ss_gemm_planes(int n, int rows, int cols, int K, bool planes_operand)
 size_t ss_gemm_scratch_bytes(int n, int rows, int cols, int K)
 {
     // room for either form of the second operand (tiles may take the 16-row kernel, limb planes never do)
-    const int a = plan_gemm(n, rows, cols, K, false).slots, b = plan_gemm(n, rows, cols, K, true).slots;
-    const int planes = a > b ? a : b;
-    return (size_t)(planes - 1) * n * rows * cols * sizeof(u64);   // the first plane is the product itself
+    const int a = ss_gemm_planes(n, rows, cols, K, true), b = ss_gemm_planes(n, rows, cols, K, false);
+    return (size_t)((a > b ? a : b) - 1) * n * rows * cols * sizeof(u64);   // the first plane is the product itself
 }
 
 size_t ss_packed_bytes(int rows, int K)
@@ -1013,7 +1188,7 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
     g.Kb = p.Kb;
     g.RT = p.RT;
     g.CT = p.CT;
-    g.units = (unsigned)p.units;
+    g.units = (unsigned)p.units;   // (gemm_ksplit_kernel: its tiles)
     g.whole = p.whole;
     g.cost0 = p.cost0;
     g.wlast = p.wlast;
@@ -1052,25 +1227,37 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
     }
     // with an event pair the launch goes through the entry point that stamps the events with the kernel's own
     // start and end (profiling only)
-#define SS_LAUNCH_PRODUCT(KERNEL, LDS)                                                                            \
-    do {                                                                                                          \
-        if (started && stopped)                                                                                   \
-            hipExtLaunchKernelGGL(KERNEL, dim3((unsigned)p.G), dim3(512), LDS, stream, started, stopped, 0, g);   \
-        else                                                                                                      \
-            hipLaunchKernelGGL(KERNEL, dim3((unsigned)p.G), dim3(512), LDS, stream, g);                           \
+#define SS_LAUNCH_PRODUCT(KERNEL, BLOCK, LDS, ...)                                                                   \
+    do {                                                                                                              \
+        if (started && stopped)                                                                                       \
+            hipExtLaunchKernelGGL(KERNEL, dim3((unsigned)p.G), dim3(BLOCK), LDS, stream, started, stopped, 0, __VA_ARGS__); \
+        else                                                                                                          \
+            hipLaunchKernelGGL(KERNEL, dim3((unsigned)p.G), dim3(BLOCK), LDS, stream, __VA_ARGS__);                   \
     } while (0)
-    if (p.skinny)
-        SS_LAUNCH_PRODUCT(gemm_skinny_kernel, LDS_BYTES_SKINNY);
-    else if (cv)
-        SS_LAUNCH_PRODUCT(gemm_limb_kernel<true>, LDS_BYTES);
-    else
-        SS_LAUNCH_PRODUCT(gemm_limb_kernel<false>, LDS_BYTES);
+#define SS_LAUNCH_KSPLIT(KS)                                                                                          \
+    SS_LAUNCH_PRODUCT((cv ? gemm_ksplit_kernel<true, KS> : gemm_ksplit_kernel<false, KS>), KS == 8 ? 512 : 256, 0, g,  \
+                      make_fdiv((u32)p.slots))
+    switch (p.ksplit) {
+        case 0:
+            if (p.skinny)
+                SS_LAUNCH_PRODUCT(gemm_skinny_kernel, 512, LDS_BYTES_SKINNY, g);
+            else
+                SS_LAUNCH_PRODUCT((cv ? gemm_limb_kernel<true> : gemm_limb_kernel<false>), 512, LDS_BYTES, g);
+            break;
+        case 1: SS_LAUNCH_KSPLIT(1); break;
+        case 2: SS_LAUNCH_KSPLIT(2); break;
+        case 4: SS_LAUNCH_KSPLIT(4); break;
+        default: SS_LAUNCH_KSPLIT(8);
+    }
+#undef SS_LAUNCH_KSPLIT
 #undef SS_LAUNCH_PRODUCT
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !add_parts || p.slots == 1) return e;
-    const unsigned first = p.whole;
-    hipLaunchKernelGGL(add_parts_kernel, dim3((unsigned)p.tiles - first, p.skinny ? 8 : 16), dim3(256), 0, stream, g, first,
-                       p.skinny ? 4 : 6, p.skinny ? 7 : 6);
+    // (log2 of a tile's rows and columns)
+    const int log_rows = p.ksplit || p.skinny ? 4 : 6, log_cols = p.ksplit ? 4 : p.skinny ? 7 : 6;
+    const unsigned first = p.ksplit || p.skinny ? 0 : p.whole;
+    hipLaunchKernelGGL(add_parts_kernel, dim3((unsigned)p.tiles - first, 1u << (log_rows + log_cols - 8)), dim3(256), 0, stream,
+                       g, first, log_rows, log_cols);
     return hipGetLastError();
 }
 

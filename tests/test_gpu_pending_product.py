@@ -211,3 +211,39 @@ def test_products_with_whole_tiles_ahead_of_the_cut_ones(n, t, p):
     geom = (B, C, H, H, Co, k, k, 1, 1)
     check_consumers(s, p, y, (B, Co, H, H), lambda: s.conv_product_planes(planes, wp, *geom), seed=94)
     assert np.array_equal(to_np(s.conv_mod_planes(planes, wp, *geom)), y)
+
+
+# rows, contraction, columns: one, two, four and eight waves to a tile of 16 x 16, contractions in parts, either side the
+# longer one, ragged edges on both, single blocks, contractions that leave waves without a unit
+SMALL_DENSE = [(17, 64, 33), (1, 1, 1), (70, 250, 790), (64, 256, 128), (300, 130, 20), (20, 2400, 30), (16, 4096, 10), (9, 590, 16),
+               (1, 400, 120), (129, 900, 48)]
+SMALL_CONV = [  # B, C, H, W, Co, k, stride, pad
+    (1, 512, 4, 4, 40, 3, 1, 1), (3, 64, 7, 5, 100, 1, 1, 0), (1, 64, 16, 15, 64, 3, 2, 1), (2, 128, 2, 2, 512, 3, 1, 1),
+    (1, 192, 9, 9, 17, 5, 1, 2)]
+
+
+@pytest.mark.parametrize("n,t,p", [(5, 2, binding.P61), (3, 1, binding.P45), (8, 3, binding.P61)])
+def test_small_and_narrow_products(n, t, p):
+    """Products whose tiles are computed by waves on their own: as tensors with full-range operands, and left to every
+    consumer."""
+    s = SSNet(n, t, f=12, seed=95, p=p)
+    bits = 11 if p == binding.P45 else 15
+    for i, (M, K, N) in enumerate(SMALL_DENSE):
+        say("small dense", n, t, hex(p), M, K, N)
+        x, w = (orc.share(small_secrets(sh, 2 * i + j, bits - 2 * j, p), n, t, p, 95, 8 + j) for j, sh in enumerate([(M, K), (K, N)]))
+        y = orc.linear(x, w, p)
+        assert np.array_equal(to_np(s.linear_mod(to_dev(x), to_dev(w))), y)
+        _, tiles = s.share_packed(to_dev(small_secrets((M, K), 2 * i, bits, p)), stream_id=8)
+        wp = s.pack_weights_linear(to_dev(w))
+        check_consumers(s, p, y, (M, N, 1, 1), lambda: s.linear_product_prepacked(tiles, wp, M, K, N), seed=95)
+        full_x, full_w = field_uniform((n, M, K), i) % np.uint64(p), field_uniform((n, K, N), 50 + i) % np.uint64(p)
+        assert np.array_equal(to_np(s.linear_mod(to_dev(full_x), to_dev(full_w))), orc.linear(full_x, full_w, p))
+    for (B, C, H, W, Co, k, stride, pad) in SMALL_CONV:
+        say("small conv", n, t, hex(p), B, C, H, W, Co, k, stride, pad)
+        xs = orc.share(small_secrets((B, C, H, W), 1, bits, p), n, t, p, 95, 5)
+        ws = orc.share(small_secrets((Co, C, k, k), 2, bits - 2, p), n, t, p, 95, 6)
+        y = orc.conv(xs, ws, stride, pad, p)
+        planes, wp = s.split_planes(to_dev(xs)), s.pack_weights_conv_taps(to_dev(ws))
+        geom = (B, C, H, W, Co, k, k, stride, pad)
+        assert np.array_equal(to_np(s.conv_mod_planes(planes, wp, *geom)), y)
+        check_consumers(s, p, y, (B, Co) + y.shape[-2:], lambda: s.conv_product_planes(planes, wp, *geom), seed=95)
