@@ -458,14 +458,6 @@ __device__ __forceinline__ int zero_planes_of_cut_tile(const gemm_args &g, unsig
     return g.slots - nc;
 }
 
-// Place of a workgroup in the list of ranges or tiles: workgroups are dealt round-robin to the 8 XCDs, and consecutive places
-// go to workgroups of the same XCD, so that neighbours in the list share an L2.
-__device__ __forceinline__ unsigned xcd_slot(unsigned block, unsigned G)
-{
-    const unsigned xcd = block & 7;
-    return xcd * (G >> 3) + min(xcd, G & 7) + (block >> 3);
-}
-
 // Persistent kernel, one workgroup of 8 waves (4 x 2) per CU.  The work is the
 // flat list of units (output tile of 64 x 64, k block of 64), tile-major; each
 // workgroup takes one contiguous range of it, of equal cost, so every CU gets

@@ -60,6 +60,14 @@ struct ss_pool_geom {
     int mode;                     // 0: maximum, 1: sum
 };
 
+// Place of a workgroup in a list (of tiles, of blocks of elements): workgroups are dealt round-robin to the 8 XCDs, and
+// consecutive places go to workgroups of the same XCD, so that neighbours in the list share an L2.
+__device__ __forceinline__ unsigned xcd_slot(unsigned block, unsigned G)
+{
+    const unsigned xcd = block & 7;
+    return xcd * (G >> 3) + min(xcd, G & 7) + (block >> 3);
+}
+
 // x / d for x < 2^31 by a multiplication: (x * m) >> s with s = 31 + ceil(log2 d), m = ceil(2^s / d) < 2^32.
 // The index arithmetic of the product kernels runs on these (a 64-bit division is some two hundred
 // instructions on this machine, and a launch of a small layer lasts only a few thousand).

@@ -15,6 +15,20 @@ namespace {
 
 constexpr int BLOCK = 256;
 
+// Block of elements that a workgroup of an element-wise kernel takes.  Where the planes of a tensor do not start on a cache
+// line (starts_lines) the blocks share lines, and workgroups are dealt round-robin to the 8 XCDs, so that neighbours write
+// their parts of a line from two L2s.  There 64 consecutive blocks go to one XCD (8 are as good for most, all of a plane's
+// eighth is worse for the larger tensors): n = 7, t = 3 reduce + truncate of 300001 elements on changing inputs 53 -> 48 us,
+// sharing among three of 2^24 + 3 118 -> 95 us, reconstruction from two 88 -> 78 us.
+__host__ __device__ __forceinline__ bool starts_lines(size_t count) { return count % 16 == 0; }
+__device__ __forceinline__ size_t element_block(size_t count)
+{
+    constexpr unsigned RUN = 64;
+    const unsigned b = blockIdx.x, base = b / (8 * RUN) * (8 * RUN);
+    if (starts_lines(count) || base + 8 * RUN > gridDim.x) return b;
+    return base + (b % 8) * RUN + (b - base) / 8;
+}
+
 template <int VEC>
 struct pack_t;
 template <>
@@ -148,17 +162,19 @@ __device__ __forceinline__ void draw_coeffs(u64 (&c)[MAXD], const u64 *keys, int
 // against 2.32 ms with four waves and 2.40 ms with the short reduction too; 2^26: 514, 548 and 570 us; 2^20: 7.6, 8.4
 // and 8.5 us).  With three planes four waves are the better ones (2^24 elements: 75.6 against 76.5 us), and the form of
 // the reduction makes no difference beyond that of two runs (long and short, 2^20: 6.3 and 6.2, 2^24: 75.5 and 75.4, 2^26:
-// 362 and 366, 2^28: 1444 and 1453 us).
-template <int NC>
-constexpr int SHARE_BLOCK = NC == 5 ? 64 : BLOCK;
+// 362 and 366, 2^28: 1444 and 1453 us).  Five planes that do not start on cache lines go through the caches, which put the
+// parts of a line together (2^24 + 3 elements 185 -> 148 us, 2^22 + 2 40 -> 37 us; three planes 95 and 92, 21 and 25 us: past them),
+// and odd counts, one element per thread, have the schemes fixed too (2^20-odd elements, n = 3: 11 -> 7 us).
+template <int VEC, int NC>
+constexpr int SHARE_BLOCK = VEC == 2 && NC == 5 ? 64 : BLOCK;
 template <int VEC, int NC, int DC>
-__global__ __launch_bounds__(SHARE_BLOCK<NC>) void share_kernel(const u64 *__restrict__ secret, u64 *__restrict__ shares,
+__global__ __launch_bounds__((SHARE_BLOCK<VEC, NC>)) void share_kernel(const u64 *__restrict__ secret, u64 *__restrict__ shares,
                                                       size_t count, int n_rt, int degree_rt, ss_keys keys)
 {
     constexpr int MAXD = DC ? DC : SS_MAXDEG;
     constexpr int MAXP = NC ? NC : SS_MAXN;
     const int n = NC ? NC : n_rt, degree = DC ? DC : degree_rt;
-    const size_t e0 = ((size_t)blockIdx.x * SHARE_BLOCK<NC> + threadIdx.x) * VEC;
+    const size_t e0 = (element_block(count) * SHARE_BLOCK<VEC, NC> + threadIdx.x) * VEC;
     if (e0 >= count) return;
     pack_t<VEC> a0;
     a0.load(secret + e0);
@@ -171,7 +187,10 @@ __global__ __launch_bounds__(SHARE_BLOCK<NC>) void share_kernel(const u64 *__res
 #pragma unroll
         for (int u = 0; u < VEC; u++) eval_points<DC, NC, true>(a0.v[u], c[u], [&](int p, u64 v) { s[p].v[u] = v; });
 #pragma unroll
-        for (int p = 0; p < NC; p++) s[p].store_streaming(shares + (size_t)p * count + e0);   // written, not read again
+        for (int p = 0; p < NC; p++) {   // written, not read again
+            u64 *to = shares + (size_t)p * count + e0;
+            NC == 5 && !starts_lines(count) ? s[p].store(to) : s[p].store_streaming(to);
+        }
     } else {
 #pragma unroll
         for (int i = 1; i <= MAXP; i++) {
@@ -194,7 +213,7 @@ __global__ __launch_bounds__(BLOCK) void reconstruct_kernel(const u64 *__restric
                                                             u64 *__restrict__ secret, size_t count,
                                                             ss_rec_params rp)
 {
-    const size_t e0 = ((size_t)blockIdx.x * BLOCK + threadIdx.x) * VEC;
+    const size_t e0 = (element_block(count) * BLOCK + threadIdx.x) * VEC;
     if (e0 >= count) return;
     pack_t<VEC> out;
     ss_sacc acc[VEC];
@@ -427,7 +446,7 @@ __global__ __launch_bounds__(BLOCK, T == 3 ? 4 : 1) void degree_reduce_kernel(co
                                                               u64 *__restrict__ rec, size_t count, ss_dr_params dp,
                                                               ss_tr_params tp, ss_part_src ps)
 {
-    const size_t e = (size_t)blockIdx.x * BLOCK + threadIdx.x;
+    const size_t e = element_block(count) * BLOCK + threadIdx.x;
     if (e >= count) return;
     u64 o[MAXP<N>], secret;
     reduce_truncate<N, T, TRUNC, STREAM>(e, count, e, count, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
@@ -492,7 +511,7 @@ template <int N, int T, bool STREAM>
 __global__ __launch_bounds__(BLOCK) void truncate_kernel(const u64 *x, u64 *__restrict__ umsg, u64 *__restrict__ wsh,
                                                          u64 *out, size_t count, size_t first, ss_tr_params tp)
 {
-    const size_t e = first + (size_t)blockIdx.x * BLOCK + threadIdx.x;
+    const size_t e = first + element_block(count) * BLOCK + threadIdx.x;
     if (e >= count) return;
     constexpr int K = T + 1;
     const u64 counter = ss_counter(e);
@@ -668,7 +687,7 @@ __global__ __launch_bounds__(BLOCK) void reduce_truncate_direct_kernel(const u64
                                                                        ss_nl_params open_all, ss_tr_params tp,
                                                                        ss_part_src ps)
 {
-    const size_t e = first + (size_t)blockIdx.x * BLOCK + threadIdx.x;   // from element `first` on
+    const size_t e = first + element_block(count) * BLOCK + threadIdx.x;   // from element `first` on
     if (e >= count) return;
     ss_sacc2 acc;
     acc.clear();
@@ -749,7 +768,7 @@ __global__ __launch_bounds__(BLOCK) void relu_kernel(const u64 *x, const u64 *__
                                                      u64 *__restrict__ yplain, u64 *out, size_t count,
                                                      ss_nl_params np)
 {
-    const size_t e0 = ((size_t)blockIdx.x * BLOCK + threadIdx.x) * VEC;
+    const size_t e0 = (element_block(count) * BLOCK + threadIdx.x) * VEC;
     if (e0 >= count) return;
     const int nr = 2 * np.t + 1;
     // all operands are requested up front, so that the three steps wait for memory once
@@ -933,7 +952,10 @@ constexpr size_t LANES_MAX_COUNT = 16 * 1024;
 // Messages are written once and not read by the library again.  Left to the caches they cost nothing while a call's
 // traffic fits the 256 MB of the last level (the next call overwrites them there); beyond, writing them past the
 // caches is faster.  44 planes written per 5 read, no arithmetic, the same call repeated, MI355X: 24.4 / 26.7 us (cached /
-// streamed) at 157 MB, 56.2 / 53.1 us at 315 MB, 324 / 273 us at 1.65 GB.
+// streamed) at 157 MB, 56.2 / 53.1 us at 315 MB, 324 / 273 us at 1.65 GB.  With inputs that change from call to call the line
+// lies there too (at 64, 128, 600 MB stacks and single calls are 0 to 8 % slower).  The reductions' many planes only where they
+// start on cache lines: parts of lines past the caches cost more (reduce + truncate of 1.2 M + 1 elements, n = 5: 130 us
+// streamed, 108 cached; n = 7: 238 and 198 us).
 inline bool streams_messages(size_t words) { return words * sizeof(u64) > ((size_t)256 << 20); }
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -965,7 +987,8 @@ hipError_t ss_launch_share(const u64 *secret, u64 *shares, size_t count, int n, 
     const bool v2 = (count % 2 == 0) && aligned16(secret) && aligned16(shares);
     if (!fits_launch(blocks_for(count, v2 ? 2 : 1))) return hipErrorInvalidConfiguration;
 #define SS_SHARE(VEC, NC, DC)                                                                                       \
-    hipLaunchKernelGGL((share_kernel<VEC, NC, DC>), dim3(blocks_for(count, VEC, SHARE_BLOCK<NC>)), dim3(SHARE_BLOCK<NC>), \
+    hipLaunchKernelGGL((share_kernel<VEC, NC, DC>), dim3(blocks_for(count, VEC, (SHARE_BLOCK<VEC, NC>))), \
+                       dim3((SHARE_BLOCK<VEC, NC>)), \
                        0, stream, secret, shares, count, n, degree, keys)
     if (v2 && n == 5 && degree == 2)
         SS_SHARE(2, 5, 2);
@@ -973,6 +996,10 @@ hipError_t ss_launch_share(const u64 *secret, u64 *shares, size_t count, int n, 
         SS_SHARE(2, 3, 1);
     else if (v2)
         SS_SHARE(2, 0, 0);
+    else if (n == 5 && degree == 2)
+        SS_SHARE(1, 5, 2);
+    else if (n == 3 && degree == 1)
+        SS_SHARE(1, 3, 1);
     else
         SS_SHARE(1, 0, 0);
 #undef SS_SHARE
@@ -1019,7 +1046,7 @@ hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out,
         return hipGetLastError();
     }
     const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
-    const bool streams = streams_messages((nr + n + nr * k + k * n) * count);
+    const bool streams = starts_lines(count) && streams_messages((nr + n + nr * k + k * n) * count);
 #define SS_LAUNCH(NC, TC)                                                                                               \
     hipLaunchKernelGGL((streams ? degree_reduce_kernel<NC, TC, false, true> : degree_reduce_kernel<NC, TC, false, false>), \
                        dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, \
@@ -1035,7 +1062,7 @@ hipError_t ss_launch_degree_reduce_truncate(const u64 *c, u64 *msg1, u64 *msg2, 
 {
     if (!fits_launch(blocks_for(count, 1))) return hipErrorInvalidConfiguration;
     const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
-    const bool streams = streams_messages((nr + n + nr * k + k * n + k + n) * count);
+    const bool streams = starts_lines(count) && streams_messages((nr + n + nr * k + k * n + k + n) * count);
 #define SS_LAUNCH(NC, TC)                                                                                               \
     hipLaunchKernelGGL((streams ? degree_reduce_kernel<NC, TC, true, true> : degree_reduce_kernel<NC, TC, true, false>), \
                        dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, u, wsh, out, rec, count, dp, tp, ps)

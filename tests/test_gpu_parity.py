@@ -821,3 +821,36 @@ def test_reduce_truncate_direct_beyond_one_launch():
         assert out[:, e].tolist() == [(e % m + (p + 1) * slope) % P61 for p in range(n)], e
     del c, out, rec, again
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n,t", [(3, 1), (5, 2), (4, 1), (7, 3)])
+def test_planes_off_the_cache_lines(n, t):
+    """Counts whose planes do not start on cache lines, below, at and past the 512 workgroups whose order changes there (one
+    and two elements per thread; workgroups of one wave and of four), and the reductions' first aligned count past the
+    caches, which off the lines stay in them: every call's result and messages against the oracle."""
+    s = SSNet(n, t, f=13, seed=19)
+    k, nr = t + 1, 2 * t + 1
+    past = LAST_LEVEL_WORDS // (nr + n + nr * k + k * n) + 16 & ~15
+    for count in (131071, 131073, 262146, 2 * 131072 + 2 * 64 * 512 - 2, past, past + 2):
+        say("off the lines", n, t, count)
+        xs = np.random.default_rng(count).integers(-(1 << 31), 1 << 31, count, dtype=np.int64)
+        x = np.where(xs < 0, xs + P61, xs).astype(np.uint64)
+        ids = list(range(n, n - k, -1))
+        sh = s.share(to_dev(x), stream_id=5)
+        want = orc.share(x, n, t, P61, 19, 5)
+        assert np.array_equal(to_np(sh), want)
+        assert np.array_equal(to_np(s.reconstruct(sh, ids)), x)
+        want_t, u, wsh = orc.truncate(want, n, t, 13, P61, 19, 9, full=True)
+        assert np.array_equal(to_np(s.truncate(sh, stream_id=9)), want_t)
+        assert np.array_equal(to_np(s.messages()[: (k + n) * count]), np.concatenate([u.ravel(), wsh.ravel()]))
+        c = orc.share(x, n, 2 * t, P61, 5, 0)
+        red, m1, m2, _ = orc.degree_reduce(c, n, t, P61, 19, 9, full=True)
+        want_t, u, wsh = orc.truncate(red, n, t, 13, P61, 19, 9, full=True)
+        d = to_dev(c)
+        assert np.array_equal(to_np(s.degree_reduce(d, stream_id=9)), red)
+        assert np.array_equal(to_np(s.degree_reduce_truncate(d, stream_id=9)), want_t)
+        got = to_np(s.messages()[: (nr * k + k * n + k + n) * count])
+        assert np.array_equal(got, np.concatenate([a.ravel() for a in (m1, m2, u, wsh)]))
+        assert np.array_equal(to_np(s.reduce_truncate_direct(d, stream_id=9)[0]), want_t)
+        sb, sbi = s.nonlinear_masks((count,), stream_id=4)
+        assert np.array_equal(to_np(s.relu(sh, sb, sbi)), orc.relu(want, to_np(sb), to_np(sbi), n, t, P61))
