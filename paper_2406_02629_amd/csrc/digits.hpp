@@ -18,6 +18,23 @@ __device__ __forceinline__ u32 limb_dword(const u64 (&y)[4], int limb)
     return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, sel), __builtin_amdgcn_perm(b, a, sel), 0x05040100u);
 }
 
+// the values of v in the four lanes r, r + 16, r + 32, r + 48 of the caller's r, which all four call (register swaps: a
+// shuffle by index goes through LDS)
+__device__ __forceinline__ void gather_rows(u64 v, u64 (&y)[4])
+{
+    u32 h[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const u32 x = (u32)(v >> (32 * i));
+        const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);   // rows 0 1 0 1, rows 2 3 2 3
+        const auto lo = __builtin_amdgcn_permlane16_swap(a[0], a[0], false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(a[1], a[1], false, false);
+        h[i][0] = lo[0], h[i][1] = lo[1], h[i][2] = hi[0], h[i][3] = hi[1];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) y[q] = (u64)h[1][q] << 32 | h[0][q];
+}
+
 // Limb dwords of the digit words that the lanes of a 256-thread block hold one per party: lane l of wave w has row (pixel)
 // l%16 and contraction index (channel) 4 w + l/16 of the block -> stage[party][limb][row][w].  The four lanes of a row
 // swap their digit words, after which each of them owns all four and writes two of the limb dwords.
@@ -29,8 +46,7 @@ __device__ __forceinline__ void stage_limbs(const u64 (&dig)[MAXP], u32 (&stage)
     for (int p = 0; p < MAXP; p++) {
         if (p < n) {
             u64 y[4];
-#pragma unroll
-            for (int q = 0; q < 4; q++) y[q] = __shfl(dig[p], r16 + 16 * q);
+            gather_rows(dig[p], y);
             if (2 * j < SS_NLIMB) {
                 stage[p][2 * j][r16][w] = limb_dword(y, 2 * j);
                 stage[p][2 * j + 1][r16][w] = limb_dword(y, 2 * j + 1);

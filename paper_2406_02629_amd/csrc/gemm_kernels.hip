@@ -32,70 +32,89 @@ namespace {
 // 16 bytes = TILE 16-byte words
 constexpr int NL = SS_NLIMB, ND = 2 * NL - 1, TILE = NL * 64;
 
-// Digit words of four consecutive contraction indices -> one dword per limb
-// (byte c of dword `limb` is digit `limb` of y[c]) and store them: the thread
-// owns bytes [4*(kq%4), +4) of lane (row + 16*(kq/4)) in each of the eight limb
-// slices of its tile.
-__device__ __forceinline__ void store_digits(const u64 (&y)[4], v4i *tile, int row, int kq)
+// Lane (r, j) = r + 16 j of a wave holds the digit words y of the contraction indices (or channels) 4 j .. 4 j + 3 of row r,
+// that is one dword per limb.  Transposed over j by register swaps, it holds the 16 bytes of limb j and those of limb
+// 4 + j of its row, so that a wave stores 256 contiguous bytes per limb, 16 per lane, in two stores.  (As dwords, 8 stores,
+// each quarter of a wave met two cache lines in parts and the four quarters the same two: the stores bound the kernels.
+// Limb planes of 8 images of 64 x 56 x 56 with their sharing, n = 3: 21.9 -> 15.1 us; limb tiles of 4 shares of 500 x 1201 and
+// 1201 x 333: 23.3 -> 14.9 us; of a 7 x 7 stem at 224 x 224, n = 5: 37.7 -> 26.3 us.)  store(limb, 16 bytes); the four
+// lanes of a row call together.
+template <typename F>
+__device__ __forceinline__ void store_limbs(const u64 (&y)[4], int j, F &&store)
 {
-    u32 *base = reinterpret_cast<u32 *>(tile) + (row + 16 * (kq >> 2)) * 4 + (kq & 3);
+    u32 w[8];
 #pragma unroll
-    for (int limb = 0; limb < NL; limb++) {
-        const int i = limb & 3;
-        const u32 a = limb < 4 ? (u32)y[0] : (u32)(y[0] >> 32), b = limb < 4 ? (u32)y[1] : (u32)(y[1] >> 32);
-        const u32 c = limb < 4 ? (u32)y[2] : (u32)(y[2] >> 32), d = limb < 4 ? (u32)y[3] : (u32)(y[3] >> 32);
-        // v_perm_b32: selector byte k picks byte k of {second operand (0..3), first operand (4..7)}; 0x0c = zero
-        const u32 sel = (u32)i | ((u32)(4 + i) << 8) | 0x0c0c0000u;
-        const u32 ab = __builtin_amdgcn_perm(b, a, sel), cd = __builtin_amdgcn_perm(d, c, sel);
-        base[limb * 256] = __builtin_amdgcn_perm(cd, ab, 0x05040100u);
+    for (int limb = 0; limb < 8; limb++) w[limb] = limb < NL ? limb_dword(y, limb) : 0;
+#pragma unroll
+    for (int h = 0; h < 8; h += 4) {
+        const auto a = __builtin_amdgcn_permlane32_swap(w[h], w[h + 2], false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap(w[h + 1], w[h + 3], false, false);
+        const auto lo = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+        if (h + j < NL) store(h + j, (v4i){(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]});
     }
 }
 
-// One workgroup per (row block, k block) tile, one thread per (row, 4 contraction indices).
-// grid (Rb, Kb, n), block 256: thread t -> row t%16, k group t/16.
+// One workgroup per (row block, k block) tile, one thread per (row, 4 contraction indices): thread t -> row t%16, k group
+// t/16.  grid (Rb * Kb, n), block 256; the index along which the source is contiguous runs fastest over the workgroups
+// (k_first), an XCD's workgroups are neighbours, and elements outside the matrix are loaded from its first one, so that a
+// thread's four loads are in flight together (a load per branch waits for each).
 // taps > 0: the contraction index of the packed operand runs (tap, channel) while the source runs (channel,
 // tap) with `taps` taps per channel (convolution weights for the kernel that reads its other operand from
 // limb planes); stride_k is then the stride of the source's own index.
 __global__ __launch_bounds__(256) void pack_matrix_kernel(const u64 *__restrict__ src, v4i *__restrict__ dst,
-                                                          int rows, int K, int Kb, size_t party_stride,
-                                                          size_t stride_r, size_t stride_k, size_t dst_party_stride,
-                                                          int taps)
+                                                          int rows, int K, int Rb, int Kb, fdiv dRb, fdiv dKb, bool k_first,
+                                                          size_t party_stride, size_t stride_r, size_t stride_k,
+                                                          size_t dst_party_stride, int taps)
 {
-    const int rb = blockIdx.x, kb = blockIdx.y, r16 = threadIdx.x & 15, kq = threadIdx.x >> 4;
-    const int row = rb * 16 + r16, k0 = kb * 64 + 4 * kq;
-    const u64 *s = src + (size_t)blockIdx.z * party_stride + (size_t)row * stride_r;
+    const int b = (int)xcd_slot(blockIdx.x, gridDim.x), q = (int)fd_div((u32)b, k_first ? dKb : dRb);
+    const int rb = k_first ? q : b - q * Rb, kb = k_first ? b - q * Kb : q;
+    const int r16 = threadIdx.x & 15, kq = threadIdx.x >> 4, row = rb * 16 + r16, k0 = kb * 64 + 4 * kq;
+    const u64 *s = src + (size_t)blockIdx.y * party_stride + (row < rows ? (size_t)row * stride_r : 0);
     const int C = taps ? K / taps : 1;
     u64 y[4];
 #pragma unroll
     for (int c = 0; c < 4; c++) {
-        const int k = k0 + c, ks = taps ? (k % C) * taps + k / C : k;
-        y[c] = (row < rows && k < K) ? balanced_digits(s[(size_t)ks * stride_k]) : 0;
+        const int k = k0 + c, ks = k >= K ? 0 : taps ? (k % C) * taps + k / C : k;
+        y[c] = s[(size_t)ks * stride_k];
     }
-    store_digits(y, dst + (size_t)blockIdx.z * dst_party_stride + ((size_t)rb * Kb + kb) * TILE, r16, kq);
+#pragma unroll
+    for (int c = 0; c < 4; c++) y[c] = row < rows && k0 + c < K ? balanced_digits(y[c]) : 0;
+    v4i *tile = dst + (size_t)blockIdx.y * dst_party_stride + ((size_t)rb * Kb + kb) * TILE + r16 + 16 * (kq >> 2);
+    store_limbs(y, kq & 3, [&](int limb, v4i v) { tile[limb * 64] = v; });
 }
 
-// rows = (b, ho, wo), k = (c, r, s) gathered from x [n][B][C][H][W]; zero padding
-__global__ __launch_bounds__(256) void pack_im2col_kernel(const u64 *__restrict__ x, v4i *__restrict__ dst, int B,
-                                                          int C, int H, int W, int kh, int kw, int stride, int pad,
-                                                          int Ho, int Wo, int Kb, size_t dst_party_stride)
+// rows = (b, ho, wo), k = (c, r, s) gathered from x [n][B][C][H][W]; zero padding.  An element is gathered once per tap, so
+// the index arithmetic is kept short: divisions by constants of the launch, and a thread's four loads unconditional (taps in the
+// padding and indices past the matrix load the tensor's first element).
+struct im2col_args {
+    int H, W, kh, kw, stride, pad, M, K, Kb;
+    fdiv dTaps, dKw, dWo, dHoWo;
+    int HoWo, Wo;
+    size_t image, party;     // elements
+};
+__global__ __launch_bounds__(256) void pack_im2col_kernel(const u64 *__restrict__ x, v4i *__restrict__ dst, im2col_args g,
+                                                          size_t dst_party_stride)
 {
     const int rb = blockIdx.x, kb = blockIdx.y, r16 = threadIdx.x & 15, kq = threadIdx.x >> 4;
-    const int M = B * Ho * Wo, K = C * kh * kw;
-    const int row = rb * 16 + r16, k0 = kb * 64 + 4 * kq;
-    const u64 *xi = x + (size_t)blockIdx.z * B * C * H * W;
-    u64 y[4] = {0, 0, 0, 0};
-    if (row < M) {
-        const int wo = row % Wo, ho = (row / Wo) % Ho, b = row / (Wo * Ho);
-        int c = k0 / (kh * kw), rs = k0 % (kh * kw), r = rs / kw, s = rs % kw;
+    const int row = rb * 16 + r16, k0 = kb * 64 + 4 * kq, taps = g.kh * g.kw;
+    const int b = (int)fd_div((u32)row, g.dHoWo), hw = row - b * g.HoWo, ho = (int)fd_div((u32)hw, g.dWo), wo = hw - ho * g.Wo;
+    int c = (int)fd_div((u32)k0, g.dTaps), rs = k0 - c * taps, r = (int)fd_div((u32)rs, g.dKw), s = rs - r * g.kw;
+    const int h0 = ho * g.stride - g.pad, w0 = wo * g.stride - g.pad;
+    const u64 *xi = x + blockIdx.z * g.party;
+    u64 y[4];
+    bool in[4];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const int hi = ho * stride - pad + r, wi = wo * stride - pad + s;
-            if (k0 + q < K && hi >= 0 && hi < H && wi >= 0 && wi < W)
-                y[q] = balanced_digits(xi[(((size_t)b * C + c) * H + hi) * W + wi]);
-            if (++s == kw) { s = 0; if (++r == kh) { r = 0; ++c; } }
-        }
+    for (int q = 0; q < 4; q++) {
+        const int hi = h0 + r, wi = w0 + s;
+        in[q] = row < g.M && k0 + q < g.K && (unsigned)hi < (unsigned)g.H && (unsigned)wi < (unsigned)g.W;
+        y[q] = xi[in[q] ? b * g.image + ((size_t)c * g.H + hi) * g.W + wi : 0];
+        if (++s == g.kw) { s = 0; if (++r == g.kh) { r = 0; ++c; } }
     }
-    store_digits(y, dst + (size_t)blockIdx.z * dst_party_stride + ((size_t)rb * Kb + kb) * TILE, r16, kq);
+#pragma unroll
+    for (int q = 0; q < 4; q++) y[q] = in[q] ? balanced_digits(y[q]) : 0;
+    v4i *tile = dst + (size_t)blockIdx.z * dst_party_stride + ((size_t)rb * g.Kb + kb) * TILE + r16 + 16 * (kq >> 2);
+    store_limbs(y, kq & 3, [&](int limb, v4i v) { tile[limb * 64] = v; });
 }
 
 // The two kernels below take one element per thread: lane l of a wave holds row (or pixel) l%16 and the
@@ -247,9 +266,8 @@ __global__ __launch_bounds__(256) void planes4_kernel(const u64 *__restrict__ in
 #pragma unroll
     for (int p = 0; p < MAXP; p++) {
         if (p < n) {
-            u32 *dst = reinterpret_cast<u32 *>(planes + p * party_bytes + ((size_t)(c0 >> 4) * (B * HW) + pix) * 16 + (c0 & 15));
-#pragma unroll
-            for (int limb = 0; limb < NL; limb++) dst[limb * (plane / 4)] = limb_dword(y[p], limb);
+            v4i *dst = reinterpret_cast<v4i *>(planes + p * party_bytes) + (size_t)(c0 >> 4) * (B * HW) + pix;
+            store_limbs(y[p], (c0 >> 2) & 3, [&](int limb, v4i v) { dst[limb * (plane / 16)] = v; });
         }
     }
 }
@@ -1078,8 +1096,9 @@ hipError_t ss_launch_pack_matrix(const u64 *src, void *dst, int n, int rows, int
                                  size_t stride_r, size_t stride_k, int taps, hipStream_t stream)
 {
     const int Rb = (rows + 15) / 16, Kb = (K + 63) / 64;
-    hipLaunchKernelGGL(pack_matrix_kernel, dim3(Rb, Kb, n), dim3(256), 0, stream, src, (v4i *)dst, rows, K, Kb,
-                       party_stride, stride_r, stride_k, ss_packed_bytes(rows, K) / 16, taps);
+    hipLaunchKernelGGL(pack_matrix_kernel, dim3((unsigned)Rb * (unsigned)Kb, n), dim3(256), 0, stream, src, (v4i *)dst, rows, K, Rb,
+                       Kb, make_fdiv((u32)Rb), make_fdiv((u32)Kb), stride_k == 1, party_stride, stride_r, stride_k,
+                       ss_packed_bytes(rows, K) / 16, taps);
     return hipGetLastError();
 }
 
@@ -1135,8 +1154,12 @@ hipError_t ss_launch_pack_im2col(const u64 *x, void *dst, int n, int B, int C, i
 {
     const int M = B * Ho * Wo, K = C * kh * kw;
     const int Rb = (M + 15) / 16, Kb = (K + 63) / 64;
-    hipLaunchKernelGGL(pack_im2col_kernel, dim3(Rb, Kb, n), dim3(256), 0, stream, x, (v4i *)dst, B, C, H, W, kh, kw,
-                       stride, pad, Ho, Wo, Kb, ss_packed_bytes(M, K) / 16);
+    im2col_args g;
+    g.H = H, g.W = W, g.kh = kh, g.kw = kw, g.stride = stride, g.pad = pad, g.M = M, g.K = K, g.Kb = Kb;
+    g.dTaps = make_fdiv((u32)(kh * kw)), g.dKw = make_fdiv((u32)kw), g.dWo = make_fdiv((u32)Wo), g.dHoWo = make_fdiv((u32)(Ho * Wo));
+    g.HoWo = Ho * Wo, g.Wo = Wo;
+    g.image = (size_t)C * H * W, g.party = B * g.image;
+    hipLaunchKernelGGL(pack_im2col_kernel, dim3(Rb, Kb, n), dim3(256), 0, stream, x, (v4i *)dst, g, ss_packed_bytes(M, K) / 16);
     return hipGetLastError();
 }
 

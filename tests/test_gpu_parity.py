@@ -854,3 +854,49 @@ def test_planes_off_the_cache_lines(n, t):
         assert np.array_equal(to_np(s.reduce_truncate_direct(d, stream_id=9)[0]), want_t)
         sb, sbi = s.nonlinear_masks((count,), stream_id=4)
         assert np.array_equal(to_np(s.relu(sh, sb, sbi)), orc.relu(want, to_np(sb), to_np(sbi), n, t, P61))
+
+
+def digit_bytes(v, limbs):
+    """[..., limbs] balanced base-256 digits of field elements, as bytes"""
+    half = np.uint64(0x8080808080808080)
+    d = (np.ascontiguousarray(v, dtype=np.uint64) + half) ^ half
+    return d.view(np.uint8).reshape(*v.shape, 8)[..., :limbs]
+
+
+def limb_tiles(m, limbs):
+    """operand [n][rows][K] -> tiles [n][row block][k block][limb][k / 16 % 4][row % 16][k % 16], zero-padded"""
+    n, rows, K = m.shape
+    R, C = -(-rows // 16) * 16, -(-K // 64) * 64
+    d = np.zeros((n, R, C, limbs), np.uint8)
+    d[:, :rows, :K] = digit_bytes(m, limbs)
+    return d.reshape(n, R // 16, 16, C // 64, 4, 16, limbs).transpose(0, 1, 3, 6, 4, 2, 5).reshape(-1)
+
+
+@pytest.mark.parametrize("p", [P61, binding.P45])
+@pytest.mark.parametrize("n,t", [(3, 1), (5, 2)])
+def test_limb_tiles_and_planes_byte_for_byte(n, t, p):
+    """The packing kernels at the edges of their tiles, against the layout: both orders of a matrix, weights in tap order,
+    tiles and planes made together with shares, planes with one and with four channels per thread and a ragged last block."""
+    s = SSNet(n, t, f=12, seed=3, p=p)
+    limbs = 8 if p == P61 else 6
+    elements = lambda shape, seed: field_uniform(shape, seed) % np.uint64(p)
+    for K, N in ((1, 1), (63, 16), (64, 17), (65, 15), (200, 333)):
+        say("tiles", n, p, K, N)
+        w = elements((n, K, N), K + N)
+        assert np.array_equal(s.pack_weights_linear(to_dev(w)).cpu().numpy(), limb_tiles(w.transpose(0, 2, 1), limbs))
+        x = elements((N, K), K)
+        shares, packed = s.share_packed(to_dev(x), stream_id=2)
+        assert np.array_equal(packed.cpu().numpy()[: n * -(-N // 16) * -(-K // 64) * 1024 * limbs], limb_tiles(to_np(shares), limbs))
+    for Co, C, k in ((17, 64, 3), (5, 128, 2)):
+        w = elements((n, Co, C, k, k), Co)
+        taps = w.reshape(n, Co, C, k * k).transpose(0, 1, 3, 2).reshape(n, Co, -1)
+        assert np.array_equal(s.pack_weights_conv_taps(to_dev(w)).cpu().numpy(), limb_tiles(taps, limbs))
+        assert np.array_equal(s.pack_weights_conv(to_dev(w)).cpu().numpy(), limb_tiles(w.reshape(n, Co, -1), limbs))
+    for B, C, H in ((1, 64, 1), (2, 128, 7), (1, 64, 91), (3, 192, 31)):
+        say("planes", n, p, B, C, H)
+        x = elements((B, C, H, H), H)
+        shares, planes = s.share_planes(to_dev(x), stream_id=2)
+        want = digit_bytes(to_np(shares).reshape(n, B, C // 16, 16, H * H), limbs).transpose(0, 5, 2, 1, 4, 3).reshape(n, -1)
+        for got in (planes, s.split_planes(shares)):
+            got = got.view(n, -1).cpu().numpy()[:, : want.shape[1] + 16]
+            assert np.array_equal(got[:, :-16], want) and not got[:, -16:].any()
