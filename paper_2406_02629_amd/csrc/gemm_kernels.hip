@@ -780,8 +780,11 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void gemm_ksplit_kernel(gem
 // column blocks per unit, twice the column blocks of the square tile in the same LDS, and no MFMA is spent on
 // row blocks that do not exist.  Wave w copies column block w and limb slice w of the row block, and owns
 // the 16 x 16 outputs of column block w.  Units, ranges, planes and fold are those of the kernel above.
+// (Four units of half the width in the same LDS, three on their way: 0.81 to 0.98 of the rate, n = 5.)
+// STREAM: the second operand is read past the caches, see streams_operand.
 constexpr int SKINNY_COLS = 128;
 
+template <bool STREAM>
 __global__ __launch_bounds__(512) void gemm_skinny_kernel(gemm_args g)
 {
     extern __shared__ v4i lds[];   // 2 stages x (1 row block + 8 column blocks) x TILE
@@ -814,7 +817,7 @@ __global__ __launch_bounds__(512) void gemm_skinny_kernel(gemm_args g)
         v4i *dst = lds + stage * STAGE;
 #pragma unroll
         for (int q = 0; q < NL; q++)
-            __builtin_amdgcn_global_load_lds(bs + (size_t)k * TILE + q * 64, dst + (1 + wave) * TILE + q * 64, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(bs + (size_t)k * TILE + q * 64, dst + (1 + wave) * TILE + q * 64, 16, 0, STREAM ? 2 : 0);   // 2: nt
         if (wave < NL) __builtin_amdgcn_global_load_lds(as + (size_t)k * TILE, dst + wave * 64, 16, 0, 0);
     };
 
@@ -961,6 +964,12 @@ bool ksplit_is_faster(const gemm_plan &k, bool skinny, double busy, unsigned lon
     if (NL == 8) return busy * 5.87 < (double)big + 12.7 && (k.Kb > 1 || k.tiles <= 2560);
     return busy * 6.2 < (double)big + 62 && (k.Kb > 1 || k.tiles <= 10240);
 }
+
+// A second operand that gemm_skinny_kernel reads once and that the 256 MB of the last level cannot hold is read past it; one that
+// they hold may be there from its last use.  The same call repeated, n = 5 / n = 3 / n = 3 over the 45-bit prime, us, through the
+// caches -> past them (rows x columns x contraction): 2 x 12000 x 800 72.6 -> 63.9 (384 MB) / 36.2 -> 39.1 (230 MB) / 27.4 -> 29.9;
+// 4 x 4096 x 4096 121 -> 116 / 72.6 -> 65.7 (402 MB) / 49.0 -> 48.8 (302 MB); 5 x 1200 x 4800 37.9 -> 39.7 (230 MB) / - / -.
+bool streams_operand(size_t bytes) { return bytes > ((size_t)256 << 20); }
 
 // How the units are dealt: one workgroup per CU unless there is too little work for that; slots = the most
 // workgroups that can share one tile.
@@ -1183,7 +1192,10 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
             e = hipFuncSetAttribute((const void *)gemm_limb_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     LDS_BYTES);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)gemm_skinny_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+            e = hipFuncSetAttribute((const void *)gemm_skinny_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    LDS_BYTES_SKINNY);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute((const void *)gemm_skinny_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     LDS_BYTES_SKINNY);
         if (e != hipSuccess) return e;
         lds_opt_in = true;
@@ -1255,7 +1267,8 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
     switch (p.ksplit) {
         case 0:
             if (p.skinny)
-                SS_LAUNCH_PRODUCT(gemm_skinny_kernel, 512, LDS_BYTES_SKINNY, g);
+                SS_LAUNCH_PRODUCT((streams_operand(n * ss_packed_bytes(cols, K)) ? gemm_skinny_kernel<true> : gemm_skinny_kernel<false>),
+                                  512, LDS_BYTES_SKINNY, g);
             else
                 SS_LAUNCH_PRODUCT((cv ? gemm_limb_kernel<true> : gemm_limb_kernel<false>), 512, LDS_BYTES, g);
             break;

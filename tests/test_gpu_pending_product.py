@@ -247,3 +247,19 @@ def test_small_and_narrow_products(n, t, p):
         geom = (B, C, H, W, Co, k, k, stride, pad)
         assert np.array_equal(to_np(s.conv_mod_planes(planes, wp, *geom)), y)
         check_consumers(s, p, y, (B, Co) + y.shape[-2:], lambda: s.conv_product_planes(planes, wp, *geom), seed=95)
+
+
+@pytest.mark.parametrize("p,N", [(binding.P61, 5472), (binding.P45, 7296)])
+def test_second_operand_past_the_last_level(p, N):
+    """16-row products on both sides of the 256 MB from which the second operand is read past the caches"""
+    n, K, s = 3, 2048, SSNet(3, 1, f=12, seed=2, p=p)
+    per = n * s.lib.ssnet_packed_weight_bytes(16, K)
+    assert per * (N // 16 - 1) <= 256 << 20 < per * (N // 16)
+    w = field_uniform((n, K, N), 1) % np.uint64(p)
+    x = field_uniform((n, 3, K), 2) % np.uint64(p)
+    want = orc.linear(x, w, p)
+    for cols in (N - 16, N):
+        say("last level", p, cols)
+        wc = np.ascontiguousarray(w[:, :, :cols])
+        got = s.linear_mod_packed(to_dev(x), s.pack_weights_linear(to_dev(wc)), cols)
+        assert np.array_equal(to_np(got), want[:, :, :cols])
