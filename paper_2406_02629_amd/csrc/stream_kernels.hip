@@ -14,18 +14,22 @@ namespace SS_NS {
 namespace {
 
 constexpr int BLOCK = 256;
+constexpr size_t LAUNCH_ELEMENTS = (size_t)1 << 31;   // of a tensor that goes in several launches, one thread each
 
 // Block of elements that a workgroup of an element-wise kernel takes.  Where the planes of a tensor do not start on a cache
 // line (starts_lines) the blocks share lines, and workgroups are dealt round-robin to the 8 XCDs, so that neighbours write
 // their parts of a line from two L2s.  There 64 consecutive blocks go to one XCD (8 are as good for most, all of a plane's
 // eighth is worse for the larger tensors): n = 7, t = 3 reduce + truncate of 300001 elements on changing inputs 53 -> 48 us,
-// sharing among three of 2^24 + 3 118 -> 95 us, reconstruction from two 88 -> 78 us.
+// sharing among three of 2^24 + 3 118 -> 95 us, reconstruction from two 88 -> 78 us.  PER elements of a launch's `count` per
+// workgroup; planes of `plane` elements.  (The grid is worked out from the count, which arrives in registers: read from the launch it
+// puts a memory access in front of a small kernel's first load.)
 __host__ __device__ __forceinline__ bool starts_lines(size_t count) { return count % 16 == 0; }
-__device__ __forceinline__ size_t element_block(size_t count)
+template <int PER>
+__device__ __forceinline__ size_t element_block(size_t count, size_t plane)
 {
     constexpr unsigned RUN = 64;
     const unsigned b = blockIdx.x, base = b / (8 * RUN) * (8 * RUN);
-    if (starts_lines(count) || base + 8 * RUN > gridDim.x) return b;
+    if (starts_lines(plane) || (size_t)(base + 8 * RUN) * PER >= count + PER) return b;   // past the last whole 8 * RUN workgroups
     return base + (b % 8) * RUN + (b - base) / 8;
 }
 
@@ -174,7 +178,7 @@ __global__ __launch_bounds__((SHARE_BLOCK<VEC, NC>)) void share_kernel(const u64
     constexpr int MAXD = DC ? DC : SS_MAXDEG;
     constexpr int MAXP = NC ? NC : SS_MAXN;
     const int n = NC ? NC : n_rt, degree = DC ? DC : degree_rt;
-    const size_t e0 = (element_block(count) * SHARE_BLOCK<VEC, NC> + threadIdx.x) * VEC;
+    const size_t e0 = (element_block<SHARE_BLOCK<VEC, NC> * VEC>(count, count) * SHARE_BLOCK<VEC, NC> + threadIdx.x) * VEC;
     if (e0 >= count) return;
     pack_t<VEC> a0;
     a0.load(secret + e0);
@@ -213,7 +217,7 @@ __global__ __launch_bounds__(BLOCK) void reconstruct_kernel(const u64 *__restric
                                                             u64 *__restrict__ secret, size_t count,
                                                             ss_rec_params rp)
 {
-    const size_t e0 = (element_block(count) * BLOCK + threadIdx.x) * VEC;
+    const size_t e0 = (element_block<BLOCK * VEC>(count, count) * BLOCK + threadIdx.x) * VEC;
     if (e0 >= count) return;
     pack_t<VEC> out;
     ss_sacc acc[VEC];
@@ -370,7 +374,10 @@ __device__ __forceinline__ void reduce_truncate(size_t e, size_t count, size_t e
     u64 cin[NR];
 #pragma unroll
     for (int i = 0; i < NR; i++) cin[i] = c[(size_t)i * count + e];
-    if (ps.planes > 1) add_planes<NR>(cin, c, count, e, ps);
+    // (t = 3 has no registers to spare: with the sum of planes out of its straight path the compiler spills elsewhere, n = 7 reduce +
+    // truncate of 4629 elements 9.0 -> 8.6 us, over the 45-bit prime 10.2 -> 9.3)
+    const bool several = ps.planes > 1;
+    if (T == 3 ? __builtin_expect(several, 0) : several) add_planes<NR>(cin, c, count, e, ps);
 
     // step 1, and of step 2 the sums coef[q][j] = sum_i msg1[i][q] * D binv[i][j] (j = 0: without D, see ilambda0)
     ss_sacc2 coef[K][K];
@@ -446,7 +453,7 @@ __global__ __launch_bounds__(BLOCK, T == 3 ? 4 : 1) void degree_reduce_kernel(co
                                                               u64 *__restrict__ rec, size_t count, ss_dr_params dp,
                                                               ss_tr_params tp, ss_part_src ps)
 {
-    const size_t e = element_block(count) * BLOCK + threadIdx.x;
+    const size_t e = element_block<BLOCK>(count, count) * BLOCK + threadIdx.x;
     if (e >= count) return;
     u64 o[MAXP<N>], secret;
     reduce_truncate<N, T, TRUNC, STREAM>(e, count, e, count, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
@@ -511,7 +518,7 @@ template <int N, int T, bool STREAM>
 __global__ __launch_bounds__(BLOCK) void truncate_kernel(const u64 *x, u64 *__restrict__ umsg, u64 *__restrict__ wsh,
                                                          u64 *out, size_t count, size_t first, ss_tr_params tp)
 {
-    const size_t e = first + element_block(count) * BLOCK + threadIdx.x;
+    const size_t e = first + element_block<BLOCK>(min(count - first, LAUNCH_ELEMENTS), count) * BLOCK + threadIdx.x;
     if (e >= count) return;
     constexpr int K = T + 1;
     const u64 counter = ss_counter(e);
@@ -687,7 +694,7 @@ __global__ __launch_bounds__(BLOCK) void reduce_truncate_direct_kernel(const u64
                                                                        ss_nl_params open_all, ss_tr_params tp,
                                                                        ss_part_src ps)
 {
-    const size_t e = first + element_block(count) * BLOCK + threadIdx.x;   // from element `first` on
+    const size_t e = first + element_block<BLOCK>(min(count - first, LAUNCH_ELEMENTS), count) * BLOCK + threadIdx.x;   // from element `first` on
     if (e >= count) return;
     ss_sacc2 acc;
     acc.clear();
@@ -768,7 +775,7 @@ __global__ __launch_bounds__(BLOCK) void relu_kernel(const u64 *x, const u64 *__
                                                      u64 *__restrict__ yplain, u64 *out, size_t count,
                                                      ss_nl_params np)
 {
-    const size_t e0 = (element_block(count) * BLOCK + threadIdx.x) * VEC;
+    const size_t e0 = (element_block<BLOCK * VEC>(count, count) * BLOCK + threadIdx.x) * VEC;
     if (e0 >= count) return;
     const int nr = 2 * np.t + 1;
     // all operands are requested up front, so that the three steps wait for memory once
@@ -969,7 +976,6 @@ inline unsigned blocks_for(size_t count, int vec, int block = BLOCK)
 // A launch holds less than 2^32 threads in each direction.  The runtime takes a larger grid without an error and runs a
 // part of it, so that no launcher may reach it: a tensor goes in several launches or is refused.
 inline bool fits_launch(size_t blocks, int block = BLOCK) { return blocks * block < ((size_t)1 << 32); }
-constexpr size_t LAUNCH_ELEMENTS = (size_t)1 << 31;   // of a tensor that goes in several launches, one thread each
 template <typename F>
 inline void for_each_launch(size_t count, F &&launch)
 {
