@@ -1008,8 +1008,13 @@ gemm_plan plan_gemm(int n, int rows, int cols, int K, bool allow_skinny)
         // tile and so two planes, as without.  (A workgroup whose whole tiles are ragged ones idles a little: rows of
         // tiles are long where there are that many.)
         if (!p.skinny && p.Kb > 1 && p.tiles >= 2 * SS_GEMM_CUS) {
-            p.whole = (unsigned)(p.tiles / SS_GEMM_CUS - 1) * SS_GEMM_CUS;
-            p.cost0 = (unsigned)(p.whole / p.CT * rowcost + p.whole % p.CT * p.tcost);
+            // (Where ragged tiles leave the ranges shorter than a full tile, one round less: two planes are what the workspace
+            // of such a product has held all along.)
+            p.whole = (unsigned)(p.tiles / SS_GEMM_CUS) * SS_GEMM_CUS;
+            do {
+                p.whole -= SS_GEMM_CUS;
+                p.cost0 = (unsigned)(p.whole / p.CT * rowcost + p.whole % p.CT * p.tcost);
+            } while (p.whole && (p.cost - p.cost0) / p.G < p.tcost);
         }
         // a tile of cost <= tcost meets at most this many ranges of length >= share; ranges are cut between
         // units, so a tile of Kb units has at most Kb parts

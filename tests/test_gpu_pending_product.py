@@ -263,3 +263,20 @@ def test_second_operand_past_the_last_level(p, N):
         wc = np.ascontiguousarray(w[:, :, :cols])
         got = s.linear_mod_packed(to_dev(x), s.pack_weights_linear(to_dev(wc)), cols)
         assert np.array_equal(to_np(got), want[:, :, :cols])
+
+
+def test_whole_tiles_stop_earlier_where_ragged_ones_shorten_the_ranges():
+    """1041 ragged tiles of one column: with 768 of them whole the ranges behind would be shorter than a full tile.  Workspace of
+    two planes, the product as a tensor and through a reduction."""
+    n, M, K, N = 3, 347 * 64 - 5, 128, 48
+    s = SSNet(n, 1, f=12, seed=3)
+    assert s.lib.ssnet_product_bytes_linear(s._ctx, M, K, N) <= 2 * 8 * n * M * N + 256
+    x, w = field_uniform((n, M, K), 1), field_uniform((n, K, N), 2)
+    y = orc.linear(x, w, binding.P61)
+    d, wp = to_dev(x), s.pack_weights_linear(to_dev(w))
+    assert np.array_equal(to_np(s.linear_mod_packed(d, wp, N)), y)
+    tiles = s.pack_weights_linear(to_dev(np.ascontiguousarray(x.transpose(0, 2, 1))))   # the same tiles, rows as columns
+    out = torch.empty((n, M, N), dtype=torch.int64, device="cuda")
+    s.linear_product_prepacked(tiles, wp, M, K, N)
+    s.degree_reduce(None, stream_id=3, out=out)
+    assert np.array_equal(to_np(out), to_np(s.degree_reduce(to_dev(y), stream_id=3)))
