@@ -1,0 +1,175 @@
+// How a product is given to the kernels of gemm_kernels.hip and cut into work for their workgroups.  Plain C++, so that the
+// rules can be checked without a GPU.  SS_NLIMB: limbs of a field element (8, or 6 over the 45-bit prime).
+#pragma once
+#include <stddef.h>
+
+namespace SS_NS {
+
+#define SS_GEMM_CUS 256
+
+// cost of a unit (64 x 64 outputs, one k block) and of a tile's fold and stores
+constexpr unsigned SS_UNIT_COST = 18;
+constexpr unsigned SS_FOLD_COST = 16;
+
+// A launch holds less than 2^32 threads: the runtime takes a larger grid without an error and runs a part of it.
+constexpr bool fits_grid(long workgroups, int threads) { return workgroups * threads < (1L << 32); }
+
+constexpr int SKINNY_COLS = 128;   // columns of a tile of gemm_skinny_kernel
+
+struct gemm_plan {
+    bool skinny;               // first operand of at most 16 rows: tiles of 16 x 128 (gemm_skinny_kernel)
+    int ksplit;                // waves that share a tile of 16 x 16 in gemm_ksplit_kernel; 0: gemm_limb_kernel
+    long tiles, units;         // units == 0: whole tiles only
+    int Kb, G, slots, RT, CT;   // G: workgroups, 0 if the launch would be too large
+    int threads;               // of a workgroup
+    unsigned whole;            // tiles dealt whole, ahead of the ranges
+    unsigned wlast, tcost, tlast, cost, cost0;
+};
+
+// Relative duration of a unit in which `vb` of the four column blocks exist: a fixed part (copy, barrier,
+// LDS reads) plus one part per column block.  Measured on MI355X: 3.1 us for a full unit, 1.55 us with one
+// column block.
+inline unsigned unit_cost(int vb)
+{
+    static const unsigned w[5] = {0, 9, 12, 15, SS_UNIT_COST};
+    return w[vb];
+}
+
+// A further plane of the output is written here and read by whoever takes the product: bytes that take as long as a cost
+// of one (0.15 us at 5 TB/s, what many streams at a time reach).
+constexpr unsigned long long SS_BYTES_PER_COST = 750 * 1000;
+
+// Plan for gemm_ksplit_kernel and what it takes, in units (16 x 16, one k block, four side by side on a CU): a CU's waves get
+// their operand blocks out of the caches at about 30 bytes per clock, so a launch lasts as long as the fullest CU has units.
+inline gemm_plan plan_ksplit(int n, int rows, int cols, int Kb, double *busy)
+{
+    gemm_plan best = {};
+    const long Rb = (rows + 15) / 16, Cb = (cols + 15) / 16, blocks = n * Rb * Cb;
+    best.Kb = Kb;
+    best.RT = (int)(Rb < Cb ? Cb : Rb);
+    best.CT = (int)(Rb < Cb ? Rb : Cb);
+    best.tiles = best.units = blocks;
+    if (blocks >= (1L << 28)) return best;   // (refused by the caller: busy stays)
+    for (int ks = 1; ks <= 8 && (ks == 1 || ks <= Kb); ks *= 2) {
+        const int cw = ks == 8 ? 1 : 4 / ks, fours = ks == 8 ? 2 : 1;   // tiles, and groups of four waves, of a workgroup
+        const long groups = (blocks + cw - 1) / cw;
+        int parts = 1;
+        // CUs left over: k blocks in parts, as long as every wave keeps two units
+        while (ks == 8 && (parts + 1) * groups <= SS_GEMM_CUS && Kb >= 16 * (parts + 1)) parts++;
+        const long wgs = groups * parts, units = (Kb + ks * parts - 1) / (ks * parts);
+        const int threads = ks == 8 ? 512 : 256;
+        // (a convolution of a few channels with a wide padding has that many tiles of 16 x 16 in a few gigabytes)
+        if (!fits_grid(wgs, threads)) continue;
+        // workgroups of four that the fullest CU runs; over many rounds they even out
+        const double fullest = wgs <= 2 * SS_GEMM_CUS ? (double)((wgs + SS_GEMM_CUS - 1) / SS_GEMM_CUS * fours)
+                                                      : (double)wgs / SS_GEMM_CUS * fours + 0.3 * fours;
+        // (a lone wave on a SIMD waits for its operands a little; half a unit for a wave's fold and start)
+        const double cost = fullest * ((fullest == 1 ? 1.15 : 1.0) * units + 0.5);
+        if (best.G == 0 || cost < *busy) {
+            *busy = cost;
+            best.ksplit = ks;
+            best.slots = parts;
+            best.threads = threads;
+            best.G = (int)wgs;
+        }
+    }
+    return best;
+}
+
+// gemm_ksplit_kernel takes 3.4 us and 0.88 us (0.53 us over the 45-bit prime) for each of those; the big kernel 5.3 us and 0.15 us
+// (8.5 and 0.085 us) for a cost of one of its busiest workgroup.  With a single k block the stores decide from some 2560 tiles
+// on.  Measured on both sides of the line, n = 5 / n = 3 / n = 3 over the 45-bit prime, us, big kernel -> this one (rows x columns x
+// contraction): 64 x 128 x 256 9.3 -> 4.7 / 8.8 -> 4.5 / 8.1 -> 4.3; 128 x 784 x 512 19.4 -> 16.7 / 14.2 -> 12.7 / 13.8 -> 9.7;
+// 1024 x 196 x 256 20.6 -> 19.7 / 15.3 -> 13.3 / 13.1 -> 9.3; 256 x 196 x 1024 20.3 -> 21.2 / 14.2 -> 12.7 / 14.6 -> 8.8; 512 x 64 x 4608
+// 41 -> 51 / 26 -> 32 / 20.7 -> 23.1; 256 x 3136 x 64 21.1 -> 25.0 / 16.6 -> 16.1 / 16.4 -> 14.1.  Against the 16-row kernel:
+// 4 x 4096 x 512 16.7 -> 17.2 / 12.2 -> 11.4 / 9.3 -> 9.8; 1 x 1000 x 2048 17.3 -> 21.7 / 13.1 -> 13.2 / 10.0 -> 9.6.
+inline bool ksplit_is_faster(const gemm_plan &k, bool skinny, double busy, unsigned long long big)
+{
+    if (k.G <= 0 || k.tiles * k.Kb >= (1L << 31)) return false;
+    if (skinny) return k.tiles * k.Kb <= 6144;
+    if (SS_NLIMB == 8) return busy * 5.87 < (double)big + 12.7 && (k.Kb > 1 || k.tiles <= 2560);
+    return busy * 6.2 < (double)big + 62 && (k.Kb > 1 || k.tiles <= 10240);
+}
+
+// A second operand that gemm_skinny_kernel reads once and that the 256 MB of the last level cannot hold is read past it; one that
+// they hold may be there from its last use.  The same call repeated, n = 5 / n = 3 / n = 3 over the 45-bit prime, us, through the
+// caches -> past them (rows x columns x contraction): 2 x 12000 x 800 72.6 -> 63.9 (384 MB) / 36.2 -> 39.1 (230 MB) / 27.4 -> 29.9;
+// 4 x 4096 x 4096 121 -> 116 / 72.6 -> 65.7 (402 MB) / 49.0 -> 48.8 (302 MB); 5 x 1200 x 4800 37.9 -> 39.7 (230 MB) / - / -.
+inline bool streams_operand(size_t bytes) { return bytes > ((size_t)256 << 20); }
+
+// How the units are dealt: one workgroup per CU unless there is too little work for that; slots = the most
+// workgroups that can share one tile.
+// Whole tiles first and the price of the planes, against every tile dealt by cost with two planes, MI355X: layers of eight
+// images of ResNet-50 (n = 5) 16.12 -> 15.30 ms with their tails, 64 channels of 56 x 56 (3 x 3, n = 3, eight images) as a
+// tensor 238 -> 227 us; whole tiles as workgroups of their own instead of runs of one workgroup per CU: 16 rounds of two
+// units 125 us, in runs 107.
+inline gemm_plan plan_gemm(int n, int rows, int cols, int K, bool allow_skinny)
+{
+    typedef unsigned long long ull;
+    gemm_plan p = {};
+    p.Kb = (K + 63) / 64;
+    p.threads = 512;
+    p.skinny = allow_skinny && rows <= 16;
+    p.CT = p.skinny ? (cols + SKINNY_COLS - 1) / SKINNY_COLS : (cols + 63) / 64;
+    p.RT = p.skinny ? 1 : (rows + 63) / 64;
+    p.tiles = (long)n * p.RT * p.CT;
+    p.units = p.tiles * p.Kb;
+    const int vb_last = p.skinny ? 4 : (cols + 15) / 16 - 4 * (p.CT - 1);
+    p.wlast = unit_cost(vb_last);   // (every unit of the 16-row kernel copies the same nine blocks: one cost for all)
+    p.tcost = (unsigned)p.Kb * SS_UNIT_COST + SS_FOLD_COST;
+    p.tlast = (unsigned)p.Kb * p.wlast + (vb_last == 1 ? SS_FOLD_COST / 2 : SS_FOLD_COST);   // one block per wave to fold
+    const ull rowcost = (ull)(p.CT - 1) * p.tcost + p.tlast, cost = (ull)(p.tiles / p.CT) * rowcost;
+    // With one whole tile per workgroup the launch lasts as many tiles as the fullest CU gets.  Dealt by cost, a workgroup
+    // is busy for its share plus the fold of the tile its range ends in, and the tiles that are dealt so have `slots`
+    // planes.  With a single k block tiles are never cut, so there is nothing to choose; launches too large for the
+    // 32-bit range arithmetic (and that of the consumers, ss_part_src) have tiles enough for every CU many times over.
+    const unsigned step = SS_UNIT_COST + SS_FOLD_COST;   // largest distance between two unit starts
+    ull busy = ~0ull;   // cost of the busiest workgroup
+    bool all_whole = cost >= (1ull << 31) || p.units >= (1L << 31) || (ull)rows * cols >= (1ull << 31);
+    if (!all_whole) {
+        p.cost = (unsigned)cost;
+        // every range must hold at least one unit start
+        const unsigned most = p.cost / step;
+        p.G = (int)(most < SS_GEMM_CUS ? (most ? most : 1) : SS_GEMM_CUS);
+        // Tiles for two rounds and more: all but the last 256 to 511 of them whole, which leaves the ranges longer than a
+        // tile and so two planes, as without.  (A workgroup whose whole tiles are ragged ones idles a little: rows of
+        // tiles are long where there are that many.)
+        if (!p.skinny && p.Kb > 1 && p.tiles >= 2 * SS_GEMM_CUS) {
+            // (Where ragged tiles leave the ranges shorter than a full tile, one round less: two planes are what the workspace
+            // of such a product has held all along.)
+            p.whole = (unsigned)(p.tiles / SS_GEMM_CUS) * SS_GEMM_CUS;
+            do {
+                p.whole -= SS_GEMM_CUS;
+                p.cost0 = (unsigned)(p.whole / p.CT * rowcost + p.whole % p.CT * p.tcost);
+            } while (p.whole && (p.cost - p.cost0) / p.G < p.tcost);
+        }
+        // a tile of cost <= tcost meets at most this many ranges of length >= share; ranges are cut between
+        // units, so a tile of Kb units has at most Kb parts
+        const unsigned share = (p.cost - p.cost0) / p.G;
+        p.slots = (int)((p.tcost + share - 1) / share) + 1;
+        if (p.slots > p.Kb) p.slots = p.Kb;
+        busy = (ull)(p.whole / SS_GEMM_CUS) * p.tcost + share + SS_FOLD_COST;
+        if (p.Kb > 1) {
+            const ull plane_bytes = 16ull * n * rows * cols / p.tiles * (p.tiles - p.whole) * (p.slots - 1);
+            const ull rounds = ((ull)p.tiles + SS_GEMM_CUS - 1) / SS_GEMM_CUS;
+            all_whole = rounds * p.tcost <= busy + plane_bytes / SS_BYTES_PER_COST;
+            if (all_whole) busy = rounds * p.tcost - SS_FOLD_COST;   // (5.3 us hold a fold)
+        }
+        double kbusy = 0;
+        const gemm_plan k = plan_ksplit(n, rows, cols, p.Kb, &kbusy);
+        if (p.CT == 1 && vb_last == 2) busy = busy * 7 / 8;   // (units of two column blocks cost less than dealt with)
+        if (ksplit_is_faster(k, p.skinny, kbusy, busy)) return k;
+    }
+    if (all_whole) {
+        const long wgs = p.skinny || p.tiles < SS_GEMM_CUS ? p.tiles : SS_GEMM_CUS;
+        const bool launchable = p.tiles < (1L << 30) && fits_grid(wgs, p.threads);   // else G = 0, rejected by the caller
+        p.G = (int)(launchable ? wgs : 0);
+        p.slots = 1;
+        p.units = 0;
+        p.whole = launchable ? (unsigned)p.tiles : 0;
+        p.cost = p.cost0 = 0;
+    }
+    return p;
+}
+
+}  // namespace

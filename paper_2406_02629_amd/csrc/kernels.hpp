@@ -176,7 +176,6 @@ hipError_t ss_launch_pack_im2col(const u64 *x, void *dst, int n, int B, int C, i
 // by several workgroups, each of which stores its part in a plane of its own.  The first plane is `out`, the others follow
 // one another at `parts`; every position of every plane is written in every launch but for those of tiles that were not cut
 // (ss_gemm_parts), nothing passes between workgroups.  add_parts: one more launch adds them up, `out` is then the product.
-#define SS_GEMM_CUS 256
 int ss_gemm_planes(int n, int rows, int cols, int K, bool planes_operand);
 // the planes and the tiles they hold, for the consumers of a product whose rows run over hw columns at a time
 ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, bool planes_operand, int hw);

@@ -1,0 +1,47 @@
+"""How a product is given to the kernels and cut into work (csrc/gemm_plan.hpp, the code that the launcher uses), checked on
+the CPU over random shapes."""
+import ctypes as C
+import os
+import random
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2406_02629_amd", "csrc")
+
+
+class Plan(C.Structure):
+    _fields_ = [("skinny", C.c_bool), ("ksplit", C.c_int), ("tiles", C.c_long), ("units", C.c_long)] + \
+               [(k, C.c_int) for k in ("Kb", "G", "slots", "RT", "CT", "threads")] + \
+               [(k, C.c_uint) for k in ("whole", "wlast", "tcost", "tlast", "cost", "cost0")]
+
+
+def planner(directory, limbs):
+    """plan(n, rows, cols, K, tiles_operand) of the library whose elements have `limbs` limbs"""
+    src = directory / "gemm_plan.cpp"
+    src.write_text('#include "gemm_plan.hpp"\nextern "C" plan::gemm_plan plan_product(int n, int rows, int cols, int K, bool tiles_operand)\n'
+                   "{ return plan::plan_gemm(n, rows, cols, K, tiles_operand); }\n")
+    so = str(directory / f"gemm_plan{limbs}.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
+                    "-DSS_NS=plan", f"-DSS_NLIMB={limbs}", "-I", CSRC, "-o", so, str(src)], check=True)
+    lib = C.CDLL(so)
+    lib.plan_product.restype, lib.plan_product.argtypes = Plan, [C.c_int] * 4 + [C.c_bool]
+    return lib.plan_product
+
+
+@pytest.fixture(scope="module", params=[8, 6])
+def plan(request, tmp_path_factory):
+    return planner(tmp_path_factory.mktemp("gemm_plan"), request.param)
+
+
+def test_launches_hold_less_than_2_to_the_32_threads(plan):
+    """The runtime takes a larger grid without an error and runs a part of it.  Few rows and very many columns, as a convolution
+    with a wide padding has them: the first two, 1 x 1 kernels over 128 channels of one pixel padded by 8192 and by 7327, have that
+    many tiles of 16 x 16."""
+    rng = random.Random(3)
+    shapes = [(4, 1, 16385 ** 2, 128), (5, 1, 14655 ** 2, 128), (8, 15, 1 << 27, 384)]
+    shapes += [(rng.randint(3, 8), int(2 ** rng.uniform(0, 20)), int(2 ** rng.uniform(16, 30)), 64 * rng.randint(1, 9)) for _ in range(50000)]
+    for n, rows, cols, K in shapes:
+        p = plan(n, rows, cols, K, False)
+        assert p.G * p.threads < 1 << 32 and (p.G >= 1 or p.tiles >= 1 << 30), (n, rows, cols, K, p.G, p.threads)
+        assert p.threads == (256 if p.ksplit in (1, 2, 4) else 512)

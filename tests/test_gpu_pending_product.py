@@ -249,6 +249,26 @@ def test_small_and_narrow_products(n, t, p):
         check_consumers(s, p, y, (B, Co) + y.shape[-2:], lambda: s.conv_product_planes(planes, wp, *geom), seed=95)
 
 
+def test_more_tiles_of_16_x_16_than_a_launch_holds():
+    """One pixel of 128 channels under a 1 x 1 kernel, padded by 8192: a product of 1 x 268 million, zero but for the pixel."""
+    import ctypes as Ct
+    n, C, pad = 4, 128, 8192
+    H = 1 + 2 * pad
+    s = SSNet(n, 1, f=13, seed=5)
+    xs, ws = field_uniform((n, 1, C, 1, 1), 1), field_uniform((n, 1, C, 1, 1), 2)
+    planes, wp = s.split_planes(to_dev(xs)), s.pack_weights_conv_taps(to_dev(ws))
+    geom = (1, C, 1, 1, 1, 1, 1, 1, pad)
+    s.reserve(binding.WS_HEADER_BYTES + s.lib.ssnet_product_bytes_conv(s._ctx, *geom))
+    out = torch.ones((n, H * H), dtype=torch.int64, device="cuda")
+    assert s.lib.ssnet_conv_mod_planes(s._ctx, planes.data_ptr(), wp.data_ptr(), *geom, Ct.c_void_p(out.data_ptr())) == binding.OK
+    centre = pad * H + pad
+    assert np.array_equal(to_np(out[:, centre]), orc.conv(xs, ws, 1, 0, binding.P61).reshape(n))
+    out[:, centre] = 0
+    assert not any(bool(out[i].any()) for i in range(n))
+    del out, s
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("p,N", [(binding.P61, 5472), (binding.P45, 7296)])
 def test_second_operand_past_the_last_level(p, N):
     """16-row products on both sides of the 256 MB from which the second operand is read past the caches"""
