@@ -957,6 +957,7 @@ hipError_t ss_launch_pack_matrix(const u64 *src, void *dst, int n, int rows, int
                                  size_t stride_r, size_t stride_k, int taps, hipStream_t stream)
 {
     const int Rb = (rows + 15) / 16, Kb = (K + 63) / 64;
+    if (!fits_grid((long)Rb * Kb, 256)) return hipErrorInvalidConfiguration;   // (103 GB and more of tiles per party)
     hipLaunchKernelGGL(pack_matrix_kernel, dim3((unsigned)Rb * (unsigned)Kb, n), dim3(256), 0, stream, src, (v4i *)dst, rows, K, Rb,
                        Kb, make_fdiv((u32)Rb), make_fdiv((u32)Kb), stride_k == 1, party_stride, stride_r, stride_k,
                        ss_packed_bytes(rows, K) / 16, taps);

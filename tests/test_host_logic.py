@@ -225,7 +225,9 @@ def test_grids_of_2_to_the_32_threads_are_refused():
                        ("relu", (16, 16, 16, odd, 16)), ("pool_masks", pool + (0, 16, 16)),
                        ("relu_pool", (1 << 20, 1 << 20, 1 << 20) + pool + (0, 1 << 50)),
                        ("reduce_truncate_relu", (16, 1, 1, 1 << 28, 0, 16, 16, 16, None)),
-                       ("reduce_truncate_relu_direct", (16, 1, 1, 1 << 28, 16, 16, 16, None))]:
+                       ("reduce_truncate_relu_direct", (16, 1, 1, 1 << 28, 16, 16, 16, None)),
+                       ("pack_weights_linear", (16, 16383, 1 << 20, 16)), ("pack_weights_conv", (16, 1 << 20, 16383, 16)),
+                       ("pack_weights_conv_taps", (16, 1 << 20, 1820, 3, 3, 16))]:
         assert getattr(lib, "ssnet_" + name)(ctx, *args) == binding.EHIP, name
         assert lib.ssnet_last_hip_error(ctx) == invalid_configuration, name
 
