@@ -928,9 +928,9 @@ __global__ __launch_bounds__(256) void add_cut_tiles_kernel(gemm_args g, unsigne
 
 }  // namespace
 
-ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, bool planes_operand, int hw)
+ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, int gather, int hw)
 {
-    const gemm_plan p = plan_gemm(n, rows, cols, K, !planes_operand);
+    const gemm_plan p = plan_gemm(n, rows, cols, K, gather);
     ss_part_src ps = {};
     ps.planes = p.slots;
     ps.stride = (size_t)n * rows * cols;
@@ -944,15 +944,15 @@ ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, bool planes_operand,
     return ps;
 }
 
-int ss_gemm_planes(int n, int rows, int cols, int K, bool planes_operand)
+int ss_gemm_planes(int n, int rows, int cols, int K, int gather)
 {
-    return plan_gemm(n, rows, cols, K, !planes_operand).slots;
+    return plan_gemm(n, rows, cols, K, gather).slots;
 }
 
-size_t ss_gemm_scratch_bytes(int n, int rows, int cols, int K)
+size_t ss_gemm_scratch_bytes(int n, int rows, int cols, int K, int gather)
 {
     // room for either form of the second operand (tiles may take the 16-row kernel, limb planes never do)
-    const int a = ss_gemm_planes(n, rows, cols, K, true), b = ss_gemm_planes(n, rows, cols, K, false);
+    const int a = ss_gemm_planes(n, rows, cols, K, gather), b = ss_gemm_planes(n, rows, cols, K, 0);
     return (size_t)((a > b ? a : b) - 1) * n * rows * cols * sizeof(u64);   // the first plane is the product itself
 }
 
@@ -1061,7 +1061,7 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
         if (e != hipSuccess) return e;
         lds_opt_in = true;
     }
-    const gemm_plan p = plan_gemm(n, rows, cols, K, cv == nullptr);
+    const gemm_plan p = plan_gemm(n, rows, cols, K, cv ? ss_gather(cv->C, cv->stride) : 0);
     if (p.G <= 0) return hipErrorInvalidValue;
     gemm_args g = {};
     g.A = (const v4i *)packedA;

@@ -1,6 +1,7 @@
 // How a product is given to the kernels of gemm_kernels.hip and cut into work for their workgroups.  Plain C++, so that the
 // rules can be checked without a GPU.  SS_NLIMB: limbs of a field element (8, or 6 over the 45-bit prime).
 #pragma once
+#include <math.h>
 #include <stddef.h>
 
 namespace SS_NS {
@@ -41,7 +42,7 @@ constexpr unsigned long long SS_BYTES_PER_COST = 750 * 1000;
 
 // Plan for gemm_ksplit_kernel and what it takes, in units (16 x 16, one k block, four side by side on a CU): a CU's waves get
 // their operand blocks out of the caches at about 30 bytes per clock, so a launch lasts as long as the fullest CU has units.
-inline gemm_plan plan_ksplit(int n, int rows, int cols, int Kb, double *busy)
+inline gemm_plan plan_ksplit(int n, int rows, int cols, int Kb, double *busy, double *spread)
 {
     gemm_plan best = {};
     const long Rb = (rows + 15) / 16, Cb = (cols + 15) / 16, blocks = n * Rb * Cb;
@@ -67,6 +68,7 @@ inline gemm_plan plan_ksplit(int n, int rows, int cols, int Kb, double *busy)
         const double cost = fullest * ((fullest == 1 ? 1.15 : 1.0) * units + 0.5);
         if (best.G == 0 || cost < *busy) {
             *busy = cost;
+            *spread = (double)wgs / SS_GEMM_CUS * fours * (units + 0.5);   // a CU's share of the whole launch
             best.ksplit = ks;
             best.slots = parts;
             best.threads = threads;
@@ -76,19 +78,46 @@ inline gemm_plan plan_ksplit(int n, int rows, int cols, int Kb, double *busy)
     return best;
 }
 
-// gemm_ksplit_kernel takes 3.4 us and 0.88 us (0.53 us over the 45-bit prime) for each of those; the big kernel 5.3 us and 0.15 us
-// (8.5 and 0.085 us) for a cost of one of its busiest workgroup.  With a single k block the stores decide from some 2560 tiles
-// on.  Measured on both sides of the line, n = 5 / n = 3 / n = 3 over the 45-bit prime, us, big kernel -> this one (rows x columns x
-// contraction): 64 x 128 x 256 9.3 -> 4.7 / 8.8 -> 4.5 / 8.1 -> 4.3; 128 x 784 x 512 19.4 -> 16.7 / 14.2 -> 12.7 / 13.8 -> 9.7;
-// 1024 x 196 x 256 20.6 -> 19.7 / 15.3 -> 13.3 / 13.1 -> 9.3; 256 x 196 x 1024 20.3 -> 21.2 / 14.2 -> 12.7 / 14.6 -> 8.8; 512 x 64 x 4608
-// 41 -> 51 / 26 -> 32 / 20.7 -> 23.1; 256 x 3136 x 64 21.1 -> 25.0 / 16.6 -> 16.1 / 16.4 -> 14.1.  Against the 16-row kernel:
-// 4 x 4096 x 512 16.7 -> 17.2 / 12.2 -> 11.4 / 9.3 -> 9.8; 1 x 1000 x 2048 17.3 -> 21.7 / 13.1 -> 13.2 / 10.0 -> 9.6.
-inline bool ksplit_is_faster(const gemm_plan &k, bool skinny, double busy, unsigned long long big)
+// gemm_ksplit_kernel (plan k; busy, spread: see plan_ksplit) takes over from gemm_limb_kernel (plan p; big: the cost of its busiest
+// workgroup) where it is the faster one both with operands that repeat and with weights that come from memory.
+//
+// The same call repeated: 3.4 us and 0.88 us (0.53 us over the 45-bit prime) for each unit of its fullest CU; the big kernel 5.3 us and
+// 0.15 us (8.5 and 0.085 us) for a cost of one of its busiest workgroup.  With a single k block the stores decide from some 2560
+// tiles on.  Against the 16-row kernel, n = 5 / n = 3 / n = 3 over the 45-bit prime, us (rows x columns x contraction): 4 x 4096 x 512
+// 16.7 -> 17.2 / 12.2 -> 11.4 / 9.3 -> 9.8; 1 x 1000 x 2048 17.3 -> 21.7 / 13.1 -> 13.2 / 10.0 -> 9.6.
+//
+// Weights from memory, product and reduction together, fitted to 1130 timings of both kernels (n = 3 to 7, both fields): 1 us per 22 MB
+// of packed operands; a last row tile that is not full makes the big kernel's units shorter; 0.6 us and the loads of the consumer
+// for every plane it leaves.  A convolution that reads limb planes with a stride finds the 16 pixels of a block in twice the
+// cache lines or more, whose other halves belong to the next taps, all channels later: every tile of 16 x 16 pays for that by itself, the
+// more the more channels, and the CUs together then wait for the caches (`spread`); a tile of 64 x 64 pays once for its four row
+// blocks.
+// Big kernel -> this one with weights from memory, product + reduction + truncation + opening, us, n = 5 / n = 3 / n = 3 over the 45-bit
+// prime: taken, 64 x 128 x 256 (repeated, product alone) 9.3 -> 4.7 / 8.8 -> 4.5 / 8.1 -> 4.3; 128 x 784 x 512 30.3 -> 26.7 / 24.6 ->
+// 20.7 / 24.8 -> 16.3; 1024 x 196 x 256 41.0 -> 39.0 / 31.0 -> 25.6 / 28.5 -> 20.2 (the product alone of five parties 20.0 -> 21.4: the
+// reduction has one plane instead of two).  Left, 39 x 1800 x 4608, n = 5, 111 -> 118; 94 x 1352 x 2304, n = 3, 60.7 -> 68.5; with stride
+// 2, 43 x 578 x 4608, n = 5, 51 -> 65; 270 x 80 x 4608, n = 5, 46 -> 56; 27 x 1152 x 4608, n = 4 over the 45-bit prime, 46 -> 51.
+inline bool ksplit_is_faster(const gemm_plan &k, const gemm_plan &p, double busy, double spread, double big, bool all_whole, int n,
+                             int rows, int cols, int gather)
 {
     if (k.G <= 0 || k.tiles * k.Kb >= (1L << 31)) return false;
-    if (skinny) return k.tiles * k.Kb <= 6144;
-    if (SS_NLIMB == 8) return busy * 5.87 < (double)big + 12.7 && (k.Kb > 1 || k.tiles <= 2560);
-    return busy * 6.2 < (double)big + 62 && (k.Kb > 1 || k.tiles <= 10240);
+    if (p.skinny) return k.tiles * k.Kb <= 6144;
+    if (k.Kb == 1 && k.tiles > (SS_NLIMB == 8 ? 2560 : 10240)) return false;
+    if (SS_NLIMB == 8 ? busy * 5.87 >= big + 12.7 : busy * 6.2 >= big + 62) return false;
+    double units = busy;
+    if (gather > 1) {
+        const double far = SS_NLIMB == 8 ? 0.1 + 0.25 * log2(gather / 64.0) : 0.25 + 0.22 * log2(gather / 64.0);
+        // (waves that take neighbouring tiles share what they read of the pixels)
+        const double held = (1 + far * (k.ksplit == 1 ? 0.3 : k.ksplit == 2 ? 0.75 : 1.0)) * spread;
+        if (held > units) units = held;
+    }
+    const long Rb = (rows + 15) / 16, packed = Rb + (gather ? 0 : (cols + 15) / 16);   // blocks of the packed operands
+    const double operand_us = (double)n * packed * p.Kb * (SS_NLIMB << 10) / 22e6;
+    const double plane_us = 0.6 + (double)n * rows * cols / p.tiles * (p.tiles - p.whole) * 8 / 5e6;
+    const double unit = Rb == 4 * p.RT ? 1.0 : 0.86;
+    const double ksplit_us = operand_us + (SS_NLIMB == 8 ? 1.8 + 0.80 * units : 3.9 + 0.47 * units);
+    const double big_us = (SS_NLIMB == 8 ? 3.9 + 0.145 * unit * big : 5.4 + 0.095 * unit * big) + (all_whole ? 0 : (p.slots - 1) * plane_us);
+    return ksplit_us < big_us;
 }
 
 // A second operand that gemm_skinny_kernel reads once and that the 256 MB of the last level cannot hold is read past it; one that
@@ -103,13 +132,14 @@ inline bool streams_operand(size_t bytes) { return bytes > ((size_t)256 << 20); 
 // images of ResNet-50 (n = 5) 16.12 -> 15.30 ms with their tails, 64 channels of 56 x 56 (3 x 3, n = 3, eight images) as a
 // tensor 238 -> 227 us; whole tiles as workgroups of their own instead of runs of one workgroup per CU: 16 rounds of two
 // units 125 us, in runs 107.
-inline gemm_plan plan_gemm(int n, int rows, int cols, int K, bool allow_skinny)
+// gather: 0 for a second operand in tiles, 1 for one in limb planes; its channels if the convolution reads them with a stride.
+inline gemm_plan plan_gemm(int n, int rows, int cols, int K, int gather)
 {
     typedef unsigned long long ull;
     gemm_plan p = {};
     p.Kb = (K + 63) / 64;
     p.threads = 512;
-    p.skinny = allow_skinny && rows <= 16;
+    p.skinny = gather == 0 && rows <= 16;
     p.CT = p.skinny ? (cols + SKINNY_COLS - 1) / SKINNY_COLS : (cols + 63) / 64;
     p.RT = p.skinny ? 1 : (rows + 63) / 64;
     p.tiles = (long)n * p.RT * p.CT;
@@ -155,10 +185,10 @@ inline gemm_plan plan_gemm(int n, int rows, int cols, int K, bool allow_skinny)
             all_whole = rounds * p.tcost <= busy + plane_bytes / SS_BYTES_PER_COST;
             if (all_whole) busy = rounds * p.tcost - SS_FOLD_COST;   // (5.3 us hold a fold)
         }
-        double kbusy = 0;
-        const gemm_plan k = plan_ksplit(n, rows, cols, p.Kb, &kbusy);
+        double kbusy = 0, kspread = 0;
+        const gemm_plan k = plan_ksplit(n, rows, cols, p.Kb, &kbusy, &kspread);
         if (p.CT == 1 && vb_last == 2) busy = busy * 7 / 8;   // (units of two column blocks cost less than dealt with)
-        if (ksplit_is_faster(k, p.skinny, kbusy, busy)) return k;
+        if (ksplit_is_faster(k, p, kbusy, kspread, (double)busy, all_whole, n, rows, cols, gather)) return k;
     }
     if (all_whole) {
         const long wgs = p.skinny || p.tiles < SS_GEMM_CUS ? p.tiles : SS_GEMM_CUS;

@@ -176,11 +176,13 @@ hipError_t ss_launch_pack_im2col(const u64 *x, void *dst, int n, int B, int C, i
 // by several workgroups, each of which stores its part in a plane of its own.  The first plane is `out`, the others follow
 // one another at `parts`; every position of every plane is written in every launch but for those of tiles that were not cut
 // (ss_gemm_parts), nothing passes between workgroups.  add_parts: one more launch adds them up, `out` is then the product.
-int ss_gemm_planes(int n, int rows, int cols, int K, bool planes_operand);
+// gather: 0 for a second operand in tiles, else ss_gather of the convolution that reads it from limb planes
+int ss_gemm_planes(int n, int rows, int cols, int K, int gather);
+inline int ss_gather(int C, int stride) { return stride > 1 ? C : 1; }
 // the planes and the tiles they hold, for the consumers of a product whose rows run over hw columns at a time
-ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, bool planes_operand, int hw);
+ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, int gather, int hw);
 // bytes of all planes but the first for either form of the second operand
-size_t ss_gemm_scratch_bytes(int n, int rows, int cols, int K);
+size_t ss_gemm_scratch_bytes(int n, int rows, int cols, int K, int gather);
 // started / stopped, if given, take the times at which the product kernel itself starts and ends on the GPU (the
 // dispatch's own time stamps, without the gap between two launches that events recorded around a launch include)
 hipError_t ss_launch_gemm(const void *packedA, const void *packedB, u64 *out, u64 *parts, bool add_parts, int n, int rows,

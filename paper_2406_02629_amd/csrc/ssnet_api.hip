@@ -298,23 +298,23 @@ int run_gemm(ssnet_ctx *ctx, const void *pa, const void *pb, u64 *out, int rows,
     });
 }
 
-size_t product_bytes(const ssnet_ctx *ctx, int rows, int cols, int K, bool planes_operand)
+size_t product_bytes(const ssnet_ctx *ctx, int rows, int cols, int K, int gather)
 {
-    return align256((size_t)ss_gemm_planes(ctx->n, rows, cols, K, planes_operand) * ctx->n * rows * cols * 8);
+    return align256((size_t)ss_gemm_planes(ctx->n, rows, cols, K, gather) * ctx->n * rows * cols * 8);
 }
 
 // Room for a product of `planes` planes at the very end of the workspace; the messages of the call that
 // consumes it grow from the front.  nullptr if the workspace is too small.
-u64 *reserve_pending(ssnet_ctx *ctx, int rows, int cols, int K, bool planes_operand, int hw)
+u64 *reserve_pending(ssnet_ctx *ctx, int rows, int cols, int K, int gather, int hw)
 {
     ctx->pending.on = false;
-    const size_t bytes = product_bytes(ctx, rows, cols, K, planes_operand);
+    const size_t bytes = product_bytes(ctx, rows, cols, K, gather);
     if (!ctx->ws || ctx->ws_bytes < WS_HEADER_BYTES + bytes + 256) return nullptr;
     const uintptr_t end = ((uintptr_t)ctx->ws + ctx->ws_bytes) & ~(uintptr_t)255;
     if (end - bytes < (uintptr_t)ws_scratch(ctx)) return nullptr;
     ctx->pending.base = (u64 *)(end - bytes);
     ctx->pending.count = (size_t)rows * cols;
-    ctx->pending.src = ss_gemm_parts(ctx->n, rows, cols, K, planes_operand, hw);
+    ctx->pending.src = ss_gemm_parts(ctx->n, rows, cols, K, gather, hw);
     return ctx->pending.base;
 }
 
@@ -447,7 +447,7 @@ size_t ssnet_workspace_bytes_stream(const ssnet_ctx *ctx, size_t count)
 size_t ssnet_workspace_bytes_linear(const ssnet_ctx *ctx, int M, int K, int N)
 {
     if (!ctx || M < 1 || K < 1 || N < 1) return 0;
-    return WS_HEADER_BYTES + align256(ss_gemm_scratch_bytes(ctx->n, M, N, K)) +
+    return WS_HEADER_BYTES + align256(ss_gemm_scratch_bytes(ctx->n, M, N, K, 0)) +
            (size_t)ctx->n * (ss_packed_bytes(M, K) + ss_packed_bytes(N, K));
 }
 
@@ -459,7 +459,7 @@ size_t ssnet_workspace_bytes_conv(const ssnet_ctx *ctx, int B, int C, int H, int
     if (Ho < 1 || Wo < 1) return 0;
     const long M = (long)B * Ho * Wo, K = (long)C * kh * kw;
     if (M > INT_MAX || K > INT_MAX) return 0;
-    return WS_HEADER_BYTES + align256(ss_gemm_scratch_bytes(ctx->n, Co, (int)M, (int)K)) +
+    return WS_HEADER_BYTES + align256(ss_gemm_scratch_bytes(ctx->n, Co, (int)M, (int)K, ss_gather(C, stride))) +
            (size_t)ctx->n * (ss_packed_bytes((int)M, (int)K) + ss_packed_bytes(Co, (int)K));
 }
 
@@ -544,7 +544,7 @@ int ssnet_linear_mod_packed(ssnet_ctx *ctx, const uint64_t *d_x, const void *d_w
                             uint64_t *d_y)
 {
     if (!ctx || !d_x || !d_w_packed || !d_y || !gemm_shape_ok(M, N, K)) return SSNET_EINVAL;
-    const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, M, N, K));
+    const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, M, N, K, 0));
     if (!ws_fits(ctx, part + (size_t)ctx->n * ss_packed_bytes(M, K))) return SSNET_EWORKSPACE;
     void *px = ws_scratch(ctx) + part;
     {
@@ -559,7 +559,7 @@ int ssnet_linear_mod_prepacked(ssnet_ctx *ctx, const void *d_x_packed, const voi
                                uint64_t *d_y)
 {
     if (!ctx || !d_x_packed || !d_w_packed || !d_y || !gemm_shape_ok(M, N, K)) return SSNET_EINVAL;
-    if (!ws_fits(ctx, align256(ss_gemm_scratch_bytes(ctx->n, M, N, K)))) return SSNET_EWORKSPACE;
+    if (!ws_fits(ctx, align256(ss_gemm_scratch_bytes(ctx->n, M, N, K, 0)))) return SSNET_EWORKSPACE;
     return run_gemm(ctx, d_x_packed, d_w_packed, d_y, M, N, K, (size_t)M * N, (size_t)N, INT_MAX, 0);
 }
 
@@ -570,7 +570,7 @@ int ssnet_conv1x1_mod_prepacked(ssnet_ctx *ctx, const void *d_x_packed, const vo
         !gemm_shape_ok(Co, (long)B * HW, C))
         return SSNET_EINVAL;
     const int M = B * HW;
-    if (!ws_fits(ctx, align256(ss_gemm_scratch_bytes(ctx->n, Co, M, C)))) return SSNET_EWORKSPACE;
+    if (!ws_fits(ctx, align256(ss_gemm_scratch_bytes(ctx->n, Co, M, C, 0)))) return SSNET_EWORKSPACE;
     // rows = output channel, cols = (b, hw): y[b][co][hw]
     return run_gemm(ctx, d_w_packed, d_x_packed, d_y, Co, M, C, (size_t)B * Co * HW, (size_t)HW, HW, (size_t)Co * HW);
 }
@@ -633,7 +633,7 @@ int ssnet_conv_mod_planes(ssnet_ctx *ctx, const void *d_planes, const void *d_w_
     if (Ho < 1 || Wo < 1) return SSNET_EINVAL;
     const long M = (long)B * Ho * Wo, K = (long)C * kh * kw;
     if (!gemm_shape_ok(Co, M, K)) return SSNET_EINVAL;
-    if (!ws_fits(ctx, align256(ss_gemm_scratch_bytes(ctx->n, Co, (int)M, (int)K)))) return SSNET_EWORKSPACE;
+    if (!ws_fits(ctx, align256(ss_gemm_scratch_bytes(ctx->n, Co, (int)M, (int)K, ss_gather(C, stride))))) return SSNET_EWORKSPACE;
     return run_product(ctx, [&](u64 *parts, hipEvent_t ea, hipEvent_t eb) {
         return ss_launch_gemm_conv(d_w_packed, d_planes, d_y, parts, true, ctx->n, B, C, H, W, Co, kh, kw, stride, pad, Ho, Wo,
                                    ctx->stream, ea, eb);
@@ -643,7 +643,7 @@ int ssnet_conv_mod_planes(ssnet_ctx *ctx, const void *d_planes, const void *d_w_
 size_t ssnet_product_bytes_linear(const ssnet_ctx *ctx, int M, int K, int N)
 {
     if (!ctx || !gemm_shape_ok(M, N, K)) return 0;
-    return product_bytes(ctx, M, N, K, false);
+    return product_bytes(ctx, M, N, K, 0);
 }
 
 size_t ssnet_product_bytes_conv(const ssnet_ctx *ctx, int B, int C, int H, int W, int Co, int kh, int kw, int stride,
@@ -654,14 +654,14 @@ size_t ssnet_product_bytes_conv(const ssnet_ctx *ctx, int B, int C, int H, int W
     if (H + 2 * pad < kh || W + 2 * pad < kw || Ho < 1 || Wo < 1) return 0;
     const long M = (long)B * Ho * Wo, K = (long)C * kh * kw;
     if (!gemm_shape_ok(Co, M, K)) return 0;
-    const size_t a = product_bytes(ctx, Co, (int)M, (int)K, false), b = product_bytes(ctx, Co, (int)M, (int)K, true);
+    const size_t a = product_bytes(ctx, Co, (int)M, (int)K, 0), b = product_bytes(ctx, Co, (int)M, (int)K, ss_gather(C, stride));
     return a > b ? a : b;
 }
 
 int ssnet_linear_product_prepacked(ssnet_ctx *ctx, const void *d_x_packed, const void *d_w_packed, int M, int K, int N)
 {
     if (!ctx || !d_x_packed || !d_w_packed || !gemm_shape_ok(M, N, K)) return SSNET_EINVAL;
-    u64 *c = reserve_pending(ctx, M, N, K, false, N);
+    u64 *c = reserve_pending(ctx, M, N, K, 0, N);
     if (!c) return SSNET_EWORKSPACE;
     timed tm(ctx, SSNET_PROF_GEMM);
     kernel_span ks(ctx);
@@ -679,7 +679,7 @@ int ssnet_conv1x1_product_prepacked(ssnet_ctx *ctx, const void *d_x_packed, cons
         !gemm_shape_ok(Co, (long)B * HW, C))
         return SSNET_EINVAL;
     const int M = B * HW;
-    u64 *c = reserve_pending(ctx, Co, M, C, false, HW);
+    u64 *c = reserve_pending(ctx, Co, M, C, 0, HW);
     if (!c) return SSNET_EWORKSPACE;
     timed tm(ctx, SSNET_PROF_GEMM);
     kernel_span ks(ctx);
@@ -701,7 +701,7 @@ int ssnet_conv_product_planes(ssnet_ctx *ctx, const void *d_planes, const void *
     if (Ho < 1 || Wo < 1) return SSNET_EINVAL;
     const long M = (long)B * Ho * Wo, K = (long)C * kh * kw;
     if (!gemm_shape_ok(Co, M, K)) return SSNET_EINVAL;
-    u64 *c = reserve_pending(ctx, Co, (int)M, (int)K, true, Ho * Wo);
+    u64 *c = reserve_pending(ctx, Co, (int)M, (int)K, ss_gather(C, stride), Ho * Wo);
     if (!c) return SSNET_EWORKSPACE;
     timed tm(ctx, SSNET_PROF_GEMM);
     kernel_span ks(ctx);
@@ -715,7 +715,7 @@ int ssnet_conv_product_planes(ssnet_ctx *ctx, const void *d_planes, const void *
 int ssnet_linear_mod(ssnet_ctx *ctx, const uint64_t *d_x, const uint64_t *d_w, int M, int K, int N, uint64_t *d_y)
 {
     if (!ctx || !d_x || !d_w || !d_y || !gemm_shape_ok(M, N, K)) return SSNET_EINVAL;
-    const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, M, N, K));
+    const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, M, N, K, 0));
     const size_t xa = (size_t)ctx->n * ss_packed_bytes(M, K), wa = (size_t)ctx->n * ss_packed_bytes(N, K);
     if (!ws_fits(ctx, part + xa + wa)) return SSNET_EWORKSPACE;
     void *pw = ws_scratch(ctx) + part + xa;
@@ -734,7 +734,7 @@ int ssnet_conv_mod_packed(ssnet_ctx *ctx, const uint64_t *d_x, const void *d_w_p
     if (H + 2 * pad < kh || W + 2 * pad < kw || Ho < 1 || Wo < 1) return SSNET_EINVAL;
     const long M = (long)B * Ho * Wo, K = (long)C * kh * kw;
     if (M > (1L << 30) || !gemm_shape_ok(Co, M, K)) return SSNET_EINVAL;
-    const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, Co, (int)M, (int)K));
+    const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, Co, (int)M, (int)K, 0));
     if (!ws_fits(ctx, part + (size_t)ctx->n * ss_packed_bytes((int)M, (int)K))) return SSNET_EWORKSPACE;
     void *px = ws_scratch(ctx) + part;
     {
