@@ -37,8 +37,10 @@ inline unsigned unit_cost(int vb)
 }
 
 // A further plane of the output is written here and read by whoever takes the product: bytes that take as long as a cost
-// of one (0.15 us at 5 TB/s, what many streams at a time reach).
-constexpr unsigned long long SS_BYTES_PER_COST = 750 * 1000;
+// of one (0.15 us, over the 45-bit prime 0.085 us, at 5 TB/s, what many streams at a time reach).  Over the 45-bit prime, at 750 KB ->
+// at 425 KB, product and reduction, us: n = 5, 269 x 579 x 3245 107.9 -> 96.4; n = 3, 320 x 1800 x 576 56.6 -> 52.9 (as a tensor 43.7 ->
+// 33.0); n = 4, 52 x 3468 x 1152 45.4 -> 40.2; of 60 drawn shapes whose plan differs all but nine gain, these lose up to 4 %.
+constexpr unsigned long long SS_BYTES_PER_COST = SS_NLIMB == 8 ? 750 * 1000 : 425 * 1000;
 
 // Plan for gemm_ksplit_kernel and what it takes, in units (16 x 16, one k block, four side by side on a CU): a CU's waves get
 // their operand blocks out of the caches at about 30 bytes per clock, so a launch lasts as long as the fullest CU has units.
