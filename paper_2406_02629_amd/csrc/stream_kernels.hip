@@ -24,6 +24,7 @@ constexpr size_t LAUNCH_ELEMENTS = (size_t)1 << 31;   // of a tensor that goes i
 // workgroup; planes of `plane` elements.  (The grid is worked out from the count, which arrives in registers: read from the launch it
 // puts a memory access in front of a small kernel's first load.)
 __host__ __device__ __forceinline__ bool starts_lines(size_t count) { return count % 16 == 0; }
+__host__ __device__ __forceinline__ bool starts_halves(size_t count) { return count % 8 == 0; }   // of cache lines
 template <int PER>
 __device__ __forceinline__ size_t element_block(size_t count, size_t plane)
 {
@@ -166,8 +167,10 @@ __device__ __forceinline__ void draw_coeffs(u64 (&c)[MAXD], const u64 *keys, int
 // against 2.32 ms with four waves and 2.40 ms with the short reduction too; 2^26: 514, 548 and 570 us; 2^20: 7.6, 8.4
 // and 8.5 us).  With three planes four waves are the better ones (2^24 elements: 75.6 against 76.5 us), and the form of
 // the reduction makes no difference beyond that of two runs (long and short, 2^20: 6.3 and 6.2, 2^24: 75.5 and 75.4, 2^26:
-// 362 and 366, 2^28: 1444 and 1453 us).  Five planes that do not start on cache lines go through the caches, which put the
-// parts of a line together (2^24 + 3 elements 185 -> 148 us, 2^22 + 2 40 -> 37 us; three planes 95 and 92, 21 and 25 us: past them),
+// 362 and 366, 2^28: 1444 and 1453 us).  Five planes that do not start on halves of cache lines go through the caches, which put the
+// parts of a line together (2^24 + 3 elements 185 -> 148 us, 2^22 + 2 40 -> 37 us; on halves past them and in the order of the
+// launch: 438888 elements 5.5 -> 4.7 us, 5.8 M 43.5 -> 41.1;
+// three planes 95 and 92, 21 and 25 us: past them),
 // and odd counts, one element per thread, have the schemes fixed too (2^20-odd elements, n = 3: 11 -> 7 us).
 template <int VEC, int NC>
 constexpr int SHARE_BLOCK = VEC == 2 && NC == 5 ? 64 : BLOCK;
@@ -178,7 +181,8 @@ __global__ __launch_bounds__((SHARE_BLOCK<VEC, NC>)) void share_kernel(const u64
     constexpr int MAXD = DC ? DC : SS_MAXDEG;
     constexpr int MAXP = NC ? NC : SS_MAXN;
     const int n = NC ? NC : n_rt, degree = DC ? DC : degree_rt;
-    const size_t e0 = (element_block<SHARE_BLOCK<VEC, NC> * VEC>(count, count) * SHARE_BLOCK<VEC, NC> + threadIdx.x) * VEC;
+    const size_t e0 = (element_block<SHARE_BLOCK<VEC, NC> * VEC>(count, starts_halves(count) ? 0 : count) * SHARE_BLOCK<VEC, NC> +
+                       threadIdx.x) * VEC;
     if (e0 >= count) return;
     pack_t<VEC> a0;
     a0.load(secret + e0);
@@ -193,7 +197,7 @@ __global__ __launch_bounds__((SHARE_BLOCK<VEC, NC>)) void share_kernel(const u64
 #pragma unroll
         for (int p = 0; p < NC; p++) {   // written, not read again
             u64 *to = shares + (size_t)p * count + e0;
-            NC == 5 && !starts_lines(count) ? s[p].store(to) : s[p].store_streaming(to);
+            NC == 5 && !starts_halves(count) ? s[p].store(to) : s[p].store_streaming(to);
         }
     } else {
 #pragma unroll
@@ -961,8 +965,10 @@ constexpr size_t LANES_MAX_COUNT = 16 * 1024;
 // caches is faster.  44 planes written per 5 read, no arithmetic, the same call repeated, MI355X: 24.4 / 26.7 us (cached /
 // streamed) at 157 MB, 56.2 / 53.1 us at 315 MB, 324 / 273 us at 1.65 GB.  With inputs that change from call to call the line
 // lies there too (at 64, 128, 600 MB stacks and single calls are 0 to 8 % slower).  The reductions' many planes only where they
-// start on cache lines: parts of lines past the caches cost more (reduce + truncate of 1.2 M + 1 elements, n = 5: 130 us
-// streamed, 108 cached; n = 7: 238 and 198 us).
+// start on halves of cache lines: smaller parts past the caches cost more, whole halves do not.  Reduce + truncate, us, streamed /
+// cached, with planes 1, 2 or 4 elements off a line, then 8: n = 5, 1.2 M elements 125 / 108, 91 / 99; n = 7, 2.6 M 430 / 390, 355 / 388;
+// n = 4, 2.4 M 124 / 114, 100 / 103.  The reduction alone of t = 1 sends the fewest planes and is faster past the caches everywhere:
+// n = 4, 2.3 M elements 2 off 80 / 93, n = 3, 2.7 M 78 / 82.
 inline bool streams_messages(size_t words) { return words * sizeof(u64) > ((size_t)256 << 20); }
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -1052,7 +1058,7 @@ hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out,
         return hipGetLastError();
     }
     const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
-    const bool streams = starts_lines(count) && streams_messages((nr + n + nr * k + k * n) * count);
+    const bool streams = (starts_halves(count) || dp.t == 1) && streams_messages((nr + n + nr * k + k * n) * count);
 #define SS_LAUNCH(NC, TC)                                                                                               \
     hipLaunchKernelGGL((streams ? degree_reduce_kernel<NC, TC, false, true> : degree_reduce_kernel<NC, TC, false, false>), \
                        dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, \
@@ -1068,7 +1074,7 @@ hipError_t ss_launch_degree_reduce_truncate(const u64 *c, u64 *msg1, u64 *msg2, 
 {
     if (!fits_launch(blocks_for(count, 1))) return hipErrorInvalidConfiguration;
     const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
-    const bool streams = starts_lines(count) && streams_messages((nr + n + nr * k + k * n + k + n) * count);
+    const bool streams = starts_halves(count) && streams_messages((nr + n + nr * k + k * n + k + n) * count);
 #define SS_LAUNCH(NC, TC)                                                                                               \
     hipLaunchKernelGGL((streams ? degree_reduce_kernel<NC, TC, true, true> : degree_reduce_kernel<NC, TC, true, false>), \
                        dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, u, wsh, out, rec, count, dp, tp, ps)

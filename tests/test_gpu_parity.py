@@ -827,11 +827,12 @@ def test_reduce_truncate_direct_beyond_one_launch():
 def test_planes_off_the_cache_lines(n, t):
     """Counts whose planes do not start on cache lines, below, at and past the 512 workgroups whose order changes there (one
     and two elements per thread; workgroups of one wave and of four), and the reductions' first aligned count past the
-    caches, which off the lines stay in them: every call's result and messages against the oracle."""
+    caches, which off the lines stay in them unless they start on half a line: every call's result and messages against the
+    oracle."""
     s = SSNet(n, t, f=13, seed=19)
     k, nr = t + 1, 2 * t + 1
     past = LAST_LEVEL_WORDS // (nr + n + nr * k + k * n) + 16 & ~15
-    for count in (131071, 131073, 262146, 2 * 131072 + 2 * 64 * 512 - 2, past, past + 2):
+    for count in (131071, 131073, 262146, 2 * 131072 + 2 * 64 * 512 - 2, past, past + 2, past + 8):
         say("off the lines", n, t, count)
         xs = np.random.default_rng(count).integers(-(1 << 31), 1 << 31, count, dtype=np.int64)
         x = np.where(xs < 0, xs + P61, xs).astype(np.uint64)
