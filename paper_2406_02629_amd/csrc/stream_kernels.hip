@@ -102,14 +102,15 @@ __device__ __forceinline__ int first_cut_party(const ss_part_src &ps, size_t e)
     return i;
 }
 
-// the further planes of the first NR shares of element e, added to v[]: two planes requested at a time
-template <int NR>
+// the further planes of the first NR shares of element e, added to v[]: two planes requested at a time; LEAN: every tile has all
+// planes, which come one by one
+template <int NR, bool LEAN = false>
 __device__ __forceinline__ void add_planes(u64 (&v)[NR], const u64 *c, size_t count, size_t e, const ss_part_src &ps)
 {
     c += e;
-    if (ps.first_cut == 0) {   // uniform: every tile has all planes
+    if (LEAN || ps.first_cut == 0) {   // uniform: every tile has all planes
         int s = 1;
-        for (; s + 1 < ps.planes; s += 2) {
+        for (; !LEAN && s + 1 < ps.planes; s += 2) {
             u64 x[NR], y[NR];
 #pragma unroll
             for (int i = 0; i < NR; i++) {
@@ -119,7 +120,7 @@ __device__ __forceinline__ void add_planes(u64 (&v)[NR], const u64 *c, size_t co
 #pragma unroll
             for (int i = 0; i < NR; i++) v[i] = ss_add(v[i], ss_add(x[i], y[i]));
         }
-        if (s < ps.planes) {
+        for (; s < ps.planes; s++) {
             u64 x[NR];
 #pragma unroll
             for (int i = 0; i < NR; i++) x[i] = c[(size_t)s * ps.stride + (size_t)i * count];
@@ -364,7 +365,7 @@ __device__ __forceinline__ void shift_and_unmask(u64 opened, u64 ev, u64 counter
 // RED + RERAND and, with TRUNC, truncation of element e: the new shares come back in o[], their secret (what any k of
 // them reconstruct to) in `secret`
 // (em, mcount: position and plane size of this element in the message buffers, which need not be e, count)
-template <int N, int T, bool TRUNC, bool STREAM>
+template <int N, int T, bool TRUNC, bool STREAM, bool LEAN>
 __device__ __forceinline__ void reduce_truncate(size_t e, size_t count, size_t em, size_t mcount, const u64 *c,
                                                 u64 *__restrict__ msg1, u64 *__restrict__ msg2, u64 *__restrict__ umsg,
                                                 u64 *__restrict__ wsh, const ss_dr_params &dp, const ss_tr_params &tp,
@@ -381,7 +382,7 @@ __device__ __forceinline__ void reduce_truncate(size_t e, size_t count, size_t e
     // (t = 3 has no registers to spare: with the sum of planes out of its straight path the compiler spills elsewhere, n = 7 reduce +
     // truncate of 4629 elements 9.0 -> 8.6 us, over the 45-bit prime 10.2 -> 9.3)
     const bool several = ps.planes > 1;
-    if (T == 3 ? __builtin_expect(several, 0) : several) add_planes<NR>(cin, c, count, e, ps);
+    if (T == 3 ? __builtin_expect(several, 0) : several) add_planes<NR, LEAN>(cin, c, count, e, ps);
 
     // step 1, and of step 2 the sums coef[q][j] = sum_i msg1[i][q] * D binv[i][j] (j = 0: without D, see ilambda0)
     ss_sacc2 coef[K][K];
@@ -451,7 +452,8 @@ __device__ __forceinline__ void reduce_truncate(size_t e, size_t count, size_t e
 }
 
 // (t = 3: without the second bound the compiler takes 157 registers, three waves per SIMD, to no gain)
-template <int N, int T, bool TRUNC, bool STREAM>
+// LEAN: without the code for products of which only a part of the tiles is cut, see HAS_LEAN.
+template <int N, int T, bool TRUNC, bool STREAM, bool LEAN>
 __global__ __launch_bounds__(BLOCK, T == 3 ? 4 : 1) void degree_reduce_kernel(const u64 *c, u64 *__restrict__ msg1, u64 *__restrict__ msg2,
                                                               u64 *__restrict__ umsg, u64 *__restrict__ wsh, u64 *out,
                                                               u64 *__restrict__ rec, size_t count, ss_dr_params dp,
@@ -460,7 +462,7 @@ __global__ __launch_bounds__(BLOCK, T == 3 ? 4 : 1) void degree_reduce_kernel(co
     const size_t e = element_block<BLOCK>(count, count) * BLOCK + threadIdx.x;
     if (e >= count) return;
     u64 o[MAXP<N>], secret;
-    reduce_truncate<N, T, TRUNC, STREAM>(e, count, e, count, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
+    reduce_truncate<N, T, TRUNC, STREAM, LEAN>(e, count, e, count, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
 #pragma unroll
     for (int m = 0; m < MAXP<N>; m++)
         if (N != 0 || m < dp.n) out[(size_t)m * count + e] = o[m];
@@ -580,7 +582,7 @@ __device__ __forceinline__ void relu_fixed(const u64 (&x)[N], size_t em, size_t 
 // order of this kernel's threads (so that a wave writes 512 consecutive bytes of every message plane): the
 // element of thread t of block (x, y) is at position (y gridDim.x + x) 256 + t of a plane of gridDim.x
 // gridDim.y 256 positions.
-template <int N, int T, bool STREAM>
+template <int N, int T, bool STREAM, bool LEAN>
 __global__ __launch_bounds__(BLOCK) void layer_tail_kernel(const u64 *c, u64 *__restrict__ msg1, u64 *__restrict__ msg2,
                                                            u64 *__restrict__ umsg, u64 *__restrict__ wsh,
                                                            u64 *__restrict__ rmsg, u64 *__restrict__ yplain,
@@ -616,7 +618,7 @@ __global__ __launch_bounds__(BLOCK) void layer_tail_kernel(const u64 *c, u64 *__
 #pragma unroll
         for (int m = 0; m < N; m++) mbi[m] = sh_bi[(size_t)m * count + e];
         u64 secret;
-        reduce_truncate<N, T, true, STREAM>(e, count, em, mcount, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
+        reduce_truncate<N, T, true, STREAM, LEAN>(e, count, em, mcount, c, msg1, msg2, umsg, wsh, dp, tp, ps, o, secret);
         relu_fixed<N, T, STREAM>(o, em, mcount, mb, mbi, rmsg, yplain, np, r);
 #pragma unroll
         for (int p = 0; p < N; p++) {
@@ -1047,6 +1049,18 @@ hipError_t ss_launch_reconstruct(const u64 *shares, u64 *secret, size_t count, c
         else LAUNCH(8, 3);                      \
     } while (0)
 
+// Reductions with an instance without the code for cut tiles, which costs registers (n = 6: seven waves per SIMD instead of eight): what
+// tensors and products of at most two planes per tile take where it is the faster one.  Reduce + truncate + open, us, with -> without:
+// messages past the caches, 802816 elements n = 4 35.1 -> 32.3, n = 3 30.9 -> 29.1, layer tail of eight images of 64 x 56 x 56 98.0 -> 93.9;
+// n = 6, 50176 elements 8.55 -> 8.08; small tensors of t = 1, 10000 elements n = 3 3.62 -> 3.50.  Between those t = 1 is faster with it (n = 3,
+// 200704 elements 9.6 -> 9.0), as are (5,2) and t = 3 at most sizes.
+template <int N, int T>
+constexpr bool HAS_LEAN = T == 1 || (N == 0 && T == 2);
+inline bool takes_lean(const ss_part_src &ps, int t, bool streams, size_t count)
+{
+    return (ps.planes <= 1 || (ps.planes == 2 && ps.first_cut == 0)) && (t != 1 || streams || count < 65536);
+}
+
 hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out, size_t count,
                                    const ss_dr_params &dp, const ss_part_src &ps, hipStream_t stream)
 {
@@ -1059,8 +1073,12 @@ hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out,
     }
     const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
     const bool streams = (starts_halves(count) || dp.t == 1) && streams_messages((nr + n + nr * k + k * n) * count);
+    const bool lean = takes_lean(ps, dp.t, streams, count);
 #define SS_LAUNCH(NC, TC)                                                                                               \
-    hipLaunchKernelGGL((streams ? degree_reduce_kernel<NC, TC, false, true> : degree_reduce_kernel<NC, TC, false, false>), \
+    hipLaunchKernelGGL((streams ? lean ? degree_reduce_kernel<NC, TC, false, true, HAS_LEAN<NC, TC>>                        \
+                                      : degree_reduce_kernel<NC, TC, false, true, false>                                          \
+                               : lean ? degree_reduce_kernel<NC, TC, false, false, HAS_LEAN<NC, TC>>                       \
+                                      : degree_reduce_kernel<NC, TC, false, false, false>),                                       \
                        dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, \
                        out, (u64 *)nullptr, count, dp, none, ps)
     SS_SCHEME(dp.n, dp.t, SS_LAUNCH);
@@ -1075,8 +1093,12 @@ hipError_t ss_launch_degree_reduce_truncate(const u64 *c, u64 *msg1, u64 *msg2, 
     if (!fits_launch(blocks_for(count, 1))) return hipErrorInvalidConfiguration;
     const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
     const bool streams = starts_halves(count) && streams_messages((nr + n + nr * k + k * n + k + n) * count);
+    const bool lean = takes_lean(ps, dp.t, streams, count);
 #define SS_LAUNCH(NC, TC)                                                                                               \
-    hipLaunchKernelGGL((streams ? degree_reduce_kernel<NC, TC, true, true> : degree_reduce_kernel<NC, TC, true, false>), \
+    hipLaunchKernelGGL((streams ? lean ? degree_reduce_kernel<NC, TC, true, true, HAS_LEAN<NC, TC>>                        \
+                                      : degree_reduce_kernel<NC, TC, true, true, false>                                          \
+                               : lean ? degree_reduce_kernel<NC, TC, true, false, HAS_LEAN<NC, TC>>                       \
+                                      : degree_reduce_kernel<NC, TC, true, false, false>),                                       \
                        dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, u, wsh, out, rec, count, dp, tp, ps)
     SS_SCHEME(dp.n, dp.t, SS_LAUNCH);
 #undef SS_LAUNCH
@@ -1198,8 +1220,12 @@ hipError_t ss_launch_layer_tail(const u64 *c, u64 *msg1, u64 *msg2, u64 *umsg, u
     const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
     // shares in and out, mask shares, messages
     const bool streams = streams_messages((2 * n + nr + n + nr * k + k * n + k + n + nr + 1) * (size_t)B * C * HW);
+    const bool lean = streams && takes_lean(ps, dp.t, streams, (size_t)B * C * HW);
 #define SS_TAIL(NC, TC)                                                                                                \
-    hipLaunchKernelGGL((streams ? layer_tail_kernel<NC, TC, true> : layer_tail_kernel<NC, TC, false>), grid, block, 0, \
+    hipLaunchKernelGGL((!streams ? layer_tail_kernel<NC, TC, false, false>                                             \
+                        : lean  ? layer_tail_kernel<NC, TC, true, HAS_LEAN<NC, TC>>                                     \
+                                : layer_tail_kernel<NC, TC, true, false>),                                              \
+                       grid, block, 0,                                                                                 \
                        stream, c, msg1, msg2, umsg, wsh, rmsg, yplain, sh_b, sh_bi, out, (signed char *)planes, B, C, HW, \
                        party_bytes, dp, tp, np, ps)
     if (dp.n == 5 && dp.t == 2)
