@@ -62,25 +62,37 @@ __device__ __forceinline__ void store_limbs(const u64 (&y)[4], int j, F &&store)
 // thread's four loads are in flight together (a load per branch waits for each).
 // taps > 0: the contraction index of the packed operand runs (tap, channel) while the source runs (channel,
 // tap) with `taps` taps per channel (convolution weights for the kernel that reads its other operand from
-// limb planes); stride_k is then the stride of the source's own index.
+// limb planes); stride_k is then the stride of the source's own index.  tap_blocks > 0: k blocks of a tap (C a multiple of 64);
+// the taps of 64 channels, which share their cache lines, are neighbours then (in the order of the packed operand an XCD's
+// workgroups took one tap of all channels and every XCD read all of them; 3 x 3 taps, n = 5, us: 9 x 512 channels 5.1 -> 3.4, 453 x 512
+// 65 -> 48).
 __global__ __launch_bounds__(256) void pack_matrix_kernel(const u64 *__restrict__ src, v4i *__restrict__ dst,
                                                           int rows, int K, int Rb, int Kb, fdiv dRb, fdiv dKb, bool k_first,
                                                           size_t party_stride, size_t stride_r, size_t stride_k,
-                                                          size_t dst_party_stride, int taps)
+                                                          size_t dst_party_stride, int taps, int tap_blocks, fdiv dTaps)
 {
     const int b = (int)xcd_slot(blockIdx.x, gridDim.x), q = (int)fd_div((u32)b, k_first ? dKb : dRb);
-    const int rb = k_first ? q : b - q * Rb, kb = k_first ? b - q * Kb : q;
-    const int r16 = threadIdx.x & 15, kq = threadIdx.x >> 4, row = rb * 16 + r16, k0 = kb * 64 + 4 * kq;
+    const int rb = k_first ? q : b - q * Rb;
+    int kb = k_first ? b - q * Kb : q;
+    const int r16 = threadIdx.x & 15, kq = threadIdx.x >> 4, row = rb * 16 + r16;
     const u64 *s = src + (size_t)blockIdx.y * party_stride + (row < rows ? (size_t)row * stride_r : 0);
-    const int C = taps ? K / taps : 1;
     u64 y[4];
+    if (tap_blocks) {   // uniform
+        const int channels = (int)fd_div((u32)kb, dTaps), tap = kb - channels * taps;   // block of channels
+        kb = tap * tap_blocks + channels;
+        s += (size_t)(channels * 64 + 4 * kq) * taps + tap;
 #pragma unroll
-    for (int c = 0; c < 4; c++) {
-        const int k = k0 + c, ks = k >= K ? 0 : taps ? (k % C) * taps + k / C : k;
-        y[c] = s[(size_t)ks * stride_k];
+        for (int c = 0; c < 4; c++) y[c] = s[c * taps];
+    } else {
+        const int C = taps ? K / taps : 1;
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            const int k = kb * 64 + 4 * kq + c, ks = k >= K ? 0 : taps ? (k % C) * taps + k / C : k;
+            y[c] = s[(size_t)ks * stride_k];
+        }
     }
 #pragma unroll
-    for (int c = 0; c < 4; c++) y[c] = row < rows && k0 + c < K ? balanced_digits(y[c]) : 0;
+    for (int c = 0; c < 4; c++) y[c] = row < rows && kb * 64 + 4 * kq + c < K ? balanced_digits(y[c]) : 0;
     v4i *tile = dst + (size_t)blockIdx.y * dst_party_stride + ((size_t)rb * Kb + kb) * TILE + r16 + 16 * (kq >> 2);
     store_limbs(y, kq & 3, [&](int limb, v4i v) { tile[limb * 64] = v; });
 }
@@ -968,7 +980,7 @@ hipError_t ss_launch_pack_matrix(const u64 *src, void *dst, int n, int rows, int
     if (!fits_grid((long)Rb * Kb, 256)) return hipErrorInvalidConfiguration;   // (103 GB and more of tiles per party)
     hipLaunchKernelGGL(pack_matrix_kernel, dim3((unsigned)Rb * (unsigned)Kb, n), dim3(256), 0, stream, src, (v4i *)dst, rows, K, Rb,
                        Kb, make_fdiv((u32)Rb), make_fdiv((u32)Kb), stride_k == 1, party_stride, stride_r, stride_k,
-                       ss_packed_bytes(rows, K) / 16, taps);
+                       ss_packed_bytes(rows, K) / 16, taps, taps && K / taps % 64 == 0 ? K / taps / 64 : 0, make_fdiv(taps ? (u32)taps : 1));
     return hipGetLastError();
 }
 

@@ -888,7 +888,7 @@ def test_limb_tiles_and_planes_byte_for_byte(n, t, p):
         x = elements((N, K), K)
         shares, packed = s.share_packed(to_dev(x), stream_id=2)
         assert np.array_equal(packed.cpu().numpy()[: n * -(-N // 16) * -(-K // 64) * 1024 * limbs], limb_tiles(to_np(shares), limbs))
-    for Co, C, k in ((17, 64, 3), (5, 128, 2)):
+    for Co, C, k in ((17, 64, 3), (5, 128, 2), (33, 192, 1), (20, 70, 3)):
         w = elements((n, Co, C, k, k), Co)
         taps = w.reshape(n, Co, C, k * k).transpose(0, 1, 3, 2).reshape(n, Co, -1)
         assert np.array_equal(s.pack_weights_conv_taps(to_dev(w)).cpu().numpy(), limb_tiles(taps, limbs))
