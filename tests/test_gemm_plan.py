@@ -71,3 +71,33 @@ def test_planes_are_priced_by_what_a_unit_of_the_field_takes(tmp_path):
     for shape in [(5, 269, 579, 3245, 0), (3, 320, 1800, 576, 1), (4, 585, 310, 1010, 0)]:
         p = plans[6](*shape)
         assert p.slots == 1 and not p.ksplit and plans[8](*shape).slots > 1, shape
+
+
+def test_products_of_the_gpu_tests_take_what_these_are_written_for(tmp_path):
+    """Kernel (waves of a 16 x 16 tile, 0: tiles of 64 x 64), planes and whole tiles ahead, per product of
+    tests/test_gpu_pending_product.py.  A change of the rules that moves one of them asks for another shape there."""
+    import test_gpu_pending_product as g
+    plans = {limbs: planner(tmp_path, limbs) for limbs in (8, 6)}
+
+    def taken(limbs, *shape):
+        p = plans[limbs](*shape)
+        return p.ksplit, p.slots, p.whole
+
+    def conv(limbs, n, B, C, H, W, Co, k, stride, pad):
+        Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+        return taken(limbs, n, Co, B * Ho * Wo, C * k * k, C if stride > 1 else 1)
+
+    assert [conv(8, 5, *c) for c in g.CONV_CASES[:6]] == [(0, 5, 0), (0, 1, 0), (2, 1, 0), (0, 27, 0), (4, 1, 0), (4, 1, 0)]
+    assert [conv(8, 3, *g.CONV_CASES[i]) for i in (0, 3)] == [(0, 8, 0), (0, 40, 0)]
+    assert [conv(8, 7, *g.CONV_CASES[i]) for i in (0, 3)] == [(0, 4, 0), (0, 20, 0)]
+    assert [conv(6, 5, *g.CONV_CASES[i]) for i in (0, 3, 6)] == [(4, 1, 0), (8, 1, 0), (0, 11, 0)]
+    assert [conv(8, 5, 1, C, H, H, Co, 3, 1, 1) for C, H, Co in g.FULL_RANGE] == [(8, 2, 0), (0, 27, 0), (0, 5, 0)]
+    for limbs, n in ((8, 5), (6, 3)):
+        (M, K, N), (B, C, H, Co) = g.whole_ahead_shapes(n)
+        assert taken(limbs, n, M, N, K, 0) == conv(limbs, n, B, C, H, H, Co, 3, 1, 1) == (0, 2, 256)
+    n, M, K, N = g.RAGGED
+    assert taken(8, n, M, N, K, 0) == (0, 2, 256) and plans[8](n, M, N, K, 0).tiles >= 3 * 256
+    # one, two, four and eight waves, and a contraction in parts
+    small = [taken(limbs, n, M, N, K, 0) for limbs, n in ((8, 5), (6, 3), (8, 8)) for M, K, N in g.SMALL_DENSE]
+    small += [conv(limbs, n, *c) for limbs, n in ((8, 5), (6, 3), (8, 8)) for c in g.SMALL_CONV]
+    assert {k for k, _, _ in small} >= {1, 2, 4, 8} and max(slots for k, slots, _ in small if k) > 1

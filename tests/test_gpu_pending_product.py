@@ -88,14 +88,16 @@ def check_consumers(s, p, y, shape, leave_product, f=12, seed=0):
         assert bool(torch.equal(planes6.view(n, per)[:, :data], ref.view(n, per)[:, :data]))
 
 
+# (tests/test_gemm_plan.py holds the kernel and the planes that each of the products here is computed with)
 CONV_CASES = [
-    # B, C, H, W, Co, k, stride, pad
-    (1, 256, 14, 14, 256, 3, 1, 1),     # 80 tiles of 36 k blocks: every tile split over several workgroups
+    # B, C, H, W, Co, k, stride, pad; over the 61-bit prime, five parties:
+    (1, 256, 14, 14, 256, 3, 1, 1),     # 80 tiles of 36 k blocks: every tile split over several workgroups, five planes
     (1, 64, 14, 14, 1024, 1, 1, 0),     # more tiles than workgroups, one k block
-    (1, 256, 14, 14, 64, 1, 1, 0),      # few tiles, four k blocks
-    (1, 512, 7, 7, 128, 3, 1, 1),       # 49 pixels: one ragged column tile
-    (2, 128, 9, 7, 65, 3, 2, 1),        # ragged rows and columns, stride 2
+    (1, 256, 14, 14, 64, 1, 1, 0),      # tiles of 16 x 16, two waves each
+    (1, 512, 7, 7, 128, 3, 1, 1),       # 49 pixels: one ragged column tile, 27 planes
+    (2, 128, 9, 7, 65, 3, 2, 1),        # tiles of 16 x 16, ragged rows and columns, stride 2
     (1, 64, 5, 5, 7, 3, 1, 1),          # at most 16 output channels
+    (2, 512, 9, 9, 65, 3, 1, 1),        # over the 45-bit prime too in parts: eleven planes
 ]
 
 
@@ -103,7 +105,9 @@ CONV_CASES = [
 def test_conv_product_on_planes_then_every_consumer(n, t, p):
     s = SSNet(n, t, f=12, seed=91, p=p)
     bits = 11 if p == binding.P45 else 15
-    cases = CONV_CASES if (n, t, p) == (5, 2, binding.P61) else CONV_CASES[:1] + CONV_CASES[3:5]
+    cases = CONV_CASES[:6] if (n, t, p) == (5, 2, binding.P61) else CONV_CASES[:1] + CONV_CASES[3:5]
+    if p == binding.P45:
+        cases = cases + CONV_CASES[6:]
     for (B, C, H, W, Co, k, stride, pad) in cases:
         say("conv product", n, t, hex(p), B, C, H, W, Co, k, stride, pad)
         xs = orc.share(small_secrets((B, C, H, W), 1, bits, p), n, t, p, 91, 5)
@@ -141,21 +145,30 @@ def test_prepacked_products_then_every_consumer(n, t, p):
         check_consumers(s, p, y, (M, N, 1, 1), lambda: s.linear_product_prepacked(tiles, wp, M, K, N), seed=92)
 
 
-def test_pending_product_full_range_operands_and_plane_sums():
-    """Uniform field elements as operands (what shares are), a contraction long enough that every tile is
-    shared: the reduction of the pending product equals the reduction of the oracle's product."""
+# C, H, Co of 3 x 3 convolutions, five parties over the 61-bit prime
+FULL_RANGE = [(512, 7, 96),     # tiles of 16 x 16, eight waves each, the contraction in two parts
+              (512, 7, 128),    # tiles of 64 x 64, every one shared by up to 26 workgroups: 27 planes, most of them zeros
+              (256, 14, 256)]   # five planes
+
+
+@pytest.mark.parametrize("C,H,Co", FULL_RANGE)
+def test_pending_product_full_range_operands_and_plane_sums(C, H, Co):
+    """Uniform field elements as operands (what shares are), a contraction long enough that every tile has
+    parts: the reduction of the pending product equals the reduction of the oracle's product."""
     n, t, p = 5, 2, binding.P61
     s = SSNet(n, t, f=13, seed=93)
-    B, C, H, W, Co, k = 1, 512, 7, 7, 96, 3
+    B, W, k = 1, H, 3
     xs, ws = field_uniform((n, B, C, H, W), 7), field_uniform((n, Co, C, k, k), 8)
     y = orc.conv(xs, ws, 1, 1, p)
-    s.conv_product_planes(s.split_planes(to_dev(xs)), s.pack_weights_conv_taps(to_dev(ws)), B, C, H, W, Co, k, k, 1, 1)
+    planes, wp = s.split_planes(to_dev(xs)), s.pack_weights_conv_taps(to_dev(ws))
+    s.conv_product_planes(planes, wp, B, C, H, W, Co, k, k, 1, 1)
     out = torch.empty((n, B * Co * H * W), dtype=torch.int64, device="cuda")
     s.degree_reduce(None, stream_id=1, out=out)
     assert np.array_equal(to_np(out), orc.degree_reduce(y.reshape(n, -1), n, t, p, 93, 1))
     # repeated launches give the same bits (planes are rewritten in full every time)
-    for _ in range(20):
-        s.conv_product_planes(s.split_planes(to_dev(xs)), s.pack_weights_conv_taps(to_dev(ws)), B, C, H, W, Co, k, k, 1, 1)
+    for i in range(20):
+        s._ws[binding.WS_HEADER_BYTES:].fill_(1 + 7 * i)
+        s.conv_product_planes(planes, wp, B, C, H, W, Co, k, k, 1, 1)
         again = torch.empty_like(out)
         s.degree_reduce(None, stream_id=1, out=again)
         assert bool(torch.equal(again, out))
@@ -185,14 +198,20 @@ def test_pending_product_errors():
     assert ei.value.code == binding.EINVAL
 
 
+def whole_ahead_shapes(n):
+    """(M, K, N) of a dense layer: three row tiles, the last one ragged; (B, C, H, Co) of a 3 x 3 convolution"""
+    per = -(-560 // n)                                   # tiles of a party
+    return (187, 640, 64 * (-(-per // 3)) - 37), (-(-64 * per // (2 * 14 * 14)), 64, 14, 128)
+
+
 @pytest.mark.parametrize("n,t,p", [(5, 2, binding.P61), (3, 1, binding.P45)])
 def test_products_with_whole_tiles_ahead_of_the_cut_ones(n, t, p):
-    """Tiles for two rounds of the chip and more: all but the last 256 to 511 lie in the first plane alone.  Ragged rows
+    """Tiles for two rounds of the chip and more: the first 256 lie in the first plane alone, the others in two.  Ragged rows
     and columns, columns that run over several images, and the same product as a tensor (the parts added up)."""
     s = SSNet(n, t, f=12, seed=94, p=p)
     bits = 11 if p == binding.P45 else 15
-    per = -(-560 // n)                                   # tiles of a party
-    M, K, N = 130, 320, 64 * (-(-per // 3)) - 37         # three row tiles, the last one ragged
+    (M, K, N), (B, C, H, Co) = whole_ahead_shapes(n)
+    assert s.lib.ssnet_product_bytes_linear(s._ctx, M, K, N) == 2 * 8 * n * M * N + 255 & ~255
     say("dense product, whole tiles first", n, t, hex(p), M, K, N)
     x = small_secrets((M, K), 5, bits, p)
     ws = orc.share(small_secrets((K, N), 6, bits - 2, p), n, t, p, 94, 9)
@@ -201,8 +220,7 @@ def test_products_with_whole_tiles_ahead_of_the_cut_ones(n, t, p):
     wp = s.pack_weights_linear(to_dev(ws))
     check_consumers(s, p, y, (M, N, 1, 1), lambda: s.linear_product_prepacked(tiles, wp, M, K, N), seed=94)
     assert np.array_equal(to_np(s.linear_mod_prepacked(tiles, wp, M, K, N)), y)
-    C, Co, H, k = 64, 128, 14, 3
-    B = -(-64 * per // (2 * H * H))
+    k = 3
     say("conv product, whole tiles first", n, t, hex(p), B, C, H, Co)
     xs = orc.share(small_secrets((B, C, H, H), 1, bits, p), n, t, p, 94, 5)
     ws = orc.share(small_secrets((Co, C, k, k), 2, bits - 2, p), n, t, p, 94, 6)
@@ -285,12 +303,15 @@ def test_second_operand_past_the_last_level(p, N):
         assert np.array_equal(to_np(got), want[:, :, :cols])
 
 
+RAGGED = (7, 304, 307, 1347)   # n, M, K, N
+
+
 def test_whole_tiles_stop_earlier_where_ragged_ones_shorten_the_ranges():
-    """1041 ragged tiles of one column: with 768 of them whole the ranges behind would be shorter than a full tile.  Workspace of
-    two planes, the product as a tensor and through a reduction."""
-    n, M, K, N = 3, 347 * 64 - 5, 128, 48
-    s = SSNet(n, 1, f=12, seed=3)
-    assert s.lib.ssnet_product_bytes_linear(s._ctx, M, K, N) <= 2 * 8 * n * M * N + 256
+    """770 tiles with a ragged last column each: with 512 of them whole the ranges behind would be shorter than a full tile, and
+    three of them could meet in one.  Workspace of two planes, the product as a tensor and through a reduction."""
+    n, M, K, N = RAGGED
+    s = SSNet(n, 3, f=12, seed=3)
+    assert s.lib.ssnet_product_bytes_linear(s._ctx, M, K, N) == 2 * 8 * n * M * N + 255 & ~255
     x, w = field_uniform((n, M, K), 1), field_uniform((n, K, N), 2)
     y = orc.linear(x, w, binding.P61)
     d, wp = to_dev(x), s.pack_weights_linear(to_dev(w))
