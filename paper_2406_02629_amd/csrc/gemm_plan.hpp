@@ -88,7 +88,7 @@ inline gemm_plan plan_ksplit(int n, int rows, int cols, int Kb, double *busy, do
 // tiles on.  Against the 16-row kernel, n = 5 / n = 3 / n = 3 over the 45-bit prime, us (rows x columns x contraction): 4 x 4096 x 512
 // 16.7 -> 17.2 / 12.2 -> 11.4 / 9.3 -> 9.8; 1 x 1000 x 2048 17.3 -> 21.7 / 13.1 -> 13.2 / 10.0 -> 9.6.
 //
-// Weights from memory, product and reduction together, fitted to 1130 timings of both kernels (n = 3 to 7, both fields): 1 us per 22 MB
+// Weights from memory, product and reduction together, fitted to 1680 timings of both kernels (n = 3 to 7, both fields): 1 us per 20 MB
 // of packed operands; a last row tile that is not full makes the big kernel's units shorter; 0.6 us and the loads of the consumer
 // for every plane it leaves.  A convolution that reads limb planes with a stride finds the 16 pixels of a block in twice the
 // cache lines or more, whose other halves belong to the next taps, all channels later: every tile of 16 x 16 pays for that by itself, the
@@ -108,17 +108,18 @@ inline bool ksplit_is_faster(const gemm_plan &k, const gemm_plan &p, double busy
     if (SS_NLIMB == 8 ? busy * 5.87 >= big + 12.7 : busy * 6.2 >= big + 62) return false;
     double units = busy;
     if (gather > 1) {
-        const double far = SS_NLIMB == 8 ? 0.1 + 0.25 * log2(gather / 64.0) : 0.25 + 0.22 * log2(gather / 64.0);
-        // (waves that take neighbouring tiles share what they read of the pixels)
-        const double held = (1 + far * (k.ksplit == 1 ? 0.3 : k.ksplit == 2 ? 0.75 : 1.0)) * spread;
+        const double far = SS_NLIMB == 8 ? 0.05 + 0.20 * log2(gather / 64.0) : 0.10 + 0.20 * log2(gather / 64.0);
+        // (four waves on neighbouring tiles share what they read of the pixels)
+        const double held = (1 + (k.ksplit == 1 ? 0.25 : 1.0) * far) * spread;
         if (held > units) units = held;
     }
     const long Rb = (rows + 15) / 16, packed = Rb + (gather ? 0 : (cols + 15) / 16);   // blocks of the packed operands
-    const double operand_us = (double)n * packed * p.Kb * (SS_NLIMB << 10) / 22e6;
-    const double plane_us = 0.6 + (double)n * rows * cols / p.tiles * (p.tiles - p.whole) * 8 / 5e6;
+    const double operand_us = (double)n * packed * p.Kb * (SS_NLIMB << 10) / 20e6;
+    const double plane_us = 0.62 + (double)n * rows * cols / p.tiles * (p.tiles - p.whole) * 8 / 5e6;
     const double unit = Rb == 4 * p.RT ? 1.0 : 0.86;
-    const double ksplit_us = operand_us + (SS_NLIMB == 8 ? 1.8 + 0.80 * units : 3.9 + 0.47 * units);
-    const double big_us = (SS_NLIMB == 8 ? 3.9 + 0.145 * unit * big : 5.4 + 0.095 * unit * big) + (all_whole ? 0 : (p.slots - 1) * plane_us);
+    // (waves of one tile share no operand)
+    const double ksplit_us = operand_us + (k.ksplit >= 4 ? 1.13 : 1.0) * (SS_NLIMB == 8 ? 1.6 + 0.83 * units : 3.9 + 0.46 * units);
+    const double big_us = (SS_NLIMB == 8 ? 6.0 + 0.145 * unit * big : 5.4 + 0.095 * unit * big) + (all_whole ? 0 : (p.slots - 1) * plane_us);
     return ksplit_us < big_us;
 }
 
