@@ -985,8 +985,8 @@ constexpr size_t LANES_MAX_COUNT = 16 * 1024;
 // lies there too (at 64, 128, 600 MB stacks and single calls are 0 to 8 % slower).  The reductions' many planes only where they
 // start on halves of cache lines: smaller parts past the caches cost more, whole halves do not.  Reduce + truncate, us, streamed /
 // cached, with planes 1, 2 or 4 elements off a line, then 8: n = 5, 1.2 M elements 125 / 108, 91 / 99; n = 7, 2.6 M 430 / 390, 355 / 388;
-// n = 4, 2.4 M 124 / 114, 100 / 103.  The reduction alone of t = 1 sends the fewest planes and is faster past the caches everywhere:
-// n = 4, 2.3 M elements 2 off 80 / 93, n = 3, 2.7 M 78 / 82.
+// n = 4, 2.4 M 124 / 114, 100 / 103.  The reduction alone of t = 1 sends the fewest planes and off the halves is faster past
+// the caches from 300 MB on: n = 4, 2.3 M elements 2 off 80 / 93, n = 3, 2.7 M 78 / 82, 1.9 M (269 MB) 56 / 50.
 inline bool streams_messages(size_t words) { return words * sizeof(u64) > ((size_t)256 << 20); }
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -1088,7 +1088,8 @@ hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out,
         return hipGetLastError();
     }
     const size_t k = dp.t + 1, nr = 2 * dp.t + 1, n = dp.n;
-    const bool streams = (starts_halves(count) || dp.t == 1) && streams_messages((nr + n + nr * k + k * n) * count);
+    const size_t words = (nr + n + nr * k + k * n) * count;
+    const bool streams = starts_halves(count) ? streams_messages(words) : dp.t == 1 && streams_messages(words - words / 8);
     const bool lean = takes_lean(ps, dp.t, streams, count);
 #define SS_LAUNCH(NC, TC)                                                                                               \
     hipLaunchKernelGGL((streams ? lean ? degree_reduce_kernel<NC, TC, false, true, HAS_LEAN<NC, TC>>                        \
