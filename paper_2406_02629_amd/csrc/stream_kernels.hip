@@ -706,7 +706,10 @@ __global__ __launch_bounds__(BLOCK) void tail_direct_kernel(const u64 *c, const 
 // it as in truncation steps 2 and 3.  Same residues in `out` (and `rec`) as the
 // protocol kernels; no message is formed, so this is not what the parties of the
 // protocol compute, only what they end up with.
-template <int N, int T>
+// SEVERAL: the product is in several planes.  Tensors and products of one plane take the instance without the code that adds them up:
+// it holds no registers for it and does not wait for the launch's arguments to know (300000 elements, n = 3 5.10 -> 4.60 us, n = 5 over
+// the 45-bit prime 7.42 -> 6.72; the reductions with messages gain nothing by it, t = 3 loses up to 15 %).
+template <int N, int T, bool SEVERAL>
 __global__ __launch_bounds__(BLOCK) void reduce_truncate_direct_kernel(const u64 *c, u64 *out, u64 *__restrict__ rec,
                                                                        size_t count, size_t first,
                                                                        ss_nl_params open_all, ss_tr_params tp,
@@ -714,12 +717,11 @@ __global__ __launch_bounds__(BLOCK) void reduce_truncate_direct_kernel(const u64
 {
     const size_t e = first + element_block<BLOCK>(min(count - first, LAUNCH_ELEMENTS), count) * BLOCK + threadIdx.x;   // from element `first` on
     if (e >= count) return;
-    // (the shares are requested before it is known whether there are further planes: that takes the launch's arguments, which arrive
-    // as late as an element.  n = 5, 50176 elements 3.16 -> 3.01 us; after a product in eight planes, 512 x 49 x 4608, 49 -> 43 us)
+    // (the shares are requested ahead of the planes' bounds: after a product in eight planes, 512 x 49 x 4608, 49 -> 43 us)
     u64 cin[2 * T + 1];
 #pragma unroll
     for (int i = 0; i < 2 * T + 1; i++) cin[i] = c[(size_t)i * count + e];
-    if (ps.planes > 1) add_planes(cin, c, count, e, ps);
+    if constexpr (SEVERAL) add_planes(cin, c, count, e, ps);
     ss_sacc2 acc;
     acc.clear();
 #pragma unroll
@@ -1206,7 +1208,8 @@ hipError_t ss_launch_reduce_truncate_direct(const u64 *c, u64 *out, u64 *rec, si
                                             const ss_tr_params &tp, const ss_part_src &ps, hipStream_t stream)
 {
 #define SS_LAUNCH(NC, TC)                                                                                       \
-    hipLaunchKernelGGL((reduce_truncate_direct_kernel<NC, TC>), grid, dim3(BLOCK), 0, stream, c, out, rec, count, first, \
+    hipLaunchKernelGGL((ps.planes > 1 ? reduce_truncate_direct_kernel<NC, TC, true> : reduce_truncate_direct_kernel<NC, TC, false>), \
+                       grid, dim3(BLOCK), 0, stream, c, out, rec, count, first, \
                        open_all, tp, ps)
     for_each_launch(count, [&](size_t first, dim3 grid) { SS_SCHEME(tp.n, tp.t, SS_LAUNCH); });
 #undef SS_LAUNCH
