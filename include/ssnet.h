@@ -184,8 +184,11 @@ int ssnet_conv_mod_planes(ssnet_ctx *ctx, const void *d_planes, const void *d_w_
  * batch-1 network are small, a product kernel then has fewer output tiles than
  * the chip has compute units and splits the contraction over them, and in this
  * form it does not gather the pieces: every workgroup stores what it has, as
- * planes whose sum mod p is the product, and the reduction adds the planes while
- * it reads them.  Nothing is exchanged or waited for inside the product kernel.
+ * planes, and the reduction adds them while it reads.  A tile of the product that
+ * was cut is the sum mod p of its places in all planes; one that a single
+ * workgroup computed lies in the first plane alone, and its places in the further
+ * ones may hold anything: they are neither written nor read.  Nothing is exchanged
+ * or waited for inside the product kernel.
  *   ssnet_*_product_*: same operands, shapes and checks as ssnet_linear_mod_prepacked,
  *     ssnet_conv1x1_mod_prepacked and ssnet_conv_mod_planes, but no d_y: the
  *     product (count = M*N, resp. B*Co*Ho*Wo elements per party) becomes the

@@ -376,8 +376,9 @@ __device__ __forceinline__ u64 fold_diagonals(const v4i (&acc)[15], int r)
 // bound(s + 1), bound(s) = cost0 + floor(s (cost - cost0) / G).  (cost - cost0) / G >= SS_UNIT_COST + SS_FOLD_COST, the
 // largest step between two unit starts, so no range is empty.
 //
-// Where there are tiles for several rounds of the chip, the workgroups first take equal runs of whole tiles and only the
-// last 256 to 511 tiles are dealt by cost: the others need no second plane.
+// Where there are tiles for several rounds of the chip, the workgroups first take equal runs of whole tiles and the rest is dealt by
+// cost: the last 256 to 511 tiles, or one or more rounds besides (all tiles, if it comes to that) where ragged tiles among them would
+// leave ranges shorter than a full tile.  The tiles taken whole need no second plane.
 __device__ __forceinline__ unsigned range_bound(const gemm_args &g, unsigned s)
 {
     return g.cost0 + s * g.share + fd_div(s * g.rest, g.dG);   // s <= G <= 256, rest < G

@@ -43,7 +43,8 @@ inline unsigned unit_cost(int vb)
 constexpr unsigned long long SS_BYTES_PER_COST = SS_NLIMB == 8 ? 750 * 1000 : 425 * 1000;
 
 // Plan for gemm_ksplit_kernel and what it takes, in units (16 x 16, one k block, four side by side on a CU): a CU's waves get
-// their operand blocks out of the caches at about 30 bytes per clock, so a launch lasts as long as the fullest CU has units.
+// their operand blocks out of the caches, 64 KB (48 KB over the 45-bit prime) per unit in about 0.83 us (0.46 us), so a launch lasts as
+// long as the fullest CU has units.
 inline gemm_plan plan_ksplit(int n, int rows, int cols, int Kb, double *busy, double *spread)
 {
     gemm_plan best = {};
@@ -164,12 +165,11 @@ inline gemm_plan plan_gemm(int n, int rows, int cols, int K, int gather)
         // every range must hold at least one unit start
         const unsigned most = p.cost / step;
         p.G = (int)(most < SS_GEMM_CUS ? (most ? most : 1) : SS_GEMM_CUS);
-        // Tiles for two rounds and more: all but the last 256 to 511 of them whole, which leaves the ranges longer than a
-        // tile and so two planes, as without.  (A workgroup whose whole tiles are ragged ones idles a little: rows of
-        // tiles are long where there are that many.)
+        // Tiles for two rounds and more: all but the last 256 to 511 of them whole, as long as that leaves the ranges longer than
+        // a full tile and so two planes, as without; where ragged tiles leave them shorter, whole tiles are given up a round at a
+        // time, all of them if need be.  (A workgroup whose whole tiles are ragged ones idles a little: rows of tiles are long
+        // where there are that many.)
         if (!p.skinny && p.Kb > 1 && p.tiles >= 2 * SS_GEMM_CUS) {
-            // (Where ragged tiles leave the ranges shorter than a full tile, one round less: two planes are what the workspace
-            // of such a product has held all along.)
             p.whole = (unsigned)(p.tiles / SS_GEMM_CUS) * SS_GEMM_CUS;
             do {
                 p.whole -= SS_GEMM_CUS;

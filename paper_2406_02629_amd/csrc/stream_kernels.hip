@@ -17,12 +17,13 @@ constexpr int BLOCK = 256;
 constexpr size_t LAUNCH_ELEMENTS = (size_t)1 << 31;   // of a tensor that goes in several launches, one thread each
 
 // Block of elements that a workgroup of an element-wise kernel takes.  Where the planes of a tensor do not start on a cache
-// line (starts_lines) the blocks share lines, and workgroups are dealt round-robin to the 8 XCDs, so that neighbours write
-// their parts of a line from two L2s.  There 64 consecutive blocks go to one XCD (8 are as good for most, all of a plane's
-// eighth is worse for the larger tensors): n = 7, t = 3 reduce + truncate of 300001 elements on changing inputs 53 -> 48 us,
-// sharing among three of 2^24 + 3 118 -> 95 us, reconstruction from two 88 -> 78 us.  PER elements of a launch's `count` per
-// workgroup; planes of `plane` elements.  (The grid is worked out from the count, which arrives in registers: read from the launch it
-// puts a memory access in front of a small kernel's first load.)
+// line (starts_lines, which goes by the plane's size: a tensor whose first word is off a line counts by its planes alone) the blocks
+// share lines, and workgroups are dealt round-robin to the 8 XCDs, so that neighbours write their parts of a line from two L2s.
+// There 64 consecutive blocks go to one XCD (8 are as good for most, all of a plane's eighth is worse for the larger tensors):
+// n = 7, t = 3 reduce + truncate of 640003 elements 123 -> 100 us with operands that change from call to call (300001: 45.0 -> 44.7,
+// where only the same call repeated gains, 53 -> 48), sharing among three of 2^24 + 3 118 -> 95 us, reconstruction from two 88 -> 78 us.
+// PER elements of a launch's `count` per workgroup; planes of `plane` elements.  (The grid is worked out from the count, which arrives
+// in registers: read from the launch it puts a memory access in front of a small kernel's first load.)
 __host__ __device__ __forceinline__ bool starts_lines(size_t count) { return count % 16 == 0; }
 __host__ __device__ __forceinline__ bool starts_halves(size_t count) { return count % 8 == 0; }   // of cache lines
 template <int PER>
@@ -172,9 +173,10 @@ __device__ __forceinline__ void draw_coeffs(u64 (&c)[MAXD], const u64 *keys, int
 // the reduction makes no difference beyond that of two runs (long and short, 2^20: 6.3 and 6.2, 2^24: 75.5 and 75.4, 2^26:
 // 362 and 366, 2^28: 1444 and 1453 us).  Five planes that do not start on halves of cache lines go through the caches, which put the
 // parts of a line together (2^24 + 3 elements 185 -> 148 us, 2^22 + 2 40 -> 37 us; on halves past them and in the order of the
-// launch: 438888 elements 5.5 -> 4.7 us, 5.8 M 43.5 -> 41.1;
-// three planes 95 and 92, 21 and 25 us: past them),
-// and odd counts, one element per thread, have the schemes fixed too (2^20-odd elements, n = 3: 11 -> 7 us).
+// launch: 438888 elements 5.5 -> 4.7 us, 5.8 M 43.5 -> 41.1; three planes 95 and 92, 21 and 25 us: past them).  That choice, a branch
+// before each of the five stores, also keeps them where their plane is ready; without it the compiler gathers four at the end, and planes
+// on the lines are written slower (2^28 elements 2160 -> 2076 us, 2^25 271 -> 260, 2^24 equal).
+// Odd counts, one element per thread, have the schemes fixed too (2^20-odd elements, n = 3: 11 -> 7 us).
 template <int VEC, int NC>
 constexpr int SHARE_BLOCK = VEC == 2 && NC == 5 ? 64 : BLOCK;
 template <int VEC, int NC, int DC>
@@ -989,6 +991,9 @@ constexpr size_t LANES_MAX_COUNT = 16 * 1024;
 // cached, with planes 1, 2 or 4 elements off a line, then 8: n = 5, 1.2 M elements 125 / 108, 91 / 99; n = 7, 2.6 M 430 / 390, 355 / 388;
 // n = 4, 2.4 M 124 / 114, 100 / 103.  The reduction alone of t = 1 sends the fewest planes and off the halves is faster past
 // the caches from 300 MB on: n = 4, 2.3 M elements 2 off 80 / 93, n = 3, 2.7 M 78 / 82, 1.9 M (269 MB) 56 / 50.
+// The other kernels go by the size alone.  Streamed / cached with planes 1 or 2 off a line and operands that change: reconstruction, m = 3,
+// 349 MB 55 / 60, 670 MB 103 / 114; truncation, n = 5, 349 MB 63 / 73, 670 MB 145 / 136; ReLU, n = 5, 349 MB 84 / 88, 670 MB 163 / 160: past
+// 600 MB the last two are 0 to 15 % faster cached there.
 inline bool streams_messages(size_t words) { return words * sizeof(u64) > ((size_t)256 << 20); }
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
