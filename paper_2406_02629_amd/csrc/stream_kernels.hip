@@ -104,7 +104,9 @@ __device__ __forceinline__ int first_cut_party(const ss_part_src &ps, size_t e)
 }
 
 // the further planes of the first NR shares of element e, added to v[]: two planes requested at a time; LEAN: every tile has all
-// planes, which come one by one
+// planes, which come one by one.  (For three shares the last plane is a loop as well, though it runs once: written straight the kernels
+// are slower on tensors too, reduce + truncate of 802816 elements, n = 4, 31.7 -> 34.1 us.  For five it makes no difference, for
+// seven the loop spills eight more scalar registers: over the 45-bit prime 43565 elements, n = 7, 11.6 -> 11.9 us.)
 template <int NR, bool LEAN = false>
 __device__ __forceinline__ void add_planes(u64 (&v)[NR], const u64 *c, size_t count, size_t e, const ss_part_src &ps)
 {
@@ -127,6 +129,7 @@ __device__ __forceinline__ void add_planes(u64 (&v)[NR], const u64 *c, size_t co
             for (int i = 0; i < NR; i++) x[i] = c[(size_t)s * ps.stride + (size_t)i * count];
 #pragma unroll
             for (int i = 0; i < NR; i++) v[i] = ss_add(v[i], x[i]);
+            if (!LEAN && NR > 3) break;
         }
         return;
     }
@@ -1074,7 +1077,7 @@ hipError_t ss_launch_reconstruct(const u64 *shares, u64 *secret, size_t count, c
 
 // Reductions with an instance without the code for cut tiles, which costs registers (n = 6: seven waves per SIMD instead of eight): what
 // tensors and products of at most two planes per tile take where it is the faster one.  Reduce + truncate + open, us, with -> without:
-// messages past the caches, 802816 elements n = 4 35.1 -> 32.3, n = 3 30.9 -> 29.1, layer tail of eight images of 64 x 56 x 56 98.0 -> 93.9;
+// messages past the caches, 1605632 elements n = 4 66.2 -> 64.7, layer tail of eight images of 64 x 56 x 56, n = 3, 98.0 -> 93.9;
 // n = 6, 50176 elements 8.55 -> 8.08; small tensors of t = 1, 10000 elements n = 3 3.62 -> 3.50.  Between those t = 1 is faster with it (n = 3,
 // 200704 elements 9.6 -> 9.0), as are (5,2) and t = 3 at most sizes.
 template <int N, int T>
