@@ -18,7 +18,6 @@
 #include "kernels.hpp"
 #include "eval.hpp"
 #include "digits.hpp"
-#include "gemm_plan.hpp"
 
 #include <hip/hip_ext.h>
 
@@ -785,6 +784,85 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void gemm_ksplit_kernel(gem
     }
 }
 
+// Products of a few to some tens of units per CU: four waves share two row blocks and two column blocks through LDS, so that the
+// caches give 32 KB (24 KB over the 45-bit prime) for four units of 16 x 16, where a wave of the kernel above takes them 64 KB (48 KB)
+// by itself.  A workgroup owns a tile of 32 x 32 and one of `runs` equal runs of its k blocks (each run has a plane); wave w
+// copies block w.  There is one stage: the operands of a unit go to registers, and the next ones are copied while the MFMAs run; three
+// workgroups on a CU (four) fill each other's waits (two stages and two workgroups: 16.6 -> 17.4 us for 1024 x 196 x 256, n = 5, which waves on
+// their own take 19.5 for; its matrix work lasts 8.2).  What the first copies need arrives in registers: the rest of the arguments
+// is loaded meanwhile.
+// (blocks: row blocks | column blocks << 16; ks: k blocks | runs << 16; reciprocals of the tiles along the shorter and the longer side and of
+// the runs; G: workgroups, which gridDim would load from memory)
+template <bool IMPLICIT>
+__global__ __launch_bounds__(256, NL == 8 ? 3 : 4) void gemm_square_kernel(const v4i *A, const v4i *B, u32 blocks, u32 ks, u32 minor_m, u32 minor_s,
+                                                                          u32 major_m, u32 major_s, u32 runs_m, u32 runs_s, u32 G, gemm_args g)
+{
+    __shared__ v4i lds[4 * TILE];   // 2 row blocks + 2 column blocks
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wr = wave & 1, wc = wave >> 1;
+    const int Rb = (int)(blocks & 0xffff), Cb = (int)(blocks >> 16), Kb = (int)(ks & 0xffff);
+    const unsigned runs = ks >> 16;
+    // party, run, longer side of the product, shorter side: workgroups that read the same blocks are neighbours, and those of a run read
+    // its share of them only (run by run against run fastest: 512 x 392 x 2048, n = 5, two runs, 103 -> 101 us; 512 x 196 x 1024 29.6 -> 29.0)
+    const unsigned place = xcd_slot(blockIdx.x, G), q = fd_div(place, fdiv{minor_m, minor_s}), upper = fd_div(q, fdiv{major_m, major_s});
+    const unsigned Rt = (unsigned)(Rb + 1) / 2, Ct = (unsigned)(Cb + 1) / 2, minor = place - q * min(Rt, Ct), major = q - upper * max(Rt, Ct);
+    const int party = (int)fd_div(upper, fdiv{runs_m, runs_s}), rt = (int)(Rt < Ct ? minor : major), ct = (int)(Rt < Ct ? major : minor);
+    const unsigned run = upper - (unsigned)party * runs;
+    const int k0 = (int)fd_div(run * (unsigned)Kb, fdiv{runs_m, runs_s}), k1 = (int)fd_div((run + 1) * (unsigned)Kb, fdiv{runs_m, runs_s});
+
+    const bool row_block = wave < 2;   // this wave copies one of these (else a column block)
+    wave_src src = {nullptr, 0, 0};
+    if (row_block || !IMPLICIT) {
+        const int count = row_block ? Rb : Cb, block = row_block ? rt * 2 + wave : ct * 2 + wave - 2;
+        src.p = (row_block ? A : B) + ((size_t)party * count + min(block, count - 1)) * Kb * TILE + lane;
+    } else {
+        src = column_source<IMPLICIT>(g, party, ct * 2 + wave - 2, lane);
+    }
+    v4i *mine = lds + wave * TILE;
+    auto copy = [&](int kb) {
+        unsigned qs = 64;
+        const v4i *p = row_block || !IMPLICIT ? src.p + (size_t)kb * TILE : column_base<IMPLICIT>(g, src, kb, lane, qs);
+#pragma unroll
+        for (int i = 0; i < NL; i++) __builtin_amdgcn_global_load_lds(p + (size_t)i * qs, mine + i * 64, 16, 0, 0);
+    };
+    copy(k0);
+    const int rb = rt * 2 + wr, cb = ct * 2 + wc;
+    const bool inside = rb < Rb && cb < Cb;
+    v4i acc[ND];
+#pragma unroll
+    for (int s = 0; s < ND; s++) acc[s] = (v4i){0, 0, 0, 0};
+    const v4i *sa = lds + wr * TILE + lane, *sb = lds + (2 + wc) * TILE + lane;
+    for (int kb = k0; kb < k1; kb++) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's block is in LDS
+        __syncthreads();                      // everyone's is
+        v4i a[NL], b[NL];
+#pragma unroll
+        for (int i = 0; i < NL; i++) {
+            a[i] = sa[i * 64];
+            b[i] = sb[i * 64];
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): they are in registers
+        __syncthreads();                      // everyone's are: the blocks may be replaced
+        if (kb + 1 < k1) copy(kb + 1);
+        if (inside) {
+#pragma unroll
+            for (int i = 0; i < NL; i++)
+#pragma unroll
+                for (int j = 0; j < NL; j++)
+                    acc[i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b[j], acc[i + j], 0, 0, 0);
+        }
+    }
+    if (!inside) return;
+    // lane holds column lane%16 and rows 4*(lane/16)+r of its tile
+    const int row = rb * 16 + 4 * (lane >> 4), col = cb * 16 + (lane & 15);
+    if (col >= g.cols) return;
+    const u32 cq = fd_div((u32)col, g.dCdiv);
+    u64 *out = plane_at(g, run) + (size_t)party * g.out_party_stride + (size_t)cq * g.stride_cb + ((u32)col - cq * (u32)g.cdiv) +
+               (size_t)row * g.stride_row;
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+        if (row + r < g.rows) out[(size_t)r * g.stride_row] = fold_diagonals(acc, r);
+}
+
 // The same contraction for a first operand of at most 16 rows and a large second one (dense layers at a small batch).
 // There the time goes into reading the second operand once, so a launch is as
 // fast as it keeps bytes in flight: a workgroup's tile is 16 rows x 128 columns, one row block and eight
@@ -941,15 +1019,14 @@ __global__ __launch_bounds__(256) void add_cut_tiles_kernel(gemm_args g, unsigne
 
 }  // namespace
 
-ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, int gather, int hw)
+ss_part_src ss_gemm_parts(const product_plan &r, int n, int rows, int cols, int hw)
 {
-    const gemm_plan p = plan_gemm(n, rows, cols, K, gather);
     ss_part_src ps = {};
-    ps.planes = p.slots;
+    ps.planes = r.planes();
     ps.stride = (size_t)n * rows * cols;
-    ps.first_cut = p.whole;
-    ps.party_tiles = (unsigned)p.RT * (unsigned)p.CT;
-    ps.row_tiles = (unsigned)p.CT;
+    ps.first_cut = r.sq.runs ? 0 : r.p.whole;
+    ps.party_tiles = (unsigned)r.p.RT * (unsigned)r.p.CT;
+    ps.row_tiles = (unsigned)r.p.CT;
     ps.hw = (unsigned)hw;
     ps.rows = (unsigned)rows;
     ps.dHw = make_fdiv(ps.hw);
@@ -959,13 +1036,14 @@ ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, int gather, int hw)
 
 int ss_gemm_planes(int n, int rows, int cols, int K, int gather)
 {
-    return plan_gemm(n, rows, cols, K, gather).slots;
+    const product_plan r = plan_product(n, rows, cols, K, gather, false, SQUARE_RUNS);
+    return r.planes() > r.p.slots ? r.planes() : r.p.slots;
 }
 
 size_t ss_gemm_scratch_bytes(int n, int rows, int cols, int K, int gather)
 {
     // room for either form of the second operand (tiles may take the 16-row kernel, limb planes never do)
-    const int a = ss_gemm_planes(n, rows, cols, K, gather), b = ss_gemm_planes(n, rows, cols, K, 0);
+    const int a = plan_gemm(n, rows, cols, K, gather).slots, b = gather ? plan_gemm(n, rows, cols, K, 0).slots : a;
     return (size_t)((a > b ? a : b) - 1) * n * rows * cols * sizeof(u64);   // the first plane is the product itself
 }
 
@@ -1053,8 +1131,8 @@ struct conv_planes {   // geometry of an operand given as limb planes
     int B, C, H, W, kh, kw, stride, pad, Ho, Wo;
 };
 
-hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_planes *cv, u64 *out, u64 *parts, bool add_parts,
-                       int n, int rows, int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv,
+hipError_t launch_gemm(const product_plan &plan, const void *packedA, const void *packedB, const conv_planes *cv, u64 *out, u64 *parts,
+                       bool add_parts, int n, int rows, int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv,
                        size_t stride_cb, hipStream_t stream, hipEvent_t started, hipEvent_t stopped)
 {
     static bool lds_opt_in = false;
@@ -1074,7 +1152,7 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
         if (e != hipSuccess) return e;
         lds_opt_in = true;
     }
-    const gemm_plan p = plan_gemm(n, rows, cols, K, cv ? ss_gather(cv->C, cv->stride) : 0);
+    const gemm_plan &p = plan.p;
     if (p.G <= 0) return hipErrorInvalidValue;
     gemm_args g = {};
     g.A = (const v4i *)packedA;
@@ -1128,16 +1206,22 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
     }
     // with an event pair the launch goes through the entry point that stamps the events with the kernel's own
     // start and end (profiling only)
-#define SS_LAUNCH_PRODUCT(KERNEL, LDS, ...)                                                                          \
+#define SS_LAUNCH_PRODUCT_AS(KERNEL, GRID, THREADS, LDS, ...)                                                          \
     do {                                                                                                              \
         if (started && stopped)                                                                                       \
-            hipExtLaunchKernelGGL(KERNEL, dim3((unsigned)p.G), dim3(p.threads), LDS, stream, started, stopped, 0, __VA_ARGS__); \
+            hipExtLaunchKernelGGL(KERNEL, dim3((unsigned)(GRID)), dim3(THREADS), LDS, stream, started, stopped, 0, __VA_ARGS__); \
         else                                                                                                          \
-            hipLaunchKernelGGL(KERNEL, dim3((unsigned)p.G), dim3(p.threads), LDS, stream, __VA_ARGS__);               \
+            hipLaunchKernelGGL(KERNEL, dim3((unsigned)(GRID)), dim3(THREADS), LDS, stream, __VA_ARGS__);              \
     } while (0)
+#define SS_LAUNCH_PRODUCT(KERNEL, LDS, ...) SS_LAUNCH_PRODUCT_AS(KERNEL, p.G, p.threads, LDS, __VA_ARGS__)
 #define SS_LAUNCH_KSPLIT(KS) \
     SS_LAUNCH_PRODUCT((cv ? gemm_ksplit_kernel<true, KS> : gemm_ksplit_kernel<false, KS>), 0, g, make_fdiv((u32)p.slots))
-    switch (p.ksplit) {
+    if (const int runs = plan.sq.runs) {
+        const fdiv minors = make_fdiv(plan.sq.minors), majors = make_fdiv(plan.sq.majors), dRuns = make_fdiv((u32)runs);
+        SS_LAUNCH_PRODUCT_AS((cv ? gemm_square_kernel<true> : gemm_square_kernel<false>), plan.sq.G, 256, 0, g.A, g.B,
+                             (u32)g.Rb | (u32)g.Cb << 16, (u32)g.Kb | (u32)runs << 16, minors.m, minors.s, majors.m, majors.s, dRuns.m,
+                             dRuns.s, plan.sq.G, g);
+    } else switch (p.ksplit) {
         case 0:
             if (p.skinny)
                 SS_LAUNCH_PRODUCT((streams_operand(n * ss_packed_bytes(cols, K)) ? gemm_skinny_kernel<true> : gemm_skinny_kernel<false>),
@@ -1152,16 +1236,17 @@ hipError_t launch_gemm(const void *packedA, const void *packedB, const conv_plan
     }
 #undef SS_LAUNCH_KSPLIT
 #undef SS_LAUNCH_PRODUCT
+#undef SS_LAUNCH_PRODUCT_AS
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !add_parts || p.slots == 1) return e;
-    if (p.whole) {
+    if (e != hipSuccess || !add_parts || plan.planes() == 1) return e;
+    if (!plan.sq.runs && p.whole) {
         hipLaunchKernelGGL(add_cut_tiles_kernel, dim3((unsigned)p.tiles - p.whole, 16), dim3(256), 0, stream, g, p.whole);
         return hipGetLastError();
     }
     for (size_t first = 0; first < g.part_stride; first += (size_t)1 << 31) {   // one thread per element: see fits_grid
         const size_t count = g.part_stride - first < ((size_t)1 << 31) ? g.part_stride - first : (size_t)1 << 31;
         hipLaunchKernelGGL(add_planes_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream, out + first,
-                           parts + first, g.part_stride, count, p.slots);
+                           parts + first, g.part_stride, count, plan.planes());
     }
     return hipGetLastError();
 }
@@ -1173,22 +1258,22 @@ size_t ss_planes_bytes(int B, int C, int H, int W)
     return (size_t)NL * B * H * W * C + 256;   // the limb planes and a pad that starts with 16 zero bytes
 }
 
-hipError_t ss_launch_gemm(const void *packedA, const void *packedB, u64 *out, u64 *parts, bool add_parts, int n, int rows,
+hipError_t ss_launch_gemm(const product_plan &plan, const void *packedA, const void *packedB, u64 *out, u64 *parts, bool add_parts, int n, int rows,
                           int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv, size_t stride_cb,
                           hipStream_t stream, hipEvent_t started, hipEvent_t stopped)
 {
-    return launch_gemm(packedA, packedB, nullptr, out, parts, add_parts, n, rows, cols, K, out_party_stride, stride_row, cdiv,
+    return launch_gemm(plan, packedA, packedB, nullptr, out, parts, add_parts, n, rows, cols, K, out_party_stride, stride_row, cdiv,
                        stride_cb, stream, started, stopped);
 }
 
-hipError_t ss_launch_gemm_conv(const void *packedW, const void *planes, u64 *out, u64 *parts, bool add_parts, int n, int B,
+hipError_t ss_launch_gemm_conv(const product_plan &plan, const void *packedW, const void *planes, u64 *out, u64 *parts, bool add_parts, int n, int B,
                                int C, int H, int W, int Co, int kh, int kw, int stride, int pad, int Ho, int Wo,
                                hipStream_t stream, hipEvent_t started, hipEvent_t stopped)
 {
     const conv_planes cv = {planes, B, C, H, W, kh, kw, stride, pad, Ho, Wo};
     const size_t HW = (size_t)Ho * Wo;
     // rows = output channel, cols = (b, ho, wo): y[b][co][hw]
-    return launch_gemm(packedW, nullptr, &cv, out, parts, add_parts, n, Co, (int)(B * HW), C * kh * kw, (size_t)B * Co * HW, HW,
+    return launch_gemm(plan, packedW, nullptr, &cv, out, parts, add_parts, n, Co, (int)(B * HW), C * kh * kw, (size_t)B * Co * HW, HW,
                        (int)HW, (size_t)Co * HW, stream, started, stopped);
 }
 

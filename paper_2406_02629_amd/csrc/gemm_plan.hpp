@@ -100,9 +100,16 @@ inline gemm_plan plan_ksplit(int n, int rows, int cols, int Kb, double *busy, do
 // 20.7 / 24.8 -> 16.3; 1024 x 196 x 256 41.0 -> 39.0 / 31.0 -> 25.6 / 28.5 -> 20.2 (the product alone of five parties 20.0 -> 21.4: the
 // reduction has one plane instead of two).  Left, 39 x 1800 x 4608, n = 5, 111 -> 118; 94 x 1352 x 2304, n = 3, 60.7 -> 68.5; with stride
 // 2, 43 x 578 x 4608, n = 5, 51 -> 65; 270 x 80 x 4608, n = 5, 46 -> 56; 27 x 1152 x 4608, n = 4 over the 45-bit prime, 46 -> 51.
+// us: the estimate for the kernel that is taken.
 inline bool ksplit_is_faster(const gemm_plan &k, const gemm_plan &p, double busy, double spread, double big, bool all_whole, int n,
-                             int rows, int cols, int gather)
+                             int rows, int cols, int gather, double *us)
 {
+    const long Rb = (rows + 15) / 16, packed = Rb + (gather ? 0 : (cols + 15) / 16);   // blocks of the packed operands
+    const double operand_us = (double)n * packed * p.Kb * (SS_NLIMB << 10) / 20e6;
+    const double plane_us = 0.62 + (double)n * rows * cols / p.tiles * (p.tiles - p.whole) * 8 / 5e6;
+    const double unit = Rb == 4 * p.RT ? 1.0 : 0.86;
+    const double big_us = (SS_NLIMB == 8 ? 6.0 + 0.145 * unit * big : 5.4 + 0.095 * unit * big) + (all_whole ? 0 : (p.slots - 1) * plane_us);
+    *us = big_us;
     if (k.G <= 0 || k.tiles * k.Kb >= (1L << 31)) return false;
     if (p.skinny) return k.tiles * k.Kb <= 6144;
     if (k.Kb == 1 && k.tiles > (SS_NLIMB == 8 ? 2560 : 10240)) return false;
@@ -114,13 +121,9 @@ inline bool ksplit_is_faster(const gemm_plan &k, const gemm_plan &p, double busy
         const double held = (1 + (k.ksplit == 1 ? 0.25 : 1.0) * far) * spread;
         if (held > units) units = held;
     }
-    const long Rb = (rows + 15) / 16, packed = Rb + (gather ? 0 : (cols + 15) / 16);   // blocks of the packed operands
-    const double operand_us = (double)n * packed * p.Kb * (SS_NLIMB << 10) / 20e6;
-    const double plane_us = 0.62 + (double)n * rows * cols / p.tiles * (p.tiles - p.whole) * 8 / 5e6;
-    const double unit = Rb == 4 * p.RT ? 1.0 : 0.86;
     // (waves of one tile share no operand)
     const double ksplit_us = operand_us + (k.ksplit >= 4 ? 1.13 : 1.0) * (SS_NLIMB == 8 ? 1.6 + 0.83 * units : 3.9 + 0.46 * units);
-    const double big_us = (SS_NLIMB == 8 ? 6.0 + 0.145 * unit * big : 5.4 + 0.095 * unit * big) + (all_whole ? 0 : (p.slots - 1) * plane_us);
+    if (ksplit_us < big_us) *us = ksplit_us;
     return ksplit_us < big_us;
 }
 
@@ -137,7 +140,8 @@ inline bool streams_operand(size_t bytes) { return bytes > ((size_t)256 << 20); 
 // tensor 238 -> 227 us; whole tiles as workgroups of their own instead of runs of one workgroup per CU: 16 rounds of two
 // units 125 us, in runs 107.
 // gather: 0 for a second operand in tiles, 1 for one in limb planes; its channels if the convolution reads them with a stride.
-inline gemm_plan plan_gemm(int n, int rows, int cols, int K, int gather)
+// us: what the product, its operands from memory, and its further planes take.
+inline gemm_plan plan_gemm(int n, int rows, int cols, int K, int gather, double *us = nullptr)
 {
     typedef unsigned long long ull;
     gemm_plan p = {};
@@ -191,7 +195,10 @@ inline gemm_plan plan_gemm(int n, int rows, int cols, int K, int gather)
         double kbusy = 0, kspread = 0;
         const gemm_plan k = plan_ksplit(n, rows, cols, p.Kb, &kbusy, &kspread);
         if (p.CT == 1 && vb_last == 2) busy = busy * 7 / 8;   // (units of two column blocks cost less than dealt with)
-        if (ksplit_is_faster(k, p, kbusy, kspread, (double)busy, all_whole, n, rows, cols, gather)) return k;
+        double estimate = 0;
+        const bool ksplit = ksplit_is_faster(k, p, kbusy, kspread, (double)busy, all_whole, n, rows, cols, gather, &estimate);
+        if (us) *us = estimate;
+        if (ksplit) return k;
     }
     if (all_whole) {
         const long wgs = p.skinny || p.tiles < SS_GEMM_CUS ? p.tiles : SS_GEMM_CUS;
@@ -203,6 +210,78 @@ inline gemm_plan plan_gemm(int n, int rows, int cols, int K, int gather)
         p.cost = p.cost0 = 0;
     }
     return p;
+}
+
+// gemm_square_kernel: a workgroup per tile of 32 x 32 and run of k blocks, `runs` runs of equal length with a plane each.  runs == 0: the
+// product is left to the plan's kernels.
+struct square_plan {
+    int runs;
+    unsigned minors, majors, G;   // tiles along the shorter and the longer side; workgroups
+};
+constexpr int SQUARE_RUNS = 8;
+
+// Which products take it (p, p_us: what plan_gemm gives them to otherwise), and how many runs: where it is estimated 3 % faster than that, over
+// the 61-bit prime 15 % (22 % from limb planes) from 60 us on: there tiles of 64 x 64 that fill the matrix and the chip are as fast or
+// faster, with half the reads (128 x 6272 x 1152, n = 5, 191 -> 206 us, estimated 10 % faster; 256 x 1568 x 1024 89 -> 95).  Below 7 us (8.5 us) launches decide and
+// nothing is gained (4000 shapes: 0.7 % slower on average).
+// most: planes that there is room for; tensor: the planes are added up by one more launch, where there are several.
+// A unit (32 x 32, one k block) keeps a CU busy for 0.605 us (0.365 us over the 45-bit prime), however many workgroups share the CU, down
+// to two; less where blocks of the tile lie outside the matrix, more where it is gathered from limb planes.  Three (four)
+// workgroups are on a CU at a time.
+// Fitted to 10000 shapes, 62000 timings of product + reduction, operands from memory, n = 3 to 7, both fields, 10 us to 6 ms; on 2200 others of up to 60
+// us of matrix work 6.5 % faster on average over all of them, 5 % of them more than 3 % slower.  Before -> after, us, product + reduction +
+// truncation (rows x columns x contraction, runs): n = 5, 128 x 784 x 1152 44.2 -> 38.3 (1), 256 x 196 x 1024 29.0 -> 25.3 (2), 512 x 49 x 2048 31.0 ->
+// 26.7 (3); n = 3, 128 x 49 x 4608 32.6 -> 15.9 (8), 128 x 1024 x 1152 34.5 -> 30.2 (2); over the 45-bit prime, n = 3, 512 x 49 x 4608 28.7 -> 22.7 (5), 256 x
+// 196 x 2304 24.6 -> 19.8 (3).  Left: n = 5, 64 x 3136 x 576 44.4 -> 45.0; n = 3, 66 x 256 x 6400 27.0 -> 30.0.  Large convolutions whose weights
+// no L2 holds are left too: there a tile of 64 x 64 reads them half as often (895 x 8712 x 3200, n = 3, 3.20 -> 3.55 ms).
+inline square_plan plan_square(const gemm_plan &p, double p_us, int n, int rows, int cols, int K, int gather, bool tensor, int most)
+{
+    constexpr bool P61 = SS_NLIMB == 8;
+    square_plan best = {};
+    const long Rb = (rows + 15) / 16, Cb = ((long)cols + 15) / 16, Rt = (Rb + 1) / 2, Ct = (Cb + 1) / 2;
+    const int Kb = (K + 63) / 64;
+    if (p_us < (P61 ? 7.0 : 8.5) || p.G <= 0 || p.skinny || Rb < 2 || Cb < 2 || Rb > 0xffff || Cb > 0xffff || !fits_grid(n * Rt * Ct, 256)) return best;
+    const double elements = (double)n * rows * cols, far = gather > 1 ? 1 + log2(gather / 64.0) : 0;
+    if (gather && elements > 10e6 && (double)rows * K * SS_NLIMB > 12e6) return best;
+    const double valid = (double)(Rb * Cb) / (4 * Rt * Ct);
+    const double unit = (P61 ? 0.605 * (0.84 + 0.16 * valid) * (1 + 0.043 * far) : 0.365 * (0.86 + 0.14 * valid) * (1 + 0.054 * far)) *
+                        (gather == 1 ? 1.06 : 1.0);
+    const double plane = P61 ? 0.30 + elements * 3.5e-6 : 0.30 + elements * 4.7e-6;
+    const double operands = (double)n * (Rb + (gather ? 0 : Cb)) * Kb * (SS_NLIMB << 10) * (P61 ? 0.032e-6 : 0.035e-6);
+    const double add = tensor ? 3.5 + elements * 3.5e-6 : 0;   // (a launch, the first plane once more)
+    const double other = p_us + (p.slots > 1 ? add * (p.tiles - p.whole) / p.tiles : 0);
+    double best_us = other / (P61 && p_us > 60 ? gather ? 1.22 : 1.15 : 1.03);
+    for (int runs = 1; runs <= SQUARE_RUNS && runs <= Kb && runs <= most; runs++) {
+        const long G = n * Rt * Ct * runs;
+        if (!fits_grid(G, 256)) break;
+        const double at_a_time = P61 ? 3 : 4, per_cu = (double)G / SS_GEMM_CUS, rounds = per_cu / at_a_time;
+        const double share = per_cu > at_a_time ? per_cu + 0.58 : per_cu > 1 ? ceil(per_cu) : P61 ? 1.27 : 1.62;
+        // (from the second round on a workgroup's start hides behind the others)
+        const double us = (P61 ? 2.4 : 3.7) + (Kb + runs - 1) / runs * unit * share - (P61 ? 1.45 : 2.1) * fmin(fmax(rounds - 1, 0.0), 6.5) +
+                          (runs - 1) * plane + operands + (runs > 1 ? add : 0);
+        if (us < best_us) {
+            best_us = us;
+            best = {runs, (unsigned)(Rt < Ct ? Rt : Ct), (unsigned)(Rt < Ct ? Ct : Rt), (unsigned)G};
+        }
+    }
+    return best;
+}
+
+// What a product is launched with: gemm_square_kernel where sq.runs > 0, else the plan's kernel.  room: planes that there is memory for,
+// plan_gemm's or more; 0: as many as plan_gemm has.
+struct product_plan {
+    gemm_plan p;
+    square_plan sq;
+    int planes() const { return sq.runs ? sq.runs : p.slots; }
+};
+
+inline product_plan plan_product(int n, int rows, int cols, int K, int gather, bool tensor, int room)
+{
+    product_plan r = {};
+    double us = 0;
+    r.p = plan_gemm(n, rows, cols, K, gather, &us);
+    if (us > 0) r.sq = plan_square(r.p, us, n, rows, cols, K, gather, tensor, room > r.p.slots ? room : r.p.slots);
+    return r;
 }
 
 }  // namespace

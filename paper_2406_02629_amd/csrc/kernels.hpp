@@ -2,6 +2,7 @@
 // files.  Every launcher enqueues on `stream` and returns hipGetLastError().
 #pragma once
 #include "field.hpp"
+#include "gemm_plan.hpp"
 
 // Everything below lives in a namespace named after the field (ss61 / ss45), so that the two libraries built
 // from these sources never share a C++ symbol or a kernel name.
@@ -163,29 +164,32 @@ size_t ss_planes_bytes(int B, int C, int H, int W);   // per party
 hipError_t ss_launch_planes(const u64 *in, u64 *shares, void *planes, int n, int t, int B, int C, int HW, bool gen,
                             const ss_keys &keys, hipStream_t stream);
 // convolution with the input given as planes and the weights packed with contraction index (tap, channel);
-// out, parts and add_parts as for ss_launch_gemm
+// plan, out, parts and add_parts as for ss_launch_gemm
 // (started, stopped: see ss_launch_gemm)
-hipError_t ss_launch_gemm_conv(const void *packedW, const void *planes, u64 *out, u64 *parts, bool add_parts, int n, int B,
+hipError_t ss_launch_gemm_conv(const product_plan &plan, const void *packedW, const void *planes, u64 *out, u64 *parts, bool add_parts, int n, int B,
                                int C, int H, int W, int Co, int kh, int kw, int stride, int pad, int Ho, int Wo,
                                hipStream_t stream, hipEvent_t started = nullptr, hipEvent_t stopped = nullptr);
 // rows = (b, ho, wo), k = (c, r, s) of x [n][B][C][H][W]
 hipError_t ss_launch_pack_im2col(const u64 *x, void *dst, int n, int B, int C, int H, int W, int kh, int kw,
                                  int stride, int pad, int Ho, int Wo, hipStream_t stream);
 // product[i][row*stride_row + (col / cdiv)*stride_cb + col % cdiv] = sum_k A_i[row][k] * B_i[col][k] mod p, left as
-// ss_gemm_planes(...) planes of that layout whose sum mod p is the product: a tile of the output may be computed in parts
+// plan.planes() planes of that layout whose sum mod p is the product: a tile of the output may be computed in parts
 // by several workgroups, each of which stores its part in a plane of its own.  The first plane is `out`, the others follow
 // one another at `parts`; every position of every plane is written in every launch but for those of tiles that were not cut
-// (ss_gemm_parts), nothing passes between workgroups.  add_parts: one more launch adds them up, `out` is then the product.
-// gather: 0 for a second operand in tiles, else ss_gather of the convolution that reads it from limb planes
+// (ss_gemm_parts), nothing passes between workgroups.  add_parts: one more launch adds them up, `out` is then the product
+// (a plan for a tensor, in the room of ss_gemm_scratch_bytes).
+// plan: plan_product of n, rows, cols, K, gather; gather: 0 for a second operand in tiles, else ss_gather of the convolution that reads
+// it from limb planes.
+// ss_gemm_planes: the planes of a pending product with room for any number.  A smaller room may have another kernel, with plan_gemm's.
 int ss_gemm_planes(int n, int rows, int cols, int K, int gather);
 inline int ss_gather(int C, int stride) { return stride > 1 ? C : 1; }
 // the planes and the tiles they hold, for the consumers of a product whose rows run over hw columns at a time
-ss_part_src ss_gemm_parts(int n, int rows, int cols, int K, int gather, int hw);
+ss_part_src ss_gemm_parts(const product_plan &plan, int n, int rows, int cols, int hw);
 // bytes of all planes but the first for either form of the second operand
 size_t ss_gemm_scratch_bytes(int n, int rows, int cols, int K, int gather);
 // started / stopped, if given, take the times at which the product kernel itself starts and ends on the GPU (the
 // dispatch's own time stamps, without the gap between two launches that events recorded around a launch include)
-hipError_t ss_launch_gemm(const void *packedA, const void *packedB, u64 *out, u64 *parts, bool add_parts, int n, int rows,
+hipError_t ss_launch_gemm(const product_plan &plan, const void *packedA, const void *packedB, u64 *out, u64 *parts, bool add_parts, int n, int rows,
                           int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv, size_t stride_cb,
                           hipStream_t stream, hipEvent_t started = nullptr, hipEvent_t stopped = nullptr);
 

@@ -293,7 +293,7 @@ int run_gemm(ssnet_ctx *ctx, const void *pa, const void *pb, u64 *out, int rows,
              size_t out_party_stride, size_t stride_row, int cdiv, size_t stride_cb)
 {
     return run_product(ctx, [&](u64 *parts, hipEvent_t ea, hipEvent_t eb) {
-        return ss_launch_gemm(pa, pb, out, parts, true, ctx->n, rows, cols, K, out_party_stride, stride_row, cdiv, stride_cb,
+        return ss_launch_gemm(plan_product(ctx->n, rows, cols, K, 0, true, 0), pa, pb, out, parts, true, ctx->n, rows, cols, K, out_party_stride, stride_row, cdiv, stride_cb,
                               ctx->stream, ea, eb);
     });
 }
@@ -303,18 +303,38 @@ size_t product_bytes(const ssnet_ctx *ctx, int rows, int cols, int K, int gather
     return align256((size_t)ss_gemm_planes(ctx->n, rows, cols, K, gather) * ctx->n * rows * cols * 8);
 }
 
-// Room for a product of `planes` planes at the very end of the workspace; the messages of the call that
-// consumes it grow from the front.  nullptr if the workspace is too small.
-u64 *reserve_pending(ssnet_ctx *ctx, int rows, int cols, int K, int gather, int hw)
+// positions per message plane of the layer-tail call: the threads of its one-launch kernel (blocks of 16
+// pixels x 16 channels), or the elements themselves where the separate kernels run
+size_t tail_plane(const ssnet_ctx *ctx, int B, int C, int HW)
+{
+    const bool fused = (ctx->n == 5 && ctx->t == 2) || (ctx->n == 3 && ctx->t == 1);
+    return fused ? (size_t)((B * HW + 15) / 16) * ((C + 15) / 16) * 256 : (size_t)B * C * HW;
+}
+
+size_t tail_message_bytes(const ssnet_ctx *ctx, int B, int C, int HW)
+{
+    const size_t k = ctx->t + 1, nr = 2 * ctx->t + 1, n = ctx->n;
+    return align256((nr * k + k * n + k + n + nr + 1) * tail_plane(ctx, B, C, HW) * 8);
+}
+
+// Room for a product at the very end of the workspace; the messages of the call that consumes it grow from the front.  It takes the
+// planes that make it fastest where they leave room for any consumer's messages (those of the layer tail, on the product as [B][C][HW], are
+// the most), else the fewest it can be computed with: what fits a smaller workspace still fits.  nullptr if the workspace is too small.
+u64 *reserve_pending(ssnet_ctx *ctx, int rows, int cols, int K, int gather, int hw, int B, int C, int HW, product_plan *plan)
 {
     ctx->pending.on = false;
-    const size_t bytes = product_bytes(ctx, rows, cols, K, gather);
+    const size_t plane = (size_t)ctx->n * rows * cols * 8;
+    const uintptr_t start = (uintptr_t)ws_scratch(ctx), end = ((uintptr_t)ctx->ws + ctx->ws_bytes) & ~(uintptr_t)255;
+    *plan = plan_product(ctx->n, rows, cols, K, gather, false, SQUARE_RUNS);
+    if (plan->planes() > plan->p.slots &&
+        (!ctx->ws || end < start + tail_message_bytes(ctx, B, C, HW) + align256(plan->planes() * plane)))
+        *plan = plan_product(ctx->n, rows, cols, K, gather, false, 0);
+    const size_t bytes = align256((plan->planes() > plan->p.slots ? plan->planes() : plan->p.slots) * plane);
     if (!ctx->ws || ctx->ws_bytes < WS_HEADER_BYTES + bytes + 256) return nullptr;
-    const uintptr_t end = ((uintptr_t)ctx->ws + ctx->ws_bytes) & ~(uintptr_t)255;
-    if (end - bytes < (uintptr_t)ws_scratch(ctx)) return nullptr;
+    if (end - bytes < start) return nullptr;
     ctx->pending.base = (u64 *)(end - bytes);
     ctx->pending.count = (size_t)rows * cols;
-    ctx->pending.src = ss_gemm_parts(ctx->n, rows, cols, K, gather, hw);
+    ctx->pending.src = ss_gemm_parts(*plan, ctx->n, rows, cols, hw);
     return ctx->pending.base;
 }
 
@@ -635,7 +655,8 @@ int ssnet_conv_mod_planes(ssnet_ctx *ctx, const void *d_planes, const void *d_w_
     if (!gemm_shape_ok(Co, M, K)) return SSNET_EINVAL;
     if (!ws_fits(ctx, align256(ss_gemm_scratch_bytes(ctx->n, Co, (int)M, (int)K, ss_gather(C, stride))))) return SSNET_EWORKSPACE;
     return run_product(ctx, [&](u64 *parts, hipEvent_t ea, hipEvent_t eb) {
-        return ss_launch_gemm_conv(d_w_packed, d_planes, d_y, parts, true, ctx->n, B, C, H, W, Co, kh, kw, stride, pad, Ho, Wo,
+        return ss_launch_gemm_conv(plan_product(ctx->n, Co, (int)M, (int)K, ss_gather(C, stride), true, 0), d_w_packed, d_planes, d_y,
+                                   parts, true, ctx->n, B, C, H, W, Co, kh, kw, stride, pad, Ho, Wo,
                                    ctx->stream, ea, eb);
     });
 }
@@ -661,11 +682,12 @@ size_t ssnet_product_bytes_conv(const ssnet_ctx *ctx, int B, int C, int H, int W
 int ssnet_linear_product_prepacked(ssnet_ctx *ctx, const void *d_x_packed, const void *d_w_packed, int M, int K, int N)
 {
     if (!ctx || !d_x_packed || !d_w_packed || !gemm_shape_ok(M, N, K)) return SSNET_EINVAL;
-    u64 *c = reserve_pending(ctx, M, N, K, 0, N);
+    product_plan plan;
+    u64 *c = reserve_pending(ctx, M, N, K, 0, N, M, N, 1, &plan);
     if (!c) return SSNET_EWORKSPACE;
     timed tm(ctx, SSNET_PROF_GEMM);
     kernel_span ks(ctx);
-    hipError_t e = ss_launch_gemm(d_x_packed, d_w_packed, c, c + (size_t)ctx->n * M * N, false, ctx->n, M, N, K, (size_t)M * N,
+    hipError_t e = ss_launch_gemm(plan, d_x_packed, d_w_packed, c, c + (size_t)ctx->n * M * N, false, ctx->n, M, N, K, (size_t)M * N,
                                   (size_t)N, INT_MAX, 0, ctx->stream, ks.started(), ks.stopped());
     ks.done(e);
     ctx->pending.on = e == hipSuccess;
@@ -679,11 +701,12 @@ int ssnet_conv1x1_product_prepacked(ssnet_ctx *ctx, const void *d_x_packed, cons
         !gemm_shape_ok(Co, (long)B * HW, C))
         return SSNET_EINVAL;
     const int M = B * HW;
-    u64 *c = reserve_pending(ctx, Co, M, C, 0, HW);
+    product_plan plan;
+    u64 *c = reserve_pending(ctx, Co, M, C, 0, HW, B, Co, HW, &plan);
     if (!c) return SSNET_EWORKSPACE;
     timed tm(ctx, SSNET_PROF_GEMM);
     kernel_span ks(ctx);
-    hipError_t e = ss_launch_gemm(d_w_packed, d_x_packed, c, c + (size_t)ctx->n * Co * M, false, ctx->n, Co, M, C,
+    hipError_t e = ss_launch_gemm(plan, d_w_packed, d_x_packed, c, c + (size_t)ctx->n * Co * M, false, ctx->n, Co, M, C,
                                   (size_t)B * Co * HW, (size_t)HW, HW, (size_t)Co * HW, ctx->stream, ks.started(),
                                   ks.stopped());
     ks.done(e);
@@ -701,11 +724,12 @@ int ssnet_conv_product_planes(ssnet_ctx *ctx, const void *d_planes, const void *
     if (Ho < 1 || Wo < 1) return SSNET_EINVAL;
     const long M = (long)B * Ho * Wo, K = (long)C * kh * kw;
     if (!gemm_shape_ok(Co, M, K)) return SSNET_EINVAL;
-    u64 *c = reserve_pending(ctx, Co, (int)M, (int)K, ss_gather(C, stride), Ho * Wo);
+    product_plan plan;
+    u64 *c = reserve_pending(ctx, Co, (int)M, (int)K, ss_gather(C, stride), Ho * Wo, B, Co, Ho * Wo, &plan);
     if (!c) return SSNET_EWORKSPACE;
     timed tm(ctx, SSNET_PROF_GEMM);
     kernel_span ks(ctx);
-    hipError_t e = ss_launch_gemm_conv(d_w_packed, d_planes, c, c + (size_t)ctx->n * Co * M, false, ctx->n, B, C, H, W, Co, kh, kw,
+    hipError_t e = ss_launch_gemm_conv(plan, d_w_packed, d_planes, c, c + (size_t)ctx->n * Co * M, false, ctx->n, B, C, H, W, Co, kh, kw,
                                        stride, pad, Ho, Wo, ctx->stream, ks.started(), ks.stopped());
     ks.done(e);
     ctx->pending.on = e == hipSuccess;
@@ -997,14 +1021,6 @@ int ssnet_reduce_truncate_direct(ssnet_ctx *ctx, const uint64_t *d_c, size_t cou
 
 namespace {
 
-// positions per message plane of the layer-tail call: the threads of its one-launch kernel (blocks of 16
-// pixels x 16 channels), or the elements themselves where the separate kernels run
-static size_t tail_plane(const ssnet_ctx *ctx, int B, int C, int HW)
-{
-    const bool fused = (ctx->n == 5 && ctx->t == 2) || (ctx->n == 3 && ctx->t == 1);
-    return fused ? (size_t)((B * HW + 15) / 16) * ((C + 15) / 16) * 256 : (size_t)B * C * HW;
-}
-
 static bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
 {
     const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
@@ -1021,10 +1037,8 @@ size_t ssnet_layer_tail_message_plane(const ssnet_ctx *ctx, int B, int C, int HW
 
 size_t ssnet_workspace_bytes_layer_tail(const ssnet_ctx *ctx, int B, int C, int HW)
 {
-    const size_t plane = ssnet_layer_tail_message_plane(ctx, B, C, HW);
-    if (!plane) return 0;
-    const size_t k = ctx->t + 1, nr = 2 * ctx->t + 1, n = ctx->n;
-    return WS_HEADER_BYTES + align256((nr * k + k * n + k + n + nr + 1) * plane * 8);
+    if (!ssnet_layer_tail_message_plane(ctx, B, C, HW)) return 0;
+    return WS_HEADER_BYTES + tail_message_bytes(ctx, B, C, HW);
 }
 
 int ssnet_reduce_truncate_relu(ssnet_ctx *ctx, const uint64_t *d_c, int B, int C, int HW, uint64_t stream_id,
