@@ -305,6 +305,12 @@ struct gemm_args {
     unsigned plane16, party16;         // strides of a limb plane and of a party, in 16-byte units
     int cvH, cvW, cvPixels, cvKw, cvStride, cvPad, cvHoWo, cvWo, cvKbTap;   // Pixels = images * H * W, KbTap = C/64
     fdiv dHoWo, dWo, dKbTap, dKw;
+    // second operand read straight from field elements (gemm_ksplit_kernel): the rows of a dense input [party][cols][K], or the taps of a
+    // convolution input [party][b][c][h][w] with contraction index (channel, tap)
+    const u64 *raw;
+    size_t raw_party, raw_image;       // elements
+    int K, cvTaps;
+    fdiv dTaps;
 };
 
 // where one wave's block of a unit comes from: limb slice q is the 64 lanes x 16 bytes at base + q * qs
@@ -467,6 +473,53 @@ __device__ __forceinline__ const v4i *unit_base(const gemm_args &g, const wave_s
         return ws.p + (size_t)kb * TILE;
     }
     return column_base<IMPLICIT>(g, ws, kb, lane, qs);
+}
+
+// What the column operand of gemm_ksplit_kernel is.
+enum column_operand { IN_TILES, IN_PLANES, IN_ROWS, IN_IMAGES };
+
+// The 16 elements that lane l of a block in MFMA order holds of an operand given as field elements: column 16 cb + l%16, contraction
+// indices 64 kb + 16 (l/16) and on; zero outside the matrix and in the padding of an image.  (Places outside are loaded from the
+// tensor's first element, so that a lane's loads are in flight together.)
+template <column_operand OPERAND>
+__device__ __forceinline__ void load_elements(const gemm_args &g, int party, int cb, int kb, int lane, u64 (&y)[16], unsigned &inside)
+{
+    const int col = cb * 16 + (lane & 15), k0 = kb * 64 + 16 * (lane >> 4);
+    const u64 *x = g.raw + (size_t)party * g.raw_party;
+    inside = 0;
+    if constexpr (OPERAND == IN_ROWS) {
+        const size_t row = (size_t)col * g.K;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const bool in = col < g.cols && k0 + i < g.K;
+            inside |= (unsigned)in << i;
+            y[i] = x[in ? row + (k0 + i) : 0];
+        }
+    } else {
+        const int b = (int)fd_div((u32)col, g.dHoWo), hw = col - b * g.cvHoWo, ho = (int)fd_div((u32)hw, g.dWo), wo = hw - ho * g.cvWo;
+        const int h0 = ho * g.cvStride - g.cvPad, w0 = wo * g.cvStride - g.cvPad;
+        int c = (int)fd_div((u32)k0, g.dTaps), rs = k0 - c * g.cvTaps, r = (int)fd_div((u32)rs, g.dKw), q = rs - r * g.cvKw;
+        const int kh = g.cvTaps / g.cvKw;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int hi = h0 + r, wi = w0 + q;
+            const bool in = col < g.cols && k0 + i < g.K && (unsigned)hi < (unsigned)g.cvH && (unsigned)wi < (unsigned)g.cvW;
+            inside |= (unsigned)in << i;
+            y[i] = x[in ? b * g.raw_image + ((size_t)c * g.cvH + hi) * g.cvW + wi : 0];
+            if (++q == g.cvKw) { q = 0; if (++r == kh) { r = 0; ++c; } }
+        }
+    }
+}
+
+// ... as the lane's 16 bytes of every limb
+__device__ __forceinline__ void limbs_of(const u64 (&y)[16], unsigned inside, v4i (&b)[NL])
+{
+    u64 d[4][4];
+#pragma unroll
+    for (int i = 0; i < 16; i++) d[i >> 2][i & 3] = inside >> i & 1 ? balanced_digits(y[i]) : 0;
+#pragma unroll
+    for (int l = 0; l < NL; l++)
+        b[l] = (v4i){(int)limb_dword(d[0], l), (int)limb_dword(d[1], l), (int)limb_dword(d[2], l), (int)limb_dword(d[3], l)};
 }
 
 __device__ __forceinline__ u64 *plane_at(const gemm_args &g, unsigned plane)
@@ -698,9 +751,12 @@ __global__ __launch_bounds__(512) void gemm_limb_kernel(gemm_args g)
 // next unit's while the MFMAs of the current one run; the KS waves that share a tile add their residues through LDS.  CW
 // tiles, neighbours in the list, make a workgroup.  Where that leaves CUs idle the k blocks are also divided into `parts` equal
 // runs, each with a plane of its own (every tile has all of them).
-template <bool IMPLICIT, int KS>
+// Of the smallest products (element_waves) the column operand may be field elements: a wave takes the digits of its block itself, once per
+// row block, which saves the launch that would pack them.
+template <column_operand OPERAND, int KS>
 __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void gemm_ksplit_kernel(gemm_args g, fdiv dParts)
 {
+    constexpr bool ELEMENTS = OPERAND == IN_ROWS || OPERAND == IN_IMAGES;
     constexpr int NW = KS == 8 ? 8 : 4, CW = NW / KS;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), cw = wave % CW, ks = wave / CW;
     const unsigned slot = xcd_slot(blockIdx.x, gridDim.x);
@@ -724,15 +780,9 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void gemm_ksplit_kernel(gem
     for (int s = 0; s < ND; s++) acc[s] = (v4i){0, 0, 0, 0};
     if (inside) {
         const v4i *const pa = g.A + (size_t)party * g.a_party_stride + (size_t)rb * g.Kb * TILE + lane;
-        const wave_src src = column_source<IMPLICIT>(g, party, cb, lane);
-        auto load = [&](v4i (&a)[NL], v4i (&b)[NL], int kb) {
-            unsigned qs;
-            const v4i *pb = column_base<IMPLICIT>(g, src, kb, lane, qs);
+        auto load_row_block = [&](v4i (&a)[NL], int kb) {
 #pragma unroll
-            for (int q = 0; q < NL; q++) {
-                a[q] = pa[(size_t)kb * TILE + q * 64];
-                b[q] = pb[(size_t)q * qs];
-            }
+            for (int q = 0; q < NL; q++) a[q] = pa[(size_t)kb * TILE + q * 64];
         };
         auto multiply = [&](const v4i (&a)[NL], const v4i (&b)[NL]) {
 #pragma unroll
@@ -741,14 +791,36 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void gemm_ksplit_kernel(gem
                 for (int j = 0; j < NL; j++)
                     acc[i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b[j], acc[i + j], 0, 0, 0);
         };
-        v4i a0[NL], b0[NL], a1[NL], b1[NL];
-        if (k0 < k1) load(a0, b0, k0);
-        for (int kb = k0; kb < k1; kb += 2 * KS) {
-            if (kb + KS < k1) load(a1, b1, kb + KS);
-            multiply(a0, b0);
-            if (kb + KS < k1) {
-                if (kb + 2 * KS < k1) load(a0, b0, kb + 2 * KS);
-                multiply(a1, b1);
+        if constexpr (ELEMENTS) {
+            for (int kb = k0; kb < k1; kb += KS) {   // (one, see element_waves)
+                u64 y[16];
+                unsigned in = 0;
+                v4i a[NL], b[NL];
+                load_elements<OPERAND>(g, party, cb, kb, lane, y, in);
+                load_row_block(a, kb);
+                limbs_of(y, in, b);
+                multiply(a, b);
+            }
+        } else {
+            const wave_src src = column_source<OPERAND == IN_PLANES>(g, party, cb, lane);
+            auto load = [&](v4i (&a)[NL], v4i (&b)[NL], int kb) {
+                unsigned qs;
+                const v4i *pb = column_base<OPERAND == IN_PLANES>(g, src, kb, lane, qs);
+#pragma unroll
+                for (int q = 0; q < NL; q++) {
+                    a[q] = pa[(size_t)kb * TILE + q * 64];
+                    b[q] = pb[(size_t)q * qs];
+                }
+            };
+            v4i a0[NL], b0[NL], a1[NL], b1[NL];
+            if (k0 < k1) load(a0, b0, k0);
+            for (int kb = k0; kb < k1; kb += 2 * KS) {
+                if (kb + KS < k1) load(a1, b1, kb + KS);
+                multiply(a0, b0);
+                if (kb + KS < k1) {
+                    if (kb + 2 * KS < k1) load(a0, b0, kb + 2 * KS);
+                    multiply(a1, b1);
+                }
             }
         }
     }
@@ -1126,13 +1198,14 @@ hipError_t ss_launch_pack_im2col(const u64 *x, void *dst, int n, int B, int C, i
 
 namespace {
 
-struct conv_planes {   // geometry of an operand given as limb planes
+struct conv_planes {   // geometry of an operand given as limb planes or (elements) as field elements
     const void *planes;
     int B, C, H, W, kh, kw, stride, pad, Ho, Wo;
+    const u64 *elements;
 };
 
-hipError_t launch_gemm(const product_plan &plan, const void *packedA, const void *packedB, const conv_planes *cv, u64 *out, u64 *parts,
-                       bool add_parts, int n, int rows, int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv,
+hipError_t launch_gemm(const product_plan &plan, const void *packedA, const void *packedB, const u64 *rowsB, const conv_planes *cv, u64 *out,
+                       u64 *parts, bool add_parts, int n, int rows, int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv,
                        size_t stride_cb, hipStream_t stream, hipEvent_t started, hipEvent_t stopped)
 {
     static bool lds_opt_in = false;
@@ -1191,6 +1264,16 @@ hipError_t launch_gemm(const product_plan &plan, const void *packedA, const void
     g.stride_row = stride_row;
     g.stride_cb = stride_cb;
     g.cdiv = cdiv;
+    g.K = K;
+    g.raw = rowsB;
+    g.raw_party = (size_t)cols * K;
+    if (cv && cv->elements) {
+        g.raw = cv->elements;
+        g.raw_image = (size_t)cv->C * cv->H * cv->W;
+        g.raw_party = cv->B * g.raw_image;
+        g.cvTaps = cv->kh * cv->kw;
+        g.dTaps = fdz((unsigned)g.cvTaps);
+    }
     if (cv) {
         const size_t plane = (size_t)cv->B * cv->H * cv->W * cv->C;   // bytes
         g.planes = (const v4i *)cv->planes;
@@ -1201,7 +1284,7 @@ hipError_t launch_gemm(const product_plan &plan, const void *packedA, const void
         g.cvHoWo = cv->Ho * cv->Wo, g.cvWo = cv->Wo, g.cvKbTap = cv->C / 64;
         g.dHoWo = fdz((unsigned)g.cvHoWo);
         g.dWo = fdz((unsigned)g.cvWo);
-        g.dKbTap = fdz((unsigned)g.cvKbTap);
+        g.dKbTap = fdz((unsigned)g.cvKbTap);   // (elements: not used)
         g.dKw = fdz((unsigned)g.cvKw);
     }
     // with an event pair the launch goes through the entry point that stamps the events with the kernel's own
@@ -1214,8 +1297,10 @@ hipError_t launch_gemm(const product_plan &plan, const void *packedA, const void
             hipLaunchKernelGGL(KERNEL, dim3((unsigned)(GRID)), dim3(THREADS), LDS, stream, __VA_ARGS__);              \
     } while (0)
 #define SS_LAUNCH_PRODUCT(KERNEL, LDS, ...) SS_LAUNCH_PRODUCT_AS(KERNEL, p.G, p.threads, LDS, __VA_ARGS__)
-#define SS_LAUNCH_KSPLIT(KS) \
-    SS_LAUNCH_PRODUCT((cv ? gemm_ksplit_kernel<true, KS> : gemm_ksplit_kernel<false, KS>), 0, g, make_fdiv((u32)p.slots))
+#define SS_LAUNCH_KSPLIT(KS)                                                                                          \
+    SS_LAUNCH_PRODUCT((g.raw ? cv ? gemm_ksplit_kernel<IN_IMAGES, KS> : gemm_ksplit_kernel<IN_ROWS, KS>                 \
+                       : cv  ? gemm_ksplit_kernel<IN_PLANES, KS> : gemm_ksplit_kernel<IN_TILES, KS>),                   \
+                      0, g, make_fdiv((u32)p.slots))
     if (const int runs = plan.sq.runs) {
         const fdiv minors = make_fdiv(plan.sq.minors), majors = make_fdiv(plan.sq.majors), dRuns = make_fdiv((u32)runs);
         SS_LAUNCH_PRODUCT_AS((cv ? gemm_square_kernel<true> : gemm_square_kernel<false>), plan.sq.G, 256, 0, g.A, g.B,
@@ -1262,7 +1347,7 @@ hipError_t ss_launch_gemm(const product_plan &plan, const void *packedA, const v
                           int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv, size_t stride_cb,
                           hipStream_t stream, hipEvent_t started, hipEvent_t stopped)
 {
-    return launch_gemm(plan, packedA, packedB, nullptr, out, parts, add_parts, n, rows, cols, K, out_party_stride, stride_row, cdiv,
+    return launch_gemm(plan, packedA, packedB, nullptr, nullptr, out, parts, add_parts, n, rows, cols, K, out_party_stride, stride_row, cdiv,
                        stride_cb, stream, started, stopped);
 }
 
@@ -1270,10 +1355,28 @@ hipError_t ss_launch_gemm_conv(const product_plan &plan, const void *packedW, co
                                int C, int H, int W, int Co, int kh, int kw, int stride, int pad, int Ho, int Wo,
                                hipStream_t stream, hipEvent_t started, hipEvent_t stopped)
 {
-    const conv_planes cv = {planes, B, C, H, W, kh, kw, stride, pad, Ho, Wo};
+    const conv_planes cv = {planes, B, C, H, W, kh, kw, stride, pad, Ho, Wo, nullptr};
     const size_t HW = (size_t)Ho * Wo;
     // rows = output channel, cols = (b, ho, wo): y[b][co][hw]
-    return launch_gemm(plan, packedW, nullptr, &cv, out, parts, add_parts, n, Co, (int)(B * HW), C * kh * kw, (size_t)B * Co * HW, HW,
+    return launch_gemm(plan, packedW, nullptr, nullptr, &cv, out, parts, add_parts, n, Co, (int)(B * HW), C * kh * kw, (size_t)B * Co * HW, HW,
+                       (int)HW, (size_t)Co * HW, stream, started, stopped);
+}
+
+hipError_t ss_launch_gemm_rows(const product_plan &plan, const u64 *x, const void *packedW, u64 *out, u64 *parts, int n, int M, int K, int N,
+                               hipStream_t stream, hipEvent_t started, hipEvent_t stopped)
+{
+    // rows = output column, cols = row of x: y[col][row]
+    return launch_gemm(plan, packedW, nullptr, x, nullptr, out, parts, true, n, N, M, K, (size_t)M * N, 1, 1, (size_t)N, stream, started,
+                       stopped);
+}
+
+hipError_t ss_launch_gemm_images(const product_plan &plan, const void *packedW, const u64 *x, u64 *out, u64 *parts, int n, int B, int C, int H,
+                                 int W, int Co, int kh, int kw, int stride, int pad, int Ho, int Wo, hipStream_t stream,
+                                 hipEvent_t started, hipEvent_t stopped)
+{
+    const conv_planes cv = {nullptr, B, C, H, W, kh, kw, stride, pad, Ho, Wo, x};
+    const size_t HW = (size_t)Ho * Wo;
+    return launch_gemm(plan, packedW, nullptr, nullptr, &cv, out, parts, true, n, Co, (int)(B * HW), C * kh * kw, (size_t)B * Co * HW, HW,
                        (int)HW, (size_t)Co * HW, stream, started, stopped);
 }
 

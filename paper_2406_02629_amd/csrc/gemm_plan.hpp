@@ -273,6 +273,28 @@ struct product_plan {
     gemm_plan p;
     square_plan sq;
     int planes() const { return sq.runs ? sq.runs : p.slots; }
+    // Waves that share a tile where gemm_ksplit_kernel takes its column operand as field elements, without the launch that would pack them; 0:
+    // it does not.  The digits of a unit take a wave longer than its products, so that a wave has one unit and the launch few enough waves for
+    // all to run at once.  Both kernels -> this one, us, without the 1.5 to 2 us between the two (n = 3): 1 x 120 x 400 7.6 -> 6.1, 16 x 120 x 100 6.9 ->
+    // 5.5, 64 x 300 x 180 7.9 -> 6.9, 64 channels of 32 x 32 from three 7.1 -> 6.8; left, with two units and more, 16 x 500 x 1000 9.2 -> 11.1,
+    // 200 channels of 14 x 14 from twenty, four images, 13.7 -> 16.3.  input_rows: of a dense input (0: images), whose loads meet a cache line per
+    // row: 16 x 1000 x 512 8.5 -> 11.7 us, 16 x 120 x 400 8.0 -> 7.9.
+    int element_waves(int input_rows) const
+    {
+        if (sq.runs || !p.ksplit || p.Kb > 8) return 0;
+        const int ks = p.Kb > 4 ? 8 : p.Kb > 2 ? 4 : p.Kb;
+        return p.tiles * ks * (ks == 8 && input_rows > 8 ? 3 : 1) <= 8 * SS_GEMM_CUS ? ks : 0;
+    }
+    product_plan for_elements(int waves) const
+    {
+        product_plan e = *this;
+        e.p.ksplit = waves;
+        e.p.slots = 1;
+        e.p.threads = e.p.ksplit == 8 ? 512 : 256;
+        const int cw = e.p.ksplit == 8 ? 1 : 4 / e.p.ksplit;
+        e.p.G = (int)((p.tiles + cw - 1) / cw);
+        return e;
+    }
 };
 
 inline product_plan plan_product(int n, int rows, int cols, int K, int gather, bool tensor, int room)

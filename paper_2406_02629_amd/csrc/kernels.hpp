@@ -193,4 +193,13 @@ hipError_t ss_launch_gemm(const product_plan &plan, const void *packedA, const v
                           int cols, int K, size_t out_party_stride, size_t stride_row, int cdiv, size_t stride_cb,
                           hipStream_t stream, hipEvent_t started = nullptr, hipEvent_t stopped = nullptr);
 
+// The same as a tensor with the second operand given as field elements (plan: for_elements of one with element_waves): a dense input
+// x [n][M][K] times packed weights (N rows), y [n][M][N]; a convolution input x [n][B][C][H][W], weights packed with contraction index
+// (channel, tap)
+hipError_t ss_launch_gemm_rows(const product_plan &plan, const u64 *x, const void *packedW, u64 *out, u64 *parts, int n, int M, int K, int N,
+                               hipStream_t stream, hipEvent_t started = nullptr, hipEvent_t stopped = nullptr);
+hipError_t ss_launch_gemm_images(const product_plan &plan, const void *packedW, const u64 *x, u64 *out, u64 *parts, int n, int B, int C, int H,
+                                 int W, int Co, int kh, int kw, int stride, int pad, int Ho, int Wo, hipStream_t stream,
+                                 hipEvent_t started = nullptr, hipEvent_t stopped = nullptr);
+
 }  // namespace SS_NS

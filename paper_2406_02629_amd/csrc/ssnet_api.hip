@@ -289,11 +289,11 @@ int run_product(ssnet_ctx *ctx, F &&launch)
     return e == hipSuccess ? SSNET_OK : fail_hip(ctx, e);
 }
 
-int run_gemm(ssnet_ctx *ctx, const void *pa, const void *pb, u64 *out, int rows, int cols, int K,
+int run_gemm(ssnet_ctx *ctx, const product_plan &plan, const void *pa, const void *pb, u64 *out, int rows, int cols, int K,
              size_t out_party_stride, size_t stride_row, int cdiv, size_t stride_cb)
 {
     return run_product(ctx, [&](u64 *parts, hipEvent_t ea, hipEvent_t eb) {
-        return ss_launch_gemm(plan_product(ctx->n, rows, cols, K, 0, true, 0), pa, pb, out, parts, true, ctx->n, rows, cols, K, out_party_stride, stride_row, cdiv, stride_cb,
+        return ss_launch_gemm(plan, pa, pb, out, parts, true, ctx->n, rows, cols, K, out_party_stride, stride_row, cdiv, stride_cb,
                               ctx->stream, ea, eb);
     });
 }
@@ -566,13 +566,18 @@ int ssnet_linear_mod_packed(ssnet_ctx *ctx, const uint64_t *d_x, const void *d_w
     if (!ctx || !d_x || !d_w_packed || !d_y || !gemm_shape_ok(M, N, K)) return SSNET_EINVAL;
     const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, M, N, K, 0));
     if (!ws_fits(ctx, part + (size_t)ctx->n * ss_packed_bytes(M, K))) return SSNET_EWORKSPACE;
+    const product_plan plan = plan_product(ctx->n, M, N, K, 0, true, 0);
+    if (const int waves = plan.element_waves(M))
+        return run_product(ctx, [&](u64 *parts, hipEvent_t ea, hipEvent_t eb) {
+            return ss_launch_gemm_rows(plan.for_elements(waves), d_x, d_w_packed, d_y, parts, ctx->n, M, K, N, ctx->stream, ea, eb);
+        });
     void *px = ws_scratch(ctx) + part;
     {
         timed tm(ctx, SSNET_PROF_PACK_X);
         hipError_t e = ss_launch_pack_matrix(d_x, px, ctx->n, M, K, (size_t)M * K, (size_t)K, 1, 0, ctx->stream);
         if (e != hipSuccess) return fail_hip(ctx, e);
     }
-    return run_gemm(ctx, px, d_w_packed, d_y, M, N, K, (size_t)M * N, (size_t)N, INT_MAX, 0);
+    return run_gemm(ctx, plan, px, d_w_packed, d_y, M, N, K, (size_t)M * N, (size_t)N, INT_MAX, 0);
 }
 
 int ssnet_linear_mod_prepacked(ssnet_ctx *ctx, const void *d_x_packed, const void *d_w_packed, int M, int K, int N,
@@ -580,7 +585,7 @@ int ssnet_linear_mod_prepacked(ssnet_ctx *ctx, const void *d_x_packed, const voi
 {
     if (!ctx || !d_x_packed || !d_w_packed || !d_y || !gemm_shape_ok(M, N, K)) return SSNET_EINVAL;
     if (!ws_fits(ctx, align256(ss_gemm_scratch_bytes(ctx->n, M, N, K, 0)))) return SSNET_EWORKSPACE;
-    return run_gemm(ctx, d_x_packed, d_w_packed, d_y, M, N, K, (size_t)M * N, (size_t)N, INT_MAX, 0);
+    return run_gemm(ctx, plan_product(ctx->n, M, N, K, 0, true, 0), d_x_packed, d_w_packed, d_y, M, N, K, (size_t)M * N, (size_t)N, INT_MAX, 0);
 }
 
 int ssnet_conv1x1_mod_prepacked(ssnet_ctx *ctx, const void *d_x_packed, const void *d_w_packed, int B, int C, int HW,
@@ -592,7 +597,8 @@ int ssnet_conv1x1_mod_prepacked(ssnet_ctx *ctx, const void *d_x_packed, const vo
     const int M = B * HW;
     if (!ws_fits(ctx, align256(ss_gemm_scratch_bytes(ctx->n, Co, M, C, 0)))) return SSNET_EWORKSPACE;
     // rows = output channel, cols = (b, hw): y[b][co][hw]
-    return run_gemm(ctx, d_w_packed, d_x_packed, d_y, Co, M, C, (size_t)B * Co * HW, (size_t)HW, HW, (size_t)Co * HW);
+    return run_gemm(ctx, plan_product(ctx->n, Co, M, C, 0, true, 0), d_w_packed, d_x_packed, d_y, Co, M, C, (size_t)B * Co * HW, (size_t)HW,
+                    HW, (size_t)Co * HW);
 }
 
 namespace {
@@ -760,6 +766,12 @@ int ssnet_conv_mod_packed(ssnet_ctx *ctx, const uint64_t *d_x, const void *d_w_p
     if (M > (1L << 30) || !gemm_shape_ok(Co, M, K)) return SSNET_EINVAL;
     const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, Co, (int)M, (int)K, 0));
     if (!ws_fits(ctx, part + (size_t)ctx->n * ss_packed_bytes((int)M, (int)K))) return SSNET_EWORKSPACE;
+    const product_plan plan = plan_product(ctx->n, Co, (int)M, (int)K, 0, true, 0);
+    if (const int waves = plan.element_waves(0))
+        return run_product(ctx, [&](u64 *parts, hipEvent_t ea, hipEvent_t eb) {
+            return ss_launch_gemm_images(plan.for_elements(waves), d_w_packed, d_x, d_y, parts, ctx->n, B, C, H, W, Co, kh, kw, stride, pad, Ho, Wo, ctx->stream,
+                                         ea, eb);
+        });
     void *px = ws_scratch(ctx) + part;
     {
         timed tm(ctx, SSNET_PROF_PACK_X);
@@ -768,7 +780,7 @@ int ssnet_conv_mod_packed(ssnet_ctx *ctx, const uint64_t *d_x, const void *d_w_p
     }
     const size_t HW = (size_t)Ho * Wo;
     // rows = output channel, cols = (b, ho, wo): y[b][co][hw]
-    return run_gemm(ctx, d_w_packed, px, d_y, Co, (int)M, (int)K, (size_t)B * Co * HW, HW, (int)HW, (size_t)Co * HW);
+    return run_gemm(ctx, plan, d_w_packed, px, d_y, Co, (int)M, (int)K, (size_t)B * Co * HW, HW, (int)HW, (size_t)Co * HW);
 }
 
 int ssnet_conv_mod(ssnet_ctx *ctx, const uint64_t *d_x, const uint64_t *d_w, int B, int C, int H, int W, int Co, int kh,
