@@ -96,6 +96,32 @@ __global__ __launch_bounds__(256) void pack_matrix_kernel(const u64 *__restrict_
     store_limbs(y, kq & 3, [&](int limb, v4i v) { tile[limb * 64] = v; });
 }
 
+// The same for two operands with one contraction in one launch (a dense layer whose operands both change: 500 x 333 x 1201, n = 4, 14.9 us in
+// two launches, 12.6 us in one, and no gap): the blocks of `a` come first, in the order of its contraction, then those of `b`, in the order of its rows.
+struct pack_job {
+    const u64 *src;
+    v4i *dst;
+    int rows, Rb, blocks;
+    fdiv dFast;              // of the blocks along the index that runs fastest
+    size_t party_stride, stride_r, stride_k, dst_party_stride;
+};
+__global__ __launch_bounds__(256) void pack_pair_kernel(pack_job a, pack_job b, int K, int Kb)
+{
+    const bool first = (int)blockIdx.x < a.blocks;   // uniform
+    const pack_job j = first ? a : b;
+    const int at = (int)xcd_slot(first ? blockIdx.x : blockIdx.x - a.blocks, j.blocks), q = (int)fd_div((u32)at, j.dFast);
+    const int rb = first ? q : at - q * j.Rb, kb = first ? at - q * Kb : q;
+    const int r16 = threadIdx.x & 15, kq = threadIdx.x >> 4, row = rb * 16 + r16, k0 = kb * 64 + 4 * kq;
+    const u64 *s = j.src + (size_t)blockIdx.y * j.party_stride + (row < j.rows ? (size_t)row * j.stride_r : 0);
+    u64 y[4];
+#pragma unroll
+    for (int c = 0; c < 4; c++) y[c] = s[(size_t)(k0 + c < K ? k0 + c : 0) * j.stride_k];
+#pragma unroll
+    for (int c = 0; c < 4; c++) y[c] = row < j.rows && k0 + c < K ? balanced_digits(y[c]) : 0;
+    v4i *tile = j.dst + (size_t)blockIdx.y * j.dst_party_stride + ((size_t)rb * Kb + kb) * TILE + r16 + 16 * (kq >> 2);
+    store_limbs(y, kq & 3, [&](int limb, v4i v) { tile[limb * 64] = v; });
+}
+
 // rows = (b, ho, wo), k = (c, r, s) gathered from x [n][B][C][H][W]; zero padding.  An element is gathered once per tap, so
 // the index arithmetic is kept short: divisions by constants of the launch, and a thread's four loads unconditional (taps in the
 // padding and indices past the matrix load the tensor's first element).
@@ -1132,6 +1158,21 @@ hipError_t ss_launch_pack_matrix(const u64 *src, void *dst, int n, int rows, int
     hipLaunchKernelGGL(pack_matrix_kernel, dim3((unsigned)Rb * (unsigned)Kb, n), dim3(256), 0, stream, src, (v4i *)dst, rows, K, Rb,
                        Kb, make_fdiv((u32)Rb), make_fdiv((u32)Kb), stride_k == 1, party_stride, stride_r, stride_k,
                        ss_packed_bytes(rows, K) / 16, taps, taps && K / taps % 64 == 0 ? K / taps / 64 : 0, make_fdiv(taps ? (u32)taps : 1));
+    return hipGetLastError();
+}
+
+hipError_t ss_launch_pack_operands(const u64 *x, void *packedX, const u64 *w, void *packedW, int n, int M, int K, int N, hipStream_t stream)
+{
+    const int Kb = (K + 63) / 64;
+    const long xblocks = (long)((M + 15) / 16) * Kb, wblocks = (long)((N + 15) / 16) * Kb;
+    if (!fits_grid(xblocks + wblocks, 256)) {
+        const hipError_t e = ss_launch_pack_matrix(w, packedW, n, N, K, (size_t)K * N, 1, (size_t)N, 0, stream);
+        return e == hipSuccess ? ss_launch_pack_matrix(x, packedX, n, M, K, (size_t)M * K, (size_t)K, 1, 0, stream) : e;
+    }
+    const pack_job a = {x, (v4i *)packedX, M, (M + 15) / 16, (int)xblocks, make_fdiv((u32)Kb), (size_t)M * K, (size_t)K, 1, ss_packed_bytes(M, K) / 16};
+    const int Nb = (N + 15) / 16;
+    const pack_job b = {w, (v4i *)packedW, N, Nb, (int)wblocks, make_fdiv((u32)Nb), (size_t)K * N, 1, (size_t)N, ss_packed_bytes(N, K) / 16};
+    hipLaunchKernelGGL(pack_pair_kernel, dim3((unsigned)(xblocks + wblocks), n), dim3(256), 0, stream, a, b, K, Kb);
     return hipGetLastError();
 }
 

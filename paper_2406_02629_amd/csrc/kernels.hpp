@@ -154,6 +154,8 @@ size_t ss_packed_bytes(int rows, int K);
 // tap*C + c reads source index c*taps + tap (C = K / taps)
 hipError_t ss_launch_pack_matrix(const u64 *src, void *dst, int n, int rows, int K, size_t party_stride,
                                  size_t stride_r, size_t stride_k, int taps, hipStream_t stream);
+// both operands of a dense layer in one launch: x [n][M][K] with its rows, w [n][K][N] with its columns as packed rows
+hipError_t ss_launch_pack_operands(const u64 *x, void *packedX, const u64 *w, void *packedW, int n, int M, int K, int N, hipStream_t stream);
 // degree-t shares of secret [B][K][HW] -> shares [n][B][K][HW] and their packed operand (rows (b, hw), k)
 hipError_t ss_launch_share_pack(const u64 *secret, u64 *shares, void *dst, int n, int t, int B, int K, int HW,
                                 const ss_keys &keys, hipStream_t stream);

@@ -748,10 +748,19 @@ int ssnet_linear_mod(ssnet_ctx *ctx, const uint64_t *d_x, const uint64_t *d_w, i
     const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, M, N, K, 0));
     const size_t xa = (size_t)ctx->n * ss_packed_bytes(M, K), wa = (size_t)ctx->n * ss_packed_bytes(N, K);
     if (!ws_fits(ctx, part + xa + wa)) return SSNET_EWORKSPACE;
-    void *pw = ws_scratch(ctx) + part + xa;
-    int rc = ssnet_pack_weights_linear(ctx, d_w, K, N, pw);
-    if (rc) return rc;
-    return ssnet_linear_mod_packed(ctx, d_x, pw, M, K, N, d_y);
+    if (!gemm_shape_ok(N, 1, K)) return SSNET_EINVAL;   // rows of a packed operand
+    void *px = ws_scratch(ctx) + part, *pw = ws_scratch(ctx) + part + xa;
+    const product_plan plan = plan_product(ctx->n, M, N, K, 0, true, 0);
+    if (plan.element_waves(M)) {   // x is not packed
+        int rc = ssnet_pack_weights_linear(ctx, d_w, K, N, pw);
+        return rc ? rc : ssnet_linear_mod_packed(ctx, d_x, pw, M, K, N, d_y);
+    }
+    {
+        timed tm(ctx, SSNET_PROF_PACK_X);
+        hipError_t e = ss_launch_pack_operands(d_x, px, d_w, pw, ctx->n, M, K, N, ctx->stream);
+        if (e != hipSuccess) return fail_hip(ctx, e);
+    }
+    return run_gemm(ctx, plan, px, pw, d_y, M, N, K, (size_t)M * N, (size_t)N, INT_MAX, 0);
 }
 
 int ssnet_conv_mod_packed(ssnet_ctx *ctx, const uint64_t *d_x, const void *d_w_packed, int B, int C, int H, int W,
