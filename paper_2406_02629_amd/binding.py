@@ -1,4 +1,5 @@
-"""ctypes binding of libssnet.so (the C ABI of include/ssnet.h).
+"""Binding of libssnet.so (the C ABI of include/ssnet.h): ctypes, and the extension module
+_calls (csrc/calls.c) for the entry points that a network calls layer by layer.
 
 Argument marshalling only: every operation on share data runs in the HIP
 kernels of the library.  torch supplies device memory (int64 tensors hold the
@@ -7,6 +8,7 @@ kernels of the library.  torch supplies device memory (int64 tensors hold the
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import Optional, Sequence
 
@@ -87,6 +89,31 @@ SIGNATURES = {
 }
 
 _libs = {}
+_calls = None     # the extension module
+
+
+class _Entries:
+    """Entry points of a library as callables of _calls, by name without the prefix."""
+
+    NAMES = ("share", "reconstruct", "linear_mod", "linear_mod_packed", "conv_mod_packed", "share_packed", "linear_mod_prepacked",
+             "conv1x1_mod_prepacked", "share_planes", "split_planes", "conv_mod_planes", "linear_product_prepacked",
+             "conv1x1_product_prepacked", "conv_product_planes", "degree_reduce", "truncate", "degree_reduce_truncate",
+             "degree_reduce_truncate_div", "degree_reduce_truncate_reconstruct", "reduce_truncate_direct", "reduce_truncate_relu",
+             "reduce_truncate_relu_direct", "relu", "relu_pool")
+
+    def __init__(self, lib: C.CDLL):
+        global _calls
+        if _calls is None:
+            if not os.path.exists(_build.CALLS):
+                _build.build_calls()
+            spec = importlib.util.spec_from_file_location("_calls", _build.CALLS)
+            module = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(module)
+            _calls = module
+        for name in self.NAMES:
+            fn = getattr(lib, "ssnet_" + name)
+            pointers = sum(1 << i for i, kind in enumerate(fn.argtypes) if kind not in (_int, _sz, _u64))
+            setattr(self, name, _calls.bind(C.cast(fn, _ptr).value, len(fn.argtypes), pointers))
 
 
 def load_library(p: int = P61) -> C.CDLL:
@@ -101,6 +128,7 @@ def load_library(p: int = P61) -> C.CDLL:
         for name, (res, args) in SIGNATURES.items():
             fn = getattr(lib, name)
             fn.restype, fn.argtypes = res, args
+        lib.entries = _Entries(lib)
         _libs[path] = lib
     return _libs[path]
 
@@ -144,6 +172,7 @@ class SSNet:
         if rc:
             self._ctx = None
             raise SSNetError(rc, "ssnet_create")
+        self._handle, self._call = self._ctx.value, self.lib.entries
         self._ws: Optional[torch.Tensor] = None
         # sizes that the library has given for a shape, and the largest element count whose messages are known to fit
         # the present workspace: asking again costs a foreign call (0.5 to 1.1 us), which small layers feel
@@ -153,7 +182,7 @@ class SSNet:
     def close(self):
         if getattr(self, "_ctx", None):
             self.lib.ssnet_destroy(self._ctx)
-            self._ctx = None
+            self._ctx = self._handle = None
 
     def __del__(self):
         try:
@@ -211,7 +240,7 @@ class SSNet:
         degree = self.t if degree is None else degree
         if out is None:
             out = torch.empty((self.n,) + tuple(secret.shape), dtype=torch.int64, device=secret.device)
-        self._ok(self.lib.ssnet_share(self._ctx, _dptr(secret), secret.numel(), degree, stream_id, _dptr(out)),
+        self._ok(self._call.share(self._handle, _dptr(secret), secret.numel(), degree, stream_id, _dptr(out)),
                  "ssnet_share")
         return out
 
@@ -223,7 +252,7 @@ class SSNet:
         if out is None:
             out = torch.empty(tuple(shares.shape[1:]), dtype=torch.int64, device=shares.device)
         arr = (_int * len(ids))(*ids)
-        self._ok(self.lib.ssnet_reconstruct(self._ctx, _dptr(shares), count, arr, len(ids), degree, _dptr(out)),
+        self._ok(self._call.reconstruct(self._handle, _dptr(shares), count, C.addressof(arr), len(ids), degree, _dptr(out)),
                  "ssnet_reconstruct")
         return out
 
@@ -237,7 +266,7 @@ class SSNet:
         self.reserve(self.workspace_bytes_linear(M, K, N))
         if out is None:
             out = torch.empty((n, M, N), dtype=torch.int64, device=x.device)
-        self._ok(self.lib.ssnet_linear_mod(self._ctx, _dptr(x), _dptr(w), M, K, N, _dptr(out)), "ssnet_linear_mod")
+        self._ok(self._call.linear_mod(self._handle, _dptr(x), _dptr(w), M, K, N, _dptr(out)), "ssnet_linear_mod")
         return out
 
     def conv_mod(self, x: torch.Tensor, w: torch.Tensor, stride: int, pad: int,
@@ -282,7 +311,7 @@ class SSNet:
         self.reserve(self.workspace_bytes_linear(M, K, N))
         if out is None:
             out = torch.empty((n, M, N), dtype=torch.int64, device=x.device)
-        self._ok(self.lib.ssnet_linear_mod_packed(self._ctx, _dptr(x), _dptr(w_packed), M, K, N, _dptr(out)),
+        self._ok(self._call.linear_mod_packed(self._handle, _dptr(x), _dptr(w_packed), M, K, N, _dptr(out)),
                  "ssnet_linear_mod_packed")
         return out
 
@@ -304,7 +333,7 @@ class SSNet:
             packed = torch.empty(nbytes, dtype=torch.uint8, device=secret.device)
         elif packed.numel() * packed.element_size() < nbytes:
             raise SSNetError(EINVAL, "share_packed: packed buffer too small")
-        self._ok(self.lib.ssnet_share_packed(self._ctx, _dptr(secret), B, K, HW, stream_id, _dptr(out), _dptr(packed)),
+        self._ok(self._call.share_packed(self._handle, _dptr(secret), B, K, HW, stream_id, _dptr(out), _dptr(packed)),
                  "ssnet_share_packed")
         return out, packed
 
@@ -313,7 +342,7 @@ class SSNet:
         self.reserve(self.workspace_bytes_linear(M, K, N))
         if out is None:
             out = torch.empty((self.n, M, N), dtype=torch.int64, device=x_packed.device)
-        self._ok(self.lib.ssnet_linear_mod_prepacked(self._ctx, _dptr(x_packed), _dptr(w_packed), M, K, N, _dptr(out)),
+        self._ok(self._call.linear_mod_prepacked(self._handle, _dptr(x_packed), _dptr(w_packed), M, K, N, _dptr(out)),
                  "ssnet_linear_mod_prepacked")
         return out
 
@@ -322,8 +351,8 @@ class SSNet:
         self.reserve(self.workspace_bytes_conv(B, C, H, W, Co, 1, 1, 1, 0))
         if out is None:
             out = torch.empty((self.n, B, Co, H, W), dtype=torch.int64, device=x_packed.device)
-        self._ok(self.lib.ssnet_conv1x1_mod_prepacked(self._ctx, _dptr(x_packed), _dptr(w_packed), B, C, H * W, Co,
-                                                      _dptr(out)), "ssnet_conv1x1_mod_prepacked")
+        self._ok(self._call.conv1x1_mod_prepacked(self._handle, _dptr(x_packed), _dptr(w_packed), B, C, H * W, Co,
+                                                  _dptr(out)), "ssnet_conv1x1_mod_prepacked")
         return out
 
     # ---- convolution on limb planes (no im2col matrix) ----
@@ -348,7 +377,7 @@ class SSNet:
         planes = self._planes_buffer(B, C, H, W, planes, secret.device)
         if out is None:
             out = torch.empty((self.n,) + tuple(secret.shape), dtype=torch.int64, device=secret.device)
-        self._ok(self.lib.ssnet_share_planes(self._ctx, _dptr(secret), B, C, H, W, stream_id, _dptr(out), _dptr(planes)),
+        self._ok(self._call.share_planes(self._handle, _dptr(secret), B, C, H, W, stream_id, _dptr(out), _dptr(planes)),
                  "ssnet_share_planes")
         return out, planes
 
@@ -356,7 +385,7 @@ class SSNet:
         _check_i64(x, "x")
         n, B, C, H, W = x.shape
         planes = self._planes_buffer(B, C, H, W, planes, x.device)
-        self._ok(self.lib.ssnet_split_planes(self._ctx, _dptr(x), B, C, H, W, _dptr(planes)), "ssnet_split_planes")
+        self._ok(self._call.split_planes(self._handle, _dptr(x), B, C, H, W, _dptr(planes)), "ssnet_split_planes")
         return planes
 
     def pack_weights_conv_taps(self, w: torch.Tensor) -> torch.Tensor:
@@ -377,37 +406,41 @@ class SSNet:
         Ho, Wo = (H + 2 * pad - kh) // stride + 1, (W + 2 * pad - kw) // stride + 1
         if out is None:
             out = torch.empty((self.n, B, Co, Ho, Wo), dtype=torch.int64, device=planes.device)
-        self._ok(self.lib.ssnet_conv_mod_planes(self._ctx, _dptr(planes), _dptr(w_packed), B, C, H, W, Co, kh, kw, stride,
-                                                pad, _dptr(out)), "ssnet_conv_mod_planes")
+        self._ok(self._call.conv_mod_planes(self._handle, _dptr(planes), _dptr(w_packed), B, C, H, W, Co, kh, kw, stride,
+                                            pad, _dptr(out)), "ssnet_conv_mod_planes")
         return out
 
     # ---- products left in the workspace for the reduction that follows (d_c = NULL there) ----
-    def _reserve_product(self, product_bytes: int, B: int, C: int, HW: int):
-        """room for the pending product plus the messages of whichever call consumes it"""
-        if product_bytes == 0:
-            raise SSNetError(EINVAL, "ssnet_product_bytes")
-        msgs = max(self._size("ssnet_workspace_bytes_stream", B * C * HW),
-                   self._size("ssnet_workspace_bytes_layer_tail", B, C, HW))
-        self.reserve(msgs + product_bytes)
+    def _reserve_product(self, fn: str, shape: tuple, B: int, C: int, HW: int):
+        """room for the pending product (`fn` of `shape` bytes, of B x C x HW elements) plus the messages of whichever call consumes it"""
+        key = ("product and messages", fn, shape)
+        nbytes = self._sizes.get(key)
+        if nbytes is None:
+            product_bytes = self._size(fn, *shape)
+            if product_bytes == 0:
+                raise SSNetError(EINVAL, "ssnet_product_bytes")
+            nbytes = product_bytes + max(self._size("ssnet_workspace_bytes_stream", B * C * HW),
+                                         self._size("ssnet_workspace_bytes_layer_tail", B, C, HW))
+            self._sizes[key] = nbytes
+        self.reserve(nbytes)
 
     def linear_product_prepacked(self, x_packed: torch.Tensor, w_packed: torch.Tensor, M: int, K: int, N: int):
-        self._reserve_product(self._size("ssnet_product_bytes_linear", M, K, N), M, N, 1)
-        self._ok(self.lib.ssnet_linear_product_prepacked(self._ctx, _dptr(x_packed), _dptr(w_packed), M, K, N),
+        self._reserve_product("ssnet_product_bytes_linear", (M, K, N), M, N, 1)
+        self._ok(self._call.linear_product_prepacked(self._handle, _dptr(x_packed), _dptr(w_packed), M, K, N),
                  "ssnet_linear_product_prepacked")
 
     def conv1x1_product_prepacked(self, x_packed: torch.Tensor, w_packed: torch.Tensor, B: int, C: int, H: int, W: int,
                                   Co: int):
-        self._reserve_product(self._size("ssnet_product_bytes_conv", B, C, H, W, Co, 1, 1, 1, 0), B, Co, H * W)
-        self._ok(self.lib.ssnet_conv1x1_product_prepacked(self._ctx, _dptr(x_packed), _dptr(w_packed), B, C, H * W, Co),
+        self._reserve_product("ssnet_product_bytes_conv", (B, C, H, W, Co, 1, 1, 1, 0), B, Co, H * W)
+        self._ok(self._call.conv1x1_product_prepacked(self._handle, _dptr(x_packed), _dptr(w_packed), B, C, H * W, Co),
                  "ssnet_conv1x1_product_prepacked")
 
     def conv_product_planes(self, planes: torch.Tensor, w_packed: torch.Tensor, B: int, C: int, H: int, W: int, Co: int,
                             kh: int, kw: int, stride: int, pad: int):
         Ho, Wo = (H + 2 * pad - kh) // stride + 1, (W + 2 * pad - kw) // stride + 1
-        self._reserve_product(self._size("ssnet_product_bytes_conv", B, C, H, W, Co, kh, kw, stride, pad), B, Co,
-                              Ho * Wo)
-        self._ok(self.lib.ssnet_conv_product_planes(self._ctx, _dptr(planes), _dptr(w_packed), B, C, H, W, Co, kh, kw,
-                                                    stride, pad), "ssnet_conv_product_planes")
+        self._reserve_product("ssnet_product_bytes_conv", (B, C, H, W, Co, kh, kw, stride, pad), B, Co, Ho * Wo)
+        self._ok(self._call.conv_product_planes(self._handle, _dptr(planes), _dptr(w_packed), B, C, H, W, Co, kh, kw,
+                                                stride, pad), "ssnet_conv_product_planes")
 
     def conv_mod_packed(self, x: torch.Tensor, w_packed: torch.Tensor, Co: int, kh: int, kw: int, stride: int,
                         pad: int, out: Optional[torch.Tensor] = None) -> torch.Tensor:
@@ -420,8 +453,8 @@ class SSNet:
         Ho, Wo = (H + 2 * pad - kh) // stride + 1, (W + 2 * pad - kw) // stride + 1
         if out is None:
             out = torch.empty((n, B, Co, Ho, Wo), dtype=torch.int64, device=x.device)
-        self._ok(self.lib.ssnet_conv_mod_packed(self._ctx, _dptr(x), _dptr(w_packed), B, Ci, H, W, Co, kh, kw, stride,
-                                                pad, _dptr(out)), "ssnet_conv_mod_packed")
+        self._ok(self._call.conv_mod_packed(self._handle, _dptr(x), _dptr(w_packed), B, Ci, H, W, Co, kh, kw, stride,
+                                            pad, _dptr(out)), "ssnet_conv_mod_packed")
         return out
 
     # ---- RED + RERAND, truncation ----
@@ -441,7 +474,7 @@ class SSNet:
         self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(c)
-        self._ok(self.lib.ssnet_degree_reduce(self._ctx, cp, count, stream_id, _dptr(out)),
+        self._ok(self._call.degree_reduce(self._handle, cp, count, stream_id, _dptr(out)),
                  "ssnet_degree_reduce")
         return out
 
@@ -460,7 +493,7 @@ class SSNet:
         self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(x)
-        self._ok(self.lib.ssnet_truncate(self._ctx, _dptr(x), count, stream_id, _dptr(out)), "ssnet_truncate")
+        self._ok(self._call.truncate(self._handle, _dptr(x), count, stream_id, _dptr(out)), "ssnet_truncate")
         return out
 
     def degree_reduce_truncate(self, c: Optional[torch.Tensor], stream_id: int,
@@ -470,7 +503,7 @@ class SSNet:
         self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(c)
-        self._ok(self.lib.ssnet_degree_reduce_truncate(self._ctx, cp, count, stream_id, _dptr(out)),
+        self._ok(self._call.degree_reduce_truncate(self._handle, cp, count, stream_id, _dptr(out)),
                  "ssnet_degree_reduce_truncate")
         return out
 
@@ -490,7 +523,7 @@ class SSNet:
         self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(c)
-        self._ok(self.lib.ssnet_degree_reduce_truncate_div(self._ctx, cp, count, kdiv, stream_id, _dptr(out)),
+        self._ok(self._call.degree_reduce_truncate_div(self._handle, cp, count, kdiv, stream_id, _dptr(out)),
                  "ssnet_degree_reduce_truncate_div")
         return out
 
@@ -508,8 +541,8 @@ class SSNet:
         else:
             _check_i64(secret, "secret")
         arr = (_int * len(ids))(*ids)
-        self._ok(self.lib.ssnet_degree_reduce_truncate_reconstruct(self._ctx, cp, count, stream_id, _dptr(out),
-                                                                   arr, len(ids), _dptr(secret)),
+        self._ok(self._call.degree_reduce_truncate_reconstruct(self._handle, cp, count, stream_id, _dptr(out),
+                                                               C.addressof(arr), len(ids), _dptr(secret)),
                  "ssnet_degree_reduce_truncate_reconstruct")
         return out, secret
 
@@ -524,9 +557,10 @@ class SSNet:
         if ids is not None and secret is None:
             secret = torch.empty(c.shape[1:], dtype=torch.int64, device=c.device)
         arr = (_int * len(ids))(*ids) if ids is not None else None
-        self._ok(self.lib.ssnet_reduce_truncate_direct(self._ctx, cp, count, stream_id, _dptr(out), arr,
-                                                       len(ids) if ids is not None else 0,
-                                                       _dptr(secret) if secret is not None else None),
+        self._ok(self._call.reduce_truncate_direct(self._handle, cp, count, stream_id, _dptr(out),
+                                                   C.addressof(arr) if ids is not None else None,
+                                                   len(ids) if ids is not None else 0,
+                                                   _dptr(secret) if secret is not None else None),
                  "ssnet_reduce_truncate_direct")
         return out, secret
 
@@ -544,8 +578,8 @@ class SSNet:
             out = torch.empty_like(c)
         if want_planes and planes is None:
             planes = self._planes_buffer(B, C, HW, 1, None, c.device)
-        self._ok(self.lib.ssnet_reduce_truncate_relu(self._ctx, cp, B, C, HW, stream_id, _dptr(beta), _dptr(betainv),
-                                                     _dptr(out), _dptr(planes) if planes is not None else None),
+        self._ok(self._call.reduce_truncate_relu(self._handle, cp, B, C, HW, stream_id, _dptr(beta), _dptr(betainv),
+                                                 _dptr(out), _dptr(planes) if planes is not None else None),
                  "ssnet_reduce_truncate_relu")
         return out, planes
 
@@ -562,8 +596,8 @@ class SSNet:
             out = torch.empty_like(c)
         if want_planes and planes is None:
             planes = self._planes_buffer(B, C, HW, 1, None, c.device)
-        self._ok(self.lib.ssnet_reduce_truncate_relu_direct(self._ctx, cp, B, C, HW, _dptr(beta), _dptr(betainv), _dptr(out),
-                                                            _dptr(planes) if planes is not None else None),
+        self._ok(self._call.reduce_truncate_relu_direct(self._handle, cp, B, C, HW, _dptr(beta), _dptr(betainv), _dptr(out),
+                                                        _dptr(planes) if planes is not None else None),
                  "ssnet_reduce_truncate_relu_direct")
         return out, planes
 
@@ -588,7 +622,7 @@ class SSNet:
         self._reserve_stream(count)
         if out is None:
             out = torch.empty_like(x)
-        self._ok(self.lib.ssnet_relu(self._ctx, _dptr(x), _dptr(beta), _dptr(betainv), count, _dptr(out)), "ssnet_relu")
+        self._ok(self._call.relu(self._handle, _dptr(x), _dptr(beta), _dptr(betainv), count, _dptr(out)), "ssnet_relu")
         return out
 
     POOL_MAX, POOL_SUM = 0, 1
@@ -626,8 +660,8 @@ class SSNet:
             out = torch.empty(tuple(x.shape[:-2]) + (Ho, Wo), dtype=torch.int64, device=x.device)
         elif out.numel() != self.n * planes * Ho * Wo:
             raise SSNetError(EINVAL, "relu_pool: out has the wrong size")
-        self._ok(self.lib.ssnet_relu_pool(self._ctx, _dptr(x), _dptr(beta), _dptr(betainv), planes, H, W, kh, kw, sh, sw,
-                                          ph, pw, mode, _dptr(out)), "ssnet_relu_pool")
+        self._ok(self._call.relu_pool(self._handle, _dptr(x), _dptr(beta), _dptr(betainv), planes, H, W, kh, kw, sh, sw,
+                                      ph, pw, mode, _dptr(out)), "ssnet_relu_pool")
         return out
 
     PROF_CLASSES = ("share", "reconstruct", "pack_w", "pack_x", "gemm", "degree_reduce", "truncate", "nonlinear",

@@ -4,11 +4,13 @@ over p = 2^45 - 55.
 
 hipcc cross-compiles without a GPU.  Each .hip file is compiled to an object
 and the objects are linked into one shared library per field that exports the
-C ABI of include/ssnet.h.
+C ABI of include/ssnet.h.  csrc/calls.c, the calls from Python into that ABI, becomes
+the extension module _calls.so.
 """
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -16,6 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libssnet.so")
 LIB_P45 = os.path.join(HERE, "libssnet_p45.so")
+CALLS = os.path.join(HERE, "_calls.so")
 VARIANTS = {"p61": (LIB, []), "p45": (LIB_P45, ["-DSS_FIELD_P45"])}
 SOURCES = ["stream_kernels.hip", "gemm_kernels.hip", "ssnet_api.hip", "probes.hip"]
 HEADERS = ["field.hpp", "kernels.hpp", "eval.hpp", "digits.hpp", "gemm_plan.hpp", "pool_plan.hpp", os.path.join("..", "..", "include", "ssnet.h")]
@@ -28,13 +31,24 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 
 
 def _newest_source() -> float:
-    paths = [os.path.join(CSRC, s) for s in SOURCES + HEADERS]
+    paths = [os.path.join(CSRC, s) for s in SOURCES + HEADERS + ["calls.c"]]
     return max(os.path.getmtime(p) for p in paths)
 
 
 def is_current() -> bool:
     newest = _newest_source()
-    return all(os.path.exists(lib) and os.path.getmtime(lib) >= newest for lib, _ in VARIANTS.values())
+    return all(os.path.exists(lib) and os.path.getmtime(lib) >= newest for lib in [CALLS] + [lib for lib, _ in VARIANTS.values()])
+
+
+def build_calls() -> str:
+    """Build the extension module alone (a second of gcc)."""
+    tmp = f"{CALLS}.{os.getpid()}.tmp"
+    cmd = ["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "calls.c"), "-o", tmp]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"gcc failed on calls.c:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, CALLS)
+    return CALLS
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
@@ -42,6 +56,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     if not force and is_current():
         return LIB
     os.makedirs(OBJ, exist_ok=True)
+    build_calls()
 
     def compile_one(job):
         tag, src = job
