@@ -466,6 +466,7 @@ __global__ __launch_bounds__(BLOCK, T == 3 ? 4 : 1) void degree_reduce_kernel(co
                                                               u64 *__restrict__ rec, size_t count, ss_dr_params dp,
                                                               ss_tr_params tp, ss_part_src ps)
 {
+    request_arguments<8 * 8 + sizeof(ss_dr_params) + sizeof(ss_tr_params) + sizeof(ss_part_src)>();
     const size_t e = element_block<BLOCK>(count, count) * BLOCK + threadIdx.x;
     if (e >= count) return;
     u64 o[MAXP<N>], secret;
