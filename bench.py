@@ -294,7 +294,7 @@ def p45_chain(layers, steps, warmup, batch=1):
     return {"workload": f"headline stack over p = 2^45 - 55 (libssnet_p45.so), n=5 t=2 f=13 batch {batch}",
             "ms_per_step": ms, "field_MAC_per_s": macs / (ms * 1e-3),
             "kernel_ms_per_step": {k: {"ms": round(v[0], 4), "spans": v[1]} for k, v in prof.items()},
-            "roofline": {"bound": "mfma", "kernel": "gemm_limb_kernel, gemm_ksplit_kernel, gemm_skinny_kernel (6 limbs)",
+            "roofline": {"bound": "mfma", "kernel": "gemm_square_kernel, gemm_limb_kernel, gemm_ksplit_kernel, gemm_skinny_kernel (6 limbs)",
                          "achieved": ops / (gemm_ms * 1e-3) / 1e12,
                          "peak": INT8_PEAK_TOPS, "unit": "TOP/s", "frac": ops / (gemm_ms * 1e-3) / 1e12 / INT8_PEAK_TOPS,
                          "launches": gemm_launches, "int8_ops_per_step": ops}}
@@ -490,7 +490,7 @@ def main():
                                                 "degree_reduce+rerand+truncate+reconstruct (one launch)"},
             # ms_per_step is wall time over the K steps; these are the same K steps one by one (HIP events)
             "ms_per_step_events": {k: round(v, 4) if k != "n" else v for k, v in stats(per_step).items()},
-            "roofline": {"bound": "mfma", "kernel": "gemm_limb_kernel, gemm_ksplit_kernel (shorter layers), gemm_skinny_kernel (classifier)",
+            "roofline": {"bound": "mfma", "kernel": "gemm_square_kernel, gemm_skinny_kernel (classifier)",
                          "achieved": achieved, "peak": INT8_PEAK_TOPS,
                          "unit": "TOP/s", "frac": achieved / INT8_PEAK_TOPS,
                          "traffic": traffic, "traffic_unit": "bytes per launch (HBM)",

@@ -232,7 +232,7 @@ constexpr int SQUARE_RUNS = 8;
 // us of matrix work 6.5 % faster on average over all of them, 5 % of them more than 3 % slower.  Before -> after, us, product + reduction +
 // truncation (rows x columns x contraction, runs): n = 5, 128 x 784 x 1152 44.2 -> 38.3 (1), 256 x 196 x 1024 29.0 -> 25.3 (2), 512 x 49 x 2048 31.0 ->
 // 26.7 (3); n = 3, 128 x 49 x 4608 32.6 -> 15.9 (8), 128 x 1024 x 1152 34.5 -> 30.2 (2); over the 45-bit prime, n = 3, 512 x 49 x 4608 28.7 -> 22.7 (5), 256 x
-// 196 x 2304 24.6 -> 19.8 (3).  Left: n = 5, 64 x 3136 x 576 44.4 -> 45.0; n = 3, 66 x 256 x 6400 27.0 -> 30.0.  Large convolutions whose weights
+// 196 x 2304 24.6 -> 19.8 (3).  Left: n = 5, 64 x 3136 x 576 44.4 -> 45.0; n = 3, 66 x 256 x 6400 27.0 -> 30.0; n = 7, 203 x 576 x 500 (252 tiles of 64 x 64) 62.6 -> 64.0.  Large convolutions whose weights
 // no L2 holds are left too: there a tile of 64 x 64 reads them half as often (895 x 8712 x 3200, n = 3, 3.20 -> 3.55 ms).
 inline square_plan plan_square(const gemm_plan &p, double p_us, int n, int rows, int cols, int K, int gather, bool tensor, int most)
 {

@@ -71,16 +71,13 @@ __device__ __forceinline__ unsigned xcd_slot(unsigned block, unsigned G)
 
 // Requests the cache lines of a kernel's first BYTES of arguments together and waits for them.  What does not arrive in registers is loaded
 // where it is used, and in a launch of a few workgroups, which nobody's loads precede, each of a dozen lines in turn comes from memory:
-// a chain of four or five such waits.  Workgroups from the 1024th on find the lines in the caches and would only wait for their own request
-// (asked for by every workgroup, 802816 elements took 2 % longer).  Reduction and truncation, back to back on operands that change, us:
-// n = 3 2000 elements 4.6 -> 4.1, 50176 4.35 -> 3.95; n = 5 5.05 -> 4.5, 6.9 -> 6.5, 200704 15.15 -> 15.05; n = 7 8.0 -> 7.65, 10.4 -> 10.1,
-// 26.1 -> 25.2; from 800 K elements on the same.  (Asked for by the layer tail's kernel, networks took up to 1 % longer.)
+// a chain of four or five such waits.  For short launches: in longer ones most workgroups find the lines in the caches and would only wait
+// for their own request.  (Asked for by the layer tail's kernel, networks took up to 1 % longer.)
 template <size_t BYTES>
 __device__ __forceinline__ void request_arguments()
 {
     constexpr size_t LINES = (BYTES + 63) / 64;
     static_assert(LINES <= 20);
-    if (blockIdx.x >= 1024) return;
     const auto *args = (const u32 __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
     u32 w[20];
 #pragma unroll

@@ -458,15 +458,24 @@ __device__ __forceinline__ void reduce_truncate(size_t e, size_t count, size_t e
     }
 }
 
+// Most elements of a reduction that asks for its arguments together (request_arguments): further on the time is the same, or longer by 2 %
+// (n = 3, 200704 elements 8.1 -> 8.3, 802816 23.1 -> 23.6; n = 5, 802816 47.2 -> 47.5).  Reduction and truncation, back to back on operands
+// that change, us: n = 3, 2000 elements 4.6 -> 4.1, 50176 4.35 -> 3.95; n = 5 5.1 -> 4.6 (5.05 where the host is slower), 6.9 -> 6.6, 120000
+// 9.6 -> 9.2; n = 7 8.0 -> 7.7, 10.5 -> 9.9, 16.2 -> 15.5, 200704 25.9 -> 24.7, 400000 49.4 -> 49.4.
+template <int T>
+constexpr size_t REQUEST_MAX_COUNT = (size_t)1 << (T == 3 ? 18 : 17);
+
+// One thread per element.  `count` stands among the arguments that arrive in registers: whether a launch is short enough to ask for the others together is
+// known without a load.
 // (t = 3: without the second bound the compiler takes 157 registers, three waves per SIMD, to no gain)
 // LEAN: without the code for products of which only a part of the tiles is cut, see HAS_LEAN.
 template <int N, int T, bool TRUNC, bool STREAM, bool LEAN>
 __global__ __launch_bounds__(BLOCK, T == 3 ? 4 : 1) void degree_reduce_kernel(const u64 *c, u64 *__restrict__ msg1, u64 *__restrict__ msg2,
                                                               u64 *__restrict__ umsg, u64 *__restrict__ wsh, u64 *out,
-                                                              u64 *__restrict__ rec, size_t count, ss_dr_params dp,
+                                                              size_t count, u64 *__restrict__ rec, ss_dr_params dp,
                                                               ss_tr_params tp, ss_part_src ps)
 {
-    request_arguments<8 * 8 + sizeof(ss_dr_params) + sizeof(ss_tr_params) + sizeof(ss_part_src)>();
+    if (count <= REQUEST_MAX_COUNT<T>) request_arguments<8 * 8 + sizeof(ss_dr_params) + sizeof(ss_tr_params) + sizeof(ss_part_src)>();
     const size_t e = element_block<BLOCK>(count, count) * BLOCK + threadIdx.x;
     if (e >= count) return;
     u64 o[MAXP<N>], secret;
@@ -1108,7 +1117,7 @@ hipError_t ss_launch_degree_reduce(const u64 *c, u64 *msg1, u64 *msg2, u64 *out,
                                : lean ? degree_reduce_kernel<NC, TC, false, false, HAS_LEAN<NC, TC>>                       \
                                       : degree_reduce_kernel<NC, TC, false, false, false>),                                       \
                        dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, (u64 *)nullptr, (u64 *)nullptr, \
-                       out, (u64 *)nullptr, count, dp, none, ps)
+                       out, count, (u64 *)nullptr, dp, none, ps)
     SS_SCHEME(dp.n, dp.t, SS_LAUNCH);
 #undef SS_LAUNCH
     return hipGetLastError();
@@ -1127,7 +1136,7 @@ hipError_t ss_launch_degree_reduce_truncate(const u64 *c, u64 *msg1, u64 *msg2, 
                                       : degree_reduce_kernel<NC, TC, true, true, false>                                          \
                                : lean ? degree_reduce_kernel<NC, TC, true, false, HAS_LEAN<NC, TC>>                       \
                                       : degree_reduce_kernel<NC, TC, true, false, false>),                                       \
-                       dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, u, wsh, out, rec, count, dp, tp, ps)
+                       dim3(blocks_for(count, 1)), dim3(BLOCK), 0, stream, c, msg1, msg2, u, wsh, out, count, rec, dp, tp, ps)
     SS_SCHEME(dp.n, dp.t, SS_LAUNCH);
 #undef SS_LAUNCH
     return hipGetLastError();
