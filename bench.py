@@ -157,7 +157,7 @@ def conv_layer_roofline(reps):
         ss.conv_mod_packed(x, wp, Co, k, k, 1, 1, out=y2)
     prof2 = ss.profile_end()
     return {"workload": "conv 3x3 64->64 on 8x64x56x56, n=3 (configs[2]): M=25088 K=576 N=64 per party",
-            "bound": "mfma", "kernel": "gemm_limb_kernel<true> (input gathered from limb planes)", "achieved": achieved,
+            "bound": "mfma", "kernel": "gemm_square_kernel<true> (input gathered from limb planes)", "achieved": achieved,
             "peak": INT8_PEAK_TOPS, "unit": "TOP/s", "frac": achieved / INT8_PEAK_TOPS, "gemm_ms": gemm_ms,
             "split_planes_ms": prof["pack_x"][0] / reps, "field_macs": macs,
             "via_im2col_matrix": {"gemm_ms": prof2["gemm_kernel"][0] / reps, "pack_im2col_ms": prof2["pack_x"][0] / reps,
