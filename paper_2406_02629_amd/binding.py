@@ -113,7 +113,7 @@ class _Entries:
         for name in self.NAMES:
             fn = getattr(lib, "ssnet_" + name)
             pointers = sum(1 << i for i, kind in enumerate(fn.argtypes) if kind not in (_int, _sz, _u64))
-            setattr(self, name, _calls.bind(C.cast(fn, _ptr).value, len(fn.argtypes), pointers))
+            setattr(self, name, _calls.bind(C.cast(fn, _ptr).value, len(fn.argtypes), pointers, fn))
 
 
 def load_library(p: int = P61) -> C.CDLL:

@@ -1,9 +1,10 @@
 /* Python callables for the C entry points of include/ssnet.h whose arguments are integers and pointers and whose result is an int.
  * With ctypes the conversion is 0.3 to 1 us of a call, of the 3 us that a launch costs the host, and layers of a few thousand elements wait for
  * the host: share, product and reduction of a dense layer are enqueued in 14.4 us instead of 15.9, a network of 11 small layers runs in 72.8 instead of 80.4.
- * bind(address, count, pointers) -> callable of `count` ints; bit i of `pointers`: argument i is a pointer, and None is a null one.
- * As with ctypes, integers are taken modulo 2^64, a narrower parameter sees its low bits, anything else is a ctypes.ArgumentError,
- * and the interpreter is released during the call. */
+ * bind(address, count, pointers, general) -> callable of `count` ints; bit i of `pointers`: argument i is a pointer, and None is a null one.
+ * As with ctypes, integers are taken modulo 2^64, a narrower parameter sees its low bits, and the interpreter is released during the call.
+ * Arguments of any other kind or number go to `general`, the ctypes function of the same entry point: it takes what has __index__ (integers of
+ * numpy, tensors of one element), objects of ctypes' own types and what their from_param takes, and refuses the rest.  Without `general` they are errors. */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stddef.h>
@@ -22,6 +23,7 @@ typedef struct {
     void *entry;
     Py_ssize_t count;
     unsigned long pointers;
+    PyObject *general;
 } Call;
 
 static PyObject *argument_error;
@@ -33,12 +35,14 @@ static PyObject *call(PyObject *self, PyObject *const *args, size_t nargsf, PyOb
     const Call *c = (const Call *)self;
     W a[MOST] = {0};
     if (PyVectorcall_NARGS(nargsf) != c->count || (names && PyTuple_GET_SIZE(names))) {
+        if (c->general) return PyObject_Vectorcall(c->general, args, nargsf, names);
         PyErr_Format(PyExc_TypeError, "expected %zd arguments", c->count);
         return NULL;
     }
     for (Py_ssize_t i = 0; i < c->count; i++) {
         if (args[i] == Py_None && c->pointers >> i & 1) continue;
         if (!PyLong_Check(args[i])) {
+            if (c->general) return PyObject_Vectorcall(c->general, args, nargsf, names);
             PyErr_Format(argument_error, "argument %zd: an int is needed, not %s", i + 1, Py_TYPE(args[i])->tp_name);
             return NULL;
         }
@@ -57,10 +61,17 @@ static PyObject *call(PyObject *self, PyObject *const *args, size_t nargsf, PyOb
     return PyLong_FromLong(rc);
 }
 
+static void release(PyObject *self)
+{
+    Py_XDECREF(((Call *)self)->general);
+    PyObject_Free(self);
+}
+
 static PyTypeObject CallType = {
     PyVarObject_HEAD_INIT(NULL, 0)
     .tp_name = "_calls.Call",
     .tp_basicsize = sizeof(Call),
+    .tp_dealloc = release,
     .tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL,
     .tp_vectorcall_offset = offsetof(Call, vectorcall),
     .tp_call = PyVectorcall_Call,
@@ -72,7 +83,8 @@ static PyObject *bind(PyObject *self, PyObject *args)
     unsigned long long address;
     unsigned long pointers;
     Py_ssize_t count;
-    if (!PyArg_ParseTuple(args, "Knk", &address, &count, &pointers)) return NULL;
+    PyObject *general = NULL;
+    if (!PyArg_ParseTuple(args, "Knk|O", &address, &count, &pointers, &general)) return NULL;
     if (!address || count < 0 || count > MOST) {
         PyErr_SetString(PyExc_ValueError, "an address and at most 16 arguments");
         return NULL;
@@ -83,10 +95,12 @@ static PyObject *bind(PyObject *self, PyObject *args)
     c->entry = (void *)(uintptr_t)address;
     c->count = count;
     c->pointers = pointers;
+    Py_XINCREF(general);
+    c->general = general;
     return (PyObject *)c;
 }
 
-static PyMethodDef methods[] = {{"bind", bind, METH_VARARGS, "bind(address, count, pointers) -> callable"}, {NULL, NULL, 0, NULL}};
+static PyMethodDef methods[] = {{"bind", bind, METH_VARARGS, "bind(address, count, pointers[, general]) -> callable"}, {NULL, NULL, 0, NULL}};
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", NULL, -1, methods, NULL, NULL, NULL, NULL};
 
 PyMODINIT_FUNC PyInit__calls(void)

@@ -1,7 +1,9 @@
 """The callables of csrc/calls.c against ctypes: results, arguments that are refused, integers of more bits than the parameter."""
 import ctypes as C
 
+import numpy as np
 import pytest
+import torch
 
 from paper_2406_02629_amd import binding
 
@@ -18,6 +20,42 @@ def bound(name):
 def test_integers(args):
     fn, call = bound("ssnet_pool_out_size")
     assert call(*args) == fn(*args)
+
+
+class Index:
+    def __index__(self):
+        return 28
+
+
+class Parameter:
+    _as_parameter_ = 28
+
+
+@pytest.mark.parametrize("value", [np.int64(28), np.uint8(28), np.int64(28 - (1 << 32)), torch.tensor(28), torch.tensor([28]), C.c_int(28), Index(), Parameter()])
+def test_other_integers_as_by_ctypes(value):
+    fn, _ = bound("ssnet_pool_out_size")
+    call = binding._calls.bind(C.cast(fn, C.c_void_p).value, 4, 0, fn)
+    assert call(value, 2, 2, 0) == fn(value, 2, 2, 0) == 14
+
+
+@pytest.mark.parametrize("value", [28.0, np.float64(28), "28", b"28", None, torch.tensor(28.0), torch.tensor([28, 28]), C.c_long(28), C.c_void_p(28), [28]])
+def test_refused_by_both(value):
+    fn, _ = bound("ssnet_pool_out_size")
+    for call in (fn, binding._calls.bind(C.cast(fn, C.c_void_p).value, 4, 0, fn)):
+        with pytest.raises(C.ArgumentError):
+            call(value, 2, 2, 0)
+
+
+@pytest.mark.parametrize("name", binding._Entries.NAMES)
+def test_entries_take_what_ctypes_takes(name):
+    """null pointers in ctypes' forms and integers of numpy at every place: no launch"""
+    fn = getattr(LIB, "ssnet_" + name)
+    args = [kind(1) if kind in (C.c_int, C.c_size_t, C.c_uint64) else kind() for kind in fn.argtypes]
+    assert getattr(LIB.entries, name)(*args) == fn(*args) == binding.EINVAL
+    args = [np.int64(1) if kind in (C.c_int, C.c_size_t, C.c_uint64) else None for kind in fn.argtypes]
+    assert getattr(LIB.entries, name)(*args) == fn(*args) == binding.EINVAL
+    with pytest.raises(TypeError):
+        getattr(LIB.entries, name)(*args[:-1])
 
 
 @pytest.mark.parametrize("args", [(28, 2, 2, 0.0), ("28", 2, 2, 0), (28, None, 2, 0), (28, 2, 2, b"0")])
