@@ -5,7 +5,7 @@ over p = 2^45 - 55.
 hipcc cross-compiles without a GPU.  Each .hip file is compiled to an object
 and the objects are linked into one shared library per field that exports the
 C ABI of include/ssnet.h.  csrc/calls.c, the calls from Python into that ABI, becomes
-the extension module _calls.so.
+the extension module _calls, named after the interpreter that it is built for.
 """
 import os
 import subprocess
@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libssnet.so")
 LIB_P45 = os.path.join(HERE, "libssnet_p45.so")
-CALLS = os.path.join(HERE, "_calls.so")
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))   # one interpreter's: another builds its own
 VARIANTS = {"p61": (LIB, []), "p45": (LIB_P45, ["-DSS_FIELD_P45"])}
 SOURCES = ["stream_kernels.hip", "gemm_kernels.hip", "ssnet_api.hip", "probes.hip"]
 HEADERS = ["field.hpp", "kernels.hpp", "eval.hpp", "digits.hpp", "gemm_plan.hpp", "pool_plan.hpp", os.path.join("..", "..", "include", "ssnet.h")]

@@ -1,5 +1,7 @@
 """The callables of csrc/calls.c against ctypes: results, arguments that are refused, integers of more bits than the parameter."""
 import ctypes as C
+import importlib.machinery
+import os
 
 import numpy as np
 import pytest
@@ -95,3 +97,9 @@ def test_places_of_arguments(count):
 def test_more_arguments_than_there_are_places_for():
     with pytest.raises(ValueError):
         binding._calls.bind(1, 17, 0)
+
+
+def test_module_is_named_after_its_interpreter():
+    """an interpreter of another version finds no module of this one"""
+    name = os.path.basename(binding._calls.__file__)
+    assert name == "_calls" + importlib.machinery.EXTENSION_SUFFIXES[0] and name != "_calls.so"
