@@ -262,6 +262,12 @@ int conv_out(int H, int k, int stride, int pad) { return (H + 2 * pad - k) / str
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
+    return a0 < b0 + b_bytes && b0 < a0 + a_bytes;
+}
+
 // The first bytes of the workspace are a reserved header (SSNET_WS_HEADER_BYTES); everything else lives
 // behind it.
 constexpr size_t WS_HEADER_BYTES = SSNET_WS_HEADER_BYTES;
@@ -567,7 +573,9 @@ int ssnet_linear_mod_packed(ssnet_ctx *ctx, const uint64_t *d_x, const void *d_w
     const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, M, N, K, 0));
     if (!ws_fits(ctx, part + (size_t)ctx->n * ss_packed_bytes(M, K))) return SSNET_EWORKSPACE;
     const product_plan plan = plan_product(ctx->n, M, N, K, 0, true, 0);
-    if (const int waves = plan.element_waves(M))
+    // (an input in the memory of the output is read before the product starts to write)
+    const int waves = overlap(d_x, (size_t)ctx->n * M * K * 8, d_y, (size_t)ctx->n * M * N * 8) ? 0 : plan.element_waves(M);
+    if (waves)
         return run_product(ctx, [&](u64 *parts, hipEvent_t ea, hipEvent_t eb) {
             return ss_launch_gemm_rows(plan.for_elements(waves), d_x, d_w_packed, d_y, parts, ctx->n, M, K, N, ctx->stream, ea, eb);
         });
@@ -776,7 +784,8 @@ int ssnet_conv_mod_packed(ssnet_ctx *ctx, const uint64_t *d_x, const void *d_w_p
     const size_t part = align256(ss_gemm_scratch_bytes(ctx->n, Co, (int)M, (int)K, 0));
     if (!ws_fits(ctx, part + (size_t)ctx->n * ss_packed_bytes((int)M, (int)K))) return SSNET_EWORKSPACE;
     const product_plan plan = plan_product(ctx->n, Co, (int)M, (int)K, 0, true, 0);
-    if (const int waves = plan.element_waves(0))
+    const int waves = overlap(d_x, (size_t)ctx->n * B * C * H * W * 8, d_y, (size_t)ctx->n * Co * M * 8) ? 0 : plan.element_waves(0);
+    if (waves)
         return run_product(ctx, [&](u64 *parts, hipEvent_t ea, hipEvent_t eb) {
             return ss_launch_gemm_images(plan.for_elements(waves), d_w_packed, d_x, d_y, parts, ctx->n, B, C, H, W, Co, kh, kw, stride, pad, Ho, Wo, ctx->stream,
                                          ea, eb);
@@ -1039,16 +1048,6 @@ int ssnet_reduce_truncate_direct(ssnet_ctx *ctx, const uint64_t *d_c, size_t cou
                                                     ctx->stream);
     return e == hipSuccess ? SSNET_OK : fail_hip(ctx, e);
 }
-
-namespace {
-
-static bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
-{
-    const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
-    return a0 < b0 + b_bytes && b0 < a0 + a_bytes;
-}
-
-}  // namespace
 
 size_t ssnet_layer_tail_message_plane(const ssnet_ctx *ctx, int B, int C, int HW)
 {

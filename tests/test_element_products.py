@@ -5,6 +5,7 @@ import subprocess
 
 import numpy as np
 import pytest
+import torch
 
 import oracle as orc
 from paper_2406_02629_amd import SSNet, binding
@@ -79,3 +80,38 @@ def test_products_of_elements(n, t, p):
             x, w = (field_uniform((n,) + sh, i) % np.uint64(p) for i, sh in enumerate(((B, Ci, H, W), (Co, Ci, k, k))))
             got = s.conv_mod_packed(to_dev(x), s.pack_weights_conv(to_dev(w)), Co, k, k, stride, pad)
             assert np.array_equal(to_np(got), orc.conv(x, w, stride, pad, p))
+
+
+# (M, K = N) and (B, C = Co, H, W, k, pad): the output has the size of the input, and lies in its memory or reaches into it
+IN_PLACE = [(8, 512), (40, 31), (1, 257), (200, 64), (2, 6, 14, 14, 3, 1), (1, 40, 9, 7, 1, 0), (3, 2, 5, 5, 5, 2)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", IN_PLACE)
+def test_output_in_the_memory_of_the_input(shape):
+    """Other workgroups read the input after the first ones have stored their outputs: the input is packed first, as for every larger product."""
+    n, dense = 3, len(shape) == 2
+    s = SSNet(n, 1, f=12, seed=97)
+    xshape = (n,) + (shape if dense else shape[:4])
+    wshape = (n, shape[1], shape[1]) if dense else (n, shape[1], shape[1], shape[4], shape[4])
+    x, w = field_uniform(xshape, 1), field_uniform(wshape, 2)
+    want = orc.linear(x, w, P61) if dense else orc.conv(x, w, 1, shape[5], P61)
+    wp = s.pack_weights_linear(to_dev(w)) if dense else s.pack_weights_conv(to_dev(w))
+
+    def product(src, dst):
+        if dense:
+            return s.linear_mod_packed(src, wp, shape[1], out=dst)
+        return s.conv_mod_packed(src, wp, shape[1], shape[4], shape[4], 1, shape[5], out=dst)
+
+    count = x.size
+    for shift in (0, 1, -1, count - 1, 1 - count, count, -count):   # elements from the input's start to the output's
+        print("in place", shape, shift, flush=True)
+        memory = torch.zeros(3 * count, dtype=torch.int64, device="cuda")
+        src, dst = (memory[at:at + count].view(xshape) for at in (count, count + shift))
+        src.copy_(to_dev(x))
+        s.profile_begin()
+        assert np.array_equal(to_np(product(src, dst)), want), shift
+        assert s.profile_end()["pack_x"][1] == (abs(shift) < count), shift
+    if dense:
+        src = to_dev(x)
+        assert np.array_equal(to_np(s.linear_mod(src, to_dev(w), out=src)), want)
