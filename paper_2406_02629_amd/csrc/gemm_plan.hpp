@@ -220,20 +220,26 @@ struct square_plan {
 };
 constexpr int SQUARE_RUNS = 8;
 
-// Which products take it (p, p_us: what plan_gemm gives them to otherwise), and how many runs: where it is estimated 3 % faster than that, over
-// the 61-bit prime 15 % (22 % from limb planes) from 60 us on: there tiles of 64 x 64 that fill the matrix and the chip are as fast or
-// faster, with half the reads (128 x 6272 x 1152, n = 5, 191 -> 206 us, estimated 10 % faster; 256 x 1568 x 1024 89 -> 95).  Below 7 us (8.5 us) launches decide and
-// nothing is gained (4000 shapes: 0.7 % slower on average).
+// Which products take it (p, p_us: what plan_gemm gives them to otherwise), and how many runs: where it is estimated 3 % faster than that.
+// Over the 61-bit prime more is asked where tiles of 64 x 64 fill the matrix and the chip and are as fast or faster with half the reads: from
+// tiles 15 % from 60 us on, from limb planes a margin that grows to 22 % between 40 and 60 us (128 x 6272 x 1152 from planes, n = 5, 191 -> 206 us,
+// estimated 10 % faster; 256 x 1568 x 1024 89 -> 95; 384 x 338 x 2304, n = 3, 55.3 -> 58.6).  One round of whole tiles of 64 x 64 takes 15 % less than
+// plan_gemm estimates, and here it leaves a second round of a few workgroups (64 x 3136 x 576 from planes, n = 5, 44.0 against 44.8; 690 x 441 x 576,
+// n = 3, 36.8 against 38.9; 203 x 576 x 500 from tiles, n = 7, 62.6 against 64.0).  Eight waves on a long contraction from planes are
+// faster than estimated too (66 x 256 x 6400, n = 3, 27.0 against 30.0).  Below 7 us (8.5 us) launches decide and nothing is gained (4000 shapes: 0.7 %
+// slower on average).
 // most: planes that there is room for; tensor: the planes are added up by one more launch, where there are several.
 // A unit (32 x 32, one k block) keeps a CU busy for 0.605 us (0.365 us over the 45-bit prime), however many workgroups share the CU, down
 // to two; less where blocks of the tile lie outside the matrix, more where it is gathered from limb planes.  Three (four)
 // workgroups are on a CU at a time.
-// Fitted to 10000 shapes, 62000 timings of product + reduction, operands from memory, n = 3 to 7, both fields, 10 us to 6 ms; on 2200 others of up to 60
-// us of matrix work 6.5 % faster on average over all of them, 5 % of them more than 3 % slower.  Before -> after, us, product + reduction +
-// truncation (rows x columns x contraction, runs): n = 5, 128 x 784 x 1152 44.2 -> 38.3 (1), 256 x 196 x 1024 29.0 -> 25.3 (2), 512 x 49 x 2048 31.0 ->
-// 26.7 (3); n = 3, 128 x 49 x 4608 32.6 -> 15.9 (8), 128 x 1024 x 1152 34.5 -> 30.2 (2); over the 45-bit prime, n = 3, 512 x 49 x 4608 28.7 -> 22.7 (5), 256 x
-// 196 x 2304 24.6 -> 19.8 (3).  Left: n = 5, 64 x 3136 x 576 44.4 -> 45.0; n = 3, 66 x 256 x 6400 27.0 -> 30.0; n = 7, 203 x 576 x 500 (252 tiles of 64 x 64) 62.6 -> 64.0.  Large convolutions whose weights
-// no L2 holds are left too: there a tile of 64 x 64 reads them half as often (895 x 8712 x 3200, n = 3, 3.20 -> 3.55 ms).
+// Fitted to 10000 shapes, 62000 timings of product + reduction, operands from memory, n = 3 to 7, both fields, 10 us to 6 ms; the lines above set by
+// 8000 others of up to 80 us of matrix work and 541 layers of ResNet, VGG and AlexNet at batch 1 to 8, weights from memory: 6 % faster on average over all of
+// them, 3 % of those that are taken more than 3 % slower.  Before -> after, us, product + reduction + truncation (rows x columns x contraction, runs):
+// n = 5, 128 x 784 x 1152 43.6 -> 37.4 (1), 256 x 196 x 1024 26.8 -> 25.1 (4), 512 x 49 x 2048 30.2 -> 25.6 (3), from planes 256 x 196 x 2304 42.7 -> 40.8
+// (4) and 512 x 49 x 4608 46.6 -> 44.2 (3); product + layer tail, n = 3, 128 x 1024 x 1152 35.8 -> 30.5 (2); over the 45-bit prime 512 x 49 x 4608 30.1 -> 25.1
+// (5), 256 x 196 x 2304 25.7 -> 21.9 (3).  Taken and slower: from planes read with stride 2, n = 5, 512 x 49 x 4608 45.1 -> 46.8 (3), 256 x 392 x 1152 44.8 -> 47.4 (3);
+// n = 3, 196 x 196 x 1600 19.1 -> 21.6 (5); over the 45-bit prime, n = 3, 256 x 676 x 3456 63.7 -> 66.8 (3).  Large convolutions whose weights no L2 holds
+// are left: there a tile of 64 x 64 reads them half as often (895 x 8712 x 3200, n = 3, 3.20 -> 3.55 ms).
 inline square_plan plan_square(const gemm_plan &p, double p_us, int n, int rows, int cols, int K, int gather, bool tensor, int most)
 {
     constexpr bool P61 = SS_NLIMB == 8;
@@ -249,13 +255,18 @@ inline square_plan plan_square(const gemm_plan &p, double p_us, int n, int rows,
     const double plane = P61 ? 0.30 + elements * 3.5e-6 : 0.30 + elements * 4.7e-6;
     const double operands = (double)n * (Rb + (gather ? 0 : Cb)) * Kb * (SS_NLIMB << 10) * (P61 ? 0.032e-6 : 0.035e-6);
     const double add = tensor ? 3.5 + elements * 3.5e-6 : 0;   // (a launch, the first plane once more)
-    const double other = p_us + (p.slots > 1 ? add * (p.tiles - p.whole) / p.tiles : 0);
-    double best_us = other / (P61 && p_us > 60 ? gather ? 1.22 : 1.15 : 1.03);
+    const bool one_round = !p.ksplit && p.slots == 1 && p.tiles <= SS_GEMM_CUS;   // of whole tiles of 64 x 64
+    const double other = p_us * (P61 && one_round ? 0.85 : 1) + (p.slots > 1 ? add * (p.tiles - p.whole) / p.tiles : 0);
+    double margin = 1.03;
+    if (P61 && gather) margin += 0.19 * fmin(fmax((p_us - 40) / 20, 0.0), 1.0);
+    else if (P61 && p_us > 60) margin = 1.15;
+    if (P61 && gather && p.ksplit == 8 && Kb >= 64) margin *= 1.15;
+    double best_us = other / margin;
     for (int runs = 1; runs <= SQUARE_RUNS && runs <= Kb && runs <= most; runs++) {
         const long G = n * Rt * Ct * runs;
         if (!fits_grid(G, 256)) break;
         const double at_a_time = P61 ? 3 : 4, per_cu = (double)G / SS_GEMM_CUS, rounds = per_cu / at_a_time;
-        const double share = per_cu > at_a_time ? per_cu + 0.58 : per_cu > 1 ? ceil(per_cu) : P61 ? 1.27 : 1.62;
+        const double share = per_cu > at_a_time ? per_cu + 0.58 : per_cu > 3 ? 3.8 : per_cu > 2 ? 2.95 : per_cu > 1 ? 2 : P61 ? 1.27 : 1.62;
         // (from the second round on a workgroup's start hides behind the others)
         const double us = (P61 ? 2.4 : 3.7) + (Kb + runs - 1) / runs * unit * share - (P61 ? 1.45 : 2.1) * fmin(fmax(rounds - 1, 0.0), 6.5) +
                           (runs - 1) * plane + operands + (runs > 1 ? add : 0);

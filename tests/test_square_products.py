@@ -85,6 +85,20 @@ def test_shapes_of_the_gpu_tests_take_what_they_are_written_for(plans):
             assert {"planes": slots >= 5, "whole": slots == 1 and whole > 0, "ahead": slots == 2 and whole >= 256}[kind], (n, shape)
 
 
+# limbs, (n, rows, columns, contraction, gather) -> runs of the pending product, as the comment at plan_square has them: faster there, and left (0) to
+# tiles of 64 x 64 and to waves on their own, which are faster
+TIMED = {(8, (5, 128, 784, 1152, 1)): 1, (8, (5, 128, 784, 1152, 128)): 1, (8, (5, 256, 196, 1024, 0)): 4, (8, (5, 512, 49, 2048, 0)): 3,
+         (8, (5, 256, 196, 2304, 1)): 4, (8, (5, 512, 49, 4608, 1)): 3, (8, (3, 128, 1024, 1152, 1)): 2, (6, (3, 512, 49, 4608, 1)): 5, (6, (3, 256, 196, 2304, 1)): 3,
+         (8, (5, 64, 3136, 576, 1)): 0, (8, (3, 690, 441, 576, 1)): 0, (8, (7, 203, 576, 500, 0)): 0, (8, (3, 66, 256, 6400, 1)): 0,
+         (8, (3, 384, 338, 2304, 1)): 0, (8, (5, 128, 6272, 1152, 1)): 0, (8, (5, 256, 1568, 1024, 0)): 0, (8, (5, 256, 1568, 1024, 1)): 0, (8, (3, 895, 8712, 3200, 1)): 0,
+         (8, (5, 512, 49, 4608, 512)): 3, (8, (5, 256, 392, 1152, 128)): 3, (8, (3, 196, 196, 1600, 1)): 5, (6, (3, 256, 676, 3456, 1)): 3}   # (the last row: taken and slower)
+
+
+def test_timed_products_take_what_their_comment_says(plans):
+    for (limbs, product), runs in TIMED.items():
+        assert plans[limbs](*product, 0, 8)[0] == runs, (limbs, product)
+
+
 def test_planes_stay_within_the_room_and_workgroups_within_a_launch(plans):
     rng = random.Random(11)
     taken = 0
