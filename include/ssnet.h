@@ -442,7 +442,11 @@ int ssnet_host_reduction_matrix(const ssnet_ctx *ctx, uint64_t *out);
  * time between the kernel's own start and end on the GPU, which is what a
  * profiler's kernel trace reports as its duration; the launches that take these
  * time stamps are slower to enqueue, so the bracketed spans of the same pass
- * are wider than after ssnet_profile_begin.  Not for use under stream capture. */
+ * are wider than after ssnet_profile_begin.  ssnet_linear_mod packs both of its
+ * operands in one launch, which is a span of SSNET_PROF_PACK_X; a product small
+ * enough to read its input as field elements (by shape, in ssnet_linear_mod(_packed)
+ * and ssnet_conv_mod(_packed)) packs its weights alone, SSNET_PROF_PACK_W, if at all.
+ * Not for use under stream capture. */
 #define SSNET_PROF_SHARE 0
 #define SSNET_PROF_RECONSTRUCT 1
 #define SSNET_PROF_PACK_W 2

@@ -115,3 +115,17 @@ def test_output_in_the_memory_of_the_input(shape):
     if dense:
         src = to_dev(x)
         assert np.array_equal(to_np(s.linear_mod(src, to_dev(w), out=src)), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,pack_w,pack_x", [((40, 256, 31), 1, 0), ((33, 700, 129), 0, 1)])
+def test_profile_classes_of_a_fresh_dense_layer(shape, pack_w, pack_x):
+    """weights alone where the input is read as field elements, else both operands in one launch: include/ssnet.h at ssnet_profile_begin"""
+    M, K, N = shape
+    s = SSNet(3, 1, f=12, seed=97)
+    x, w = to_dev(field_uniform((3, M, K), 1)), to_dev(field_uniform((3, K, N), 2))
+    s.linear_mod(x, w)
+    s.profile_begin()
+    s.linear_mod(x, w)
+    spans = {name: count for name, (_, count) in s.profile_end().items()}
+    assert (spans["pack_w"], spans["pack_x"], spans["gemm"]) == (pack_w, pack_x, 1)
