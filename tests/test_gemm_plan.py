@@ -30,6 +30,27 @@ def planner(directory, limbs):
     return lib.plan_product
 
 
+def product_planner(directory, limbs):
+    """call(n, rows, cols, K, gather, tensor, room) -> (runs, workgroups, planes, plan_gemm's ksplit, slots, whole): what the launcher takes.
+    runs > 0: gemm_square_kernel, else plan_gemm's kernel.  tensor: the planes are added up; room: planes that there is memory for."""
+    src = directory / "product_plan.cpp"
+    src.write_text('#include "gemm_plan.hpp"\nextern "C" void plan_product(int n, int rows, int cols, int K, int gather, int tensor, int room, long *v)\n'
+                   "{ const plan::product_plan r = plan::plan_product(n, rows, cols, K, gather, tensor, room);\n"
+                   "  const long w[6] = {r.sq.runs, (long)r.sq.G, r.planes(), r.p.ksplit, r.p.slots, (long)r.p.whole};\n"
+                   "  for (int i = 0; i < 6; i++) v[i] = w[i]; }\n")
+    so = str(directory / f"product_plan{limbs}.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-DSS_NS=plan", f"-DSS_NLIMB={limbs}", "-I", CSRC,
+                    "-o", so, str(src)], check=True)
+    fn = C.CDLL(so).plan_product
+    fn.restype, fn.argtypes = None, [C.c_int] * 7 + [C.POINTER(C.c_long)]
+
+    def call(n, rows, cols, K, gather, tensor, room):
+        v = (C.c_long * 6)()
+        fn(n, rows, cols, K, gather, tensor, room, v)
+        return tuple(v)
+    return call
+
+
 @pytest.fixture(scope="module", params=[8, 6])
 def plan(request, tmp_path_factory):
     return planner(tmp_path_factory.mktemp("gemm_plan"), request.param)
@@ -75,30 +96,40 @@ def test_planes_are_priced_by_what_a_unit_of_the_field_takes(tmp_path):
 
 
 def test_products_of_the_gpu_tests_take_what_these_are_written_for(tmp_path):
-    """Kernel (waves of a 16 x 16 tile, 0: tiles of 64 x 64), planes and whole tiles ahead, per product of
-    tests/test_gpu_pending_product.py.  A change of the rules that moves one of them asks for another shape there."""
+    """Kernel, planes and whole tiles ahead of each product of tests/test_gpu_pending_product.py, left in the workspace and as a tensor.
+    A change of the rules that moves one of them asks for another shape there."""
     import test_gpu_pending_product as g
-    plans = {limbs: planner(tmp_path, limbs) for limbs in (8, 6)}
+    plans = {limbs: product_planner(tmp_path, limbs) for limbs in (8, 6)}
+    limbs_of = {g.binding.P61: 8, g.binding.P45: 6}
 
     def taken(limbs, *shape):
-        p = plans[limbs](*shape)
-        return p.ksplit, p.slots, p.whole
+        """of the pending product: ("square", runs), ("waves", waves of a tile, planes) or ("tiles", planes, whole tiles ahead)"""
+        def one(tensor, room):
+            runs, _, planes, ksplit, _, whole = plans[limbs](*shape, tensor, room)
+            return ("square", runs) if runs else ("waves", ksplit, planes) if ksplit else ("tiles", planes, whole)
+        pending, tensor = one(0, 8), one(1, 0)
+        if pending[0] == "tiles":   # the tests of tiles of 64 x 64 run both forms
+            assert tensor == pending, (limbs, shape, pending, tensor)
+        return pending
 
     def conv(limbs, n, B, C, H, W, Co, k, stride, pad):
         Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
         return taken(limbs, n, Co, B * Ho * Wo, C * k * k, C if stride > 1 else 1)
 
-    assert [conv(8, 5, *c) for c in g.CONV_CASES[:6]] == [(0, 5, 0), (0, 1, 0), (2, 1, 0), (0, 27, 0), (4, 1, 0), (4, 1, 0)]
-    assert [conv(8, 3, *g.CONV_CASES[i]) for i in (0, 3)] == [(0, 8, 0), (0, 40, 0)]
-    assert [conv(8, 7, *g.CONV_CASES[i]) for i in (0, 3)] == [(0, 4, 0), (0, 20, 0)]
-    assert [conv(6, 5, *g.CONV_CASES[i]) for i in (0, 3, 6)] == [(4, 1, 0), (8, 1, 0), (0, 11, 0)]
-    assert [conv(8, 5, 1, C, H, H, Co, 3, 1, 1) for C, H, Co in g.FULL_RANGE] == [(8, 2, 0), (0, 27, 0), (0, 5, 0)]
-    for limbs, n in ((8, 5), (6, 3)):
-        (M, K, N), (B, C, H, Co) = g.whole_ahead_shapes(n)
-        assert taken(limbs, n, M, N, K, 0) == conv(limbs, n, B, C, H, H, Co, 3, 1, 1) == (0, 2, 256)
+    assert [conv(8, 5, *c) for c in g.CONV_CASES[:6]] == [("square", 4), ("square", 1), ("waves", 2, 1), ("square", 6), ("square", 6), ("waves", 4, 1)]
+    assert [conv(8, 3, *g.CONV_CASES[i]) for i in (0, 3, 4)] == [("square", 3), ("square", 8), ("square", 6)]
+    assert [conv(8, 7, *g.CONV_CASES[i]) for i in (0, 3, 4)] == [("tiles", 4, 0), ("square", 8), ("square", 6)]
+    assert [conv(6, 5, *g.CONV_CASES[i]) for i in (0, 3, 4, 6)] == [("square", 3), ("square", 6), ("waves", 4, 1), ("square", 5)]
+    assert {key: [conv(limbs_of[key[2]], key[0], *c) for c in cases] for key, cases in g.CUT_TILES.items()} == {
+        (5, 2, g.binding.P61): [("tiles", 16, 0), ("tiles", 5, 0)], (3, 1, g.binding.P61): [("tiles", 14, 0)],
+        (7, 3, g.binding.P61): [("tiles", 5, 0)], (5, 2, g.binding.P45): [("tiles", 12, 0)]}
+    assert [conv(8, 5, 1, C, H, H, Co, 3, 1, 1) for C, H, Co in g.FULL_RANGE] == [("waves", 8, 2), ("square", 6), ("square", 4), ("tiles", 16, 0)]
+    for (n, t, p), ((M, K, N), c) in g.WHOLE_AHEAD.items():
+        assert taken(limbs_of[p], n, M, N, K, 0) == conv(limbs_of[p], n, *c) == ("tiles", 2, 256)
     n, M, K, N = g.RAGGED
-    assert taken(8, n, M, N, K, 0) == (0, 2, 256) and plans[8](n, M, N, K, 0).tiles >= 3 * 256
+    assert taken(8, n, M, N, K, 0) == ("tiles", 2, 256) and planner(tmp_path, 8)(n, M, N, K, 0).tiles >= 3 * 256
     # one, two, four and eight waves, and a contraction in parts
     small = [taken(limbs, n, M, N, K, 0) for limbs, n in ((8, 5), (6, 3), (8, 8)) for M, K, N in g.SMALL_DENSE]
     small += [conv(limbs, n, *c) for limbs, n in ((8, 5), (6, 3), (8, 8)) for c in g.SMALL_CONV]
-    assert {k for k, _, _ in small} >= {1, 2, 4, 8} and max(slots for k, slots, _ in small if k) > 1
+    waves = [s[1:] for s in small if s[0] == "waves"]
+    assert {k for k, _ in waves} == {1, 2, 4, 8} and max(planes for _, planes in waves) > 1

@@ -219,8 +219,8 @@ def test_linear_parity(n, t):
 
 
 def test_linear_random_shapes_cover_the_unit_dealing():
-    """Seeded sweep of ragged shapes: whole tiles and tiles cut between 2 to 8 workgroups, light last
-    column tiles of 1 to 3 blocks, fewer units than workgroups, one party to eight."""
+    """Seeded sweep of ragged shapes: tiles of 16 x 16 by one to eight waves, of 32 x 32 in one, two and four runs, of 16 x 128 in
+    several planes, last blocks of any width, fewer units than workgroups, three parties to eight."""
     rng = np.random.default_rng(2024)
     cases = [(3, 1, 1, 1, 1), (3, 1, 1, 16383, 1), (5, 2, 64, 64, 64), (5, 2, 65, 65, 65), (8, 2, 17, 700, 49),
              (3, 1, 200, 129, 3), (5, 2, 1, 2048, 1000), (7, 3, 130, 1000, 196)]
@@ -236,7 +236,7 @@ def test_linear_random_shapes_cover_the_unit_dealing():
 
 
 def test_linear_many_tiles_one_whole_tile_per_workgroup():
-    # 3 * 130 * 130 output tiles: many more than compute units, so every workgroup takes one whole tile (one plane)
+    # 3 * 260 * 260 tiles of 32 x 32: many more than run at a time, and every workgroup takes one whole tile (one plane)
     n, t = 3, 1
     s = SSNet(n, t, seed=1)
     M, K, N = 8320, 64, 8320

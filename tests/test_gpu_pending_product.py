@@ -91,14 +91,17 @@ def check_consumers(s, p, y, shape, leave_product, f=12, seed=0):
 # (tests/test_gemm_plan.py holds the kernel and the planes that each of the products here is computed with)
 CONV_CASES = [
     # B, C, H, W, Co, k, stride, pad; over the 61-bit prime, five parties:
-    (1, 256, 14, 14, 256, 3, 1, 1),     # 80 tiles of 36 k blocks: every tile split over several workgroups, five planes
-    (1, 64, 14, 14, 1024, 1, 1, 0),     # more tiles than workgroups, one k block
+    (1, 256, 14, 14, 256, 3, 1, 1),     # tiles of 32 x 32, 36 k blocks in four runs, a plane each (seven parties: tiles of 64 x 64, four planes)
+    (1, 64, 14, 14, 1024, 1, 1, 0),     # tiles of 32 x 32, more than workgroups at a time, one k block
     (1, 256, 14, 14, 64, 1, 1, 0),      # tiles of 16 x 16, two waves each
-    (1, 512, 7, 7, 128, 3, 1, 1),       # 49 pixels: one ragged column tile, 27 planes
-    (2, 128, 9, 7, 65, 3, 2, 1),        # tiles of 16 x 16, ragged rows and columns, stride 2
+    (1, 512, 7, 7, 128, 3, 1, 1),       # 49 pixels: one ragged column tile of 32 x 32, six runs (three and seven parties: eight)
+    (2, 128, 9, 7, 65, 3, 2, 1),        # tiles of 32 x 32, ragged rows and columns, stride 2, six runs
     (1, 64, 5, 5, 7, 3, 1, 1),          # at most 16 output channels
-    (2, 512, 9, 9, 65, 3, 1, 1),        # over the 45-bit prime too in parts: eleven planes
+    (2, 512, 9, 9, 65, 3, 1, 1),        # over the 45-bit prime too in parts: five runs
 ]
+# tiles of 64 x 64, every one split over several workgroups: up to 16 planes, one pixel to a few columns of tiles
+CUT_TILES = {(5, 2, binding.P61): [(1, 1024, 1, 1, 401, 3, 1, 1), (1, 256, 71, 6, 103, 3, 1, 1)], (3, 1, binding.P61): [(1, 1024, 6, 6, 456, 3, 1, 1)],
+             (7, 3, binding.P61): [(2, 192, 17, 3, 299, 3, 1, 1)], (5, 2, binding.P45): [(1, 1024, 6, 6, 324, 3, 1, 1)]}
 
 
 @pytest.mark.parametrize("n,t,p", [(5, 2, binding.P61), (3, 1, binding.P61), (7, 3, binding.P61), (5, 2, binding.P45)])
@@ -108,6 +111,7 @@ def test_conv_product_on_planes_then_every_consumer(n, t, p):
     cases = CONV_CASES[:6] if (n, t, p) == (5, 2, binding.P61) else CONV_CASES[:1] + CONV_CASES[3:5]
     if p == binding.P45:
         cases = cases + CONV_CASES[6:]
+    cases = cases + CUT_TILES[n, t, p]
     for (B, C, H, W, Co, k, stride, pad) in cases:
         say("conv product", n, t, hex(p), B, C, H, W, Co, k, stride, pad)
         xs = orc.share(small_secrets((B, C, H, W), 1, bits, p), n, t, p, 91, 5)
@@ -147,8 +151,9 @@ def test_prepacked_products_then_every_consumer(n, t, p):
 
 # C, H, Co of 3 x 3 convolutions, five parties over the 61-bit prime
 FULL_RANGE = [(512, 7, 96),     # tiles of 16 x 16, eight waves each, the contraction in two parts
-              (512, 7, 128),    # tiles of 64 x 64, every one shared by up to 26 workgroups: 27 planes, most of them zeros
-              (256, 14, 256)]   # five planes
+              (512, 7, 128),    # tiles of 32 x 32, six runs
+              (256, 14, 256),   # four runs
+              (1024, 1, 401)]   # tiles of 64 x 64, every one shared by up to 15 workgroups: 16 planes, most of them zeros
 
 
 @pytest.mark.parametrize("C,H,Co", FULL_RANGE)
@@ -198,19 +203,19 @@ def test_pending_product_errors():
     assert ei.value.code == binding.EINVAL
 
 
-def whole_ahead_shapes(n):
-    """(M, K, N) of a dense layer: three row tiles, the last one ragged; (B, C, H, Co) of a 3 x 3 convolution"""
-    per = -(-560 // n)                                   # tiles of a party
-    return (187, 640, 64 * (-(-per // 3)) - 37), (-(-64 * per // (2 * 14 * 14)), 64, 14, 128)
+# (M, K, N) of a dense layer: two row tiles, the last one ragged; (B, C, H, W, Co, k, stride, pad) of a convolution
+WHOLE_AHEAD = {(5, 2, binding.P61): ((101, 722, 3270), (3, 256, 32, 37, 128, 2, 1, 0)),
+               (3, 1, binding.P61): ((101, 715, 5479), (3, 256, 36, 53, 128, 2, 1, 0)),
+               (3, 1, binding.P45): ((99, 1968, 5487), (2, 256, 86, 67, 34, 3, 1, 0))}
 
 
-@pytest.mark.parametrize("n,t,p", [(5, 2, binding.P61), (3, 1, binding.P45)])
+@pytest.mark.parametrize("n,t,p", list(WHOLE_AHEAD))
 def test_products_with_whole_tiles_ahead_of_the_cut_ones(n, t, p):
-    """Tiles for two rounds of the chip and more: the first 256 lie in the first plane alone, the others in two.  Ragged rows
+    """Tiles of 64 x 64 for two rounds of the chip and more: the first 256 lie in the first plane alone, the others in two.  Ragged rows
     and columns, columns that run over several images, and the same product as a tensor (the parts added up)."""
     s = SSNet(n, t, f=12, seed=94, p=p)
     bits = 11 if p == binding.P45 else 15
-    (M, K, N), (B, C, H, Co) = whole_ahead_shapes(n)
+    (M, K, N), geom = WHOLE_AHEAD[n, t, p]
     assert s.lib.ssnet_product_bytes_linear(s._ctx, M, K, N) == 2 * 8 * n * M * N + 255 & ~255
     say("dense product, whole tiles first", n, t, hex(p), M, K, N)
     x = small_secrets((M, K), 5, bits, p)
@@ -220,14 +225,14 @@ def test_products_with_whole_tiles_ahead_of_the_cut_ones(n, t, p):
     wp = s.pack_weights_linear(to_dev(ws))
     check_consumers(s, p, y, (M, N, 1, 1), lambda: s.linear_product_prepacked(tiles, wp, M, K, N), seed=94)
     assert np.array_equal(to_np(s.linear_mod_prepacked(tiles, wp, M, K, N)), y)
-    k = 3
-    say("conv product, whole tiles first", n, t, hex(p), B, C, H, Co)
-    xs = orc.share(small_secrets((B, C, H, H), 1, bits, p), n, t, p, 94, 5)
+    say("conv product, whole tiles first", n, t, hex(p), geom)
+    B, C, H, W, Co, k, stride, pad = geom
+    xs = orc.share(small_secrets((B, C, H, W), 1, bits, p), n, t, p, 94, 5)
     ws = orc.share(small_secrets((Co, C, k, k), 2, bits - 2, p), n, t, p, 94, 6)
-    y = orc.conv(xs, ws, 1, 1, p)
+    y = orc.conv(xs, ws, stride, pad, p)
     planes, wp = s.split_planes(to_dev(xs)), s.pack_weights_conv_taps(to_dev(ws))
-    geom = (B, C, H, H, Co, k, k, 1, 1)
-    check_consumers(s, p, y, (B, Co, H, H), lambda: s.conv_product_planes(planes, wp, *geom), seed=94)
+    geom = (B, C, H, W, Co, k, k, stride, pad)
+    check_consumers(s, p, y, (B, Co) + y.shape[-2:], lambda: s.conv_product_planes(planes, wp, *geom), seed=94)
     assert np.array_equal(to_np(s.conv_mod_planes(planes, wp, *geom)), y)
 
 
@@ -303,7 +308,7 @@ def test_second_operand_past_the_last_level(p, N):
         assert np.array_equal(to_np(got), want[:, :, :cols])
 
 
-RAGGED = (7, 304, 307, 1347)   # n, M, K, N
+RAGGED = (7, 293, 890, 1351)   # n, M, K, N
 
 
 def test_whole_tiles_stop_earlier_where_ragged_ones_shorten_the_ranges():

@@ -1,8 +1,6 @@
 """Products on gemm_square_kernel (tiles of 32 x 32, the contraction in runs with a plane each) and the rule that takes them there
 (csrc/gemm_plan.hpp: plan_product, of which plan_gemm is what a product falls back to)."""
-import ctypes as C
 import random
-import subprocess
 
 import numpy as np
 import pytest
@@ -11,7 +9,7 @@ import torch
 import oracle as orc
 import test_gpu_pending_product as pending
 from paper_2406_02629_amd import SSNet, binding
-from test_gemm_plan import CSRC
+from test_gemm_plan import product_planner
 from util import field_uniform, to_dev, to_np
 
 P61, P45 = binding.P61, binding.P45
@@ -29,12 +27,15 @@ SHAPES = {
                   (3, 512, 29, 27, 51, 1, 2, 0): (2, 0), (1, 64, 8, 18, 17, 5, 2, 2): (5, 0)},
     (7, 3, P61): {(33, 1071, 229): (2, 2), (1, 128, 12, 3, 98, 3, 1, 1): (4, 0)},
 }
-# products that stay with tiles of 64 x 64: several planes, whole tiles alone, and whole tiles ahead of cut ones
+# products that stay with tiles of 64 x 64 -> how they are cut when left in the workspace, and as a tensor: several planes, whole tiles alone, and
+# whole tiles ahead of cut ones ("square": the tensor is a product in runs)
 OTHERS = {
-    (5, 2, P61): {(819, 1558, 8): "planes"},
-    (3, 1, P61): {(36, 521, 5092): "whole"},
-    (7, 3, P61): {(39, 516, 5766): "ahead", (2, 512, 2, 2, 578, 3, 1, 1): "planes", (1, 64, 25, 105, 100, 3, 1, 1): "ahead"},
-    (5, 2, P45): {(33, 928, 6914): "ahead", (908, 1931, 34): "planes", (1, 512, 3, 3, 842, 3, 1, 1): "planes"},
+    (5, 2, P61): {(819, 1558, 8): ("planes", "planes"), (33, 693, 7634): ("ahead", "ahead"), (3, 192, 99, 87, 40, 2, 2, 1): ("ahead", "ahead")},
+    (3, 1, P61): {(36, 521, 5092): ("whole", "whole"), (3, 192, 27, 94, 328, 2, 2, 0): ("ahead", "ahead")},
+    (7, 3, P61): {(39, 516, 5766): ("ahead", "square"), (33, 636, 5309): ("ahead", "ahead"), (2, 512, 2, 2, 578, 3, 1, 1): ("planes", "planes"),
+                  (1, 64, 25, 105, 100, 3, 1, 1): ("ahead", "square")},
+    (5, 2, P45): {(33, 928, 6914): ("ahead", "square"), (34, 1448, 6620): ("ahead", "ahead"), (908, 1931, 34): ("planes", "planes"),
+                  (1, 512, 3, 3, 842, 3, 1, 1): ("planes", "planes"), (3, 192, 16, 76, 426, 3, 2, 1): ("ahead", "ahead")},
 }
 
 
@@ -51,25 +52,7 @@ def product_of(shape):
 def plans(tmp_path_factory):
     """plans[limbs](n, rows, cols, K, gather, tensor, room) -> (runs, workgroups, planes, plan_gemm's ksplit, slots, whole)"""
     directory = tmp_path_factory.mktemp("square_plan")
-    src = directory / "plan.cpp"
-    src.write_text('#include "gemm_plan.hpp"\nextern "C" void plan_product(int n, int rows, int cols, int K, int gather, int tensor, int room, long *v)\n'
-                   "{ const plan::product_plan r = plan::plan_product(n, rows, cols, K, gather, tensor, room);\n"
-                   "  const long w[6] = {r.sq.runs, (long)r.sq.G, r.planes(), r.p.ksplit, r.p.slots, (long)r.p.whole};\n"
-                   "  for (int i = 0; i < 6; i++) v[i] = w[i]; }\n")
-    out = {}
-    for limbs in (8, 6):
-        so = str(directory / f"plan{limbs}.so")
-        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-DSS_NS=plan", f"-DSS_NLIMB={limbs}", "-I", CSRC,
-                        "-o", so, str(src)], check=True)
-        fn = C.CDLL(so).plan_product
-        fn.restype, fn.argtypes = None, [C.c_int] * 7 + [C.POINTER(C.c_long)]
-
-        def call(n, rows, cols, K, gather, tensor, room, fn=fn):
-            v = (C.c_long * 6)()
-            fn(n, rows, cols, K, gather, tensor, room, v)
-            return tuple(v)
-        out[limbs] = call
-    return out
+    return {limbs: product_planner(directory, limbs) for limbs in (8, 6)}
 
 
 def test_shapes_of_the_gpu_tests_take_what_they_are_written_for(plans):
@@ -79,10 +62,13 @@ def test_shapes_of_the_gpu_tests_take_what_they_are_written_for(plans):
             call = plans[8 if p == P61 else 6]
             assert (call(n, *product, 0, 8)[0], call(n, *product, 1, 0)[0]) == runs, (n, shape)
     for (n, t, p), shapes in OTHERS.items():
-        for shape, kind in shapes.items():
-            runs, _, planes, ksplit, slots, whole = plans[8 if p == P61 else 6](n, *product_of(shape), 0, 8)
-            assert runs == 0 and ksplit == 0 and planes == slots, (n, shape)
-            assert {"planes": slots >= 5, "whole": slots == 1 and whole > 0, "ahead": slots == 2 and whole >= 256}[kind], (n, shape)
+        for shape, kinds in shapes.items():
+            for kind, (tensor, room) in zip(kinds, ((0, 8), (1, 0))):
+                runs, _, planes, ksplit, slots, whole = plans[8 if p == P61 else 6](n, *product_of(shape), tensor, room)
+                assert (runs > 0) == (kind == "square") and ksplit == 0, (n, shape, tensor)
+                if runs == 0:
+                    assert planes == slots, (n, shape, tensor)
+                    assert {"planes": slots >= 5, "whole": slots == 1 and whole > 0, "ahead": slots == 2 and whole >= 256}[kind], (n, shape, tensor)
 
 
 # limbs, (n, rows, columns, contraction, gather) -> runs of the pending product, as the comment at plan_square has them: faster there, and left (0) to
