@@ -490,7 +490,7 @@ def main():
                                                 "degree_reduce+rerand+truncate+reconstruct (one launch)"},
             # ms_per_step is wall time over the K steps; these are the same K steps one by one (HIP events)
             "ms_per_step_events": {k: round(v, 4) if k != "n" else v for k, v in stats(per_step).items()},
-            "roofline": {"bound": "mfma", "kernel": "gemm_square_kernel, gemm_skinny_kernel (classifier)",
+            "roofline": {"bound": "mfma", "kernel": "gemm_square_kernel, gemm_limb_kernel (56 x 56 pixels to 64 channels), gemm_skinny_kernel (classifier)",
                          "achieved": achieved, "peak": INT8_PEAK_TOPS,
                          "unit": "TOP/s", "frac": achieved / INT8_PEAK_TOPS,
                          "traffic": traffic, "traffic_unit": "bytes per launch (HBM)",

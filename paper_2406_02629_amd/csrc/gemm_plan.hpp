@@ -100,6 +100,8 @@ inline gemm_plan plan_ksplit(int n, int rows, int cols, int Kb, double *busy, do
 // 20.7 / 24.8 -> 16.3; 1024 x 196 x 256 41.0 -> 39.0 / 31.0 -> 25.6 / 28.5 -> 20.2 (the product alone of five parties 20.0 -> 21.4: the
 // reduction has one plane instead of two).  Left, 39 x 1800 x 4608, n = 5, 111 -> 118; 94 x 1352 x 2304, n = 3, 60.7 -> 68.5; with stride
 // 2, 43 x 578 x 4608, n = 5, 51 -> 65; 270 x 80 x 4608, n = 5, 46 -> 56; 27 x 1152 x 4608, n = 4 over the 45-bit prime, 46 -> 51.
+// (Timed before gemm_square_kernel, which takes products from both of them now, see plan_square: of the shapes here 128 x 784 x 512 but over the
+// 45-bit prime, 1024 x 196 x 256 and 27 x 1152 x 4608.)
 // us: the estimate for the kernel that is taken.
 inline bool ksplit_is_faster(const gemm_plan &k, const gemm_plan &p, double busy, double spread, double big, bool all_whole, int n,
                              int rows, int cols, int gather, double *us)

@@ -324,8 +324,10 @@ size_t tail_message_bytes(const ssnet_ctx *ctx, int B, int C, int HW)
 }
 
 // Room for a product at the very end of the workspace; the messages of the call that consumes it grow from the front.  It takes the
-// planes that make it fastest where they leave room for any consumer's messages (those of the layer tail, on the product as [B][C][HW], are
-// the most), else the fewest it can be computed with: what fits a smaller workspace still fits.  nullptr if the workspace is too small.
+// planes that make it fastest where they leave room for the messages of every consumer that takes the product as [B][C][HW] (those of the layer
+// tail are the most), else the fewest it can be computed with: what fits a smaller workspace still fits.  A layer tail on another shape of as many
+// elements may have more messages (blocks of 16 x 16); a workspace of its size and ssnet_product_bytes_* together holds those too.  nullptr if the
+// workspace is too small.
 u64 *reserve_pending(ssnet_ctx *ctx, int rows, int cols, int K, int gather, int hw, int B, int C, int HW, product_plan *plan)
 {
     ctx->pending.on = false;
